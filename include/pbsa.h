@@ -131,6 +131,16 @@ int pbsa_pool_blocks(const pbsa_params* p, const void* X, const int32_t* len, in
 int pbsa_summary_view(const pbsa_params* p, const float* S_sum, const int32_t* S_cnt, void* Kp, void* Vp,
                       int32_t* p_len, void* hip_stream);
 
+/* Cache append: the chunk's K and V, token-major per head ([H][Nq][d] bf16 with the element strides given, last
+ * dimension contiguous), into the ring slots slot0 .. slot0 + nqb - 1 of Kl and Vl, block-major, in one launch.
+ * zero_tail != 0: the rows of the last block past the chunk's end are cleared, else they are left as they are.
+ * Kc_l (optional): the pooled keys of those slots (Eq. 6) are written as well, the same bits pbsa_select_blocks would
+ * write, so a selection that follows may start its pooling (pool_from) behind them.  K or V may be NULL: that tensor
+ * is left alone (and without K nothing is pooled).  Uses p->H, d, B, Nq, nqb and n_loc_cap. */
+int pbsa_append_chunk(const pbsa_params* p, const void* K, const void* V, int64_t k_stride_h, int64_t k_stride_t,
+                      int64_t v_stride_h, int64_t v_stride_t, int32_t slot0, int32_t zero_tail, void* Kl, void* Vl,
+                      float* Kc_l, void* hip_stream);
+
 /* Coarse routing inside the local region (Eq. 10-11).  Pools the chunk's queries into Qc, refreshes
  * the pooled keys Kc_l of logical blocks >= pool_from, scores every visible local block of every
  * query block with dot(Qc_i, Kc_l) (the argument of Eq. 10's softmax, which is monotone per row)

@@ -50,6 +50,7 @@ class PbsaCache:
         self.chunk_ids = []          # global chunk index of each
         self.n_appended = 0
         self.stale_from = 0
+        self._chunk_pooled = False   # the newest chunk's pooled keys were written together with its K
         self._maps = {}
         self._arange64 = None
         lens = torch.full((self.nqb,), B, dtype=torch.int32)
@@ -117,15 +118,34 @@ class PbsaCache:
         """Copy a chunk's K/V ([H][Nq][d] bf16, token-major) into the next ring position, block-major."""
         assert len(self.chunk_pos) <= self.w, "update() slides the window before the next append"
         pos = self.n_appended % self.ring
-        for dst, src in ((self.Kl, K), (self.Vl, V)):
-            view = dst[:, pos * self.nqb:(pos + 1) * self.nqb].view(self.H, self.nqb * self.B, self.d)
-            view[:, :self.Nq] = src
-            if self.nqb * self.B > self.Nq:
-                view[:, self.Nq:] = 0
         self.chunk_pos.append(pos)
         self.chunk_ids.append(chunk_id)
         self.n_appended += 1
         self.stale_from = min(self.stale_from, self.n_loc - self.nqb)
+        self._write_chunk(pos, K, V, True)
+
+    def _in_place(self, x):
+        """Whether pbsa_append_chunk takes tensor x as it is: bf16 on this GPU, whole, rows contiguous and aligned."""
+        return (x.dtype is torch.bfloat16 and x.device == self.Kl.device and x.shape == (self.H, self.Nq, self.d) and x.stride(2) == 1
+                and x.stride(0) % 8 == 0 and x.stride(1) % 8 == 0 and x.stride(1) >= self.d and x.data_ptr() % 16 == 0)
+
+    def _write_chunk(self, pos, K, V, zero_tail):
+        """K and V (either may be None) into ring position `pos`: one launch that also writes the pooled keys; tensors
+        of another type, device or layout go through torch, and their keys are pooled by the next selection."""
+        self._chunk_pooled = False
+        if K is None and V is None:
+            return
+        if (K is None or self._in_place(K)) and (V is None or self._in_place(V)):
+            pbsa.pbsa_append_chunk(self.params(), K, V, pos * self.nqb, zero_tail, self.Kl, self.Vl, self.Kc_l)
+            self._chunk_pooled = K is not None
+            return
+        for dst, src in ((self.Kl, K), (self.Vl, V)):
+            if src is None:
+                continue
+            view = dst[:, pos * self.nqb:(pos + 1) * self.nqb].view(self.H, self.nqb * self.B, self.d)
+            view[:, :self.Nq] = src
+            if zero_tail and self.nqb * self.B > self.Nq:
+                view[:, self.Nq:] = 0
 
     def rewrite_chunk(self, K=None, V=None):
         """Between the denoising passes of one chunk (Sec. 3.1: each chunk is denoised in T passes over the
@@ -133,10 +153,7 @@ class PbsaCache:
         with no arguments just note that the producer has.  The next selection then pools the chunk's
         blocks again; the pooled keys of the window stay cached."""
         assert self.chunk_pos, "no chunk to rewrite"
-        pos = self.chunk_pos[-1]
-        for dst, src in ((self.Kl, K), (self.Vl, V)):
-            if src is not None:
-                dst[:, pos * self.nqb:(pos + 1) * self.nqb].view(self.H, self.nqb * self.B, self.d)[:, :self.Nq] = src
+        self._write_chunk(self.chunk_pos[-1], K, V, False)
         self.stale_from = min(self.stale_from, self.n_loc - self.nqb)
 
     def adopt_chunk(self, chunk_id):
@@ -146,12 +163,15 @@ class PbsaCache:
         self.chunk_pos.append(self.n_appended % self.ring)
         self.chunk_ids.append(chunk_id)
         self.n_appended += 1
+        self._chunk_pooled = False
         self.stale_from = min(self.stale_from, self.n_loc - self.nqb)
 
     # -- the three calls ---------------------------------------------------------------------------
     def select(self, Q):
         l_map, l_len, _ = self._device_maps()
-        p = self.params(pool_from=self.stale_from, Q=Q)
+        # the newest chunk's keys may have been pooled as they were written; anything older that is stale is not
+        fresh = self._chunk_pooled and self.stale_from == self.n_loc - self.nqb
+        p = self.params(pool_from=self.n_loc if fresh else self.stale_from, Q=Q)
         if self._pending is not None:            # with the data movement of the previous chunk's update in its pooling launch
             pbsa.pbsa_select_blocks_apply(p, Q, self.Kl, l_len, l_map, self.Kc_l, self.Qc, self.sel, self.Zl, self._pending,
                                           self.Kp, self.Vp, self.p_len, self.S_sum, self.S_cnt, self.Vl, self.ws)

@@ -130,6 +130,23 @@ int pbsa_summary_view(const pbsa_params* p, const float* S_sum, const int32_t* S
   return e == hipSuccess ? PBSA_OK : hip_fail(e);
 }
 
+int pbsa_append_chunk(const pbsa_params* p, const void* K, const void* V, int64_t k_stride_h, int64_t k_stride_t,
+                      int64_t v_stride_h, int64_t v_stride_t, int32_t slot0, int32_t zero_tail, void* Kl, void* Vl,
+                      float* Kc_l, void* hip_stream) {
+  int rc = check_common(p, INT32_MAX, INT32_MAX, INT32_MAX);   // looks at no slot, selection or older block
+  if (rc) return rc;
+  if ((K && !Kl) || (V && !Vl)) return PBSA_EINVAL;
+  if (slot0 < 0 || slot0 > p->n_loc_cap - p->nqb) return PBSA_EINVAL;
+  if (K && (rc = check_strides(k_stride_h, k_stride_t, p))) return rc;
+  if (V && (rc = check_strides(v_stride_h, v_stride_t, p))) return rc;
+  if (!aligned16(K) || !aligned16(V) || !aligned16(Kl) || !aligned16(Vl) || !aligned16(Kc_l)) return PBSA_EALIGN;
+  if (!K && !V) return PBSA_OK;
+  hipError_t e = pbsa::launch_append(*p, static_cast<const pbsa::bf16_t*>(K), static_cast<const pbsa::bf16_t*>(V), k_stride_h,
+                                     k_stride_t, v_stride_h, v_stride_t, slot0, zero_tail, static_cast<pbsa::bf16_t*>(Kl),
+                                     static_cast<pbsa::bf16_t*>(Vl), Kc_l, static_cast<hipStream_t>(hip_stream));
+  return e == hipSuccess ? PBSA_OK : hip_fail(e);
+}
+
 int pbsa_select_blocks(const pbsa_params* p, const void* Q, const void* Kl, const int32_t* l_len,
                        const int32_t* l_map, float* Kc_l, float* Qc, int32_t* sel, float* Zl, void* ws,
                        size_t ws_bytes, void* hip_stream) {

@@ -37,7 +37,7 @@ __device__ __forceinline__ uint32_t f2bf_rne(float f) {
 struct PoolArgs {
   int mode;                 // 0: generic blocks, 1: select (local key blocks, then query blocks)
   int n_jobs;
-  int H, B, Nq, nqb, n_loc, n_loc_cap, pool_from, n_kjobs_per_head;
+  int H, B, Nq, nqb, n_loc, n_loc_cap, pool_from, n_kjobs_per_head;   // n_kjobs_per_head: stale local key blocks
   long q_stride_h, q_stride_t;
   const bf16_t* X;          // mode 0: [n][B][D]; mode 1: Kl
   const bf16_t* Q;
@@ -109,6 +109,61 @@ __global__ void __launch_bounds__(kThreads) pool_kernel(PoolArgs a) {
 }
 
 // ------------------------------------------------------------------------------------------------
+// Cache append: a chunk's K and V (token-major per head) into nqb consecutive ring slots, and the pooled keys of those
+// blocks (Eq. 6) from the rows as they pass.  One workgroup = one block of K or of V; a thread moves 16 bytes per
+// sweep, all sweeps in flight together.  For K the rows also go to LDS, where D / 2 threads add them in ascending
+// order (the pinned order of the pooling), two dimensions each: 64 consecutive words per row, free of bank conflicts.
+// Bound by HBM: each byte is read once and written once, and the selection that follows does not read K again: 11.1 us
+// for a chunk of 12 x 4680 x 128 (57.5 MB moved, 5.2 TB/s), where four tensor copies took 27 us and the selection's
+// own pooling launch another 8.7.
+// ------------------------------------------------------------------------------------------------
+struct AppendArgs {
+  int B, Nq, nqb, n_loc_cap, slot0, zero_tail;
+  long sh[2], st[2];        // element strides of K and of V
+  const bf16_t* src[2];
+  bf16_t* dst[2];
+  float* Kc_l;
+};
+
+template <int D, int BT>
+__global__ void __launch_bounds__(kThreads) append_kernel(AppendArgs a) {
+  constexpr int CPR = D / 8, RPS = kThreads / CPR, NS = BT / RPS;     // chunks per row, rows per sweep, sweeps
+  __shared__ __align__(16) uint4 tile[BT * CPR];
+  const int i = blockIdx.x, h = blockIdx.y, kv = blockIdx.z;
+  const bf16_t* src = a.src[kv];
+  if (!src) return;
+  const int len = min(BT, a.Nq - i * BT);
+  const int r0 = threadIdx.x / CPR, c = threadIdx.x % CPR;
+  src += (size_t)h * a.sh[kv] + (size_t)i * BT * a.st[kv] + 8 * c;
+  bf16_t* dst = a.dst[kv] + ((size_t)h * a.n_loc_cap + a.slot0 + i) * BT * D + 8 * c;
+  uint4 v[NS];
+#pragma unroll
+  for (int s = 0; s < NS; ++s) v[s] = *reinterpret_cast<const uint4*>(src + (size_t)min(r0 + s * RPS, len - 1) * a.st[kv]);
+  const bool pool = kv == 0 && a.Kc_l;
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    const int r = r0 + s * RPS;
+    if (pool) tile[r * CPR + c] = v[s];
+    if (r >= len) v[s] = make_uint4(0u, 0u, 0u, 0u);
+    if (r < len || a.zero_tail) *reinterpret_cast<uint4*>(dst + (size_t)r * D) = v[s];
+  }
+  if (!pool) return;
+  __syncthreads();
+  if (threadIdx.x >= D / 2) return;
+  const uint32_t* t32 = reinterpret_cast<const uint32_t*>(tile) + threadIdx.x;
+  float acc0 = 0.0f, acc1 = 0.0f;
+#pragma unroll 16
+  for (int r = 0; r < len; ++r) {
+    const uint32_t u = t32[r * (D / 2)];
+    acc0 = acc0 + bf_lo(u);
+    acc1 = acc1 + bf_hi(u);
+  }
+  const float fl = (float)len;
+  *reinterpret_cast<float2*>(a.Kc_l + ((size_t)h * a.n_loc_cap + a.slot0 + i) * D + 2 * threadIdx.x) =
+      make_float2(acc0 / fl, acc1 / fl);
+}
+
+// ------------------------------------------------------------------------------------------------
 // Coarse logits.  A workgroup of 4 waves handles 4 query blocks (one per wave) of one head; lane
 // `lane` of a wave owns columns j = lane + 64 m.  The pooled keys of all columns are staged through
 // LDS kXC dimensions at a time, transposed ([x][j], pitch NM*64+2 keeps both the transposing stores
@@ -167,10 +222,13 @@ struct SelectArgs {
   int H, nqb, n_loc, n_loc_cap, k, causal;
   float scale;
   const float* Kc_l;
-  const float* Qc;
+  float* Qc;
   const int32_t* l_map;
   int32_t* sel;
   float* Zl;                // optional out: scaled logits of every local block, [H][nqb][n_loc]
+  const bf16_t* Q;          // given: the query blocks are pooled here (into Qc), else Qc holds them
+  int B, Nq;
+  long q_stride_h, q_stride_t;
 };
 
 // One wave-wide global -> LDS load of 16 bytes per lane: LDS bytes [lds_off, lds_off + 1024) receive
@@ -183,6 +241,21 @@ __device__ __forceinline__ void dma16(const void* base, uint32_t voff, uint32_t 
                : "memory", "m0");
 }
 
+// Adds up to N tokens (two dimensions of them) to acc0 / acc1 in ascending order, all N loads in flight together.
+template <int N>
+__device__ __forceinline__ void pool_rows(const bf16_t* p, long pitch, int len, float& acc0, float& acc1) {
+  uint32_t v[N];
+#pragma unroll
+  for (int u = 0; u < N; ++u) v[u] = *reinterpret_cast<const uint32_t*>(p + (size_t)min(u, len - 1) * pitch);
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    if (u < len) {
+      acc0 = acc0 + bf_lo(v[u]);
+      acc1 = acc1 + bf_hi(v[u]);
+    }
+  }
+}
+
 // Selection (Eq. 10-11).  A workgroup handles 4 query blocks of one head; its NM waves split the local
 // blocks: lane `lane` of wave w owns column j = 64 w + lane and runs the four chains
 // acc_r = fma(q_r[x], k_j[x], acc_r), x ascending.  The pooled keys reach LDS by direct global -> LDS
@@ -190,7 +263,11 @@ __device__ __forceinline__ void dma16(const void* base, uint32_t voff, uint32_t 
 // columns it consumes, so the rounds need no workgroup barrier.  Within a column's round the 16-byte
 // chunks are permuted (logical chunk c of column j sits at c ^ ((j / 2) % (DX / 4))), which spreads the
 // per-lane 16-byte reads of consecutive columns over the bank groups.  The logits then go to LDS and wave
-// r ranks row r.  DX = 32 up to 8 waves; 16 beyond, where two rounds of 32 would not fit in LDS.
+// r ranks row r.  DX = 32 up to 8 waves; 16 beyond, where two rounds of 32 would not fit in LDS.  A query block is
+// looked at by exactly one workgroup, so that one pools it (Eq. 6, D / 2 threads per block, tokens added in ascending
+// order) while its first pooled keys arrive (11.1 us at 12 x 37 blocks of 128 tokens and 111 columns, against 8.5 us
+// behind a pooling launch of 9.6); at least four waves, so that the four blocks are pooled and ranked side by side
+// whatever NM is.
 template <int D, int NM, int DX>
 __device__ __forceinline__ void select_body(const SelectArgs& a, const int bx, const int h, unsigned char* smem) {
   constexpr int NCP = NM * 64;                        // padded columns
@@ -199,17 +276,20 @@ __device__ __forceinline__ void select_body(const SelectArgs& a, const int bx, c
   constexpr int CPC = DX / 4;                         // 16-byte chunks per column and round
   constexpr int NI = 64 * CPC / 64;                   // load instructions per wave and round (64 columns)
   constexpr int CPI = 64 / CPC;                       // columns per instruction
+  constexpr int NW = NM < 4 ? 4 : NM, NT = 64 * NW;   // waves, threads
   float* qs = reinterpret_cast<float*>(smem + 2 * BUF);                         // [4][D]
   float* zs = qs + 4 * D;                                                       // [4][NCP]
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int i0 = bx * 4;
+
+  const bool has_cols = NM >= 4 || wave < NM;         // the waves that own columns
 
   // this lane's share of the staging: instruction n fills columns 64 wave + CPI n + lane / CPC, physical chunk
   // lane % CPC
   uint32_t goff[NI];
 #pragma unroll
   for (int n = 0; n < NI; ++n) {
-    const int j = 64 * wave + CPI * n + lane / CPC;
+    const int j = min(64 * wave, NCP - 64) + CPI * n + lane / CPC;
     int slot = a.l_map[min(j, a.n_loc - 1)];
     slot = min(max(slot, 0), a.n_loc_cap - 1);
     const int chunk = (lane % CPC) ^ ((j >> 1) % CPC);
@@ -221,18 +301,43 @@ __device__ __forceinline__ void select_body(const SelectArgs& a, const int bx, c
 #define PBSA_STAGE(R_)                                                                                 \
   _Pragma("unroll") for (int n_ = 0; n_ < NI; ++n_)                                                     \
       dma16(kbase + (R_) * (DX * 4), goff[n_], wave_lds + ((R_) & 1) * BUF + n_ * 1024);
-  PBSA_STAGE(0)
-  if (NR > 1) PBSA_STAGE(1)
+  if (has_cols) {
+    PBSA_STAGE(0)
+    if (NR > 1) PBSA_STAGE(1)
+  }
 
-  for (int idx = threadIdx.x; idx < 4 * D; idx += 64 * NM) {
-    const int r = idx / D, x = idx % D;
-    qs[idx] = i0 + r < a.nqb ? a.Qc[((size_t)h * a.nqb + i0 + r) * D + x] : 0.0f;
+  if (a.Q) {
+    const int r = threadIdx.x / (D / 2), c = threadIdx.x % (D / 2), i = i0 + r;
+    if (r < 4) {
+      float acc0 = 0.0f, acc1 = 0.0f;
+      if (i < a.nqb) {
+        const int len = min(a.B, a.Nq - i * a.B);
+        const bf16_t* p = a.Q + (size_t)h * a.q_stride_h + (size_t)i * a.B * a.q_stride_t + 2 * c;
+        if (len > 64 && NM <= 8) {
+          pool_rows<128>(p, a.q_stride_t, len, acc0, acc1);
+        } else {
+          pool_rows<64>(p, a.q_stride_t, min(len, 64), acc0, acc1);
+          if (len > 64) pool_rows<64>(p + 64 * a.q_stride_t, a.q_stride_t, len - 64, acc0, acc1);
+        }
+        const float fl = (float)len;
+        acc0 = acc0 / fl;
+        acc1 = acc1 / fl;
+        *reinterpret_cast<float2*>(a.Qc + ((size_t)h * a.nqb + i) * D + 2 * c) = make_float2(acc0, acc1);
+      }
+      *reinterpret_cast<float2*>(qs + r * D + 2 * c) = make_float2(acc0, acc1);
+    }
+  } else {
+    for (int idx = threadIdx.x; idx < 4 * D; idx += NT) {
+      const int r = idx / D, x = idx % D;
+      qs[idx] = i0 + r < a.nqb ? a.Qc[((size_t)h * a.nqb + i0 + r) * D + x] : 0.0f;
+    }
   }
   __syncthreads();
 
   float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
   const int jcol = 64 * wave + lane;
   const int sw = (jcol >> 1) % CPC;
+  if (has_cols)
 #pragma unroll 1
   for (int r0 = 0; r0 < NR; ++r0) {
     if (r0 + 1 < NR) {
@@ -259,6 +364,7 @@ __device__ __forceinline__ void select_body(const SelectArgs& a, const int bx, c
   }
 #undef PBSA_STAGE
 
+  if (has_cols)
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const float z = acc[r] * a.scale;
@@ -267,9 +373,9 @@ __device__ __forceinline__ void select_body(const SelectArgs& a, const int bx, c
   }
   __syncthreads();
 
-  for (int r = wave; r < 4; r += NM) {
-    const int i = i0 + r;
-    if (i >= a.nqb) break;
+  {
+    const int r = wave, i = i0 + r;
+    if (r >= 4 || i >= a.nqb) return;
     // order-preserving integer keys; invisible columns get 0, below every real value
     const int nvis = a.causal ? a.n_loc - a.nqb + i + 1 : a.n_loc;
     uint32_t key[NM];
@@ -314,7 +420,7 @@ __device__ __forceinline__ void select_body(const SelectArgs& a, const int bx, c
 }
 
 template <int D, int NM, int DX>
-__global__ void __launch_bounds__(64 * NM) select_kernel(SelectArgs a) {
+__global__ void __launch_bounds__(64 * (NM < 4 ? 4 : NM)) select_kernel(SelectArgs a) {
   static_assert(DX == 32 || DX == 16, "a round is 8 or 4 load instructions per wave");
   extern __shared__ __align__(1024) unsigned char smem[];
   select_body<D, NM, DX>(a, blockIdx.x, blockIdx.y, smem);
@@ -682,6 +788,19 @@ hipError_t launch_pool_blocks(const pbsa_params& p, const bf16_t* X, const int32
   return hipGetLastError();
 }
 
+hipError_t launch_append(const pbsa_params& p, const bf16_t* K, const bf16_t* V, int64_t k_stride_h, int64_t k_stride_t,
+                         int64_t v_stride_h, int64_t v_stride_t, int32_t slot0, int32_t zero_tail, bf16_t* Kl, bf16_t* Vl,
+                         float* Kc_l, hipStream_t stream) {
+  const AppendArgs a{p.B, p.Nq, p.nqb, p.n_loc_cap, slot0, zero_tail, {(long)k_stride_h, (long)v_stride_h},
+                     {(long)k_stride_t, (long)v_stride_t}, {K, V}, {Kl, Vl}, Kc_l};
+  const dim3 grid(p.nqb, p.H, 2), block(kThreads);
+  if (p.d == 128 && p.B == 128) hipLaunchKernelGGL((append_kernel<128, 128>), grid, block, 0, stream, a);
+  else if (p.d == 128) hipLaunchKernelGGL((append_kernel<128, 64>), grid, block, 0, stream, a);
+  else if (p.B == 128) hipLaunchKernelGGL((append_kernel<64, 128>), grid, block, 0, stream, a);
+  else hipLaunchKernelGGL((append_kernel<64, 64>), grid, block, 0, stream, a);
+  return hipGetLastError();
+}
+
 hipError_t launch_summary_view(const pbsa_params& p, const float* S_sum, const int32_t* S_cnt, bf16_t* Kp, bf16_t* Vp,
                                int32_t* p_len, hipStream_t stream) {
   const int rows_per_wg = kThreads / (p.d / 4);
@@ -696,16 +815,21 @@ static hipError_t launch_select_t(const SelectArgs& a, hipStream_t stream) {
   static_assert(lds <= 160 * 1024, "two rounds of every column, the queries and the logits must fit in LDS");
   hipError_t e = allow_lds(select_kernel<D, NM, DX>, lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((select_kernel<D, NM, DX>), dim3((a.nqb + 3) / 4, a.H), dim3(64 * NM), lds, stream, a);
+  hipLaunchKernelGGL((select_kernel<D, NM, DX>), dim3((a.nqb + 3) / 4, a.H), dim3(64 * (NM < 4 ? 4 : NM)), lds, stream, a);
   return hipGetLastError();
 }
 
+// Whether the selection launch pools the query blocks itself.  Not when nothing is selected and no logits are wanted
+// (there is none).  launch_select_apply leaves the queries in its pooling launch: the fold sets that launch's length
+// and hides their 14 MB (186.3 us per chained step against 187.8 at H = 12, 4680 rows of 128, blocks of 64).
+static bool select_pools_queries(const pbsa_params& p, const float* Zl) { return p.k > 0 || Zl; }
+
 static PoolArgs select_pool_args(const pbsa_params& p, const bf16_t* Q, const bf16_t* Kl, const int32_t* l_len,
-                                 const int32_t* l_map, float* Kc_l, float* Qc) {
+                                 const int32_t* l_map, float* Kc_l, float* Qc, bool with_queries) {
   PoolArgs pa{};
   pa.mode = 1; pa.H = p.H; pa.B = p.B; pa.Nq = p.Nq; pa.nqb = p.nqb; pa.n_loc = p.n_loc; pa.n_loc_cap = p.n_loc_cap;
   pa.pool_from = p.pool_from; pa.n_kjobs_per_head = p.n_loc - p.pool_from;
-  pa.n_jobs = p.H * (pa.n_kjobs_per_head + p.nqb);
+  pa.n_jobs = p.H * (pa.n_kjobs_per_head + (with_queries ? p.nqb : 0));
   pa.q_stride_h = p.q_stride_h; pa.q_stride_t = p.q_stride_t;
   pa.X = Kl; pa.Q = Q; pa.len = l_len; pa.l_map = l_map; pa.out = Kc_l; pa.Qc = Qc;
   return pa;
@@ -717,27 +841,29 @@ static FoldArgs fold_args(const pbsa_params& p, bf16_t* Kp, bf16_t* Vp, int32_t*
                   ws.fold_src, ws.fold_len, ws.promo_slot, ws.plen_new, p_len};
 }
 
-static hipError_t launch_select_logits(const pbsa_params& p, const int32_t* l_map, float* Kc_l, float* Qc, int32_t* sel,
-                                       float* Zl, hipStream_t stream);
+static hipError_t launch_select_logits(const pbsa_params& p, const bf16_t* Q, const int32_t* l_map, float* Kc_l, float* Qc,
+                                       int32_t* sel, float* Zl, hipStream_t stream);
 
 hipError_t launch_select(const pbsa_params& p, const bf16_t* Q, const bf16_t* Kl, const int32_t* l_len,
                          const int32_t* l_map, float* Kc_l, float* Qc, int32_t* sel, float* Zl,
                          hipStream_t stream) {
-  const PoolArgs pa = select_pool_args(p, Q, Kl, l_len, l_map, Kc_l, Qc);
-  const int jpw = kThreads / (p.d / 2);
-  const dim3 grid((pa.n_jobs + jpw - 1) / jpw);
-  if (p.d == 128) hipLaunchKernelGGL(pool_kernel<128>, grid, dim3(kThreads), 0, stream, pa);
-  else hipLaunchKernelGGL(pool_kernel<64>, grid, dim3(kThreads), 0, stream, pa);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return launch_select_logits(p, l_map, Kc_l, Qc, sel, Zl, stream);
+  const PoolArgs pa = select_pool_args(p, Q, Kl, l_len, l_map, Kc_l, Qc, !select_pools_queries(p, Zl));
+  if (pa.n_jobs > 0) {
+    const int jpw = kThreads / (p.d / 2);
+    const dim3 grid((pa.n_jobs + jpw - 1) / jpw);
+    if (p.d == 128) hipLaunchKernelGGL(pool_kernel<128>, grid, dim3(kThreads), 0, stream, pa);
+    else hipLaunchKernelGGL(pool_kernel<64>, grid, dim3(kThreads), 0, stream, pa);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return launch_select_logits(p, Q, l_map, Kc_l, Qc, sel, Zl, stream);
 }
 
 hipError_t launch_select_apply(const pbsa_params& p, const bf16_t* Q, const bf16_t* Kl, const int32_t* l_len,
                                const int32_t* l_map, float* Kc_l, float* Qc, int32_t* sel, float* Zl,
                                const pbsa_params& pu, bf16_t* Kp, bf16_t* Vp, int32_t* p_len, float* S_sum,
                                const int32_t* S_cnt, const bf16_t* Vl, const UpdateWs& ws, hipStream_t stream) {
-  const PoolArgs pa = select_pool_args(p, Q, Kl, l_len, l_map, Kc_l, Qc);
+  const PoolArgs pa = select_pool_args(p, Q, Kl, l_len, l_map, Kc_l, Qc, true);
   const FoldArgs fa = fold_args(pu, Kp, Vp, p_len, S_sum, S_cnt, Kl, Vl, ws);
   // the fold / promote workgroups ride in the pooling launch: its workgroups have the same size and no LDS of their
   // own (in the logits launch, 80 KB of LDS per workgroup, they would wait for places: measured slower)
@@ -748,14 +874,15 @@ hipError_t launch_select_apply(const pbsa_params& p, const bf16_t* Q, const bf16
   else hipLaunchKernelGGL(pool_fold_kernel<64>, grid, dim3(kThreads), 0, stream, pa, fa, n_fold_x);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return launch_select_logits(p, l_map, Kc_l, Qc, sel, Zl, stream);
+  return launch_select_logits(p, nullptr, l_map, Kc_l, Qc, sel, Zl, stream);
 }
 
-static hipError_t launch_select_logits(const pbsa_params& p, const int32_t* l_map, float* Kc_l, float* Qc, int32_t* sel,
-                                       float* Zl, hipStream_t stream) {
+static hipError_t launch_select_logits(const pbsa_params& p, const bf16_t* Q, const int32_t* l_map, float* Kc_l, float* Qc,
+                                       int32_t* sel, float* Zl, hipStream_t stream) {
   if (p.k == 0 && !Zl) return hipSuccess;
 
-  SelectArgs a{p.H, p.nqb, p.n_loc, p.n_loc_cap, p.k, p.causal, p.scale, Kc_l, Qc, l_map, sel, Zl};
+  SelectArgs a{p.H, p.nqb, p.n_loc, p.n_loc_cap, p.k, p.causal, p.scale, Kc_l, Qc, l_map, sel, Zl,
+               Q, p.B, p.Nq, p.q_stride_h, p.q_stride_t};
   const int nm = (p.n_loc + 63) / 64;
   if (p.d == 128) {
     if (nm <= 2) return launch_select_t<128, 2>(a, stream);

@@ -25,6 +25,9 @@ UpdateWs carve_update_ws(const pbsa_params& p, void* base);
 
 hipError_t launch_pool_blocks(const pbsa_params& p, const bf16_t* X, const int32_t* len, int32_t n_blocks,
                               float* out, hipStream_t stream);
+hipError_t launch_append(const pbsa_params& p, const bf16_t* K, const bf16_t* V, int64_t k_stride_h, int64_t k_stride_t,
+                         int64_t v_stride_h, int64_t v_stride_t, int32_t slot0, int32_t zero_tail, bf16_t* Kl, bf16_t* Vl,
+                         float* Kc_l, hipStream_t stream);
 hipError_t launch_summary_view(const pbsa_params& p, const float* S_sum, const int32_t* S_cnt, bf16_t* Kp, bf16_t* Vp,
                                int32_t* p_len, hipStream_t stream);
 hipError_t launch_select(const pbsa_params& p, const bf16_t* Q, const bf16_t* Kl, const int32_t* l_len,

@@ -17,7 +17,7 @@ PBSA_MAX_N_LOC, PBSA_MAX_C, PBSA_MAX_C_ATTEND, PBSA_MAX_K = 672, 64, 336, 672
 PBSA_MAX_N_LOC_AUX, PBSA_MAX_C_AUX, PBSA_MAX_K_AUX = 512, 192, 512
 PBSA_STATIC_WS_BYTES = 4 << 20
 
-EXPORTS = ("pbsa_workspace_bytes", "pbsa_pool_blocks", "pbsa_summary_view", "pbsa_select_blocks", "pbsa_attention_fwd",
+EXPORTS = ("pbsa_workspace_bytes", "pbsa_pool_blocks", "pbsa_summary_view", "pbsa_append_chunk", "pbsa_select_blocks", "pbsa_attention_fwd",
            "pbsa_memory_update", "pbsa_memory_update_static", "pbsa_memory_update_plan", "pbsa_memory_update_apply", "pbsa_attention_fwd_plan",
            "pbsa_select_blocks_apply",
            "pbsa_attention_mass", "pbsa_mass_workspace_bytes", "pbsa_attention_fwd_mass",
@@ -79,6 +79,8 @@ def lib() -> ctypes.CDLL:
         L.pbsa_workspace_bytes.argtypes = [pp, ctypes.POINTER(sz)]
         L.pbsa_pool_blocks.argtypes = [pp, vp, vp, i32, vp, vp]
         L.pbsa_summary_view.argtypes = [pp] + [vp] * 6
+        i64 = ctypes.c_int64
+        L.pbsa_append_chunk.argtypes = [pp, vp, vp, i64, i64, i64, i64, i32, i32, vp, vp, vp, vp]
         L.pbsa_select_blocks.argtypes = [pp] + [vp] * 9 + [sz, vp]
         L.pbsa_attention_fwd.argtypes = [pp] + [vp] * 12 + [sz, vp]
         L.pbsa_memory_update.argtypes = [pp] + [vp] * 18 + [sz, vp]
@@ -96,8 +98,8 @@ def lib() -> ctypes.CDLL:
         pg = ctypes.POINTER(pbsa_grid)
         L.pbsa_blockify.argtypes = [pg, i32, ctypes.POINTER(vp), ctypes.POINTER(vp), ctypes.POINTER(ctypes.c_int64), vp]
         L.pbsa_unblockify.argtypes = [pg, vp, ctypes.c_int64, vp, vp]
-        for name in ("pbsa_workspace_bytes", "pbsa_pool_blocks", "pbsa_summary_view", "pbsa_select_blocks", "pbsa_attention_fwd",
-                     "pbsa_memory_update", "pbsa_memory_update_static", "pbsa_memory_update_plan", "pbsa_memory_update_apply",
+        for name in ("pbsa_workspace_bytes", "pbsa_pool_blocks", "pbsa_summary_view", "pbsa_append_chunk", "pbsa_select_blocks",
+                     "pbsa_attention_fwd", "pbsa_memory_update", "pbsa_memory_update_static", "pbsa_memory_update_plan", "pbsa_memory_update_apply",
                      "pbsa_attention_fwd_plan", "pbsa_select_blocks_apply", "pbsa_attention_mass", "pbsa_mass_workspace_bytes",
                      "pbsa_attention_fwd_mass", "pbsa_memory_update_fine", "pbsa_bwd_workspace_bytes",
                      "pbsa_attention_bwd", "pbsa_blockify", "pbsa_unblockify"):
@@ -161,6 +163,13 @@ def pbsa_pool_blocks(p, X, length, n_blocks, out, stream=None):
 
 def pbsa_summary_view(p, S_sum, S_cnt, Kp, Vp, p_len, stream=None):
     _check(lib().pbsa_summary_view(ctypes.byref(p), _ptr(S_sum), _ptr(S_cnt), _ptr(Kp), _ptr(Vp), _ptr(p_len), _stream(stream)))
+
+
+def pbsa_append_chunk(p, K, V, slot0, zero_tail, Kl, Vl, Kc_l=None, stream=None):
+    """K, V: [H][Nq][d] bf16 with a contiguous last dimension, or None."""
+    ks, vs = (x.stride() if x is not None else (0, 0, 1) for x in (K, V))
+    _check(lib().pbsa_append_chunk(ctypes.byref(p), _ptr(K), _ptr(V), ks[0], ks[1], vs[0], vs[1], slot0, int(zero_tail),
+                                   _ptr(Kl), _ptr(Vl), _ptr(Kc_l), _stream(stream)))
 
 
 def pbsa_select_blocks(p, Q, Kl, l_len, l_map, Kc_l, Qc, sel, Zl=None, ws=None, stream=None):

@@ -1,0 +1,57 @@
+"""pbsa_append_chunk against torch copies and pbsa_pool_blocks: every byte of the rings and every bit of the pooled keys
+(the same pinned additions), at the edges of a block (one token, one short of full, full) and for strided sources."""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("d,B,Nq", [(64, 64, 1), (64, 64, 256), (64, 128, 127), (128, 64, 129), (128, 128, 1000), (128, 64, 4680)])
+@pytest.mark.parametrize("strided", [False, True], ids=["dense", "strided"])
+def test_append_matches_copies_and_pooling(d, B, Nq, strided):
+    from paper_2604_21221_amd import pbsa
+    from paper_2604_21221_amd.cache import PbsaCache
+    H, w = 3, 1
+    gen = torch.Generator(device=DEV).manual_seed(Nq + d + B)
+    def draw():
+        if strided:                       # [Nq][H][3 d], one third of it, heads in the middle
+            return torch.randn(Nq, H, 3 * d, generator=gen, device=DEV).to(torch.bfloat16)[:, :, d:2 * d].permute(1, 0, 2)
+        return torch.randn(H, Nq, d, generator=gen, device=DEV).to(torch.bfloat16)
+    c = PbsaCache(H, d, B, Nq, w, 2, 1, d ** -0.5, device=DEV)
+    c.Kl.fill_(7.0), c.Vl.fill_(7.0), c.Kc_l.fill_(7.0)
+    print(f"[case] append d={d} B={B} Nq={Nq} strided={strided}", flush=True)
+    want_K, want_V = c.Kl.clone(), c.Vl.clone()
+    def put(dst, pos, x, tail):
+        rows = dst[:, pos * c.nqb:(pos + 1) * c.nqb].view(H, c.nqb * B, d)
+        rows[:, :Nq] = x
+        if tail:
+            rows[:, Nq:] = 0
+    def same(a, b):
+        return torch.equal(a.view(torch.int16), b.view(torch.int16))
+    def pooled(pos):
+        lens = c._chunk_lens.repeat(H).to(DEV)
+        X = want_K[:, pos * c.nqb:(pos + 1) * c.nqb].contiguous()
+        out = torch.empty(H * c.nqb, d, device=DEV)
+        pbsa.pbsa_pool_blocks(c.params(), X, lens, H * c.nqb, out)
+        return out.view(H, c.nqb, d)
+    for g in range(2):
+        K, V = draw(), draw()
+        c.append_chunk(K, V, g)
+        put(want_K, g, K, True), put(want_V, g, V, True)
+        assert same(c.Kl, want_K) and same(c.Vl, want_V)
+        assert torch.equal(c.Kc_l[:, g * c.nqb:(g + 1) * c.nqb], pooled(g)), "pooled keys"
+        if g == 0:
+            assert torch.all(c.Kc_l[:, c.nqb:] == 7.0), "another chunk's pooled keys were touched"
+    tail_K = c.Kl[:, -1, Nq - (c.nqb - 1) * B:].clone()
+    K = draw()
+    c.rewrite_chunk(K)                     # K alone, the rows past the chunk's end stay
+    put(want_K, 1, K, False)
+    assert same(c.Kl, want_K) and same(c.Vl, want_V) and same(c.Kl[:, -1, Nq - (c.nqb - 1) * B:], tail_K)
+    Q = draw()
+    c.select(Q)                            # the keys pooled on the way in and the selection's own pooling agree
+    kept = c.Kc_l.clone(), c.sel.clone(), c.Qc.clone()
+    c.stale_from = 0
+    c.select(Q)
+    assert all(torch.equal(a, b) for a, b in zip(kept, (c.Kc_l, c.sel, c.Qc)))
