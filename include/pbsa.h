@@ -110,9 +110,9 @@ typedef struct pbsa_params {
   int64_t o_stride_h, o_stride_t;
 } pbsa_params;
 
-/* Bytes of scratch that any call with these parameters may need (device memory, 256-byte aligned,
- * passed as `ws`).  Contents need not be preserved between calls.  Only pbsa_memory_update needs any, so
- * C is held to PBSA_MAX_C here as there. */
+/* Bytes of scratch that any call with these parameters needs (device memory, 256-byte aligned, passed as `ws`).
+ * Contents need not be preserved between calls.  Only pbsa_memory_update in all its forms needs any, so C is held to
+ * PBSA_MAX_C here as there.  (pbsa_attention_workspace_bytes: what an attention call can use beyond that.) */
 int pbsa_workspace_bytes(const pbsa_params* p, size_t* out);
 
 /* Block representatives by average pooling (Eq. 6; pooling operator of Sec. 4.1):
@@ -157,7 +157,13 @@ int pbsa_select_blocks(const pbsa_params* p, const void* Q, const void* Kl, cons
  * accumulation and fp32 online softmax; the probabilities are rounded to bf16 for the second product and
  * the normaliser is their sum after rounding; O is rounded to bf16 (nearest even).  `lse` (optional,
  * [H][Nq] fp32) receives the natural log of that normaliser (within 4e-3 of the exact one).  A row that sees no key gets O = 0,
- * lse = -inf.  Entries of sel must be -1 or in [0, n_loc).  ws may be NULL. */
+ * lse = -inf.  Entries of sel must be -1 or in [0, n_loc).
+ * ws may be NULL.  Given pbsa_attention_workspace_bytes(p) bytes (which may be 0; 256-byte aligned), a launch whose last
+ * round of workgroups would leave most of the GPU idle shares the keys of those rows out over it and puts the
+ * partial results together in fp32 in a second launch: the same softmax in another order of summation, decided by the
+ * shape alone.  pbsa_attention_fwd_plan and pbsa_attention_fwd_mass do the same when the workspaces they take are that
+ * much larger than they need. */
+int pbsa_attention_workspace_bytes(const pbsa_params* p, size_t* out);
 int pbsa_attention_fwd(const pbsa_params* p, const void* Q, const void* Kp, const void* Vp, const int32_t* p_len,
                        const void* Kl, const void* Vl, const int32_t* l_len, const int32_t* l_map,
                        const int32_t* sel, void* O, float* lse, void* ws, size_t ws_bytes, void* hip_stream);

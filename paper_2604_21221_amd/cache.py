@@ -44,8 +44,13 @@ class PbsaCache:
         self.scores = z(H, C + self.nqb, dt=torch.float32)
         full = pbsa.make_params(H, d, B, Nq, self.cap, self.cap, C, k, self.scale, n_sink, causal, n_evict=self.nqb)
         # with more slots than pbsa_memory_update maintains the cache can only be selected from and attended
+        attends = C <= pbsa.PBSA_MAX_C_ATTEND and self.cap <= pbsa.PBSA_MAX_N_LOC and k <= pbsa.PBSA_MAX_K
+        n_attn = pbsa.pbsa_attention_workspace_bytes(full) if attends else 0
         n_ws = pbsa.pbsa_workspace_bytes(full) if C <= pbsa.PBSA_MAX_C else 0
-        self.ws = torch.empty(max(n_ws, 256), dtype=torch.uint8, device=self.dev)
+        self.ws = torch.empty(max(n_ws + n_attn, 256), dtype=torch.uint8, device=self.dev)
+        # the attention's share lies behind what an update in flight still needs
+        self._attn_ws = self.ws[n_ws:] if n_attn else None
+        self._attn_bytes = n_attn
         self.chunk_pos = []          # ring position of each chunk in the local region, oldest first
         self.chunk_ids = []          # global chunk index of each
         self.n_appended = 0
@@ -186,7 +191,8 @@ class PbsaCache:
             O = torch.empty_like(Q)
         l_map, l_len, _ = self._device_maps()
         p = self.params(Q=Q, O=O)
-        pbsa.pbsa_attention_fwd(p, Q, self.Kp, self.Vp, self.p_len, self.Kl, self.Vl, l_len, l_map, self.sel, O, lse)
+        pbsa.pbsa_attention_fwd(p, Q, self.Kp, self.Vp, self.p_len, self.Kl, self.Vl, l_len, l_map, self.sel, O, lse,
+                                self._attn_ws)
         return O
 
     def _no_pending(self):
@@ -243,7 +249,7 @@ class PbsaCache:
             lse = self._lse
         if getattr(self, "_mass_ws", None) is None:
             full = pbsa.make_params(self.H, self.d, self.B, self.Nq, self.cap, self.cap, self.C, self.k, self.scale)
-            self._mass_ws = torch.empty(pbsa.pbsa_mass_workspace_bytes(full), dtype=torch.uint8, device=self.dev)
+            self._mass_ws = torch.empty(pbsa.pbsa_mass_workspace_bytes(full) + self._attn_bytes, dtype=torch.uint8, device=self.dev)
         Mt = self._mass_buffer()
         l_map, l_len, _ = self._device_maps()
         p = self.params(Q=Q, O=O)

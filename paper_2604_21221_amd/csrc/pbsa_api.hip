@@ -47,6 +47,13 @@ int check_strides(int64_t sh, int64_t st, const pbsa_params* p) {
 
 size_t workspace_bytes(const pbsa_params& p) { return pbsa::carve_update_ws(p, nullptr).bytes; }
 
+// Scratch for the split of an attention launch: what lies `used` bytes into a workspace, or nullptr where that is not
+// enough (nothing is split then).  `used` is a multiple of 256.
+void* split_scratch(const pbsa_params& p, void* ws, size_t ws_bytes, size_t used) {
+  if (!ws || (reinterpret_cast<uintptr_t>(ws) & 255u) || ws_bytes < used + pbsa::attn_split(p).bytes) return nullptr;
+  return static_cast<char*>(ws) + used;
+}
+
 }  // namespace
 
 // Scratch of pbsa_memory_update_static: device memory that belongs to the library, one copy per GPU, for callers
@@ -192,10 +199,17 @@ int pbsa_select_blocks_apply(const pbsa_params* p, const void* Q, const void* Kl
   return e == hipSuccess ? PBSA_OK : hip_fail(e);
 }
 
+int pbsa_attention_workspace_bytes(const pbsa_params* p, size_t* out) {
+  if (!out) return PBSA_EINVAL;
+  int rc = check_common(p, PBSA_MAX_C_ATTEND, PBSA_MAX_N_LOC, PBSA_MAX_K);
+  if (rc) return rc;
+  *out = pbsa::attn_split(*p).bytes;
+  return PBSA_OK;
+}
+
 int pbsa_attention_fwd(const pbsa_params* p, const void* Q, const void* Kp, const void* Vp, const int32_t* p_len,
                        const void* Kl, const void* Vl, const int32_t* l_len, const int32_t* l_map,
                        const int32_t* sel, void* O, float* lse, void* ws, size_t ws_bytes, void* hip_stream) {
-  (void)ws; (void)ws_bytes;
   int rc = check_common(p, PBSA_MAX_C_ATTEND, PBSA_MAX_N_LOC, PBSA_MAX_K);
   if (rc) return rc;
   if (!Q || !Kp || !Vp || !p_len || !Kl || !Vl || !l_len || !l_map || !O) return PBSA_EINVAL;
@@ -210,6 +224,7 @@ int pbsa_attention_fwd(const pbsa_params* p, const void* Q, const void* Kp, cons
       *p, static_cast<const pbsa::bf16_t*>(Q), static_cast<const pbsa::bf16_t*>(Kp),
       static_cast<const pbsa::bf16_t*>(Vp), p_len, static_cast<const pbsa::bf16_t*>(Kl),
       static_cast<const pbsa::bf16_t*>(Vl), l_len, l_map, sel, static_cast<pbsa::bf16_t*>(O), lse, nullptr,
+      split_scratch(*p, ws, ws_bytes, 0),
       static_cast<hipStream_t>(hip_stream));
   return e == hipSuccess ? PBSA_OK : hip_fail(e);
 }
@@ -244,7 +259,8 @@ int pbsa_attention_fwd_mass(const pbsa_params* p, const void* Q, const void* Kp,
   hipError_t e = pbsa::launch_attention(
       *p, static_cast<const pbsa::bf16_t*>(Q), static_cast<const pbsa::bf16_t*>(Kp),
       static_cast<const pbsa::bf16_t*>(Vp), p_len, static_cast<const pbsa::bf16_t*>(Kl),
-      static_cast<const pbsa::bf16_t*>(Vl), l_len, l_map, sel, static_cast<pbsa::bf16_t*>(O), lse, &rows, stream);
+      static_cast<const pbsa::bf16_t*>(Vl), l_len, l_map, sel, static_cast<pbsa::bf16_t*>(O), lse, &rows,
+      split_scratch(*p, ws, ws_bytes, rows.bytes), stream);
   if (e != hipSuccess) return hip_fail(e);
   e = pbsa::launch_mass_reduce(*p, rows, lse, Mt, stream);
   return e == hipSuccess ? PBSA_OK : hip_fail(e);
@@ -338,7 +354,8 @@ int pbsa_attention_fwd_plan(const pbsa_params* p, const void* Q, const void* Kp,
       *p, static_cast<const pbsa::bf16_t*>(Q), static_cast<const pbsa::bf16_t*>(Kp),
       static_cast<const pbsa::bf16_t*>(Vp), p_len, static_cast<const pbsa::bf16_t*>(Kl),
       static_cast<const pbsa::bf16_t*>(Vl), l_len, l_map, sel, static_cast<pbsa::bf16_t*>(O), lse, Qc, Kc_l, Zl, Kc_p,
-      p_id, S_cnt, S_cnt != nullptr, l_id, scores, slot_src, w, static_cast<hipStream_t>(hip_stream));
+      p_id, S_cnt, S_cnt != nullptr, l_id, scores, slot_src, w, split_scratch(*p, ws, ws_bytes, w.bytes),
+      static_cast<hipStream_t>(hip_stream));
   return e == hipSuccess ? PBSA_OK : hip_fail(e);
 }
 

@@ -79,6 +79,13 @@ constexpr float kInitMax = -1.0e29f;       // reference of a row that has seen n
 // the reference contributes nothing (less than 2^-46 of that score's weight), and after the first sub-tile
 // of a row a new reference needs scores that rise by a factor of 2^kLift.
 constexpr float kLift = 80.0f;
+// Splitting (attn_split): the most parts of a query tile, and the model that picks their number, in microseconds: a tile
+// of a walk on an idle chip (13 to 53 tiles: 1.3-1.5 at d = 128, 0.95 at d = 64), the second launch (4.7 in a trace), what
+// a partial result moves, and the least gain worth it (the launch's host time).  Measured, whole against split: 5 heads
+// x 1000 rows of 64, 26 tiles, 32.8 -> 17.1 + 5.0 us; 3 x 1500 rows of 64, 19 tiles, 27.6 -> 14.1 + 4.7; two heads x 256
+// rows, 7 tiles, 13.4 -> 11.1 + 4.7, which the rule leaves whole.
+constexpr int kMaxParts = 16;
+constexpr float kTileUs128 = 1.4f, kTileUs64 = 0.95f, kCombineUs = 5.0f, kPartBytesPerUs = 3e6f, kSplitWorthUs = 2.0f;
 constexpr uint32_t kTooBig = 0x40004000u;  // the top exponent bit of both halves of a bf16 pair
 
 __device__ __forceinline__ int lanes_below(unsigned long long mask) {   // set bits of `mask` below this lane
@@ -104,6 +111,10 @@ struct AttnArgs {
   float* R;
   int32_t* Rlist;
   int r_slots, list_cap;
+  // split variant only (AttnSplit): query tiles [0, n_full) whole, the others in `parts` parts each
+  int n_full, parts;
+  float* part_o;      // [split tile][part][wave][row group][DT][4][64 lanes][4] unnormalised O^T as the accumulators hold it
+  float* part_ml;     // [split tile][part][wave][row group][32 rows][2] softmax reference and sum of probabilities
 };
 
 // LDS layout of a 64-key tile: unpadded rows of D bf16 whose 16-byte chunks are permuted within the
@@ -699,7 +710,11 @@ struct PlanArgs<true> {
 // cache's metadata and pooled keys and what the selection call left, never K / V or the attention's output, and
 // a one-round launch leaves them SIMDs to run on (two workgroups per CU, 128 rows each: at 4680 rows and 12
 // heads 444 of 512 places are taken).
-template <int D, int B, bool MASS, bool PLAN>
+//
+// SPLIT: the workgroups of the last round -- all of them where the launch has less than one -- are shared out over the
+// places that round would leave empty: the tile list of a query tile goes to `parts` workgroups, an equal share of
+// every class to each, which leave O^T unnormalised with its reference and sum to combine_kernel (attn_split).
+template <int D, int B, bool MASS, bool PLAN, bool SPLIT>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1)))
 attention_kernel(AttnArgs a, PlanArgs<PLAN> pl) {
   constexpr int G = kRowsPerWg / B;        // query blocks per workgroup
@@ -743,8 +758,21 @@ attention_kernel(AttnArgs a, PlanArgs<PLAN> pl) {
     }
   }
   const int bx = (int)blockIdx.x - n_plan;
-  const int logical = (bx % 8) * per + bx / 8;
-  if (logical >= n_wg) return;
+  int logical, part = 0, n_parts = 1;
+  if constexpr (SPLIT) {
+    if (bx < a.n_full) {                   // a whole number of rounds
+      logical = (bx % 8) * (a.n_full / 8) + bx / 8;
+    } else {
+      const int nu = (n_wg - a.n_full) * a.parts, u = bx - a.n_full, lu = (u % 8) * ((nu + 7) / 8) + u / 8;
+      if (u / 8 >= (nu + 7) / 8 || lu >= nu) return;
+      logical = a.n_full + lu / a.parts;
+      part = lu % a.parts;
+      n_parts = a.parts;
+    }
+  } else {
+    logical = (bx % 8) * per + bx / 8;
+    if (logical >= n_wg) return;
+  }
   const int h = logical / n_qt;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -831,8 +859,21 @@ attention_kernel(AttnArgs a, PlanArgs<PLAN> pl) {
 #pragma unroll
     for (int c = 0; c < 4; ++c) tot[c] += __popcll(__ballot(cls == c));
   }
-  int base[4] = {0, tot[0], tot[0] + tot[1], tot[0] + tot[1] + tot[2]};
-  const int cls_end[4] = {base[1], base[2], base[3], base[3] + tot[3]};
+  // this workgroup's tiles of each class: all of them, or ranks lo .. lo + num - 1 (the classes take the parts in opposite
+  // orders, so that the remainders do not meet in one part)
+  int lo[4] = {0, 0, 0, 0}, num[4] = {tot[0], tot[1], tot[2], tot[3]};
+  if constexpr (SPLIT) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int p = c == 0 ? part : n_parts - 1 - part;
+      lo[c] = tot[c] * p / n_parts;
+      num[c] = tot[c] * (p + 1) / n_parts - lo[c];
+    }
+  }
+  const int first[4] = {0, num[0], num[0] + num[1], num[0] + num[1] + num[2]};
+  const int cls_end[4] = {first[1], first[2], first[3], first[3] + num[3]};
+  int base[4] = {first[0] - lo[0], first[1] - lo[1], first[2] - lo[2], first[3] - lo[3]};
+  int32_t* mass_list = MASS ? a.Rlist + (size_t)logical * a.list_cap : nullptr;
   for (int r = 0; r < n_rounds; ++r) {
     int src = 0, meta = 0;
     const int cls = classify(r * 64 + lane, src, meta);
@@ -842,8 +883,14 @@ attention_kernel(AttnArgs a, PlanArgs<PLAN> pl) {
       const unsigned long long m = __ballot(cls == c);
       if (cls == c && mine) {
         const int pos = base[c] + lanes_below(m);
-        t_src[pos] = src;
-        t_meta[pos] = (meta_t)meta;
+        if (!SPLIT || (pos >= first[c] && pos < cls_end[c])) {
+          t_src[pos] = src;
+          t_meta[pos] = (meta_t)meta;
+        }
+        if constexpr (SPLIT && MASS) {     // the later pass walks the whole list, whoever walked its parts
+          const int at = pos - first[c] + lo[c] + (c > 0 ? tot[0] : 0) + (c > 1 ? tot[1] : 0) + (c > 2 ? tot[2] : 0);
+          if (part == 0 && at < a.list_cap - 4) mass_list[4 + at] = meta;
+        }
       }
       base[c] += __popcll(m);
     }
@@ -859,13 +906,20 @@ attention_kernel(AttnArgs a, PlanArgs<PLAN> pl) {
   MassOut mo{nullptr, lane, lane >= 32, 0.0f, 0.0f};
   if constexpr (MASS) {
     // the later pass walks the same list: the ends of its four parts, then a descriptor per tile
-    int32_t* out = a.Rlist + (size_t)logical * a.list_cap;
-    if (tid == 0) {
-      out[0] = cls_end[0]; out[1] = cls_end[1]; out[2] = cls_end[2]; out[3] = cls_end[3];
+    if (tid == 0 && part == 0) {
+      mass_list[0] = tot[0];
+      mass_list[1] = tot[0] + tot[1];
+      mass_list[2] = tot[0] + tot[1] + tot[2];
+      mass_list[3] = tot[0] + tot[1] + tot[2] + tot[3];
     }
-    for (int i = tid; i < cls_end[3] && i < a.list_cap - 4; i += kThreads) out[4 + i] = t_meta[i];
+    if constexpr (!SPLIT)
+      for (int i = tid; i < cls_end[3] && i < a.list_cap - 4; i += kThreads) mass_list[4 + i] = t_meta[i];
     mo.rp = a.R + ((size_t)logical * 2 + wave) * a.r_slots * 64;
   }
+  // the records of a split walk go where the whole walk would leave them
+  float* const rec0 = mo.rp;
+#define PBSA_RECORDS_AT(TILE_)                                                                          \
+  if constexpr (SPLIT && MASS) mo.rp = rec0 + (size_t)(TILE_) * 64;
   const int e0 = cls_end[0];               // shared full tiles [0, e0)
   const int n_tiles = cls_end[1];          // shared ragged tiles [e0, n_tiles): the end of the shared list
   const int solo_b = wave == 0 ? n_tiles : cls_end[2];         // this wave's solo tiles [solo_b, solo_e)
@@ -1069,7 +1123,9 @@ attention_kernel(AttnArgs a, PlanArgs<PLAN> pl) {
     __syncthreads();
     int d_ksrc, d_vsrc, d_vmeta;
     PBSA_FETCH_DESC(0)
+    PBSA_RECORDS_AT(lo[0])
     PBSA_RUN_SHARED(false, 0, e0)
+    PBSA_RECORDS_AT(tot[0] + lo[1])
     PBSA_RUN_SHARED(true, e0, n_tiles)
   }
 
@@ -1089,6 +1145,7 @@ attention_kernel(AttnArgs a, PlanArgs<PLAN> pl) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (solo_b < solo_e) {
+      PBSA_RECORDS_AT(tot[0] + tot[1] + (wave == 0 ? lo[2] : lo[3]))
       const unsigned char* kl_h = reinterpret_cast<const unsigned char*>(a.Kl) + head_l;
       const unsigned char* vl_h = reinterpret_cast<const unsigned char*>(a.Vl) + head_l;
       const uint32_t kring = smem_s + wave * TILE, vring = smem_s + (2 + wave) * TILE;
@@ -1147,6 +1204,26 @@ attention_kernel(AttnArgs a, PlanArgs<PLAN> pl) {
   acc_settle<DT>(o[0]);
   acc_settle<DT>(o[1]);
   sum_settle(sr.l_run);
+  if constexpr (SPLIT) {
+    if (n_parts > 1) {
+      // one of several: whole 1 KiB stores, in the accumulators' own order
+      const size_t slot = (size_t)(logical - a.n_full) * n_parts + part;
+      float* po = a.part_o + slot * (kRowsPerWg * D) + wave * (64 * D) + lane * 4;
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+          for (int q4 = 0; q4 < 4; ++q4)
+            *reinterpret_cast<float4*>(po + ((g * DT + dt) * 4 + q4) * 256) =
+                make_float4(o[g][dt][4 * q4], o[g][dt][4 * q4 + 1], o[g][dt][4 * q4 + 2], o[g][dt][4 * q4 + 3]);
+        const float l_part = __shfl(sr.l_run[0], 32 * g + qn, 64);
+        if (half == 0)
+          *reinterpret_cast<float2*>(a.part_ml + (slot * kRowsPerWg + wave * 64 + g * 32 + qn) * 2) = make_float2(sr.m_ref[g], l_part);
+      }
+      return;
+    }
+  }
 #pragma unroll
   for (int g = 0; g < 2; ++g) {
     // row r of the group: lane 32 g + r of the running sums
@@ -1171,16 +1248,122 @@ attention_kernel(AttnArgs a, PlanArgs<PLAN> pl) {
 }
 #pragma clang diagnostic pop
 
+// ------------------------------------------------------------------------------------------------
+// Puts the parts of a split query tile together: O = sum_s w_s O_s / sum_s w_s l_s with w_s = 2^((m_s - max m) c2).  One
+// wave instruction reads one of the 1 KiB pieces the attention wave stored (same lane, same elements); the row of a
+// lane is lane % 32 of the piece's row group.  A part that met no key of a row has l_s = 0.
+// ------------------------------------------------------------------------------------------------
+constexpr int kCombineThreads = 256;
+template <int D>
+__global__ void __launch_bounds__(kCombineThreads) combine_kernel(AttnArgs a) {
+  constexpr int DT = D / 32, PIECES = 4 * DT * 4;          // per query tile: 2 waves x 2 row groups x DT x 4
+  const int lane = threadIdx.x & 63, qn = lane & 31, half = lane >> 5;
+  const int piece = blockIdx.x * (kCombineThreads / 64) + (threadIdx.x >> 6);
+  static_assert(PIECES % (kCombineThreads / 64) == 0, "whole workgroups");
+  const int wg = piece / (DT * 4), dt = piece / 4 % DT, q4 = piece % 4;      // wave and row group, output tile, quarter
+  const int n_qt = (a.Nq + kRowsPerWg - 1) / kRowsPerWg, tile = a.n_full + blockIdx.y;
+  const int h = tile / n_qt, tok = (tile % n_qt) * kRowsPerWg + wg * 32 + qn;
+  if (tok >= a.Nq) return;
+  const size_t slot0 = (size_t)blockIdx.y * a.parts;
+  const float2* ml = reinterpret_cast<const float2*>(a.part_ml) + slot0 * kRowsPerWg + wg * 32 + qn;
+  const float* po = a.part_o + slot0 * (kRowsPerWg * D) + piece * 256 + lane * 4;
+  const float c2 = a.scale * 1.4426950408889634f;
+  float m[kMaxParts], l_tot = 0.0f, m_max = kInitMax;
+  float4 acc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  float l[kMaxParts];
+#pragma unroll
+  for (int s = 0; s < kMaxParts; ++s) {
+    const float2 v = s < a.parts ? ml[(size_t)s * kRowsPerWg] : make_float2(kInitMax, 0.0f);
+    m[s] = v.x;
+    l[s] = v.y;
+    if (v.y > 0.0f) m_max = fmaxf(m_max, v.x);
+  }
+#pragma unroll
+  for (int s = 0; s < kMaxParts; ++s) {
+    if (s < a.parts) {
+      const float4 v = *reinterpret_cast<const float4*>(po + (size_t)s * (kRowsPerWg * D));
+      const float w = l[s] > 0.0f ? __builtin_amdgcn_exp2f((m[s] - m_max) * c2) : 0.0f;
+      l_tot = __builtin_fmaf(w, l[s], l_tot);
+      acc.x = __builtin_fmaf(w, v.x, acc.x);
+      acc.y = __builtin_fmaf(w, v.y, acc.y);
+      acc.z = __builtin_fmaf(w, v.z, acc.z);
+      acc.w = __builtin_fmaf(w, v.w, acc.w);
+    }
+  }
+  const float inv = l_tot > 0.0f ? 1.0f / l_tot : 0.0f;
+  bf16x4 w4;
+  w4[0] = (__bf16)(acc.x * inv);
+  w4[1] = (__bf16)(acc.y * inv);
+  w4[2] = (__bf16)(acc.z * inv);
+  w4[3] = (__bf16)(acc.w * inv);
+  *reinterpret_cast<bf16x4*>(a.O + (size_t)h * a.o_stride_h + (size_t)tok * a.o_stride_t + 32 * dt + 8 * q4 + 4 * half) = w4;
+  if (a.lse && dt == 0 && q4 == 0 && half == 0)
+    a.lse[(size_t)h * a.Nq + tok] = l_tot > 0.0f ? m_max * a.scale + __logf(l_tot) : -INFINITY;
+}
+
 }  // namespace
 
-template <bool MASS, bool PLAN>
-static void launch_attention_t(const pbsa_params& p, const AttnArgs& a, const PlanArgs<PLAN>& pl, dim3 grid,
+// How a launch is shared out (see SPLIT at attention_kernel).  The chip runs kPlaces workgroups at a time, so a launch
+// of n query tiles lasts ceil(n / kPlaces) rounds and its last round may be nearly empty: a chunk of 5 heads x 1000 rows
+// is 40 workgroups on 512 places.  The tiles of that last round are split over as many workgroups as it has places for,
+// as long as a shorter walk gains more than the second launch and the partial results cost.  Depends on the shape
+// alone, so that every call of a shape -- with decisions, with mass, plain -- takes the same parts.
+AttnSplit attn_split(const pbsa_params& p) {
+  constexpr int kPlaces = 512;
+  AttnSplit sp{0, 1, 0, 0, 0};
+  const long n_wg = (long)p.H * ((p.Nq + kRowsPerWg - 1) / kRowsPerWg), n_full = n_wg / kPlaces * kPlaces, r = n_wg - n_full;
+  const int tiles = (p.C + 1 + (p.k < p.n_loc_cap ? p.k : p.n_loc_cap)) * (p.B / kTile);
+  if (r == 0 || r > kPlaces / 2) return sp;
+  const float t_tile = p.d == 128 ? kTileUs128 : kTileUs64;
+  const float part_us = (float)(2 * kRowsPerWg * p.d * 4) / kPartBytesPerUs;
+  float best = tiles * t_tile - kSplitWorthUs;
+  for (int s = 2; s <= kMaxParts && s <= tiles && s * r <= kPlaces; ++s) {
+    const float us = (float)((tiles + s - 1) / s) * t_tile + kCombineUs + (float)(r * s) * part_us;
+    if (us < best) {
+      best = us;
+      sp.parts = s;
+    }
+  }
+  if (sp.parts == 1) return sp;
+  sp.n_full = (int)n_full;
+  sp.n_split = (int)r;
+  sp.o_bytes = (size_t)r * sp.parts * kRowsPerWg * p.d * 4;
+  sp.bytes = sp.o_bytes + (size_t)r * sp.parts * kRowsPerWg * 8;
+  return sp;
+}
+
+template <bool MASS, bool PLAN, bool SPLIT>
+static void launch_attention_b(const pbsa_params& p, const AttnArgs& a, const PlanArgs<PLAN>& pl, dim3 grid,
                                hipStream_t stream) {
   const dim3 block(kThreads);
-  if (p.d == 128 && p.B == 128) hipLaunchKernelGGL((attention_kernel<128, 128, MASS, PLAN>), grid, block, 0, stream, a, pl);
-  else if (p.d == 128 && p.B == 64) hipLaunchKernelGGL((attention_kernel<128, 64, MASS, PLAN>), grid, block, 0, stream, a, pl);
-  else if (p.d == 64 && p.B == 128) hipLaunchKernelGGL((attention_kernel<64, 128, MASS, PLAN>), grid, block, 0, stream, a, pl);
-  else hipLaunchKernelGGL((attention_kernel<64, 64, MASS, PLAN>), grid, block, 0, stream, a, pl);
+  if (p.d == 128 && p.B == 128) hipLaunchKernelGGL((attention_kernel<128, 128, MASS, PLAN, SPLIT>), grid, block, 0, stream, a, pl);
+  else if (p.d == 128 && p.B == 64) hipLaunchKernelGGL((attention_kernel<128, 64, MASS, PLAN, SPLIT>), grid, block, 0, stream, a, pl);
+  else if (p.d == 64 && p.B == 128) hipLaunchKernelGGL((attention_kernel<64, 128, MASS, PLAN, SPLIT>), grid, block, 0, stream, a, pl);
+  else hipLaunchKernelGGL((attention_kernel<64, 64, MASS, PLAN, SPLIT>), grid, block, 0, stream, a, pl);
+}
+
+// split_ws: device scratch for attn_split(p).bytes, or nullptr: every query tile whole
+template <bool MASS, bool PLAN>
+static hipError_t launch_attention_t(const pbsa_params& p, AttnArgs a, const PlanArgs<PLAN>& pl, void* split_ws,
+                                     hipStream_t stream) {
+  const int n_wg = p.H * ((p.Nq + kRowsPerWg - 1) / kRowsPerWg);
+  const int n_plan = PLAN ? 8 * ((p.H + 7) / 8) : 0;
+  const AttnSplit sp = attn_split(p);
+  if (!split_ws || sp.parts == 1) {
+    launch_attention_b<MASS, PLAN, false>(p, a, pl, dim3(n_plan + 8 * ((n_wg + 7) / 8)), stream);
+    return hipGetLastError();
+  }
+  a.n_full = sp.n_full;
+  a.parts = sp.parts;
+  a.part_o = static_cast<float*>(split_ws);
+  a.part_ml = reinterpret_cast<float*>(static_cast<char*>(split_ws) + sp.o_bytes);
+  launch_attention_b<MASS, PLAN, true>(p, a, pl, dim3(n_plan + sp.n_full + 8 * ((sp.n_split * sp.parts + 7) / 8)), stream);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const dim3 cgrid(p.d / 32 * 16 / (kCombineThreads / 64), sp.n_split);
+  if (p.d == 128) hipLaunchKernelGGL(combine_kernel<128>, cgrid, dim3(kCombineThreads), 0, stream, a);
+  else hipLaunchKernelGGL(combine_kernel<64>, cgrid, dim3(kCombineThreads), 0, stream, a);
+  return hipGetLastError();
 }
 
 static AttnArgs attn_args(const pbsa_params& p, const bf16_t* Q, const bf16_t* Kp, const bf16_t* Vp, const int32_t* p_len,
@@ -1189,36 +1372,30 @@ static AttnArgs attn_args(const pbsa_params& p, const bf16_t* Q, const bf16_t* K
   return AttnArgs{p.H, p.Nq, p.nqb, p.n_loc, p.n_loc_cap, p.C, p.k, p.scale, p.q_stride_h, p.q_stride_t,
                   p.o_stride_h, p.o_stride_t, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse,
                   rows ? rows->R : nullptr, rows ? rows->list : nullptr, rows ? rows->r_slots : 0,
-                  rows ? rows->list_cap : 0};
+                  rows ? rows->list_cap : 0, 0, 1, nullptr, nullptr};
 }
 
 hipError_t launch_attention(const pbsa_params& p, const bf16_t* Q, const bf16_t* Kp, const bf16_t* Vp,
                             const int32_t* p_len, const bf16_t* Kl, const bf16_t* Vl, const int32_t* l_len,
                             const int32_t* l_map, const int32_t* sel, bf16_t* O, float* lse, const MassRows* rows,
-                            hipStream_t stream) {
+                            void* split_ws, hipStream_t stream) {
   const AttnArgs a = attn_args(p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse, rows);
-  const int n_wg = p.H * ((p.Nq + kRowsPerWg - 1) / kRowsPerWg);
-  const dim3 grid(8 * ((n_wg + 7) / 8));
-  if (rows) launch_attention_t<true, false>(p, a, PlanArgs<false>{}, grid, stream);
-  else launch_attention_t<false, false>(p, a, PlanArgs<false>{}, grid, stream);
-  return hipGetLastError();
+  return rows ? launch_attention_t<true, false>(p, a, PlanArgs<false>{}, split_ws, stream)
+              : launch_attention_t<false, false>(p, a, PlanArgs<false>{}, split_ws, stream);
 }
 
 hipError_t launch_attention_plan(const pbsa_params& p, const bf16_t* Q, const bf16_t* Kp, const bf16_t* Vp,
                                  const int32_t* p_len, const bf16_t* Kl, const bf16_t* Vl, const int32_t* l_len,
                                  const int32_t* l_map, const int32_t* sel, bf16_t* O, float* lse, const float* Qc,
                                  const float* Kc_l, const float* Zl, float* Kc_p, int64_t* p_id, int32_t* S_cnt, int fold,
-                                 const int64_t* l_id, float* scores, int32_t* slot_src, const UpdateWs& ws,
+                                 const int64_t* l_id, float* scores, int32_t* slot_src, const UpdateWs& ws, void* split_ws,
                                  hipStream_t stream) {
   const AttnArgs a = attn_args(p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse, nullptr);
   PlanArgs<true> pl;
   pl.sa = plan_dev::make_score_args(p, Qc, Kc_l, Zl, Kc_p, p_len, l_map, ws);
   pl.ra = plan_dev::make_retain_args(p, ws.A, p.C + p.n_loc, 0, Kc_l, Kc_p, p_len, p_id, S_cnt, fold, l_len, l_map, l_id,
                                      scores, slot_src, ws);
-  const int n_wg = p.H * ((p.Nq + kRowsPerWg - 1) / kRowsPerWg);
-  const dim3 grid(8 * ((n_wg + 7) / 8) + 8 * ((p.H + 7) / 8));
-  launch_attention_t<false, true>(p, a, pl, grid, stream);
-  return hipGetLastError();
+  return launch_attention_t<false, true>(p, a, pl, split_ws, stream);
 }
 
 }  // namespace pbsa

@@ -17,7 +17,7 @@ PBSA_MAX_N_LOC, PBSA_MAX_C, PBSA_MAX_C_ATTEND, PBSA_MAX_K = 672, 64, 336, 672
 PBSA_MAX_N_LOC_AUX, PBSA_MAX_C_AUX, PBSA_MAX_K_AUX = 512, 192, 512
 PBSA_STATIC_WS_BYTES = 4 << 20
 
-EXPORTS = ("pbsa_workspace_bytes", "pbsa_pool_blocks", "pbsa_summary_view", "pbsa_append_chunk", "pbsa_select_blocks", "pbsa_attention_fwd",
+EXPORTS = ("pbsa_workspace_bytes", "pbsa_pool_blocks", "pbsa_summary_view", "pbsa_append_chunk", "pbsa_attention_workspace_bytes", "pbsa_select_blocks", "pbsa_attention_fwd",
            "pbsa_memory_update", "pbsa_memory_update_static", "pbsa_memory_update_plan", "pbsa_memory_update_apply", "pbsa_attention_fwd_plan",
            "pbsa_select_blocks_apply",
            "pbsa_attention_mass", "pbsa_mass_workspace_bytes", "pbsa_attention_fwd_mass",
@@ -77,6 +77,7 @@ def lib() -> ctypes.CDLL:
         L.pbsa_strerror.restype = ctypes.c_char_p
         L.pbsa_strerror.argtypes = [ctypes.c_int]
         L.pbsa_workspace_bytes.argtypes = [pp, ctypes.POINTER(sz)]
+        L.pbsa_attention_workspace_bytes.argtypes = [pp, ctypes.POINTER(sz)]
         L.pbsa_pool_blocks.argtypes = [pp, vp, vp, i32, vp, vp]
         L.pbsa_summary_view.argtypes = [pp] + [vp] * 6
         i64 = ctypes.c_int64
@@ -98,7 +99,7 @@ def lib() -> ctypes.CDLL:
         pg = ctypes.POINTER(pbsa_grid)
         L.pbsa_blockify.argtypes = [pg, i32, ctypes.POINTER(vp), ctypes.POINTER(vp), ctypes.POINTER(ctypes.c_int64), vp]
         L.pbsa_unblockify.argtypes = [pg, vp, ctypes.c_int64, vp, vp]
-        for name in ("pbsa_workspace_bytes", "pbsa_pool_blocks", "pbsa_summary_view", "pbsa_append_chunk", "pbsa_select_blocks",
+        for name in ("pbsa_workspace_bytes", "pbsa_pool_blocks", "pbsa_summary_view", "pbsa_append_chunk", "pbsa_attention_workspace_bytes", "pbsa_select_blocks",
                      "pbsa_attention_fwd", "pbsa_memory_update", "pbsa_memory_update_static", "pbsa_memory_update_plan", "pbsa_memory_update_apply",
                      "pbsa_attention_fwd_plan", "pbsa_select_blocks_apply", "pbsa_attention_mass", "pbsa_mass_workspace_bytes",
                      "pbsa_attention_fwd_mass", "pbsa_memory_update_fine", "pbsa_bwd_workspace_bytes",
@@ -154,6 +155,12 @@ def pbsa_strerror(code: int) -> str:
 def pbsa_workspace_bytes(p: pbsa_params) -> int:
     out = ctypes.c_size_t(0)
     _check(lib().pbsa_workspace_bytes(ctypes.byref(p), ctypes.byref(out)))
+    return out.value
+
+
+def pbsa_attention_workspace_bytes(p: pbsa_params) -> int:
+    out = ctypes.c_size_t(0)
+    _check(lib().pbsa_attention_workspace_bytes(ctypes.byref(p), ctypes.byref(out)))
     return out.value
 
 

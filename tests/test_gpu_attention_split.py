@@ -1,0 +1,52 @@
+"""The attention launch whose last round of workgroups is shared out over the keys, against the same call without scratch
+(every query tile walked whole): parts with no tile of a class, ragged and empty slots, rows without keys, whole rounds
+ahead of the split one.
+
+Bound: both sides round every probability to bf16 (2^-9 relative, in numerator and normaliser alike) relative to
+references that differ, so an output differs by at most 2 (2^-9 + 2^-9) max|V| before it is rounded to bf16 itself
+(2^-9 |O| <= 2^-9 max|V| on either side): 3 * 2^-8 max|V|; lse by twice -log(1 - 2^-9)."""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("H,d,B,Nq,w,C,k,causal", [
+    (2, 64, 64, 256, 3, 2, 12, 1),         # more parts than most classes have tiles
+    (1, 128, 128, 300, 0, 30, 1, 1),       # nearly everything persistent
+    (3, 128, 64, 1000, 2, 5, 17, 1),       # two query blocks per workgroup: solo tiles
+    (3, 64, 64, 999, 1, 0, 20, 0),         # no slots but the (empty) summary
+    (5, 64, 128, 1000, 3, 5, 7, 0),
+    (1, 64, 64, 640, 1, 40, 0, 1),         # nothing selected
+    (40, 64, 64, 1664, 1, 3, 9, 1),        # 520 query tiles: 512 whole, 8 split
+])
+def test_split_matches_whole(H, d, B, Nq, w, C, k, causal):
+    from paper_2604_21221_amd import pbsa
+    from paper_2604_21221_amd.cache import PbsaCache
+    gen = torch.Generator(device=DEV).manual_seed(H + d + Nq)
+    rnd = lambda *s: torch.randn(*s, generator=gen, device=DEV).to(torch.bfloat16)
+    c = PbsaCache(H, d, B, Nq, w, C, k, d ** -0.5, causal=causal, device=DEV)
+    print(f"[case] split H={H} d={d} B={B} Nq={Nq} C={C} k={k}", flush=True)
+    for g in range(w + 1):
+        c.append_chunk(2.0 * rnd(H, Nq, d), rnd(H, Nq, d), g)
+    if C:
+        lens = torch.randint(0, B + 1, (H, C), generator=gen, device=DEV, dtype=torch.int32)
+        c.set_persistent(2.0 * rnd(H, C, B, d), rnd(H, C, B, d), lens, torch.arange(C)[None].repeat(H, 1))
+    Q = rnd(H, Nq, d)
+    c.select(Q)
+    assert c._attn_ws is not None and c._attn_ws.numel() > 0, "this shape is meant to be split"
+    lse, lse_w = (torch.empty(H, Nq, device=DEV) for _ in range(2))
+    O = c.attention(Q, lse=lse)
+    l_map, l_len, _ = c._device_maps()
+    O_w = torch.empty_like(Q)
+    pbsa.pbsa_attention_fwd(c.params(Q=Q, O=O_w), Q, c.Kp, c.Vp, c.p_len, c.Kl, c.Vl, l_len, l_map, c.sel, O_w, lse_w)
+    fin = torch.isfinite(lse_w)
+    assert torch.equal(torch.isfinite(lse), fin) and torch.equal(lse[~fin], lse_w[~fin])
+    assert float((lse - lse_w)[fin].abs().max() if fin.any() else 0.0) <= 2 * 1.96e-3
+    v_max = max(float(c.Vl.abs().max()), float(c.Vp.abs().max()))
+    assert float((O.float() - O_w.float()).abs().max()) <= 3 * 2.0 ** -8 * v_max
+    # the variant that records the mass takes the same parts
+    O_m, _ = c.attention_with_mass(Q)
+    assert torch.equal(O_m.view(torch.int16), O.view(torch.int16))
