@@ -1,4 +1,4 @@
-"""Builds libpbsa.so (HIP kernels + C ABI) in-tree for gfx950 with hipcc."""
+"""Builds libpbsa.so (HIP kernels + C ABI) in-tree for gfx950 with hipcc, and the binding's native half with g++."""
 from __future__ import annotations
 
 import os
@@ -10,6 +10,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libpbsa.so")
+HOST_LIB = os.path.join(PKG, "_pbsa_host.so")
 BUILD_DIR = os.path.join(ROOT, "_build")
 
 # source file -> extra flags.  The coarse/update kernels implement arithmetic that is specified
@@ -52,14 +53,31 @@ def _compile(name: str, flags, keep_asm: bool) -> str:
     return obj
 
 
+def _build_host() -> str:
+    """The argument marshalling of the binding (csrc/pbsa_host.cpp), against this interpreter and torch."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+    cmd += [f"-I{p}" for p in [*cpp_extension.include_paths(), sysconfig.get_paths()["include"]]]
+    lib_dir = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd += [os.path.join(CSRC, "pbsa_host.cpp"), "-o", HOST_LIB, f"-L{lib_dir}", "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    subprocess.run(cmd, check=True)
+    return HOST_LIB
+
+
 def build(keep_asm: bool = False) -> str:
     os.makedirs(BUILD_DIR, exist_ok=True)
     ver = hipcc_version()
     if not ver.startswith(CHECKED_HIPCC):
         print(f"build.py: hipcc {ver} is not the checked {CHECKED_HIPCC}: run the GPU tests (pytest -m gpu) before "
               "trusting the inline-assembly kernels", file=sys.stderr)
-    with ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
+    with ThreadPoolExecutor(max_workers=len(SOURCES) + 1) as ex:
+        host = ex.submit(_build_host)
         objs = list(ex.map(lambda kv: _compile(kv[0], kv[1], keep_asm), SOURCES.items()))
+        host.result()
     subprocess.run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs], check=True)
     return LIB
 

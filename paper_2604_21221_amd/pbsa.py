@@ -9,6 +9,8 @@ from __future__ import annotations
 import ctypes
 import os
 
+import torch
+
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libpbsa.so")
 
@@ -124,19 +126,41 @@ def _ptr(x):
 
 def _stream(stream):
     if stream is None:
-        import torch
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        # what torch.cuda.current_stream().cuda_stream says, without the Stream object (3 us)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     if isinstance(stream, int):
-        return ctypes.c_void_p(stream)
-    return ctypes.c_void_p(stream.cuda_stream)
+        return stream
+    return stream.cuda_stream
 
 
 def _ws(ws):
     if ws is None:
         return None, 0
     if isinstance(ws, tuple):
-        return ctypes.c_void_p(ws[0]), ws[1]
-    return ctypes.c_void_p(ws.data_ptr()), ws.numel() * ws.element_size()
+        return ws
+    return ws.data_ptr(), ws.nbytes
+
+
+class _Addresses(dict):
+    """Address of each library function, looked up (and the library loaded) on first use."""
+
+    def __missing__(self, name):
+        self[name] = a = ctypes.cast(getattr(lib(), name), ctypes.c_void_p).value
+        return a
+
+
+_A = _Addresses()
+
+
+def _invoke(*args):
+    """Calls the function at address args[0] with the rest: tensors, integers, ctypes structures or None (csrc/pbsa_host.cpp)."""
+    global _invoke
+    try:
+        from ._pbsa_host import invoke
+    except ImportError as e:
+        raise ImportError("the binding's native half is missing: build it with `python -m paper_2604_21221_amd.build`") from e
+    _invoke = invoke
+    return invoke(*args)
 
 
 def _check(rc: int):
@@ -154,129 +178,113 @@ def pbsa_strerror(code: int) -> str:
 
 def pbsa_workspace_bytes(p: pbsa_params) -> int:
     out = ctypes.c_size_t(0)
-    _check(lib().pbsa_workspace_bytes(ctypes.byref(p), ctypes.byref(out)))
+    _check(_invoke(_A["pbsa_workspace_bytes"], p, ctypes.addressof(out)))
     return out.value
 
 
 def pbsa_attention_workspace_bytes(p: pbsa_params) -> int:
     out = ctypes.c_size_t(0)
-    _check(lib().pbsa_attention_workspace_bytes(ctypes.byref(p), ctypes.byref(out)))
+    _check(_invoke(_A["pbsa_attention_workspace_bytes"], p, ctypes.addressof(out)))
     return out.value
 
 
 def pbsa_pool_blocks(p, X, length, n_blocks, out, stream=None):
-    _check(lib().pbsa_pool_blocks(ctypes.byref(p), _ptr(X), _ptr(length), n_blocks, _ptr(out), _stream(stream)))
+    _check(_invoke(_A["pbsa_pool_blocks"], p, X, length, n_blocks, out, _stream(stream)))
 
 
 def pbsa_summary_view(p, S_sum, S_cnt, Kp, Vp, p_len, stream=None):
-    _check(lib().pbsa_summary_view(ctypes.byref(p), _ptr(S_sum), _ptr(S_cnt), _ptr(Kp), _ptr(Vp), _ptr(p_len), _stream(stream)))
+    _check(_invoke(_A["pbsa_summary_view"], p, S_sum, S_cnt, Kp, Vp, p_len, _stream(stream)))
 
 
 def pbsa_append_chunk(p, K, V, slot0, zero_tail, Kl, Vl, Kc_l=None, stream=None):
     """K, V: [H][Nq][d] bf16 with a contiguous last dimension, or None."""
     ks, vs = (x.stride() if x is not None else (0, 0, 1) for x in (K, V))
-    _check(lib().pbsa_append_chunk(ctypes.byref(p), _ptr(K), _ptr(V), ks[0], ks[1], vs[0], vs[1], slot0, int(zero_tail),
-                                   _ptr(Kl), _ptr(Vl), _ptr(Kc_l), _stream(stream)))
+    _check(_invoke(_A["pbsa_append_chunk"], p, K, V, ks[0], ks[1], vs[0], vs[1], slot0, int(zero_tail), Kl, Vl, Kc_l,
+                   _stream(stream)))
 
 
 def pbsa_select_blocks(p, Q, Kl, l_len, l_map, Kc_l, Qc, sel, Zl=None, ws=None, stream=None):
     w, wb = _ws(ws)
-    _check(lib().pbsa_select_blocks(ctypes.byref(p), _ptr(Q), _ptr(Kl), _ptr(l_len), _ptr(l_map), _ptr(Kc_l),
-                                    _ptr(Qc), _ptr(sel), _ptr(Zl), w, wb, _stream(stream)))
+    _check(_invoke(_A["pbsa_select_blocks"], p, Q, Kl, l_len, l_map, Kc_l, Qc, sel, Zl, w, wb, _stream(stream)))
 
 
 def pbsa_select_blocks_apply(p, Q, Kl, l_len, l_map, Kc_l, Qc, sel, Zl, p_upd, Kp, Vp, p_len, S_sum, S_cnt, Vl, ws,
                              stream=None):
     w, wb = _ws(ws)
-    _check(lib().pbsa_select_blocks_apply(ctypes.byref(p), _ptr(Q), _ptr(Kl), _ptr(l_len), _ptr(l_map), _ptr(Kc_l),
-                                          _ptr(Qc), _ptr(sel), _ptr(Zl), ctypes.byref(p_upd), _ptr(Kp), _ptr(Vp),
-                                          _ptr(p_len), _ptr(S_sum), _ptr(S_cnt), _ptr(Vl), w, wb, _stream(stream)))
+    _check(_invoke(_A["pbsa_select_blocks_apply"], p, Q, Kl, l_len, l_map, Kc_l, Qc, sel, Zl, p_upd, Kp, Vp, p_len, S_sum,
+                   S_cnt, Vl, w, wb, _stream(stream)))
 
 
 def pbsa_attention_fwd(p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse=None, ws=None, stream=None):
     w, wb = _ws(ws)
-    _check(lib().pbsa_attention_fwd(ctypes.byref(p), _ptr(Q), _ptr(Kp), _ptr(Vp), _ptr(p_len), _ptr(Kl), _ptr(Vl),
-                                    _ptr(l_len), _ptr(l_map), _ptr(sel), _ptr(O), _ptr(lse), w, wb, _stream(stream)))
+    _check(_invoke(_A["pbsa_attention_fwd"], p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse, w, wb, _stream(stream)))
 
 
 def pbsa_memory_update(p, Qc, Kc_l, Zl, Kp, Vp, Kc_p, p_len, p_id, S_sum, S_cnt, Kl, Vl, l_len, l_map, l_id, scores,
                        slot_src, ws, stream=None):
     w, wb = _ws(ws)
-    _check(lib().pbsa_memory_update(ctypes.byref(p), _ptr(Qc), _ptr(Kc_l), _ptr(Zl), _ptr(Kp), _ptr(Vp), _ptr(Kc_p),
-                                    _ptr(p_len), _ptr(p_id), _ptr(S_sum), _ptr(S_cnt), _ptr(Kl), _ptr(Vl),
-                                    _ptr(l_len), _ptr(l_map), _ptr(l_id), _ptr(scores), _ptr(slot_src), w, wb,
-                                    _stream(stream)))
+    _check(_invoke(_A["pbsa_memory_update"], p, Qc, Kc_l, Zl, Kp, Vp, Kc_p, p_len, p_id, S_sum, S_cnt, Kl, Vl, l_len, l_map,
+                   l_id, scores, slot_src, w, wb, _stream(stream)))
 
 
 def pbsa_memory_update_static(p, Qc, Kc_l, Zl, Kp, Vp, Kc_p, p_len, p_id, S_sum, S_cnt, Kl, Vl, l_len, l_map, l_id, scores,
                               slot_src, stream=None):
-    _check(lib().pbsa_memory_update_static(ctypes.byref(p), _ptr(Qc), _ptr(Kc_l), _ptr(Zl), _ptr(Kp), _ptr(Vp),
-                                           _ptr(Kc_p), _ptr(p_len), _ptr(p_id), _ptr(S_sum), _ptr(S_cnt), _ptr(Kl),
-                                           _ptr(Vl), _ptr(l_len), _ptr(l_map), _ptr(l_id), _ptr(scores),
-                                           _ptr(slot_src), _stream(stream)))
+    _check(_invoke(_A["pbsa_memory_update_static"], p, Qc, Kc_l, Zl, Kp, Vp, Kc_p, p_len, p_id, S_sum, S_cnt, Kl, Vl, l_len,
+                   l_map, l_id, scores, slot_src, _stream(stream)))
 
 
 def pbsa_memory_update_plan(p, Qc, Kc_l, Zl, Kc_p, p_len, p_id, S_cnt, l_len, l_map, l_id, scores, slot_src, ws,
                             stream=None):
     w, wb = _ws(ws)
-    _check(lib().pbsa_memory_update_plan(ctypes.byref(p), _ptr(Qc), _ptr(Kc_l), _ptr(Zl), _ptr(Kc_p), _ptr(p_len),
-                                         _ptr(p_id), _ptr(S_cnt), _ptr(l_len), _ptr(l_map), _ptr(l_id), _ptr(scores),
-                                         _ptr(slot_src), w, wb, _stream(stream)))
+    _check(_invoke(_A["pbsa_memory_update_plan"], p, Qc, Kc_l, Zl, Kc_p, p_len, p_id, S_cnt, l_len, l_map, l_id, scores,
+                   slot_src, w, wb, _stream(stream)))
 
 
 def pbsa_attention_fwd_plan(p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse, Qc, Kc_l, Zl, Kc_p, p_id, S_cnt, l_id,
                             scores, slot_src, ws, stream=None):
     w, wb = _ws(ws)
-    _check(lib().pbsa_attention_fwd_plan(ctypes.byref(p), _ptr(Q), _ptr(Kp), _ptr(Vp), _ptr(p_len), _ptr(Kl), _ptr(Vl),
-                                         _ptr(l_len), _ptr(l_map), _ptr(sel), _ptr(O), _ptr(lse), _ptr(Qc), _ptr(Kc_l),
-                                         _ptr(Zl), _ptr(Kc_p), _ptr(p_id), _ptr(S_cnt), _ptr(l_id), _ptr(scores),
-                                         _ptr(slot_src), w, wb, _stream(stream)))
+    _check(_invoke(_A["pbsa_attention_fwd_plan"], p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse, Qc, Kc_l, Zl, Kc_p,
+                   p_id, S_cnt, l_id, scores, slot_src, w, wb, _stream(stream)))
 
 
 def pbsa_memory_update_apply(p, Kp, Vp, p_len, S_sum, S_cnt, Kl, Vl, ws, stream=None):
     w, wb = _ws(ws)
-    _check(lib().pbsa_memory_update_apply(ctypes.byref(p), _ptr(Kp), _ptr(Vp), _ptr(p_len), _ptr(S_sum), _ptr(S_cnt),
-                                          _ptr(Kl), _ptr(Vl), w, wb, _stream(stream)))
+    _check(_invoke(_A["pbsa_memory_update_apply"], p, Kp, Vp, p_len, S_sum, S_cnt, Kl, Vl, w, wb, _stream(stream)))
 
 
 def pbsa_attention_mass(p, Q, Kp, p_len, Kl, l_len, l_map, sel, lse, Mt, stream=None):
-    _check(lib().pbsa_attention_mass(ctypes.byref(p), _ptr(Q), _ptr(Kp), _ptr(p_len), _ptr(Kl), _ptr(l_len),
-                                     _ptr(l_map), _ptr(sel), _ptr(lse), _ptr(Mt), _stream(stream)))
+    _check(_invoke(_A["pbsa_attention_mass"], p, Q, Kp, p_len, Kl, l_len, l_map, sel, lse, Mt, _stream(stream)))
 
 
 def pbsa_mass_workspace_bytes(p: pbsa_params) -> int:
     out = ctypes.c_size_t(0)
-    _check(lib().pbsa_mass_workspace_bytes(ctypes.byref(p), ctypes.byref(out)))
+    _check(_invoke(_A["pbsa_mass_workspace_bytes"], p, ctypes.addressof(out)))
     return out.value
 
 
 def pbsa_attention_fwd_mass(p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse, Mt, ws, stream=None):
     w, wb = _ws(ws)
-    _check(lib().pbsa_attention_fwd_mass(ctypes.byref(p), _ptr(Q), _ptr(Kp), _ptr(Vp), _ptr(p_len), _ptr(Kl), _ptr(Vl),
-                                         _ptr(l_len), _ptr(l_map), _ptr(sel), _ptr(O), _ptr(lse), _ptr(Mt), w, wb,
-                                         _stream(stream)))
+    _check(_invoke(_A["pbsa_attention_fwd_mass"], p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse, Mt, w, wb,
+                   _stream(stream)))
 
 
 def pbsa_memory_update_fine(p, Mt, Kc_l, Kp, Vp, Kc_p, p_len, p_id, S_sum, S_cnt, Kl, Vl, l_len, l_map, l_id, scores,
                             slot_src, ws, stream=None):
     w, wb = _ws(ws)
-    _check(lib().pbsa_memory_update_fine(ctypes.byref(p), _ptr(Mt), _ptr(Kc_l), _ptr(Kp), _ptr(Vp), _ptr(Kc_p),
-                                         _ptr(p_len), _ptr(p_id), _ptr(S_sum), _ptr(S_cnt), _ptr(Kl), _ptr(Vl),
-                                         _ptr(l_len), _ptr(l_map), _ptr(l_id), _ptr(scores), _ptr(slot_src), w, wb,
-                                         _stream(stream)))
+    _check(_invoke(_A["pbsa_memory_update_fine"], p, Mt, Kc_l, Kp, Vp, Kc_p, p_len, p_id, S_sum, S_cnt, Kl, Vl, l_len, l_map,
+                   l_id, scores, slot_src, w, wb, _stream(stream)))
 
 
 def pbsa_bwd_workspace_bytes(p: pbsa_params) -> int:
     out = ctypes.c_size_t(0)
-    _check(lib().pbsa_bwd_workspace_bytes(ctypes.byref(p), ctypes.byref(out)))
+    _check(_invoke(_A["pbsa_bwd_workspace_bytes"], p, ctypes.addressof(out)))
     return out.value
 
 
 def pbsa_attention_bwd(p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, dO, lse, dQ, dKp, dVp, dKl, dVl, ws, stream=None):
     w, wb = _ws(ws)
-    _check(lib().pbsa_attention_bwd(ctypes.byref(p), _ptr(Q), _ptr(Kp), _ptr(Vp), _ptr(p_len), _ptr(Kl), _ptr(Vl),
-                                    _ptr(l_len), _ptr(l_map), _ptr(sel), _ptr(O), _ptr(dO), _ptr(lse), _ptr(dQ),
-                                    _ptr(dKp), _ptr(dVp), _ptr(dKl), _ptr(dVl), w, wb, _stream(stream)))
+    _check(_invoke(_A["pbsa_attention_bwd"], p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, dO, lse, dQ, dKp, dVp, dKl,
+                   dVl, w, wb, _stream(stream)))
 
 
 def pbsa_blockify(g, X, Xblk, blk_stride_h, stream=None):
@@ -285,8 +293,8 @@ def pbsa_blockify(g, X, Xblk, blk_stride_h, stream=None):
     xs = (ctypes.c_void_p * n)(*[_ptr(x) for x in X])
     bs = (ctypes.c_void_p * n)(*[_ptr(x) for x in Xblk])
     st = (ctypes.c_int64 * n)(*[int(v) for v in blk_stride_h])
-    _check(lib().pbsa_blockify(ctypes.byref(g), n, xs, bs, st, _stream(stream)))
+    _check(_invoke(_A["pbsa_blockify"], g, n, xs, bs, st, _stream(stream)))
 
 
 def pbsa_unblockify(g, Xblk, blk_stride_h, X, stream=None):
-    _check(lib().pbsa_unblockify(ctypes.byref(g), _ptr(Xblk), int(blk_stride_h), _ptr(X), _stream(stream)))
+    _check(_invoke(_A["pbsa_unblockify"], g, Xblk, int(blk_stride_h), X, _stream(stream)))
