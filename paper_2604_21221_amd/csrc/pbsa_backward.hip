@@ -23,7 +23,7 @@
 // reads are free of bank conflicts.  Rows past a tile's valid length are never loaded: their lanes fetch the last
 // valid row, and the elementwise stage zeroes what belongs to them.  dq holds 64 fixed rows per wave, so every
 // fragment read from LDS feeds two MFMAs; dkv cannot at d = 128 (two outputs: 256 accumulator registers for 64
-// keys) and holds 32 per wave: it reads one fragment per MFMA and sits at the LDS bandwidth.
+// keys) and holds 32 per wave: it reads one fragment per MFMA.
 #include <type_traits>
 
 #include "pbsa_internal.h"
@@ -35,6 +35,7 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
 constexpr int kThreads = 128;
@@ -57,7 +58,7 @@ struct BwdArgs {
   const bf16_t* O;
   const bf16_t* dO;
   const float* lse;
-  float* Dr;          // [H][Nq] rowsum(dO o O)
+  float* rows;        // [H][ceil(Nq / 64) * 2][64]: of 32 rows, -lse log2 e (-inf: no such row), then -rowsum(dO o O)
   float* dQ;
   float* dKp;
   float* dVp;
@@ -86,6 +87,27 @@ __device__ __forceinline__ void dma4(const void* base, uint32_t lane_off, uint32
                : "memory", "m0");
 }
 
+template <int LDS_IMM>
+__device__ __forceinline__ void dma16x4(const void* base, uint32_t o0, uint32_t o1, uint32_t o2, uint32_t o3, uint32_t lds_base) {
+  // four loads 1 KiB apart in LDS and in memory alike: the instruction's offset moves both addresses
+  asm volatile("s_add_u32 m0, %0, %6\n\ts_nop 0\n\t"
+               "global_load_lds_dwordx4 %1, %5\n\t"
+               "global_load_lds_dwordx4 %2, %5 offset:1024\n\t"
+               "global_load_lds_dwordx4 %3, %5 offset:2048\n\t"
+               "global_load_lds_dwordx4 %4, %5 offset:3072"
+               :
+               : "s"(lds_base), "v"(o0), "v"(o1), "v"(o2), "v"(o3), "s"(base), "n"(LDS_IMM)
+               : "memory", "scc", "m0");
+}
+__device__ __forceinline__ void dma16x2(const void* base, uint32_t o0, uint32_t o1, uint32_t lds_off) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+               "global_load_lds_dwordx4 %1, %3\n\t"
+               "global_load_lds_dwordx4 %2, %3 offset:1024"
+               :
+               : "s"(lds_off), "v"(o0), "v"(o1), "s"(base)
+               : "memory", "m0");
+}
+
 // Where the 16-byte chunks of a tile row sit in LDS: logical chunk c of row r at chunk c ^ swz(r).  The row-wise
 // operand reads (16 consecutive rows, one logical chunk) need swz distinct over 16 consecutive rows (8 when a row
 // has 8 chunks); the transposing reads (4 consecutive rows from a multiple of 4, two adjacent chunks c, c + 1 with
@@ -98,6 +120,7 @@ __device__ __forceinline__ int swz(int r) {
 
 typedef __attribute__((address_space(3))) const bf16x8* lds_b128_t;
 typedef __attribute__((address_space(3))) bf16x4* lds_tr_t;
+typedef __attribute__((address_space(3))) const f32x4* lds_f4_t;
 __device__ __forceinline__ bf16x8 lds_read_row(uint32_t addr) { return *(lds_b128_t)(uintptr_t)addr; }
 // transposed fragment of 16 streamed rows: two transposing reads, rows r and r + 8 of the 16.  HI_XOR: what the
 // row permutation does to the byte address when the row goes up by 8.
@@ -107,6 +130,12 @@ template <int ROW, int HI_XOR>
 __device__ __forceinline__ bf16x8 lds_read_tr(uint32_t base, uint32_t off) {
   const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_tr_t)(uintptr_t)(base + off));
   const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_tr_t)(uintptr_t)(base + (off ^ HI_XOR) + 8 * ROW));
+  return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+// the same from the two addresses
+__device__ __forceinline__ bf16x8 lds_read_tr2(uint32_t at_lo, uint32_t at_hi) {
+  const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_tr_t)(uintptr_t)at_lo);
+  const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_tr_t)(uintptr_t)at_hi);
   return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 __device__ __forceinline__ void acc_mfma(f32x16& acc, const bf16x8& a, const bf16x8& b) {
@@ -121,18 +150,22 @@ __device__ __forceinline__ uint32_t pack2(float a, float b) {
 __device__ __forceinline__ bf16x8 as_bf16x8(const u32x4& w) { return __builtin_bit_cast(bf16x8, w); }
 
 // ------------------------------------------------------------------------------------------------
-// D[h][q] = dO[q] . O[q]: 16 lanes per row, 8 elements each (d = 128) or 8 lanes (d = 64)
+// Row scalars: -lse log2 e and -D, D = dO[q] . O[q]: 16 lanes per row, 8 elements each (d = 128) or 8 lanes (d = 64).
+// Rows up to the next multiple of 64 are written too: -inf and 0, so that a copy of the last row that stands in for a
+// missing one takes no part.
 // ------------------------------------------------------------------------------------------------
+__host__ __device__ inline long row_blocks(int Nq) { return (long)((Nq + kTile - 1) / kTile) * 2; }
+
 template <int D>
 __global__ void __launch_bounds__(256) bwd_prep_kernel(BwdArgs a) {
   constexpr int LPR = D / 8;               // lanes per row
   const long idx = (long)blockIdx.x * 256 + threadIdx.x;
-  const long row = idx / LPR;
+  const long row = idx / LPR, per_head = row_blocks(a.Nq) * 32;
   const int part = (int)(idx % LPR);
+  const int h = (int)(row / per_head), t = (int)(row % per_head);
   float acc = 0.0f;
-  const bool ok = row < (long)a.H * a.Nq;
+  const bool ok = h < a.H && t < a.Nq;
   if (ok) {
-    const int h = (int)(row / a.Nq), t = (int)(row % a.Nq);
     const size_t off = (size_t)h * a.o_stride_h + (size_t)t * a.o_stride_t + 8 * part;
     const bf16x8 o = *reinterpret_cast<const bf16x8*>(a.O + off);
     const bf16x8 g = *reinterpret_cast<const bf16x8*>(a.dO + off);
@@ -141,7 +174,11 @@ __global__ void __launch_bounds__(256) bwd_prep_kernel(BwdArgs a) {
   }
 #pragma unroll
   for (int s = 1; s < LPR; s <<= 1) acc += __shfl_xor(acc, s, 64);
-  if (ok && part == 0) a.Dr[row] = acc;
+  if (h < a.H && part == 0) {
+    float* at = a.rows + (row / 32) * 64 + row % 32;
+    at[0] = ok ? -a.lse[(size_t)h * a.Nq + t] * kLog2e : -INFINITY;
+    at[32] = -acc;
+  }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -155,7 +192,7 @@ __global__ void __launch_bounds__(kThreads) bwd_dkv_kernel(BwdArgs a) {
   constexpr int HI_XOR = CH == 16 ? 16 : 0;         // row + 8 flips the lowest bit of the chunk permutation when it has 4 bits
   extern __shared__ __align__(1024) unsigned char smem[];
   __shared__ int cnt_s[2 * 12];
-  __shared__ __align__(256) float rows_f[4 * 128];  // per ring entry, lse (64 floats, 32 used) then D of the half tile's rows
+  __shared__ __align__(256) float rows_f[4 * 64];   // per ring entry, the scalars of the half tile's rows (BwdArgs::rows)
   // ring: entry e holds T1 at e * 2 TILE and T2 behind it
   int* lst_a = reinterpret_cast<int*>(smem + 4 * TILE);   // per streamed tile: where it is
   const int SUB = a.B / kTile;
@@ -166,7 +203,6 @@ __global__ void __launch_bounds__(kThreads) bwd_dkv_kernel(BwdArgs a) {
 
   // ---- what this workgroup is, and the list of streamed tiles ------------------------------------
   int n_cand;
-  int* lst_b;                              // per streamed tile: its valid rows
   int* flag_s;                             // query blocks that attend the key block
   // The workgroup's 64-key tile: persistent (slot c) or local (logical block l).  The grid is one line with the
   // persistent tiles of all heads first: every query block attends them, so their workgroups walk the whole chunk
@@ -187,8 +223,7 @@ __global__ void __launch_bounds__(kThreads) bwd_dkv_kernel(BwdArgs a) {
   int fixed_len = 0, kv_slot_tile = 0;
   bool kv_local = false;
   n_cand = a.nqb * SUB;
-  lst_b = lst_a + n_cand;
-  flag_s = lst_b + n_cand;
+  flag_s = lst_a + n_cand;
   kv_local = r_tile >= n_pers;
   if (!kv_local) {
     const int c = r_tile / SUB, sub = r_tile % SUB;
@@ -217,25 +252,23 @@ __global__ void __launch_bounds__(kThreads) bwd_dkv_kernel(BwdArgs a) {
   }
   __syncthreads();
   if (fixed_len < 0) return;
-  auto classify = [&](int i, int& where, int& rows) -> bool {
+  auto classify = [&](int i, int& where) -> bool {
     if (i >= n_cand) return false;
     const int ib = i / SUB;
     if (fixed_len <= 0 || (kv_local && !flag_s[ib])) return false;
-    rows = min(kTile, a.Nq - i * kTile);            // row tile i covers tokens 64 i ..
-    where = i;
-    return rows > 0;
+    where = i;                                      // row tile i covers tokens 64 i ..
+    return a.Nq - i * kTile > 0;
   };
   constexpr int kMaxRounds = 12;           // (2 (C_max + 1) + 2 k_max) / 128 rounded up; dkv needs 8
   const int n_rounds = min((n_cand + kThreads - 1) / kThreads, kMaxRounds);
   // every candidate is looked at once (a look is a chain of dependent loads); what it found stays in registers
   // until the counts of all rounds are known
-  int c_where[kMaxRounds], c_rows[kMaxRounds];
+  int c_where[kMaxRounds];
   unsigned long long c_mask[kMaxRounds];
 #pragma unroll
   for (int r = 0; r < kMaxRounds; ++r) {
     c_where[r] = 0;
-    c_rows[r] = 0;
-    const bool on = r < n_rounds && classify(r * kThreads + tid, c_where[r], c_rows[r]);
+    const bool on = r < n_rounds && classify(r * kThreads + tid, c_where[r]);
     c_mask[r] = __ballot(on);
     if (r < n_rounds && lane == 0) cnt_s[r * 2 + wave] = __popcll(c_mask[r]);
   }
@@ -248,7 +281,6 @@ __global__ void __launch_bounds__(kThreads) bwd_dkv_kernel(BwdArgs a) {
       int pos = lanes_below(c_mask[r]);
       for (int q = 0; q < r * 2 + wave; ++q) pos += cnt_s[q];
       lst_a[pos] = c_where[r];
-      lst_b[pos] = c_rows[r];
     }
   }
   __syncthreads();
@@ -271,7 +303,7 @@ __global__ void __launch_bounds__(kThreads) bwd_dkv_kernel(BwdArgs a) {
   }
   // they have arrived before the walk starts: no wait for them inside it, where one would also wait for the tiles
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(f1[ks]), "+v"(f2[ks]));
+  for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+a"(f1[ks]), "+a"(f2[ks]));
 
   f32x16 out1[DT], out2[DT];               // dK^T and dV^T   (32 dims x 32 keys each)
 #pragma unroll
@@ -287,61 +319,67 @@ __global__ void __launch_bounds__(kThreads) bwd_dkv_kernel(BwdArgs a) {
     asm volatile("" : "+a"(out2[dt]));
   }
 
-  // ---- LDS addresses of this lane's operand reads inside ring entry 0 -------------------------------
+  // ---- LDS addresses of this lane's operand reads ----------------------------------------------------
+  // kept for one pair of ring entries each and moved to the other pair once per tile, so that everything else of an
+  // address is a constant of the instruction: rd the row-wise reads, tl / th the transposing reads of rows r and r + 8,
+  // sc_own / sc_next the row scalars of this tile's and of the next tile's pair
   const uint32_t smem_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
   const uint32_t ring_s = __builtin_amdgcn_readfirstlane(smem_lds);
   const uint32_t rows_s = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) float*)rows_f);
-  uint32_t ra[KS], ta[DT];
+  uint32_t rd[KS], tl[DT], th[DT];
   {
     const int kb = qn * ROW + ((half ^ swz<CH>(qn)) << 4);              // row lane % 32, logical chunk 2 ks + half
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) ra[ks] = smem_lds + (uint32_t)(kb ^ (ks << 5));
+    for (int ks = 0; ks < KS; ++ks) rd[ks] = smem_lds + (uint32_t)(kb ^ (ks << 5));
     const int s16 = lane & 15, q16 = (lane >> 4) & 1;
     const int row0 = 4 * half + (s16 >> 2);                              // address row within 16 streamed rows
     const int sub = 2 * q16 + ((s16 & 3) >> 1), lo = (s16 & 1) * 8;
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt) ta[dt] = (uint32_t)(row0 * ROW + (((4 * dt + sub) ^ swz<CH>(row0)) << 4) + lo);
+    for (int dt = 0; dt < DT; ++dt) {
+      const uint32_t off = (uint32_t)(row0 * ROW + (((4 * dt + sub) ^ swz<CH>(row0)) << 4) + lo);
+      tl[dt] = smem_lds + off;
+      th[dt] = smem_lds + (off ^ HI_XOR) + 8 * ROW;
+    }
   }
+  uint32_t sc_own = rows_s + 16 * half, sc_next = sc_own + 512;
 
   // ---- staging -------------------------------------------------------------------------------------
-  // The unit that travels is a half tile: 32 streamed rows of T1 and of T2 (and, dkv, the lse and D of those
-  // rows), one ring entry of four.  Wave w brings rows 16 w .. 16 w + 15 of the half.  Every wave issues the same
-  // number of loads per half tile, so that one count serves the wait; past the end of the list the last half tile
-  // is fetched again into an entry whose contents are never used.
+  // The unit that travels is a half tile: 32 streamed rows of T1 and of T2 and the scalars of those rows, one ring
+  // entry of four.  Wave w brings rows 16 w .. 16 w + 15 of the half.  Every wave issues the same number of loads per
+  // half tile, so that one count serves the wait; past the end of the list the last half tile is fetched again into an
+  // entry whose contents are never used.
   constexpr int HALF = TILE / 2, RING = 4, NH = NI / 2;    // NH: load instructions per wave, tensor and half tile
-  constexpr int PER = 2 * NH + 2;               // loads per wave and half tile
+  constexpr int PER = 2 * NH + 1;               // loads per wave and half tile
   const int rl = lane / CH;
   const int n_half = 2 * n_tiles;
-  long st1, st2;                           // row strides of the streamed tensors in bytes
-  const unsigned char *b1l, *b2l, *b1p, *b2p;
-  st1 = a.q_stride_t * 2;
-  st2 = a.o_stride_t * 2;
-  b1l = b1p = reinterpret_cast<const unsigned char*>(a.Q + (size_t)h * a.q_stride_h);
-  b2l = b2p = reinterpret_cast<const unsigned char*>(a.dO + (size_t)h * a.o_stride_h);
-  // per-lane source offsets of the wave's instructions within a half tile whose 32 rows all exist
+  const long st1 = a.q_stride_t * 2, st2 = a.o_stride_t * 2;     // row strides of the streamed tensors in bytes
+  const unsigned char* const b1 = reinterpret_cast<const unsigned char*>(a.Q + (size_t)h * a.q_stride_h);
+  const unsigned char* const b2 = reinterpret_cast<const unsigned char*>(a.dO + (size_t)h * a.o_stride_h);
+  const float* const rows_g = a.rows + (size_t)h * row_blocks(a.Nq) * 64;
+  // per-lane source offsets of the wave's instructions within a half tile whose 32 rows all exist, less what the
+  // instruction's own offset adds (a row's stride is at least its d elements: never below zero)
   uint32_t so1[NH], so2[NH];
 #pragma unroll
   for (int k = 0; k < NH; ++k) {
     const int r = 16 * wave + RPI * k + rl;
     const uint32_t chunk = (uint32_t)(((lane % CH) ^ swz<CH>(r)) << 4);
-    so1[k] = (uint32_t)(r * st1) + chunk;
-    so2[k] = (uint32_t)(r * st2) + chunk;
+    so1[k] = (uint32_t)(r * st1) + chunk - (uint32_t)(k * 1024);
+    so2[k] = (uint32_t)(r * st2) + chunk - (uint32_t)(k * 1024);
   }
-  auto stage = [&](int u, int entry) {
-    const int t = u >> 1, mg = u & 1;
-    const int where = __builtin_amdgcn_readfirstlane(lst_a[t]);
-    const int last = __builtin_amdgcn_readfirstlane(lst_b[t]) - 1;
-    const size_t tile = (size_t)(where & 0x7FFFFFFF) * kTile;          // first row of the tile in its tensor
-    const unsigned char* s1 = (where < 0 ? b1l : b1p) + tile * st1;
-    const unsigned char* s2 = (where < 0 ? b2l : b2p) + tile * st2;
+  auto stage = [&](int where, int mg, int entry) {
+    const int last = min(kTile, a.Nq - where * kTile) - 1;
+    const unsigned char* s1 = b1 + (size_t)where * kTile * st1;
+    const unsigned char* s2 = b2 + (size_t)where * kTile * st2;
     const uint32_t dst = ring_s + (uint32_t)(entry * TILE + wave * (HALF / 2));
     if (last >= 32 * mg + 31) {
       s1 += (size_t)(32 * mg) * st1;
       s2 += (size_t)(32 * mg) * st2;
-#pragma unroll
-      for (int k = 0; k < NH; ++k) {
-        dma16(s1, so1[k], dst + k * 1024);
-        dma16(s2, so2[k], dst + HALF + k * 1024);
+      if constexpr (NH == 4) {
+        dma16x4<0>(s1, so1[0], so1[1], so1[2], so1[3], dst);
+        dma16x4<0>(s2, so2[0], so2[1], so2[2], so2[3], dst + HALF);
+      } else {
+        dma16x2(s1, so1[0], so1[1], dst);
+        dma16x2(s2, so2[0], so2[1], dst + HALF);
       }
     } else {                               // rows past the last one that exists are not touched: that row again
 #pragma unroll
@@ -352,125 +390,158 @@ __global__ void __launch_bounds__(kThreads) bwd_dkv_kernel(BwdArgs a) {
         dma16(s2, (uint32_t)(src_row * st2) + chunk, dst + HALF + k * 1024);
       }
     }
-    // lse and D of the half's 32 rows, as they are (lanes 32..63 repeat lanes 0..31; both waves bring the same)
-    const int tok = min(where * kTile + min(32 * mg + qn, last), a.Nq - 1);
-    dma4(a.lse + (size_t)h * a.Nq, (uint32_t)tok * 4u, rows_s + (uint32_t)(entry * 512));
-    dma4(a.Dr + (size_t)h * a.Nq, (uint32_t)tok * 4u, rows_s + (uint32_t)(entry * 512 + 256));
-  
+    // the scalars of the half's 32 rows (both waves bring the same)
+    dma4(rows_g + (size_t)(2 * where + mg) * 64, (uint32_t)lane * 4u, rows_s + (uint32_t)(entry * 256));
   };
 
   // ---- the walk: a software pipeline over half tiles ---------------------------------------------------
-  // In turn u the wave runs the first products of half tile u+1 (A1, A2: 2 KS MFMAs) with the elementwise stage
-  // of half tile u cut into as many slices, one behind each MFMA, so that the vector unit works while the
-  // matrix pipe does; then the second products of half tile u.  Half tile u+1 must have landed when turn u
-  // starts, u+2 is on its way, u+3 is asked for at the start of the turn (into the entry u-1 has left).
+  // Turn u, in two phases.  First: the first products of half tile u + 1 (2 KS MFMAs, their row fragments already in
+  // registers), each with a slice of half tile u's elementwise stage behind it and, over the middle slices, the
+  // transposing reads of half tile u.  Then a wait and the turn's one barrier: half tile u + 2 has landed, and nobody
+  // reads half tile u any more.  Second: the second products of half tile u (4 DT MFMAs), each with a row fragment of
+  // half tile u + 2 read behind it; half tile u + 4 is sent for, into the entry u has left.
+  // The compiler orders instructions without side effects as it likes: left alone it issued all the elementwise work
+  // behind the last MFMA, and a
+  // turn took 2700 cycles for 1024 cycles of matrix work, on a compute unit of its own too (12 heads x 4680 x 128 with
+  // 32 + 48 blocks of 64: select, forward and backward 969 -> 835 us; 8 + 16 blocks of 128: 640 -> 552 us).  An empty asm with the value as
+  // its operand (pin) keeps each MFMA and each slice where it stands.
+  // Per element: fma, exp2, multiply, half of two conversions.  The row's -D is what the accumulator starts from, and
+  // rows that do not exist have -inf in the place of their -lse log2 e: their P is an exact zero without a mask.
   constexpr int NS = 2 * KS, EPS = 16 / NS;                // slices, accumulator elements per slice
-  static_assert(EPS * NS == 16 && (EPS == 1 || EPS == 2), "slices cover the 16 elements, pairs stay together");
+  static_assert(EPS * NS == 16 && (EPS == 1 || EPS == 2), "slices cover the 16 elements");
+  constexpr int NTF = 4 * DT;                              // transposed fragments of a half tile: [tensor][j][dt]
+  static_assert(NTF == NS, "a row fragment behind every second product, two transposed ones per middle slice");
   const f32x16 zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-  f32x16 c1 = zero, c2a = zero;            // A1, A2 of the half tile whose elementwise stage comes next
-  if (n_half > 0) {
-    for (int j = 0; j < RING - 1; ++j) stage(min(j, n_half - 1), j);
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((RING - 2) * PER) : "memory");
-    __syncthreads();
-    bf16x8 x1[KS], x2[KS];
+  f32x16 c1 = zero, c2a = zero;            // A1, A2 - D of the half tile whose elementwise stage comes next
+  bf16x8 x[NS];                            // row fragments: x[2 ks] of T1, x[2 ks + 1] of T2
+  f32x16 dn;                               // -D of the rows those fragments hold, in accumulator order
+  f32x4 nl0;                              // -lse log2 e of the first four rows of the next elementwise stage
+  auto read_scalar4 = [&](uint32_t addr) { return *(lds_f4_t)(uintptr_t)addr; };
+  auto read_dn4 = [&](uint32_t addr, int g) {
+    const f32x4 v = read_scalar4(addr + 128 + 32 * g);
+    dn[4 * g] = v.x; dn[4 * g + 1] = v.y; dn[4 * g + 2] = v.z; dn[4 * g + 3] = v.w;
+  };
+  auto read_dn = [&](uint32_t addr) {
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      x1[ks] = lds_read_row(ra[ks]);
-      x2[ks] = lds_read_row(ra[ks] + HALF);
+    for (int g = 0; g < 4; ++g) read_dn4(addr, g);
+  };
+  if (n_half > 0) {
+#pragma unroll
+    for (int j = 0; j < RING; ++j) {
+      const int u = min(j, n_half - 1);
+      stage(__builtin_amdgcn_readfirstlane(lst_a[u >> 1]), u & 1, j);
     }
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * PER) : "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < NS; ++i) x[i] = lds_read_row(rd[i / 2] + (i % 2) * HALF);
+    read_dn(sc_own);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      c1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x1[ks], f1[ks], c1, 0, 0, 0);
-      c2a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x2[ks], f2[ks], c2a, 0, 0, 0);
+      c1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[2 * ks], f1[ks], c1, 0, 0, 0);
+      c2a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[2 * ks + 1], f2[ks], ks == 0 ? dn : c2a, 0, 0, 0);
     }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < NS; ++i) x[i] = lds_read_row(rd[i / 2] + TILE + (i % 2) * HALF);
+    read_dn(sc_own + 256);
+    nl0 = read_scalar4(sc_own);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) rd[ks] += 2 * TILE;     // the turns of tile t read the rows of tile t + 1
   }
   // Two turns per tile, so that the accumulator sets trade places by name (no copies) and the half is a constant.
-  auto turn = [&](auto MG, int t, const f32x16& c1, const f32x16& c2a, f32x16& n1, f32x16& n2) {
+  auto turn = [&](auto MG, int t, f32x16& c1, f32x16& c2a, f32x16& n1, f32x16& n2) {
     constexpr int mg = decltype(MG)::value;
-    const int u = 2 * t + mg, e = 2 * (t & 1) + mg, en = (e + 1) % RING;
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((RING - 3) * PER) : "memory");   // this wave's rows of half tile u+1 are in
-    __syncthreads();                                        // everybody's are, and half tile u-1 has been used by all
-    stage(min(u + RING - 1, n_half - 1), (u + RING - 1) % RING);
-    const int rows = __builtin_amdgcn_readfirstlane(lst_b[t]);
-    const uint32_t off1 = (uint32_t)(e * TILE), off2 = off1 + HALF, offn = (uint32_t)(en * TILE);
-    // operand reads: the next half tile's rows for its first products, this one's transposed for its second ones
-    bf16x8 x1[KS], x2[KS];
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      x1[ks] = lds_read_row(ra[ks] + offn);
-      x2[ks] = lds_read_row(ra[ks] + offn + HALF);
-    }
-    // Row scalars and the transposed fragments are asked for inside the slices, shortly before they are
-    // needed: the scalars of four streamed rows two slices ahead of their first use, the fragments two (one) per
-    // slice over the second half of the slices, when the row fragments they replace in the register file are dead.
-    float nlv[16], dv[16];
-    auto fetch_scalars = [&](int g) {      // rows 8 g + 4 half .. + 3 of the half tile: elements 4 g .. 4 g + 3
-      const float4 n4 = *reinterpret_cast<const float4*>(&rows_f[e * 128 + 8 * g + 4 * half]);
-      const float4 d4 = *reinterpret_cast<const float4*>(&rows_f[e * 128 + 64 + 8 * g + 4 * half]);
-      nlv[4 * g] = n4.x; nlv[4 * g + 1] = n4.y; nlv[4 * g + 2] = n4.z; nlv[4 * g + 3] = n4.w;
-      dv[4 * g] = d4.x; dv[4 * g + 1] = d4.y; dv[4 * g + 2] = d4.z; dv[4 * g + 3] = d4.w;
-    
-    };
-    constexpr int NTF = 2 * 2 * DT, TPS = NTF / (NS / 2);   // transposed fragments, per slice of the second half
-    static_assert(TPS * (NS / 2) == NTF, "the transposed reads spread evenly");
-    bf16x8 tf[NTF];                        // [tensor][j][dt]
-    fetch_scalars(0);
-    __builtin_amdgcn_sched_barrier(0);
-    // accumulator element v: streamed row 32 mg + 8 (v / 4) + 4 half + v % 4, fixed row 32 w + lane % 32.  Streamed
-    // rows past the tile's length hold a copy of its last row and take no part; a fixed row that does not exist
-    // only fills its own column of the outputs, which is not written.
-    const int lim = rows - 32 * mg - 4 * half;
+    int v_where = lst_a[min(t + 2, n_tiles - 1)];
+    float nl[16], ex[16], zz[16];
+    nl[0] = nl0.x; nl[1] = nl0.y; nl[2] = nl0.z; nl[3] = nl0.w;
     u32x4 eP[2], eZ[2];
-    float pz[16], zz[16];
+    bf16x8 tf[NTF];
+    auto finish = [&](int v) {             // the later half of an element, a slice behind its exponential
+      zz[v] = ex[v] * c2a[v];
+      if (v % 2 == 1) {
+        eP[v / 8][(v % 8) / 2] = pack2(ex[v - 1], ex[v]);
+        eZ[v / 8][(v % 8) / 2] = pack2(zz[v - 1], zz[v]);
+        asm volatile("" : "+v"(eP[v / 8][(v % 8) / 2]), "+v"(eZ[v / 8][(v % 8) / 2]));
+      }
+    };
 #pragma unroll
     for (int sl = 0; sl < NS; ++sl) {
       const int ks = sl / 2;
-      if (sl % 2 == 0) n1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x1[ks], f1[ks], ks == 0 ? zero : n1, 0, 0, 0);
-      else n2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x2[ks], f2[ks], ks == 0 ? zero : n2, 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);   // the MFMA first, then the slice
-      {
-        // scalars of the group whose first element comes two slices from now
-        const int v_ahead = (sl + 2) * EPS;
-        if (v_ahead < 16 && v_ahead % 4 == 0 && (sl + 1) * EPS % 4 != 0) fetch_scalars(v_ahead / 4);
-        else if (EPS == 2 && v_ahead < 16 && v_ahead % 4 == 0) fetch_scalars(v_ahead / 4);
+      if (sl % 2 == 0) {
+        n1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[sl], f1[ks], ks == 0 ? zero : n1, 0, 0, 0);
+        asm volatile("" : "+v"(n1));
+      } else {
+        n2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[sl], f2[ks], ks == 0 ? dn : n2, 0, 0, 0);
+        asm volatile("" : "+v"(n2));
       }
-      if (sl >= NS / 2) {
+      __builtin_amdgcn_sched_barrier(0);   // the MFMA first, then the slice
+      // accumulator element v: streamed row 32 mg + 8 (v / 4) + 4 half + v % 4, fixed row 32 w + lane % 32
+      if (sl * EPS % 4 == 0 && sl * EPS < 12) {              // the scalars of the next four rows
+        const int g = sl * EPS / 4 + 1;
+        const f32x4 v = read_scalar4(sc_own + 256 * mg + 32 * g);
+        nl[4 * g] = v.x; nl[4 * g + 1] = v.y; nl[4 * g + 2] = v.z; nl[4 * g + 3] = v.w;
+      }
+      if (sl >= NS / 4 && sl < NS / 4 + NTF / 2) {
 #pragma unroll
-        for (int q = 0; q < TPS; ++q) {
-          const int i = (sl - NS / 2) * TPS + q, tensor = i / (2 * DT), j = (i / DT) % 2, dt = i % DT;
-          tf[i] = lds_read_tr<ROW, HI_XOR>(smem_lds + (uint32_t)(16 * j * ROW) + (tensor ? off2 : off1), ta[dt]);
+        for (int q = 0; q < 2; ++q) {
+          const int i = 2 * (sl - NS / 4) + q, tensor = i / (2 * DT), j = (i / DT) % 2, dt = i % DT;
+          const uint32_t at = (uint32_t)(mg * TILE + tensor * HALF + 16 * j * ROW);
+          tf[i] = lds_read_tr2(tl[dt] + at, th[dt] + at);
         }
       }
 #pragma unroll
       for (int q = 0; q < EPS; ++q) {
         const int v = sl * EPS + q;
-        const float nl = -nlv[v] * kLog2e, dd = dv[v];
-        const float pe = __builtin_amdgcn_exp2f(__builtin_fmaf(c1[v], c2, nl));
-        pz[v] = 8 * (v / 4) + (v % 4) < lim ? pe : 0.0f;
-        zz[v] = pz[v] * (c2a[v] - dd);
-        if (v % 2 == 1) {
-          eP[v / 8][(v % 8) / 2] = pack2(pz[v - 1], pz[v]);
-          eZ[v / 8][(v % 8) / 2] = pack2(zz[v - 1], zz[v]);
-        }
+        ex[v] = __builtin_amdgcn_exp2f(__builtin_fmaf(c1[v], c2, nl[v]));
       }
+#pragma unroll
+      for (int q = 0; q < EPS; ++q)
+        if (sl > 0) finish((sl - 1) * EPS + q);
+#pragma unroll
+      for (int q = 0; q < EPS; ++q) asm volatile("" : "+v"(ex[sl * EPS + q]));
       __builtin_amdgcn_sched_barrier(0);
     }
-    asm volatile("s_nop 4" ::: "memory");   // the last slice's operands are written before the products that read them issue
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt) {
-        acc_mfma(out1[dt], tf[j * DT + dt], as_bf16x8(eZ[j]));
-        acc_mfma(out2[dt], tf[(2 + j) * DT + dt], as_bf16x8(eP[j]));
-      }
+    for (int q = 0; q < EPS; ++q) finish((NS - 1) * EPS + q);
+    const int where = __builtin_amdgcn_readfirstlane(v_where);
+    // this wave's rows of half tile u + 2 are in and its reads of half tile u done; then everybody's
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER) : "memory");
+    __builtin_amdgcn_s_waitcnt(0xC07F);    // lgkmcnt(0), in the form the compiler counts
+    __builtin_amdgcn_s_barrier();
+    asm volatile("s_nop 4" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < NTF; ++i) {
+      const int tensor = i % 2, j = i / (2 * DT), dt = (i / 2) % DT;
+      acc_mfma(tensor ? out2[dt] : out1[dt], tf[(2 * tensor + j) * DT + dt], as_bf16x8(tensor ? eP[j] : eZ[j]));
+      __builtin_amdgcn_sched_barrier(0);
+      x[i] = lds_read_row(rd[i / 2] + mg * TILE + (i % 2) * HALF);
+      if (i == 1) stage(where, mg, 2 * (t & 1) + mg);
+      if (i >= NTF / 2 - 2 && i < NTF / 2 + 2) read_dn4(sc_next + 256 * mg, i - (NTF / 2 - 2));
+      if (i == NTF / 2 + 2) nl0 = read_scalar4(mg ? sc_next : sc_own + 256);
+      __builtin_amdgcn_sched_barrier(0);
+    }
   };
   {
     f32x16 d1, d2;                         // the other accumulator set
+    uint32_t step = 2 * TILE, sc_step = 512;                // to the other pair of ring entries and back
     for (int t = 0; t < n_tiles; ++t) {
       turn(std::integral_constant<int, 0>{}, t, c1, c2a, d1, d2);
       turn(std::integral_constant<int, 1>{}, t, d1, d2, c1, c2a);
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) rd[ks] -= step;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) {
+        tl[dt] += step;
+        th[dt] += step;
+      }
+      sc_own += sc_step;
+      sc_next -= sc_step;
+      step = 0u - step;
+      sc_step = 0u - sc_step;
     }
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // the trailing loads land before the workgroup goes
@@ -512,19 +583,6 @@ __global__ void __launch_bounds__(kThreads) bwd_dkv_kernel(BwdArgs a) {
 //     second products of group 0                  (2 DT MFMAs)  with the elementwise stage of group 1 behind them
 //     second products of group 1                  (2 DT MFMAs)
 // ------------------------------------------------------------------------------------------------
-template <int LDS_IMM>
-__device__ __forceinline__ void dma16x4(const void* base, uint32_t o0, uint32_t o1, uint32_t o2, uint32_t o3, uint32_t lds_base) {
-  // four loads 1 KiB apart in LDS and in memory alike: the instruction's offset moves both addresses
-  asm volatile("s_add_u32 m0, %0, %6\n\ts_nop 0\n\t"
-               "global_load_lds_dwordx4 %1, %5\n\t"
-               "global_load_lds_dwordx4 %2, %5 offset:1024\n\t"
-               "global_load_lds_dwordx4 %3, %5 offset:2048\n\t"
-               "global_load_lds_dwordx4 %4, %5 offset:3072"
-               :
-               : "s"(lds_base), "v"(o0), "v"(o1), "v"(o2), "v"(o3), "s"(base), "n"(LDS_IMM)
-               : "memory", "scc", "m0");
-}
-
 template <int D>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1))) bwd_dq_kernel(BwdArgs a) {
   constexpr int KS = D / 16, DT = D / 32, ROW = D * 2, TILE = kTile * ROW, HALF = TILE / 2;
@@ -590,7 +648,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1)))
     }
     const float l = a.lse[(size_t)h * a.Nq + tok];
     nl_fix[n] = 32 * n + qn < fixed_len && l > -INFINITY ? -l * kLog2e : -INFINITY;
-    d_fix[n] = a.Dr[(size_t)h * a.Nq + tok];
+    d_fix[n] = -a.rows[((size_t)h * row_blocks(a.Nq) + tok / 32) * 64 + 32 + tok % 32];
   }
   // only ever MFMA operands: they live in the accumulator half of the register file (and have arrived: no wait
   // for them inside the walk, where one would also wait for the tiles)
@@ -768,17 +826,17 @@ hipError_t launch_with_lds(K kernel, const BwdArgs& a, dim3 grid, int threads, s
 
 }  // namespace
 
-size_t bwd_workspace_bytes(const pbsa_params& p) { return (((size_t)p.H * p.Nq * 4) + 255) & ~(size_t)255; }
+size_t bwd_workspace_bytes(const pbsa_params& p) { return (size_t)p.H * row_blocks(p.Nq) * 64 * 4; }
 
 hipError_t launch_attention_bwd(const pbsa_params& p, const bf16_t* Q, const bf16_t* Kp, const bf16_t* Vp,
                                 const int32_t* p_len, const bf16_t* Kl, const bf16_t* Vl, const int32_t* l_len,
                                 const int32_t* l_map, const int32_t* sel, const bf16_t* O, const bf16_t* dO,
-                                const float* lse, float* dQ, float* dKp, float* dVp, float* dKl, float* dVl, float* Dr,
+                                const float* lse, float* dQ, float* dKp, float* dVp, float* dKl, float* dVl, float* rows,
                                 hipStream_t stream) {
   BwdArgs a{p.H, p.Nq, p.nqb, p.n_loc, p.n_loc_cap, p.C, p.k, p.B, p.scale, p.q_stride_h, p.q_stride_t, p.o_stride_h,
-            p.o_stride_t, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, dO, lse, Dr, dQ, dKp, dVp, dKl, dVl};
+            p.o_stride_t, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, dO, lse, rows, dQ, dKp, dVp, dKl, dVl};
   const int sub = p.B / kTile;
-  const long n_lanes = (long)p.H * p.Nq * (p.d / 8);
+  const long n_lanes = p.H * row_blocks(p.Nq) * 32 * (p.d / 8);
   const dim3 pgrid((unsigned)((n_lanes + 255) / 256));
   if (p.d == 128) hipLaunchKernelGGL(bwd_prep_kernel<128>, pgrid, dim3(256), 0, stream, a);
   else hipLaunchKernelGGL(bwd_prep_kernel<64>, pgrid, dim3(256), 0, stream, a);
@@ -796,7 +854,7 @@ hipError_t launch_attention_bwd(const pbsa_params& p, const bf16_t* Q, const bf1
   {
     const size_t n_cand = (size_t)p.nqb * sub;
     const dim3 grid((unsigned)((p.C + 1 + p.n_loc) * sub * p.H));
-    const size_t lds = ring + n_cand * 8 + (size_t)p.nqb * 4 + 16;
+    const size_t lds = ring + n_cand * 4 + (size_t)p.nqb * 4 + 16;
     e = p.d == 128 ? launch_with_lds(bwd_dkv_kernel<128>, a, grid, kThreads, lds, stream)
                    : launch_with_lds(bwd_dkv_kernel<64>, a, grid, kThreads, lds, stream);
   }
