@@ -648,7 +648,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1)))
     }
     const float l = a.lse[(size_t)h * a.Nq + tok];
     nl_fix[n] = 32 * n + qn < fixed_len && l > -INFINITY ? -l * kLog2e : -INFINITY;
-    d_fix[n] = -a.rows[((size_t)h * row_blocks(a.Nq) + tok / 32) * 64 + 32 + tok % 32];
+    d_fix[n] = a.rows[((size_t)h * row_blocks(a.Nq) + tok / 32) * 64 + 32 + tok % 32];
   }
   // only ever MFMA operands: they live in the accumulator half of the register file (and have arrived: no wait
   // for them inside the walk, where one would also wait for the tiles)
@@ -656,7 +656,15 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1)))
   for (int n = 0; n < 2; ++n) {
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+a"(f1[n][ks]), "+a"(f2[n][ks]));
-    asm volatile("" : "+v"(nl_fix[n]), "+v"(d_fix[n]));
+    asm volatile("" : "+v"(nl_fix[n]));
+  }
+  // -D of the lane's query row of each group, sixteen times: what the dP accumulators start from
+  f32x16 dn[2];
+#pragma unroll
+  for (int n = 0; n < 2; ++n) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) dn[n][v] = d_fix[n];
+    asm volatile("" : "+v"(dn[n]));
   }
   f32x16 out[2][DT];                       // dQ^T: 32 dims x 32 rows per tile
 #pragma unroll
@@ -671,16 +679,20 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1)))
   // ---- LDS addresses of this lane's operand reads inside ring entry 0 ----------------------------------
   const uint32_t smem_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
   const uint32_t ring_s = __builtin_amdgcn_readfirstlane(smem_lds);
-  uint32_t ra[KS], ta[DT];
+  uint32_t rd[KS], tl[DT], th[DT];         // row-wise reads; transposing reads of rows r and r + 8
   {
     const int kb = qn * ROW + ((half ^ swz<CH>(qn)) << 4);
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) ra[ks] = smem_lds + (uint32_t)(kb ^ (ks << 5));
+    for (int ks = 0; ks < KS; ++ks) rd[ks] = smem_lds + (uint32_t)(kb ^ (ks << 5));
     const int s16 = lane & 15, q16 = (lane >> 4) & 1;
     const int row0 = 4 * half + (s16 >> 2);
     const int sub = 2 * q16 + ((s16 & 3) >> 1), lo = (s16 & 1) * 8;
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt) ta[dt] = (uint32_t)(row0 * ROW + (((4 * dt + sub) ^ swz<CH>(row0)) << 4) + lo);
+    for (int dt = 0; dt < DT; ++dt) {
+      const uint32_t off = (uint32_t)(row0 * ROW + (((4 * dt + sub) ^ swz<CH>(row0)) << 4) + lo);
+      tl[dt] = smem_lds + off;
+      th[dt] = smem_lds + (off ^ HI_XOR) + 8 * ROW;
+    }
   }
 
   // ---- staging: the wave brings whole half tiles (32 rows of K and of V, dense rows) ---------------------
@@ -721,75 +733,126 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1)))
     }
   };
 
-  const f32x16 zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-  const int n_half = 2 * n_tiles;
-  if (n_half > 0) stage(0, 0);
-  auto turn = [&](auto MG, int t) {
-    constexpr int mg = decltype(MG)::value;
-    const int u = 2 * t + mg, e = mg;      // two turns per tile: the entry is the half
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // half tile u is in (nobody else reads or writes the ring)
-    if (u + 1 < n_half) stage(u + 1, e ^ 1);
-    const int rows = __builtin_amdgcn_readfirstlane(lst_b[t]);
-    const int lim = rows - 32 * mg - 4 * half;
-    const uint32_t off1 = (uint32_t)(e * TILE), off2 = off1 + HALF;
-    bf16x8 x1[KS], x2[KS];
+  // ---- the walk ------------------------------------------------------------------------------------------
+  // A turn works on one half tile u, whose row fragments are in registers when it starts:
+  //   1  the first products of column group 0                             (2 KS MFMAs)
+  //   2  those of group 1, with the elementwise stage of group 0 and the transposing reads behind them
+  //      then half tile u + 1 has landed (it was sent for a turn ago), and u + 2 is sent for, into the entry of u
+  //   3  second products, group 0 then group 1 (4 DT MFMAs), with the elementwise stage of group 1 behind the first
+  //      three quarters of them (its later half is due only at the last quarter) and the row reads of u + 1
+  // Per element: fma, exp2, multiply, half of a conversion; -D is what the dP accumulators start from, and a key past the
+  // tile's length has -inf in the score accumulator's start (the scale is positive), so its P is an exact zero.
+  // The empty asm statements keep MFMAs and slices where they stand; without them the compiler issues all the
+  // elementwise work behind the last MFMA of its phase.
+  bf16x8 x[NS];                            // row fragments: x[2 ks] of K, x[2 ks + 1] of V
+  f32x16 km;                               // 0 or, for a key that does not exist, -inf, in accumulator order
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      x1[ks] = lds_read_row(ra[ks] + off1);
-      x2[ks] = lds_read_row(ra[ks] + off2);
+  for (int v = 0; v < 16; ++v) km[v] = 0.0f;
+  bool km_clear = true;
+  const int n_half = 2 * n_tiles;
+  if (n_half > 0) {
+    stage(0, 0);
+    stage(1, 1);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(8 * NW) : "memory");
+#pragma unroll
+    for (int i = 0; i < NS; ++i) x[i] = lds_read_row(rd[i / 2] + (i % 2) * HALF);
+  }
+  auto turn = [&](auto MG, int t) {
+    constexpr int mg = decltype(MG)::value;                 // two turns per tile: the ring entry is the half
+    const int u = 2 * t + mg;
+    const int rows = __builtin_amdgcn_readfirstlane(lst_b[t]);
+    // accumulator element v: key 32 mg + 8 (v / 4) + 4 half + v % 4, query row 32 n + lane % 32.  Keys past the
+    // tile's length hold a copy of its last row; a query row that does not exist has nl = -inf.
+    if (rows < 32 * mg + 32) {
+      const int lim = rows - 32 * mg - 4 * half;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) km[v] = 8 * (v / 4) + (v % 4) < lim ? 0.0f : -INFINITY;
+      km_clear = false;
+    } else if (!km_clear) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) km[v] = 0.0f;
+      km_clear = true;
     }
     __builtin_amdgcn_sched_barrier(0);
     f32x16 a1[2], a2[2];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      a1[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x1[ks], f1[0][ks], ks == 0 ? zero : a1[0], 0, 0, 0);
-      a2[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x2[ks], f2[0][ks], ks == 0 ? zero : a2[0], 0, 0, 0);
+      a1[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[2 * ks], f1[0][ks], ks == 0 ? km : a1[0], 0, 0, 0);
+      a2[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[2 * ks + 1], f2[0][ks], ks == 0 ? dn[0] : a2[0], 0, 0, 0);
     }
+    asm volatile("" : "+v"(a1[0]), "+v"(a2[0]));
     __builtin_amdgcn_sched_barrier(0);
-    // accumulator element v: key 32 mg + 8 (v / 4) + 4 half + v % 4, query row 32 n + lane % 32.  Keys past the
-    // tile's length hold a copy of its last row and take no part; a query row that does not exist has nl = -inf.
     u32x4 eZ[2][2];
-    bf16x8 tf[2][DT];
-    auto element = [&](int n, int v, float (&zz)[16]) {
-      const float pe = __builtin_amdgcn_exp2f(__builtin_fmaf(a1[n][v], c2, nl_fix[n]));
-      const float pm = 8 * (v / 4) + (v % 4) < lim ? pe : 0.0f;
-      zz[v] = pm * (a2[n][v] - d_fix[n]);
-      if (v % 2 == 1) eZ[n][v / 8][(v % 8) / 2] = pack2(zz[v - 1], zz[v]);
+    bf16x8 tf[2 * DT];
+    float ex[2][16], zz[2][16];
+    auto begin = [&](int n, int v) { ex[n][v] = __builtin_amdgcn_exp2f(__builtin_fmaf(a1[n][v], c2, nl_fix[n])); };
+    auto finish = [&](int n, int v) {
+      zz[n][v] = ex[n][v] * a2[n][v];
+      if (v % 2 == 1) {
+        eZ[n][v / 8][(v % 8) / 2] = pack2(zz[n][v - 1], zz[n][v]);
+        asm volatile("" : "+v"(eZ[n][v / 8][(v % 8) / 2]));
+      }
     };
-    {
-      float zz[16];
 #pragma unroll
-      for (int sl = 0; sl < NS; ++sl) {
-        const int ks = sl / 2;
-        if (sl % 2 == 0) a1[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x1[ks], f1[1][ks], ks == 0 ? zero : a1[1], 0, 0, 0);
-        else a2[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x2[ks], f2[1][ks], ks == 0 ? zero : a2[1], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        if (sl >= NS - 2 * DT) {           // the transposed fragments, asked for over the last slices
-          const int i = sl - (NS - 2 * DT);
-          tf[i / DT][i % DT] = lds_read_tr<ROW, HI_XOR>(smem_lds + (uint32_t)(16 * (i / DT) * ROW) + off1, ta[i % DT]);
+    for (int sl = 0; sl < NS; ++sl) {
+      const int ks = sl / 2;
+      if (sl % 2 == 0) {
+        a1[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[sl], f1[1][ks], ks == 0 ? km : a1[1], 0, 0, 0);
+        asm volatile("" : "+v"(a1[1]));
+      } else {
+        a2[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[sl], f2[1][ks], ks == 0 ? dn[1] : a2[1], 0, 0, 0);
+        asm volatile("" : "+v"(a2[1]));
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if (sl >= NS / 4 && sl < NS / 4 + DT) {
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+          const int i = 2 * (sl - NS / 4) + r;
+          const uint32_t at = (uint32_t)(mg * TILE + 16 * (i / DT) * ROW);
+          tf[i] = lds_read_tr2(tl[i % DT] + at, th[i % DT] + at);
         }
-#pragma unroll
-        for (int q = 0; q < EPS; ++q) element(0, sl * EPS + q, zz);
-        __builtin_amdgcn_sched_barrier(0);
       }
+#pragma unroll
+      for (int r = 0; r < EPS; ++r) begin(0, sl * EPS + r);
+#pragma unroll
+      for (int r = 0; r < EPS; ++r)
+        if (sl > 0) finish(0, (sl - 1) * EPS + r);
+#pragma unroll
+      for (int r = 0; r < EPS; ++r) asm volatile("" : "+v"(ex[0][sl * EPS + r]));
+      __builtin_amdgcn_sched_barrier(0);
     }
+#pragma unroll
+    for (int r = 0; r < EPS; ++r) finish(0, (NS - 1) * EPS + r);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // half tile u + 1 is in
+    __builtin_amdgcn_s_waitcnt(0xC07F);                     // lgkmcnt(0): and u read (nobody else uses the ring)
     asm volatile("s_nop 4" ::: "memory");
-    {
-      float zz[16];
-      constexpr int EP2 = 16 / (2 * DT);   // elements of group 1 behind each second product of group 0
-#pragma unroll
-      for (int i = 0; i < 2 * DT; ++i) {
-        acc_mfma(out[0][i % DT], tf[i / DT][i % DT], as_bf16x8(eZ[0][i / DT]));
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int q = 0; q < EP2; ++q) element(1, i * EP2 + q, zz);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-    asm volatile("s_nop 4" ::: "memory");
-#pragma unroll
-    for (int i = 0; i < 2 * DT; ++i) acc_mfma(out[1][i % DT], tf[i / DT][i % DT], as_bf16x8(eZ[1][i / DT]));
+    if (u + 2 < n_half) stage(u + 2, mg);
     __builtin_amdgcn_sched_barrier(0);
+    constexpr int NP = 4 * DT, Q3 = 3 * DT, RPS = NS / Q3 + 1;   // products; elementwise slots; reads per slot
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const int n = i / (2 * DT), j = (i / DT) % 2, dt = i % DT;
+      acc_mfma(out[n][dt], tf[j * DT + dt], as_bf16x8(eZ[n][j]));
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int r = 0; r < RPS; ++r) {
+        const int f = i * RPS + r;
+        if (f < NS) x[f] = lds_read_row(rd[f / 2] + (mg ^ 1) * TILE + (f % 2) * HALF);
+      }
+      // group 1, elements first(i) .. first(i + 1) - 1 begun here; finished one slot later, in time for the group 1
+      // products of their half (8 elements by slot 2 DT, all by slot 3 DT)
+      if (i < Q3) {
+        const auto first = [](int s) { return s <= 0 ? 0 : s >= Q3 - 1 ? 16 : (16 * s + Q3 - 2) / (Q3 - 1); };
+#pragma unroll
+        for (int v = first(i); v < first(i + 1); ++v) begin(1, v);
+#pragma unroll
+        for (int v = first(i - 1); v < first(i); ++v) finish(1, v);
+#pragma unroll
+        for (int v = first(i); v < first(i + 1); ++v) asm volatile("" : "+v"(ex[1][v]));
+      }
+      if (i == 2 * DT - 1 || i == Q3 - 1) asm volatile("s_nop 4" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+    }
   };
   for (int t = 0; t < n_tiles; ++t) {
     turn(std::integral_constant<int, 0>{}, t);
