@@ -293,7 +293,7 @@ int pbsa_memory_update_fine(const pbsa_params* p, const float* Mt, const float* 
  *   dQ [H][Nq][d] dense;  dKp, dVp [H][C+1][B][d] (the summary slot C included);  dKl, dVl [H][n_loc_cap][B][d] by
  *   physical slot: the slots of the n_loc logical blocks are written in full -- zeros for rows past a block's
  *   length and for blocks no query block selected -- other slots are left alone.
- * ws: pbsa_bwd_workspace_bytes(p) bytes of device scratch (the row scalars), 256-byte aligned. */
+ * ws: pbsa_bwd_workspace_bytes(p) bytes of device scratch (the row scalars, the selection by local block), 256-byte aligned. */
 int pbsa_bwd_workspace_bytes(const pbsa_params* p, size_t* out);
 int pbsa_attention_bwd(const pbsa_params* p, const void* Q, const void* Kp, const void* Vp, const int32_t* p_len,
                        const void* Kl, const void* Vl, const int32_t* l_len, const int32_t* l_map, const int32_t* sel,

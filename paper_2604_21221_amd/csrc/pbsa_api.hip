@@ -446,7 +446,7 @@ int pbsa_attention_bwd(const pbsa_params* p, const void* Q, const void* Kp, cons
       *p, static_cast<const pbsa::bf16_t*>(Q), static_cast<const pbsa::bf16_t*>(Kp),
       static_cast<const pbsa::bf16_t*>(Vp), p_len, static_cast<const pbsa::bf16_t*>(Kl),
       static_cast<const pbsa::bf16_t*>(Vl), l_len, l_map, sel, static_cast<const pbsa::bf16_t*>(O),
-      static_cast<const pbsa::bf16_t*>(dO), lse, dQ, dKp, dVp, dKl, dVl, static_cast<float*>(ws),
+      static_cast<const pbsa::bf16_t*>(dO), lse, dQ, dKp, dVp, dKl, dVl, ws,
       static_cast<hipStream_t>(hip_stream));
   return e == hipSuccess ? PBSA_OK : hip_fail(e);
 }

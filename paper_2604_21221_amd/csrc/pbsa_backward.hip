@@ -4,12 +4,12 @@
 //     dQ = scale dZ K    dK = scale dZ^T Q
 // P is recomputed from the forward's log-sum-exp: exp2(z c2 - lse log2 e); nothing of the forward's
 // probabilities is stored.  Three kernels, no atomics, every output element written by exactly one lane:
-//   prep   D[h][q] = sum_x dO[q][x] O[q][x]                                      (fp32, from the bf16 tensors)
+//   prep   per row -lse log2 e and -D (fp32, D from the bf16 tensors); per local block the query blocks that attend it
 //   dq     one single-wave workgroup per 64 query rows: their Q and dO fragments stay in registers, the 64-key tiles
 //          they attend (persistent slots, then the blocks of their row of sel) stream through LDS
 //   dkv    one two-wave workgroup per 64-key tile: its K and V fragments stay in registers, the 64-row tiles of the
 //          query blocks that attend it (all of them for a persistent slot; those whose row of sel names the block
-//          otherwise, found by scanning sel) stream through LDS
+//          otherwise, which prep has written down) stream through LDS
 // Both have a fixed side in registers (MFMA B operands) and a streamed side in LDS (A operands):
 //   A1 = T1 F1^T, A2 = T2 F2^T   32 streamed rows x 32 fixed rows per MFMA chain (v_mfma_f32_32x32x16_bf16)
 //          dq:  T1 = K, T2 = V, F1 = Q, F2 = dO   ->  A1 = Z^T / scale, A2 = dP^T     (keys x queries)
@@ -59,6 +59,8 @@ struct BwdArgs {
   const bf16_t* dO;
   const float* lse;
   float* rows;        // [H][ceil(Nq / 64) * 2][64]: of 32 rows, -lse log2 e (-inf: no such row), then -rowsum(dO o O)
+  uint32_t* att;      // [H][n_loc_cap][ceil(nqb / 32)] bit i: query block i attends local block l
+  int32_t* order;     // [H][n_loc_cap] the local blocks, the most attended first
   float* dQ;
   float* dKp;
   float* dVp;
@@ -168,10 +170,64 @@ inline unsigned head_items(int n, int H) { return (unsigned)((n + 7) / 8 * 8) * 
 // ------------------------------------------------------------------------------------------------
 __host__ __device__ inline long row_blocks(int Nq) { return (long)((Nq + kTile - 1) / kTile) * 2; }
 
+// The first H workgroups of the launch turn a head's rows of sel around: which query blocks attend each local block, and
+// the local blocks by how many do, most first (a counting sort; blocks that tie come in any order).  One scan of sel per
+// head in the place of one per 64-key tile, and an order in which the long walks start first.
+__device__ __forceinline__ void plan_head(const BwdArgs& a, int h, uint32_t* smem) {
+  const int W = (a.nqb + 31) / 32, n_words = a.n_loc * W, tid = threadIdx.x;
+  int* hist = reinterpret_cast<int*>(smem + n_words);       // bucket nqb - count
+  for (int i = tid; i < n_words + a.nqb + 1; i += 256) smem[i] = 0;
+  __syncthreads();
+  const int32_t* sel_h = a.sel + (size_t)h * a.nqb * a.k;
+  const int n_sel = a.nqb * a.k;
+  for (int e0 = tid; e0 < n_sel; e0 += 8 * 256) {
+    int v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = e0 + j * 256 < n_sel ? sel_h[e0 + j * 256] : -1;
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (v[j] >= 0 && v[j] < a.n_loc) {
+        const int i = (e0 + j * 256) / a.k;
+        atomicOr(&smem[v[j] * W + (i >> 5)], 1u << (i & 31));
+      }
+  }
+  __syncthreads();
+  auto count = [&](int l) {
+    int c = 0;
+    for (int w = 0; w < W; ++w) c += __popc(smem[l * W + w]);
+    return c;
+  };
+  for (int l = tid; l < a.n_loc; l += 256) atomicAdd(&hist[a.nqb - count(l)], 1);
+  for (int i = tid; i < n_words; i += 256) a.att[(size_t)h * a.n_loc_cap * W + i] = smem[i];
+  __syncthreads();
+  if (tid < 64) {                          // counts -> first positions
+    int before = 0;
+    for (int b0 = 0; b0 <= a.nqb; b0 += 64) {
+      const int mine = b0 + tid <= a.nqb ? hist[b0 + tid] : 0;
+      int sum = mine;
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const int up = __shfl_up(sum, d, 64);
+        if (tid >= d) sum += up;
+      }
+      if (b0 + tid <= a.nqb) hist[b0 + tid] = before + sum - mine;
+      before += __shfl(sum, 63, 64);
+    }
+  }
+  __syncthreads();
+  for (int l = tid; l < a.n_loc; l += 256)
+    a.order[(size_t)h * a.n_loc_cap + atomicAdd(&hist[a.nqb - count(l)], 1)] = l;
+}
+
 template <int D>
 __global__ void __launch_bounds__(256) bwd_prep_kernel(BwdArgs a) {
+  extern __shared__ uint32_t plan_s[];
   constexpr int LPR = D / 8;               // lanes per row
-  const long idx = (long)blockIdx.x * 256 + threadIdx.x;
+  if ((int)blockIdx.x < a.H) {
+    plan_head(a, (int)blockIdx.x, plan_s);
+    return;
+  }
+  const long idx = (long)(blockIdx.x - a.H) * 256 + threadIdx.x;
   const long row = idx / LPR, per_head = row_blocks(a.Nq) * 32;
   const int part = (int)(idx % LPR);
   const int h = (int)(row / per_head), t = (int)(row % per_head);
@@ -203,7 +259,7 @@ __global__ void __launch_bounds__(kThreads) bwd_dkv_kernel(BwdArgs a) {
   constexpr int NI = 32 / RPI;                      // load instructions per wave per tile (its 32 rows)
   constexpr int HI_XOR = CH == 16 ? 16 : 0;         // row + 8 flips the lowest bit of the chunk permutation when it has 4 bits
   extern __shared__ __align__(1024) unsigned char smem[];
-  __shared__ int cnt_s[2 * 12];
+  __shared__ int cnt_s[2 * 8];
   __shared__ __align__(256) float rows_f[4 * 64];   // per ring entry, the scalars of the half tile's rows (BwdArgs::rows)
   // ring: entry e holds T1 at e * 2 TILE and T2 behind it
   int* lst_a = reinterpret_cast<int*>(smem + 4 * TILE);   // per streamed tile: where it is
@@ -214,64 +270,41 @@ __global__ void __launch_bounds__(kThreads) bwd_dkv_kernel(BwdArgs a) {
   const float c2 = a.scale * kLog2e;
 
   // ---- what this workgroup is, and the list of streamed tiles ------------------------------------
-  int n_cand;
-  int* flag_s;                             // query blocks that attend the key block
-  // The workgroup's 64-key tile: persistent (slot c) or local (logical block l).  The grid is one line with the
-  // persistent tiles of all heads first: every query block attends them, so their workgroups walk the whole chunk
-  // and run several times as long as a local block's, and a long workgroup that starts late ends the launch late.
-  const int n_pers = (a.C + 1) * SUB, n_locs = a.n_loc * SUB;
-  int h, r_tile;
-  {
-    int b = (int)blockIdx.x;
-    if (b < a.H * n_pers) {
-      h = b / n_pers;
-      r_tile = b % n_pers;
-    } else {
-      b -= a.H * n_pers;
-      h = b / n_locs;
-      r_tile = n_pers + b % n_locs;
-    }
-  }
+  // The workgroup's 64-key tile: persistent (slot c) or local (logical block l).  A head's tiles have ranks, the
+  // persistent ones first (every query block attends them: their walks are the longest), then the local ones from the
+  // most attended to the least, and the grid goes through all heads rank by rank: a long walk that starts late ends the
+  // launch late (with the local tiles in block order the last fifth of the launch ran less than half full).  12 heads x
+  // 4680 x 128, with sel scanned once per head instead of once per tile: 32 + 48 blocks of 64 423 -> 355 us, 8 + 16 blocks of
+  // 128 264 -> 225 us.
+  const int n_pers = (a.C + 1) * SUB, n_ranks = n_pers + a.n_loc * SUB, n_cand = a.nqb * SUB;
+  int h, rank;
+  head_item((int)blockIdx.x, a.H, h, rank);
+  if (rank >= n_ranks) return;             // the last eight ranks of a head need not be full
+  const bool kv_local = rank >= n_pers;
   int fixed_len = 0, kv_slot_tile = 0;
-  bool kv_local = false;
-  n_cand = a.nqb * SUB;
-  flag_s = lst_a + n_cand;
-  kv_local = r_tile >= n_pers;
+  const uint32_t* att = a.att;             // the local block's row
   if (!kv_local) {
-    const int c = r_tile / SUB, sub = r_tile % SUB;
+    const int c = rank / SUB, sub = rank % SUB;
     fixed_len = min(max(min(max(a.p_len[(size_t)h * (a.C + 1) + c], 0), a.B) - sub * kTile, 0), kTile);
-    kv_slot_tile = r_tile;
+    kv_slot_tile = rank;
   } else {
-    const int l = (r_tile - n_pers) / SUB, sub = (r_tile - n_pers) % SUB;
+    const int l = a.order[(size_t)h * a.n_loc_cap + (rank - n_pers) / SUB], sub = (rank - n_pers) % SUB;
+    att += ((size_t)h * a.n_loc_cap + l) * ((a.nqb + 31) / 32);
     const int slot = a.l_map[l];
     const bool ok = slot >= 0 && slot < a.n_loc_cap;
     fixed_len = ok ? min(max(min(max(a.l_len[l], 0), a.B) - sub * kTile, 0), kTile) : 0;
     kv_slot_tile = (ok ? slot : 0) * SUB + sub;
-    for (int i = tid; i < a.nqb; i += kThreads) flag_s[i] = 0;
-    __syncthreads();
-    // the head's rows of sel, eight loads in flight per thread (one at a time the scan is a chain of memory latencies)
-    const int32_t* sel_h = a.sel + (size_t)h * a.nqb * a.k;
-    const int n_sel = a.nqb * a.k;
-    for (int e0 = tid; e0 < n_sel; e0 += 8 * kThreads) {
-      int v[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) v[j] = e0 + j * kThreads < n_sel ? sel_h[e0 + j * kThreads] : -1;
-#pragma unroll
-      for (int j = 0; j < 8; ++j)
-        if (v[j] == l) flag_s[(e0 + j * kThreads) / a.k] = 1;
-    }
     if (!ok) fixed_len = -1;             // a block that is nowhere: nothing to write either
   }
-  __syncthreads();
   if (fixed_len < 0) return;
   auto classify = [&](int i, int& where) -> bool {
     if (i >= n_cand) return false;
     const int ib = i / SUB;
-    if (fixed_len <= 0 || (kv_local && !flag_s[ib])) return false;
+    if (fixed_len <= 0 || (kv_local && !((att[ib >> 5] >> (ib & 31)) & 1u))) return false;
     where = i;                                      // row tile i covers tokens 64 i ..
     return a.Nq - i * kTile > 0;
   };
-  constexpr int kMaxRounds = 12;           // (2 (C_max + 1) + 2 k_max) / 128 rounded up; dkv needs 8
+  constexpr int kMaxRounds = 8;            // 512 query blocks of two tiles / 128 threads
   const int n_rounds = min((n_cand + kThreads - 1) / kThreads, kMaxRounds);
   // every candidate is looked at once (a look is a chain of dependent loads); what it found stays in registers
   // until the counts of all rounds are known
@@ -903,20 +936,35 @@ hipError_t launch_with_lds(K kernel, const BwdArgs& a, dim3 grid, int threads, s
 
 }  // namespace
 
-size_t bwd_workspace_bytes(const pbsa_params& p) { return (size_t)p.H * row_blocks(p.Nq) * 64 * 4; }
+// row scalars, then the turned-around selection, then the order of the local blocks
+struct BwdWorkspace {
+  size_t att, order, bytes;
+};
+static BwdWorkspace bwd_workspace(const pbsa_params& p) {
+  const auto up = [](size_t n) { return (n + 255) & ~(size_t)255; };
+  BwdWorkspace w;
+  w.att = (size_t)p.H * row_blocks(p.Nq) * 64 * 4;
+  w.order = w.att + up((size_t)p.H * p.n_loc_cap * ((p.nqb + 31) / 32) * 4);
+  w.bytes = w.order + up((size_t)p.H * p.n_loc_cap * 4);
+  return w;
+}
+size_t bwd_workspace_bytes(const pbsa_params& p) { return bwd_workspace(p).bytes; }
 
 hipError_t launch_attention_bwd(const pbsa_params& p, const bf16_t* Q, const bf16_t* Kp, const bf16_t* Vp,
                                 const int32_t* p_len, const bf16_t* Kl, const bf16_t* Vl, const int32_t* l_len,
                                 const int32_t* l_map, const int32_t* sel, const bf16_t* O, const bf16_t* dO,
-                                const float* lse, float* dQ, float* dKp, float* dVp, float* dKl, float* dVl, float* rows,
+                                const float* lse, float* dQ, float* dKp, float* dVp, float* dKl, float* dVl, void* ws,
                                 hipStream_t stream) {
   BwdArgs a{p.H, p.Nq, p.nqb, p.n_loc, p.n_loc_cap, p.C, p.k, p.B, p.scale, p.q_stride_h, p.q_stride_t, p.o_stride_h,
-            p.o_stride_t, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, dO, lse, rows, dQ, dKp, dVp, dKl, dVl};
+            p.o_stride_t, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, dO, lse, static_cast<float*>(ws),
+            reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + bwd_workspace(p).att),
+            reinterpret_cast<int32_t*>(static_cast<char*>(ws) + bwd_workspace(p).order), dQ, dKp, dVp, dKl, dVl};
   const int sub = p.B / kTile;
   const long n_lanes = p.H * row_blocks(p.Nq) * 32 * (p.d / 8);
-  const dim3 pgrid((unsigned)((n_lanes + 255) / 256));
-  if (p.d == 128) hipLaunchKernelGGL(bwd_prep_kernel<128>, pgrid, dim3(256), 0, stream, a);
-  else hipLaunchKernelGGL(bwd_prep_kernel<64>, pgrid, dim3(256), 0, stream, a);
+  const dim3 pgrid((unsigned)((n_lanes + 255) / 256 + p.H));
+  const size_t plan_lds = ((size_t)p.n_loc * ((p.nqb + 31) / 32) + p.nqb + 1) * 4;    // at most 35 KB (512 blocks)
+  if (p.d == 128) hipLaunchKernelGGL(bwd_prep_kernel<128>, pgrid, dim3(256), plan_lds, stream, a);
+  else hipLaunchKernelGGL(bwd_prep_kernel<64>, pgrid, dim3(256), plan_lds, stream, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const size_t ring = (size_t)4 * kTile * p.d * 2;
@@ -930,8 +978,8 @@ hipError_t launch_attention_bwd(const pbsa_params& p, const bf16_t* Q, const bf1
   }
   {
     const size_t n_cand = (size_t)p.nqb * sub;
-    const dim3 grid((unsigned)((p.C + 1 + p.n_loc) * sub * p.H));
-    const size_t lds = ring + n_cand * 4 + (size_t)p.nqb * 4 + 16;
+    const dim3 grid(head_items((p.C + 1 + p.n_loc) * sub, p.H));
+    const size_t lds = ring + n_cand * 4 + 16;
     e = p.d == 128 ? launch_with_lds(bwd_dkv_kernel<128>, a, grid, kThreads, lds, stream)
                    : launch_with_lds(bwd_dkv_kernel<64>, a, grid, kThreads, lds, stream);
   }

@@ -1,0 +1,36 @@
+"""Backward where its kernels' tiles, lists and workgroup order can go wrong, every element against the fp64 oracle: a last
+row tile of 1, 31, 32, 33 and 63 rows (half tiles with no row, one row, all but one), one, three and nine heads (fewer and
+more than the eight dies the grid is dealt over), more query blocks than one word of the turned-around selection holds,
+blocks that every row, few rows and no row selected.  Bounds: those of test_gpu_parity_grad.py, derived there."""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from tests.test_gpu_parity import rnd  # noqa: E402
+from tests.test_gpu_parity_fine_mass import small_pair  # noqa: E402
+from tests.test_gpu_parity_grad import backward_both, gpu  # noqa: E402,F401
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # name,        H, d,   B,   Nq,   w, C, k, n_sink, causal, p_lens
+    ("rows1",      1, 128, 64,  65,   1, 2, 2, 0, 1, [64, 33]),
+    ("rows31",     3, 64,  64,  159,  1, 1, 2, 0, 0, [31]),
+    ("rows32",     3, 128, 128, 160,  1, 2, 1, 0, 1, [128, 97]),
+    ("rows33",     9, 64,  64,  97,   1, 2, 3, 0, 1, [1, 64]),
+    ("rows63",     9, 128, 64,  127,  0, 1, 1, 0, 1, [32]),
+    ("two_words",  1, 64,  64,  2113, 0, 1, 3, 0, 0, [64]),
+    ("three_words", 2, 128, 64, 4100, 0, 1, 2, 0, 1, [64]),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
+def test_backward_tile_edges(gpu, case):  # noqa: F811
+    st, c = small_pair(gpu, case)
+    name, H, d, B, Nq, w = case[:6]
+    for g in range(w + 1):
+        Q, K, V = rnd(140 + 3 * g, H, Nq, d), rnd(141 + 3 * g, H, Nq, d, scale=1.5), rnd(142 + 3 * g, H, Nq, d)
+        backward_both(gpu, c, st, Q, K, V, g, f"bwd tiles {name}")
+        if g < w:                            # nothing is evicted yet: both sides only close the chunk
+            st.update()
+            c.update()
