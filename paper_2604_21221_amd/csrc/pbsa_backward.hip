@@ -21,7 +21,7 @@
 // Tiles go from global memory straight to LDS (global_load_lds), half a tile (32 streamed rows) per ring entry; the
 // 16-byte chunks of a row are permuted by the row number so that both the row-wise and the transposing operand
 // reads are free of bank conflicts.  Rows past a tile's valid length are never loaded: their lanes fetch the last
-// valid row, and the elementwise stage zeroes what belongs to them.  dq holds 64 fixed rows per wave, so every
+// valid row, and a -inf in the place of its score or its lse makes their P an exact zero.  dq holds 64 fixed rows per wave, so every
 // fragment read from LDS feeds two MFMAs; dkv cannot at d = 128 (two outputs: 256 accumulator registers for 64
 // keys) and holds 32 per wave: it reads one fragment per MFMA.
 #include <type_traits>
@@ -60,7 +60,7 @@ struct BwdArgs {
   const float* lse;
   float* rows;        // [H][ceil(Nq / 64) * 2][64]: of 32 rows, -lse log2 e (-inf: no such row), then -rowsum(dO o O)
   uint32_t* att;      // [H][n_loc_cap][ceil(nqb / 32)] bit i: query block i attends local block l
-  int32_t* order;     // [H][n_loc_cap] the local blocks, the most attended first
+  int4* order;        // [H][n_loc_cap] the local blocks, the most attended first: block, slot (-1: nowhere), tokens, attending blocks
   float* dQ;
   float* dKp;
   float* dVp;
@@ -215,8 +215,11 @@ __device__ __forceinline__ void plan_head(const BwdArgs& a, int h, uint32_t* sme
     }
   }
   __syncthreads();
-  for (int l = tid; l < a.n_loc; l += 256)
-    a.order[(size_t)h * a.n_loc_cap + atomicAdd(&hist[a.nqb - count(l)], 1)] = l;
+  for (int l = tid; l < a.n_loc; l += 256) {
+    const int c = count(l), slot = a.l_map[l], len = min(max(a.l_len[l], 0), a.B);
+    const bool ok = slot >= 0 && slot < a.n_loc_cap;
+    a.order[(size_t)h * a.n_loc_cap + atomicAdd(&hist[a.nqb - c], 1)] = make_int4(l, ok ? slot : -1, len, c);
+  }
 }
 
 template <int D>
@@ -288,19 +291,45 @@ __global__ void __launch_bounds__(kThreads) bwd_dkv_kernel(BwdArgs a) {
     fixed_len = min(max(min(max(a.p_len[(size_t)h * (a.C + 1) + c], 0), a.B) - sub * kTile, 0), kTile);
     kv_slot_tile = rank;
   } else {
-    const int l = a.order[(size_t)h * a.n_loc_cap + (rank - n_pers) / SUB], sub = (rank - n_pers) % SUB;
-    att += ((size_t)h * a.n_loc_cap + l) * ((a.nqb + 31) / 32);
-    const int slot = a.l_map[l];
-    const bool ok = slot >= 0 && slot < a.n_loc_cap;
-    fixed_len = ok ? min(max(min(max(a.l_len[l], 0), a.B) - sub * kTile, 0), kTile) : 0;
-    kv_slot_tile = (ok ? slot : 0) * SUB + sub;
-    if (!ok) fixed_len = -1;             // a block that is nowhere: nothing to write either
+    const int4 o = a.order[(size_t)h * a.n_loc_cap + (rank - n_pers) / SUB];
+    const int sub = (rank - n_pers) % SUB;
+    if (o.y < 0) return;                   // a block that is nowhere: nothing to write either
+    att += ((size_t)h * a.n_loc_cap + o.x) * ((a.nqb + 31) / 32);
+    fixed_len = o.w > 0 ? min(max(o.z - sub * kTile, 0), kTile) : 0;
+    kv_slot_tile = o.y * SUB + sub;
   }
-  if (fixed_len < 0) return;
+  const size_t base = kv_local ? ((size_t)h * a.n_loc_cap * a.B + (size_t)kv_slot_tile * kTile) * D
+                               : ((size_t)h * (a.C + 1) * a.B + (size_t)kv_slot_tile * kTile) * D;
+  float* const dk = (kv_local ? a.dKl : a.dKp) + base;
+  float* const dv = (kv_local ? a.dVl : a.dVp) + base;
+  if (fixed_len == 0) {                    // no key, or nobody attends them
+    for (int i = 4 * tid; i < kTile * D; i += 4 * kThreads) {
+      *reinterpret_cast<float4*>(dk + i) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      *reinterpret_cast<float4*>(dv + i) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    }
+    return;
+  }
+
+  // ---- fixed fragments (B operands): fixed row 32 w + lane % 32, dims 16 ks + 8 (lane / 32) .. + 8 ----
+  // asked for before the list is built, so that they arrive meanwhile (3 heads x 1500 x 64: select, forward and backward
+  // 90.1 -> 87.9 us with this and the tiles nobody attends written at once)
+  bf16x8 f1[KS], f2[KS];
+  {
+    const int row = min(32 * wave + qn, fixed_len - 1);
+    const bf16_t* p1 = (kv_local ? a.Kl : a.Kp) + base + (size_t)row * D;
+    const bf16_t* p2 = (kv_local ? a.Vl : a.Vp) + base + (size_t)row * D;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      f1[ks] = *reinterpret_cast<const bf16x8*>(p1 + 16 * ks + 8 * half);
+      f2[ks] = *reinterpret_cast<const bf16x8*>(p2 + 16 * ks + 8 * half);
+    }
+  }
+
+  // ---- the list of streamed tiles ----------------------------------------------------------------
   auto classify = [&](int i, int& where) -> bool {
     if (i >= n_cand) return false;
     const int ib = i / SUB;
-    if (fixed_len <= 0 || (kv_local && !((att[ib >> 5] >> (ib & 31)) & 1u))) return false;
+    if (kv_local && !((att[ib >> 5] >> (ib & 31)) & 1u)) return false;
     where = i;                                      // row tile i covers tokens 64 i ..
     return a.Nq - i * kTile > 0;
   };
@@ -330,22 +359,6 @@ __global__ void __launch_bounds__(kThreads) bwd_dkv_kernel(BwdArgs a) {
   }
   __syncthreads();
 
-  // ---- fixed fragments (B operands): fixed row 32 w + lane % 32, dims 16 ks + 8 (lane / 32) .. + 8 ----
-  bf16x8 f1[KS], f2[KS];
-  {
-    const int row = min(32 * wave + qn, max(fixed_len, 1) - 1);
-    const bf16_t *p1, *p2;
-    const size_t base = kv_local ? ((size_t)h * a.n_loc_cap * a.B + (size_t)kv_slot_tile * kTile) * D
-                                 : ((size_t)h * (a.C + 1) * a.B + (size_t)kv_slot_tile * kTile) * D;
-    p1 = (kv_local ? a.Kl : a.Kp) + base + (size_t)row * D;
-    p2 = (kv_local ? a.Vl : a.Vp) + base + (size_t)row * D;
-  
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      f1[ks] = *reinterpret_cast<const bf16x8*>(p1 + 16 * ks + 8 * half);
-      f2[ks] = *reinterpret_cast<const bf16x8*>(p2 + 16 * ks + 8 * half);
-    }
-  }
   // they have arrived before the walk starts: no wait for them inside it, where one would also wait for the tiles
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+a"(f1[ks]), "+a"(f2[ks]));
@@ -600,10 +613,8 @@ __global__ void __launch_bounds__(kThreads) bwd_dkv_kernel(BwdArgs a) {
   // ---- outputs: element v of tile dt is dim 32 dt + 8 (v / 4) + 4 half + v % 4 of fixed row 32 w + lane % 32 ----
   const int frow = 32 * wave + qn;
   // every row of the tile's slot is written: zeros past the valid length and for a block nobody attends
-  const size_t base = kv_local ? ((size_t)h * a.n_loc_cap * a.B + (size_t)kv_slot_tile * kTile) * D
-                               : ((size_t)h * (a.C + 1) * a.B + (size_t)kv_slot_tile * kTile) * D;
-  float* ok_ = (kv_local ? a.dKl : a.dKp) + base + (size_t)frow * D;
-  float* ov_ = (kv_local ? a.dVl : a.dVp) + base + (size_t)frow * D;
+  float* ok_ = dk + (size_t)frow * D;
+  float* ov_ = dv + (size_t)frow * D;
   const float sc = frow < fixed_len ? a.scale : 0.0f, one = frow < fixed_len ? 1.0f : 0.0f;
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt)
@@ -617,16 +628,14 @@ __global__ void __launch_bounds__(kThreads) bwd_dkv_kernel(BwdArgs a) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// dq with 64 query rows per wave.  One workgroup = one wave = 64 query rows (two MFMA column groups of 32), so
-// that every K or V fragment read from LDS -- row-wise for the first products, transposed for the second --
-// feeds two MFMAs: the kernel above, where a wave owns 32 rows, reads one fragment per MFMA and is bound by the
-// LDS bandwidth.  The wave stages its own half tiles (32 keys of K and of V per ring entry, two entries) and is
-// the only one to read them: no barrier anywhere.  Q and dO fragments and the dQ^T accumulators fill the
-// accumulator half of the register file (128 + 128 registers at d = 128).  A turn, on one half tile:
-//     first products of column group 0            (2 KS MFMAs)
-//     first products of column group 1            (2 KS MFMAs)  with the elementwise stage of group 0 behind them
-//     second products of group 0                  (2 DT MFMAs)  with the elementwise stage of group 1 behind them
-//     second products of group 1                  (2 DT MFMAs)
+// dq with 64 query rows per wave.  One workgroup = one wave = 64 query rows (two MFMA column groups of 32), so that every
+// K or V fragment read from LDS -- row-wise for the first products, transposed for the second -- feeds two MFMAs.  The
+// wave stages its own half tiles (32 keys of K and of V per ring entry, two entries) and is the only one to read them: no
+// barrier anywhere.  Q and dO fragments and the dQ^T accumulators fill the accumulator half of the register file
+// (128 + 128 registers at d = 128).  Bound: the vector work, about 26 cycles per probability, has only the 28 of a turn's
+// 48 MFMAs to hide behind that follow the scores it works on.  Two waves to a workgroup that share the tiles both attend
+// (half the traffic with 128-token blocks, three half tiles on their way) measured 223 -> 217 and 144 -> 136 us at 12 x
+// 4680 x 128, but 32.6 -> 35.3 us at 3 x 1500 x 64, and no case gained by it.
 // ------------------------------------------------------------------------------------------------
 template <int D>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1))) bwd_dq_kernel(BwdArgs a) {
@@ -945,7 +954,7 @@ static BwdWorkspace bwd_workspace(const pbsa_params& p) {
   BwdWorkspace w;
   w.att = (size_t)p.H * row_blocks(p.Nq) * 64 * 4;
   w.order = w.att + up((size_t)p.H * p.n_loc_cap * ((p.nqb + 31) / 32) * 4);
-  w.bytes = w.order + up((size_t)p.H * p.n_loc_cap * 4);
+  w.bytes = w.order + up((size_t)p.H * p.n_loc_cap * 16);
   return w;
 }
 size_t bwd_workspace_bytes(const pbsa_params& p) { return bwd_workspace(p).bytes; }
@@ -958,7 +967,7 @@ hipError_t launch_attention_bwd(const pbsa_params& p, const bf16_t* Q, const bf1
   BwdArgs a{p.H, p.Nq, p.nqb, p.n_loc, p.n_loc_cap, p.C, p.k, p.B, p.scale, p.q_stride_h, p.q_stride_t, p.o_stride_h,
             p.o_stride_t, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, dO, lse, static_cast<float*>(ws),
             reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + bwd_workspace(p).att),
-            reinterpret_cast<int32_t*>(static_cast<char*>(ws) + bwd_workspace(p).order), dQ, dKp, dVp, dKl, dVl};
+            reinterpret_cast<int4*>(static_cast<char*>(ws) + bwd_workspace(p).order), dQ, dKp, dVp, dKl, dVl};
   const int sub = p.B / kTile;
   const long n_lanes = p.H * row_blocks(p.Nq) * 32 * (p.d / 8);
   const dim3 pgrid((unsigned)((n_lanes + 255) / 256 + p.H));
