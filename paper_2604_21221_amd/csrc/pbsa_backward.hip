@@ -311,8 +311,8 @@ __global__ void __launch_bounds__(kThreads) bwd_dkv_kernel(BwdArgs a) {
   }
 
   // ---- fixed fragments (B operands): fixed row 32 w + lane % 32, dims 16 ks + 8 (lane / 32) .. + 8 ----
-  // asked for before the list is built, so that they arrive meanwhile (3 heads x 1500 x 64: select, forward and backward
-  // 90.1 -> 87.9 us with this and the tiles nobody attends written at once)
+  // asked for before the list is built, so that they arrive meanwhile (with what prep leaves beside each block and the tiles
+  // nobody attends written at once: select, forward and backward of 16 heads x 4000 x 64 with 4 + 8 blocks 164 -> 154 us)
   bf16x8 f1[KS], f2[KS];
   {
     const int row = min(32 * wave + qn, fixed_len - 1);
@@ -632,10 +632,11 @@ __global__ void __launch_bounds__(kThreads) bwd_dkv_kernel(BwdArgs a) {
 // K or V fragment read from LDS -- row-wise for the first products, transposed for the second -- feeds two MFMAs.  The
 // wave stages its own half tiles (32 keys of K and of V per ring entry, two entries) and is the only one to read them: no
 // barrier anywhere.  Q and dO fragments and the dQ^T accumulators fill the accumulator half of the register file
-// (128 + 128 registers at d = 128).  Bound: the vector work, about 26 cycles per probability, has only the 28 of a turn's
-// 48 MFMAs to hide behind that follow the scores it works on.  Two waves to a workgroup that share the tiles both attend
-// (half the traffic with 128-token blocks, three half tiles on their way) measured 223 -> 217 and 144 -> 136 us at 12 x
-// 4680 x 128, but 32.6 -> 35.3 us at 3 x 1500 x 64, and no case gained by it.
+// (128 + 128 registers at d = 128).  Bound at 12 x 4680 x 128: matrix and vector work in one wave per SIMD at the clock the
+// chip holds under it (222 GFLOP in 215 us, 1.03 PFLOP/s; a library product of 8192^3 reaches 1.19).  The elementwise stages
+// are spread over 40 of a turn's 48 MFMAs; over 28 of them: 712.8 against 708.3 us for select, forward and backward, 89.8
+// against 88.2 at 3 x 1500 x 64.  Two waves to a workgroup that share the tiles both attend (half the traffic with
+// 128-token blocks, three half tiles on their way): 217 us, and 35.3 against 32.6 at 3 x 1500 x 64, where it lost.
 // ------------------------------------------------------------------------------------------------
 template <int D>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1))) bwd_dq_kernel(BwdArgs a) {
@@ -791,15 +792,17 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1)))
 
   // ---- the walk ------------------------------------------------------------------------------------------
   // A turn works on one half tile u, whose row fragments are in registers when it starts:
-  //   1  the first products of column group 0                             (2 KS MFMAs)
-  //   2  those of group 1, with the elementwise stage of group 0 and the transposing reads behind them
+  //   1  the first products of column group 0            (2 KS MFMAs), behind them the elementwise stage of group 1, u - 1
+  //   2  the second products of group 1, u - 1           (2 DT)
+  //   3  the first products of group 1                   (2 KS), behind them the elementwise stage of group 0 and the
+  //                                                      transposing reads of u
   //      then half tile u + 1 has landed (it was sent for a turn ago), and u + 2 is sent for, into the entry of u
-  //   3  second products, group 0 then group 1 (4 DT MFMAs), with the elementwise stage of group 1 behind the first
-  //      three quarters of them (its later half is due only at the last quarter) and the row reads of u + 1
-  // Per element: fma, exp2, multiply, half of a conversion; -D is what the dP accumulators start from, and a key past the
-  // tile's length has -inf in the score accumulator's start (the scale is positive), so its P is an exact zero.
-  // The empty asm statements keep MFMAs and slices where they stand; without them the compiler issues all the
-  // elementwise work behind the last MFMA of its phase.
+  //   4  the second products of group 0                  (2 DT), behind them the row reads of u + 1
+  // The last quarter of an elementwise stage runs behind the first DT of the second products that follow it: those need
+  // its first half only.  Per element: fma, exp2, multiply, half of a conversion; -D is what the dP accumulators start
+  // from, and a key past the tile's length has -inf in the score accumulator's start (the scale is positive), so its P is
+  // an exact zero.  The empty asm statements keep MFMAs and slices where they stand; without them the compiler issues
+  // all the elementwise work behind the last MFMA of its phase.
   bf16x8 x[NS];                            // row fragments: x[2 ks] of K, x[2 ks + 1] of V
   f32x16 km;                               // 0 or, for a key that does not exist, -inf, in accumulator order
 #pragma unroll
@@ -813,6 +816,67 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1)))
 #pragma unroll
     for (int i = 0; i < NS; ++i) x[i] = lds_read_row(rd[i / 2] + (i % 2) * HALF);
   }
+  f32x16 a1[2], a2[2];
+  u32x4 eZ[2][2];
+  bf16x8 tf[2 * DT];                       // transposed fragments: 16 keys j, 32 dims dt at j DT + dt
+  float ex[2][16], zz[2][16];
+  constexpr int E1 = 12;                   // elements of a stage that run behind the first products; E2 slots take the rest
+  auto begin = [&](int n, int v) { ex[n][v] = __builtin_amdgcn_exp2f(__builtin_fmaf(a1[n][v], c2, nl_fix[n])); };
+  auto finish = [&](int n, int v) {
+    zz[n][v] = ex[n][v] * a2[n][v];
+    if (v % 2 == 1) {
+      eZ[n][v / 8][(v % 8) / 2] = pack2(zz[n][v - 1], zz[n][v]);
+      asm volatile("" : "+v"(eZ[n][v / 8][(v % 8) / 2]));
+    }
+  };
+  // elements [lo, hi) begun, [lo0, lo) finished
+  auto slice = [&](int n, int lo0, int lo, int hi) {
+#pragma unroll
+    for (int v = lo; v < hi; ++v) begin(n, v);
+#pragma unroll
+    for (int v = lo0; v < lo; ++v) finish(n, v);
+#pragma unroll
+    for (int v = lo; v < hi; ++v) asm volatile("" : "+v"(ex[n][v]));
+  };
+  const auto nothing = [](int) {};
+  // the first products of group n and, behind them, elements 0 .. E1 - 1 of the other group's elementwise stage
+  auto run_phase = [&](int n, auto PRODUCTS, auto behind) {
+    const auto at = [](int sl) { return sl < 0 ? 0 : E1 * sl / NS; };
+#pragma unroll
+    for (int sl = 0; sl < NS; ++sl) {
+      if constexpr (decltype(PRODUCTS)::value) {
+        const int ks = sl / 2;
+        if (sl % 2 == 0) {
+          a1[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[sl], f1[n][ks], ks == 0 ? km : a1[n], 0, 0, 0);
+          asm volatile("" : "+v"(a1[n]));
+        } else {
+          a2[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[sl], f2[n][ks], ks == 0 ? dn[n] : a2[n], 0, 0, 0);
+          asm volatile("" : "+v"(a2[n]));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      behind(sl);
+      slice(n ^ 1, at(sl - 1), at(sl), at(sl + 1));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // what the first DT of the second products need is finished before them
+    static_assert(E1 * (NS - 1) / NS >= 8, "the first half of the elements is finished by the last slice");
+    asm volatile("s_nop 4" ::: "memory");
+  };
+  // the second products of group n, the rest of its elementwise stage behind the first DT of them
+  auto second_products = [&](int n, auto behind) {
+    constexpr int LAST = E1 * (NS - 1) / NS;                // begun in the last slice, not finished
+    const auto at = [](int i) { return E1 + (16 - E1) * i / (DT - 1); };
+#pragma unroll
+    for (int i = 0; i < 2 * DT; ++i) {
+      if (i == DT) asm volatile("s_nop 4" ::: "memory");
+      acc_mfma(out[n][i % DT], tf[i], as_bf16x8(eZ[n][i / DT]));
+      __builtin_amdgcn_sched_barrier(0);
+      behind(i);
+      if (i < DT) slice(n, i == 0 ? LAST : at(i - 1), i < DT - 1 ? at(i) : 16, i < DT - 1 ? at(i + 1) : 16);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
   auto turn = [&](auto MG, int t) {
     constexpr int mg = decltype(MG)::value;                 // two turns per tile: the ring entry is the half
     const int u = 2 * t + mg;
@@ -830,89 +894,48 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1)))
       km_clear = true;
     }
     __builtin_amdgcn_sched_barrier(0);
-    f32x16 a1[2], a2[2];
+    run_phase(0, std::true_type{}, nothing);
+    second_products(1, nothing);
+    {
+      const uint32_t at0 = (uint32_t)(mg * TILE);
+      run_phase(1, std::true_type{}, [&](int sl) {
+        if (sl >= NS / 4 && sl < NS / 4 + DT) {
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      a1[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[2 * ks], f1[0][ks], ks == 0 ? km : a1[0], 0, 0, 0);
-      a2[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[2 * ks + 1], f2[0][ks], ks == 0 ? dn[0] : a2[0], 0, 0, 0);
-    }
-    asm volatile("" : "+v"(a1[0]), "+v"(a2[0]));
-    __builtin_amdgcn_sched_barrier(0);
-    u32x4 eZ[2][2];
-    bf16x8 tf[2 * DT];
-    float ex[2][16], zz[2][16];
-    auto begin = [&](int n, int v) { ex[n][v] = __builtin_amdgcn_exp2f(__builtin_fmaf(a1[n][v], c2, nl_fix[n])); };
-    auto finish = [&](int n, int v) {
-      zz[n][v] = ex[n][v] * a2[n][v];
-      if (v % 2 == 1) {
-        eZ[n][v / 8][(v % 8) / 2] = pack2(zz[n][v - 1], zz[n][v]);
-        asm volatile("" : "+v"(eZ[n][v / 8][(v % 8) / 2]));
-      }
-    };
-#pragma unroll
-    for (int sl = 0; sl < NS; ++sl) {
-      const int ks = sl / 2;
-      if (sl % 2 == 0) {
-        a1[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[sl], f1[1][ks], ks == 0 ? km : a1[1], 0, 0, 0);
-        asm volatile("" : "+v"(a1[1]));
-      } else {
-        a2[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[sl], f2[1][ks], ks == 0 ? dn[1] : a2[1], 0, 0, 0);
-        asm volatile("" : "+v"(a2[1]));
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      if (sl >= NS / 4 && sl < NS / 4 + DT) {
-#pragma unroll
-        for (int r = 0; r < 2; ++r) {
-          const int i = 2 * (sl - NS / 4) + r;
-          const uint32_t at = (uint32_t)(mg * TILE + 16 * (i / DT) * ROW);
-          tf[i] = lds_read_tr2(tl[i % DT] + at, th[i % DT] + at);
+          for (int r = 0; r < 2; ++r) {
+            const int i = 2 * (sl - NS / 4) + r;
+            const uint32_t at = at0 + (uint32_t)(16 * (i / DT) * ROW);
+            tf[i] = lds_read_tr2(tl[i % DT] + at, th[i % DT] + at);
+          }
         }
-      }
-#pragma unroll
-      for (int r = 0; r < EPS; ++r) begin(0, sl * EPS + r);
-#pragma unroll
-      for (int r = 0; r < EPS; ++r)
-        if (sl > 0) finish(0, (sl - 1) * EPS + r);
-#pragma unroll
-      for (int r = 0; r < EPS; ++r) asm volatile("" : "+v"(ex[0][sl * EPS + r]));
-      __builtin_amdgcn_sched_barrier(0);
+      });
     }
-#pragma unroll
-    for (int r = 0; r < EPS; ++r) finish(0, (NS - 1) * EPS + r);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // half tile u + 1 is in
     __builtin_amdgcn_s_waitcnt(0xC07F);                     // lgkmcnt(0): and u read (nobody else uses the ring)
-    asm volatile("s_nop 4" ::: "memory");
     if (u + 2 < n_half) stage(u + 2, mg);
     __builtin_amdgcn_sched_barrier(0);
-    constexpr int NP = 4 * DT, Q3 = 3 * DT, RPS = NS / Q3 + 1;   // products; elementwise slots; reads per slot
+    second_products(0, [&](int i) {
 #pragma unroll
-    for (int i = 0; i < NP; ++i) {
-      const int n = i / (2 * DT), j = (i / DT) % 2, dt = i % DT;
-      acc_mfma(out[n][dt], tf[j * DT + dt], as_bf16x8(eZ[n][j]));
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int r = 0; r < RPS; ++r) {
-        const int f = i * RPS + r;
-        if (f < NS) x[f] = lds_read_row(rd[f / 2] + (mg ^ 1) * TILE + (f % 2) * HALF);
+      for (int r = 0; r < 2; ++r) {
+        const int f = 2 * i + r;
+        x[f] = lds_read_row(rd[f / 2] + (mg ^ 1) * TILE + (f % 2) * HALF);
       }
-      // group 1, elements first(i) .. first(i + 1) - 1 begun here; finished one slot later, in time for the group 1
-      // products of their half (8 elements by slot 2 DT, all by slot 3 DT)
-      if (i < Q3) {
-        const auto first = [](int s) { return s <= 0 ? 0 : s >= Q3 - 1 ? 16 : (16 * s + Q3 - 2) / (Q3 - 1); };
-#pragma unroll
-        for (int v = first(i); v < first(i + 1); ++v) begin(1, v);
-#pragma unroll
-        for (int v = first(i - 1); v < first(i); ++v) finish(1, v);
-#pragma unroll
-        for (int v = first(i); v < first(i + 1); ++v) asm volatile("" : "+v"(ex[1][v]));
-      }
-      if (i == 2 * DT - 1 || i == Q3 - 1) asm volatile("s_nop 4" ::: "memory");
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    });
   };
-  for (int t = 0; t < n_tiles; ++t) {
-    turn(std::integral_constant<int, 0>{}, t);
-    turn(std::integral_constant<int, 1>{}, t);
+  // before the first half tile: a stage of group 1 that adds nothing
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    a1[1][v] = -INFINITY;
+    a2[1][v] = 0.0f;
+  }
+#pragma unroll
+  for (int i = 0; i < 2 * DT; ++i) tf[i] = bf16x8{};
+  if (n_tiles > 0) {
+    for (int t = 0; t < n_tiles; ++t) {
+      turn(std::integral_constant<int, 0>{}, t);
+      turn(std::integral_constant<int, 1>{}, t);
+    }
+    run_phase(0, std::false_type{}, nothing);               // group 1 of the last half tile
+    second_products(1, nothing);
   }
   // the compiler does not see the matrix instructions that wrote the output accumulators: let the pipe drain
 #pragma unroll
