@@ -19,8 +19,8 @@
 //   second products are transposing LDS reads of the streamed tiles with the same enumeration:
 //          dq:  dQ^T += K^T dZ^T          dkv: dK^T += Q^T dZ,  dV^T += dO^T P
 // Tiles go from global memory straight to LDS (global_load_lds), half a tile (32 streamed rows) per ring entry; the
-// 16-byte chunks of a row are permuted by the row number so that both the row-wise and the transposing operand
-// reads are free of bank conflicts.  Rows past a tile's valid length are never loaded: their lanes fetch the last
+// 16-byte chunks of a row are permuted by the row number so that the row-wise operand reads are
+// free of bank conflicts and a transposing one has two cycles of them (a permutation without any changed no time).  Rows past a tile's valid length are never loaded: their lanes fetch the last
 // valid row, and a -inf in the place of its score or its lse makes their P an exact zero.  dq holds 64 fixed rows per wave, so every
 // fragment read from LDS feeds two MFMAs; dkv cannot at d = 128 (two outputs: 256 accumulator registers for 64
 // keys) and holds 32 per wave: it reads one fragment per MFMA.
