@@ -76,7 +76,7 @@ extern "C" {
 #define PBSA_EWS    (-4) /* workspace missing or smaller than pbsa_workspace_bytes()            */
 #define PBSA_EHIP   (-5) /* a HIP call or kernel launch failed                                   */
 
-/* Limits of pbsa_select_blocks and pbsa_attention_fwd (the largest shape of the paper's kernel benchmark,
+/* Limits of pbsa_select_blocks, pbsa_attention_fwd and pbsa_attention_fwd_split (the largest shape of the paper's kernel benchmark,
  * N_C = 21504 queries against N_L = 4 N_C local and N_P = N_L / 2 persistent tokens in blocks of 128, fits). */
 #define PBSA_MAX_N_LOC 672 /* logical local blocks          */
 #define PBSA_MAX_K     672 /* selected blocks per query block */
@@ -112,7 +112,7 @@ typedef struct pbsa_params {
 
 /* Bytes of scratch that any call with these parameters needs (device memory, 256-byte aligned, passed as `ws`).
  * Contents need not be preserved between calls.  Only pbsa_memory_update in all its forms needs any, so C is held to
- * PBSA_MAX_C here as there.  (pbsa_attention_workspace_bytes: what an attention call can use beyond that.) */
+ * PBSA_MAX_C here as there.  (pbsa_attention_workspace_bytes: what the attention can use beside that.) */
 int pbsa_workspace_bytes(const pbsa_params* p, size_t* out);
 
 /* Block representatives by average pooling (Eq. 6; pooling operator of Sec. 4.1):
@@ -157,16 +157,22 @@ int pbsa_select_blocks(const pbsa_params* p, const void* Q, const void* Kl, cons
  * accumulation and fp32 online softmax; the probabilities are rounded to bf16 for the second product and
  * the normaliser is their sum after rounding; O is rounded to bf16 (nearest even).  `lse` (optional,
  * [H][Nq] fp32) receives the natural log of that normaliser (within 4e-3 of the exact one).  A row that sees no key gets O = 0,
- * lse = -inf.  Entries of sel must be -1 or in [0, n_loc).
- * ws may be NULL.  Given pbsa_attention_workspace_bytes(p) bytes (which may be 0; 256-byte aligned), a launch whose last
- * round of workgroups would leave most of the GPU idle shares the keys of those rows out over it and puts the
- * partial results together in fp32 in a second launch: the same softmax in another order of summation, decided by the
- * shape alone.  pbsa_attention_fwd_plan and pbsa_attention_fwd_mass do the same when the workspaces they take are that
- * much larger than they need. */
-int pbsa_attention_workspace_bytes(const pbsa_params* p, size_t* out);
+ * lse = -inf.  Entries of sel must be -1 or in [0, n_loc).  ws may be NULL; it is not looked at. */
 int pbsa_attention_fwd(const pbsa_params* p, const void* Q, const void* Kp, const void* Vp, const int32_t* p_len,
                        const void* Kl, const void* Vl, const int32_t* l_len, const int32_t* l_map,
                        const int32_t* sel, void* O, float* lse, void* ws, size_t ws_bytes, void* hip_stream);
+
+/* pbsa_attention_fwd with scratch: a launch whose last round of workgroups would leave most of the GPU idle shares the
+ * keys of those rows out over it and puts the partial results together in fp32 in a second launch -- the same softmax in
+ * another order of summation, decided by p alone.  ws: pbsa_attention_workspace_bytes(p) bytes (0 where nothing is
+ * shared out; ws may be NULL then), 256-byte aligned, contents not kept.  It is written: it must not overlap a
+ * workspace that holds a plan still to be applied (pbsa_memory_update_plan, pbsa_attention_fwd_plan), nor the ws of a
+ * call that may run at the same time.  pbsa_attention_fwd_plan and pbsa_attention_fwd_mass share out in the same way
+ * when the workspace they take is that much larger than they need (the share lies behind their own part). */
+int pbsa_attention_workspace_bytes(const pbsa_params* p, size_t* out);
+int pbsa_attention_fwd_split(const pbsa_params* p, const void* Q, const void* Kp, const void* Vp, const int32_t* p_len,
+                             const void* Kl, const void* Vl, const int32_t* l_len, const int32_t* l_map,
+                             const int32_t* sel, void* O, float* lse, void* ws, size_t ws_bytes, void* hip_stream);
 
 /* Persistent-memory update (Eq. 7-9).  Scores: block-level softmax of each pooled query over
  * U = occupied slots 0..C-1 followed by all n_loc local blocks, averaged over query blocks
@@ -235,7 +241,8 @@ int pbsa_select_blocks_apply(const pbsa_params* p, const void* Q, const void* Kl
 /* pbsa_attention_fwd and pbsa_memory_update_plan of the same chunk as ONE launch (Alg. 1 with the update's
  * decisions, Eq. 7-9, taken while the fine stage of Eq. 3-5 runs): the attention's grid gets H more workgroups, one
  * per head, that do the plan call's work.  Nothing they read is written by the attention part and the other way
- * round, so the results are those of the two calls, bit for bit; a launch whose attention workgroups do not fill
+ * round, so the results are those of the two calls, bit for bit (with the share of pbsa_attention_workspace_bytes(p)
+ * behind the workspace: those of pbsa_attention_fwd_split); a launch whose attention workgroups do not fill
  * the GPU (two workgroups of 128 query rows per compute unit) has the plan's work for free.  Arguments: those of
  * pbsa_attention_fwd (p->C <= PBSA_MAX_C here), then those of pbsa_memory_update_plan that it does not have yet;
  * Zl is required (PBSA_EINVAL without), ws as for pbsa_memory_update.  pbsa_memory_update_apply completes the

@@ -191,8 +191,8 @@ class PbsaCache:
             O = torch.empty_like(Q)
         l_map, l_len, _ = self._device_maps()
         p = self.params(Q=Q, O=O)
-        pbsa.pbsa_attention_fwd(p, Q, self.Kp, self.Vp, self.p_len, self.Kl, self.Vl, l_len, l_map, self.sel, O, lse,
-                                self._attn_ws)
+        pbsa.pbsa_attention_fwd_split(p, Q, self.Kp, self.Vp, self.p_len, self.Kl, self.Vl, l_len, l_map, self.sel, O, lse,
+                                      self._attn_ws)
         return O
 
     def _no_pending(self):

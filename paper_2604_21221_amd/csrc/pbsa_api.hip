@@ -207,9 +207,10 @@ int pbsa_attention_workspace_bytes(const pbsa_params* p, size_t* out) {
   return PBSA_OK;
 }
 
-int pbsa_attention_fwd(const pbsa_params* p, const void* Q, const void* Kp, const void* Vp, const int32_t* p_len,
-                       const void* Kl, const void* Vl, const int32_t* l_len, const int32_t* l_map,
-                       const int32_t* sel, void* O, float* lse, void* ws, size_t ws_bytes, void* hip_stream) {
+// What pbsa_attention_fwd and pbsa_attention_fwd_split check alike.
+static int check_attention(const pbsa_params* p, const void* Q, const void* Kp, const void* Vp, const int32_t* p_len,
+                           const void* Kl, const void* Vl, const int32_t* l_len, const int32_t* l_map,
+                           const int32_t* sel, const void* O) {
   int rc = check_common(p, PBSA_MAX_C_ATTEND, PBSA_MAX_N_LOC, PBSA_MAX_K);
   if (rc) return rc;
   if (!Q || !Kp || !Vp || !p_len || !Kl || !Vl || !l_len || !l_map || !O) return PBSA_EINVAL;
@@ -220,12 +221,36 @@ int pbsa_attention_fwd(const pbsa_params* p, const void* Q, const void* Kp, cons
   if (rc) return rc;
   if (!aligned16(Q) || !aligned16(Kp) || !aligned16(Vp) || !aligned16(Kl) || !aligned16(Vl) || !aligned16(O))
     return PBSA_EALIGN;
+  return PBSA_OK;
+}
+
+int pbsa_attention_fwd(const pbsa_params* p, const void* Q, const void* Kp, const void* Vp, const int32_t* p_len,
+                       const void* Kl, const void* Vl, const int32_t* l_len, const int32_t* l_map,
+                       const int32_t* sel, void* O, float* lse, void* ws, size_t ws_bytes, void* hip_stream) {
+  (void)ws; (void)ws_bytes;                // a caller may hold a plan still to be applied there
+  int rc = check_attention(p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O);
+  if (rc) return rc;
+  hipError_t e = pbsa::launch_attention(
+      *p, static_cast<const pbsa::bf16_t*>(Q), static_cast<const pbsa::bf16_t*>(Kp),
+      static_cast<const pbsa::bf16_t*>(Vp), p_len, static_cast<const pbsa::bf16_t*>(Kl),
+      static_cast<const pbsa::bf16_t*>(Vl), l_len, l_map, sel, static_cast<pbsa::bf16_t*>(O), lse, nullptr, nullptr,
+      static_cast<hipStream_t>(hip_stream));
+  return e == hipSuccess ? PBSA_OK : hip_fail(e);
+}
+
+int pbsa_attention_fwd_split(const pbsa_params* p, const void* Q, const void* Kp, const void* Vp, const int32_t* p_len,
+                             const void* Kl, const void* Vl, const int32_t* l_len, const int32_t* l_map,
+                             const int32_t* sel, void* O, float* lse, void* ws, size_t ws_bytes, void* hip_stream) {
+  int rc = check_attention(p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O);
+  if (rc) return rc;
+  const size_t need = pbsa::attn_split(*p).bytes;
+  if (need > 0 && (!ws || ws_bytes < need)) return PBSA_EWS;
+  if (need > 0 && (reinterpret_cast<uintptr_t>(ws) & 255u)) return PBSA_EALIGN;
   hipError_t e = pbsa::launch_attention(
       *p, static_cast<const pbsa::bf16_t*>(Q), static_cast<const pbsa::bf16_t*>(Kp),
       static_cast<const pbsa::bf16_t*>(Vp), p_len, static_cast<const pbsa::bf16_t*>(Kl),
       static_cast<const pbsa::bf16_t*>(Vl), l_len, l_map, sel, static_cast<pbsa::bf16_t*>(O), lse, nullptr,
-      split_scratch(*p, ws, ws_bytes, 0),
-      static_cast<hipStream_t>(hip_stream));
+      need > 0 ? ws : nullptr, static_cast<hipStream_t>(hip_stream));
   return e == hipSuccess ? PBSA_OK : hip_fail(e);
 }
 

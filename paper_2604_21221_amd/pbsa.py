@@ -20,7 +20,7 @@ PBSA_MAX_N_LOC_AUX, PBSA_MAX_C_AUX, PBSA_MAX_K_AUX = 512, 192, 512
 PBSA_STATIC_WS_BYTES = 4 << 20
 
 EXPORTS = ("pbsa_workspace_bytes", "pbsa_pool_blocks", "pbsa_summary_view", "pbsa_append_chunk", "pbsa_attention_workspace_bytes", "pbsa_select_blocks", "pbsa_attention_fwd",
-           "pbsa_memory_update", "pbsa_memory_update_static", "pbsa_memory_update_plan", "pbsa_memory_update_apply", "pbsa_attention_fwd_plan",
+           "pbsa_attention_fwd_split", "pbsa_memory_update", "pbsa_memory_update_static", "pbsa_memory_update_plan", "pbsa_memory_update_apply", "pbsa_attention_fwd_plan",
            "pbsa_select_blocks_apply",
            "pbsa_attention_mass", "pbsa_mass_workspace_bytes", "pbsa_attention_fwd_mass",
            "pbsa_memory_update_fine", "pbsa_bwd_workspace_bytes", "pbsa_attention_bwd", "pbsa_blockify",
@@ -85,7 +85,7 @@ def lib() -> ctypes.CDLL:
         i64 = ctypes.c_int64
         L.pbsa_append_chunk.argtypes = [pp, vp, vp, i64, i64, i64, i64, i32, i32, vp, vp, vp, vp]
         L.pbsa_select_blocks.argtypes = [pp] + [vp] * 9 + [sz, vp]
-        L.pbsa_attention_fwd.argtypes = [pp] + [vp] * 12 + [sz, vp]
+        L.pbsa_attention_fwd.argtypes = L.pbsa_attention_fwd_split.argtypes = [pp] + [vp] * 12 + [sz, vp]
         L.pbsa_memory_update.argtypes = [pp] + [vp] * 18 + [sz, vp]
         L.pbsa_memory_update_static.argtypes = [pp] + [vp] * 18
         L.pbsa_memory_update_plan.argtypes = [pp] + [vp] * 13 + [sz, vp]
@@ -102,7 +102,7 @@ def lib() -> ctypes.CDLL:
         L.pbsa_blockify.argtypes = [pg, i32, ctypes.POINTER(vp), ctypes.POINTER(vp), ctypes.POINTER(ctypes.c_int64), vp]
         L.pbsa_unblockify.argtypes = [pg, vp, ctypes.c_int64, vp, vp]
         for name in ("pbsa_workspace_bytes", "pbsa_pool_blocks", "pbsa_summary_view", "pbsa_append_chunk", "pbsa_attention_workspace_bytes", "pbsa_select_blocks",
-                     "pbsa_attention_fwd", "pbsa_memory_update", "pbsa_memory_update_static", "pbsa_memory_update_plan", "pbsa_memory_update_apply",
+                     "pbsa_attention_fwd", "pbsa_attention_fwd_split", "pbsa_memory_update", "pbsa_memory_update_static", "pbsa_memory_update_plan", "pbsa_memory_update_apply",
                      "pbsa_attention_fwd_plan", "pbsa_select_blocks_apply", "pbsa_attention_mass", "pbsa_mass_workspace_bytes",
                      "pbsa_attention_fwd_mass", "pbsa_memory_update_fine", "pbsa_bwd_workspace_bytes",
                      "pbsa_attention_bwd", "pbsa_blockify", "pbsa_unblockify"):
@@ -218,6 +218,13 @@ def pbsa_select_blocks_apply(p, Q, Kl, l_len, l_map, Kc_l, Qc, sel, Zl, p_upd, K
 def pbsa_attention_fwd(p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse=None, ws=None, stream=None):
     w, wb = _ws(ws)
     _check(_invoke(_A["pbsa_attention_fwd"], p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse, w, wb, _stream(stream)))
+
+
+def pbsa_attention_fwd_split(p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse, ws, stream=None):
+    """pbsa_attention_fwd with pbsa_attention_workspace_bytes(p) bytes of scratch."""
+    w, wb = _ws(ws)
+    _check(_invoke(_A["pbsa_attention_fwd_split"], p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse, w, wb,
+                   _stream(stream)))
 
 
 def pbsa_memory_update(p, Qc, Kc_l, Zl, Kp, Vp, Kc_p, p_len, p_id, S_sum, S_cnt, Kl, Vl, l_len, l_map, l_id, scores,

@@ -267,6 +267,29 @@ def test_attention_with_plan_argument_checks(L):
         assert e.value.code == code, kw
 
 
+def test_split_attention_argument_checks(L):
+    """pbsa_attention_fwd_split validates like pbsa_attention_fwd and wants pbsa_attention_workspace_bytes."""
+    p = good(k=12)                           # 4 query tiles of 17 key tiles each: shared out
+    need = pbsa.pbsa_attention_workspace_bytes(p)
+    assert need >= 2 * 4 * 128 * (128 * 4 + 8) and need % 256 == 0
+    assert pbsa.pbsa_attention_workspace_bytes(good(C=0, k=0)) == 0      # one key tile: nothing to share out
+    with pytest.raises(pbsa.PbsaError) as e:
+        pbsa.pbsa_attention_workspace_bytes(good(d=96))
+    assert e.value.code == pbsa.PBSA_ESHAPE
+
+    def split(p=p, Q=P, sel=P, O=P, Vl=P, ws=(0x10000, 1 << 30)):
+        pbsa.pbsa_attention_fwd_split(p, Q, P, P, P, P, Vl, P, P, sel, O, None, ws, stream=0)
+
+    for kw, code in [(dict(Q=None), pbsa.PBSA_EINVAL), (dict(O=None), pbsa.PBSA_EINVAL), (dict(sel=None), pbsa.PBSA_EINVAL),
+                     (dict(Vl=P + 8), pbsa.PBSA_EALIGN), (dict(ws=None), pbsa.PBSA_EWS),
+                     (dict(ws=(0x10000, need - 1)), pbsa.PBSA_EWS), (dict(ws=(0x10010, need)), pbsa.PBSA_EALIGN),
+                     (dict(p=good(k=673)), pbsa.PBSA_ESHAPE), (dict(p=good(n_evict=17)), pbsa.PBSA_EINVAL),
+                     (dict(p=good(q_strides=(200 * 132, 132))), pbsa.PBSA_EALIGN)]:
+        with pytest.raises(pbsa.PbsaError) as e:
+            split(**kw)
+        assert e.value.code == code, kw
+
+
 def test_select_with_pending_apply_argument_checks(L):
     """pbsa_select_blocks_apply validates both halves and that the two parameter blocks describe the same cache."""
     p, pu = good(), good(n_evict=4)

@@ -50,3 +50,51 @@ def test_split_matches_whole(H, d, B, Nq, w, C, k, causal):
     # the variant that records the mass takes the same parts
     O_m, _ = c.attention_with_mass(Q)
     assert torch.equal(O_m.view(torch.int16), O.view(torch.int16))
+
+
+def _cache_and_chunks(n, H=5, d=64, B=128, Nq=1000, w=1, C=5, k=7):
+    """A cache of a shape that is split, and n chunks."""
+    from paper_2604_21221_amd.cache import PbsaCache
+    gen = torch.Generator(device=DEV).manual_seed(n + H)
+    c = PbsaCache(H, d, B, Nq, w, C, k, d ** -0.5, device=DEV)
+    assert c._attn_bytes > 0, "this shape is meant to be split"
+    return c, [[torch.randn(H, Nq, d, generator=gen, device=DEV).to(torch.bfloat16) for _ in range(3)] for _ in range(n)]
+
+
+def test_plain_attention_leaves_its_workspace_alone():
+    """pbsa_attention_fwd takes a workspace and does not look at it: callers hand the same one to every call, with a plan
+    still to be applied in it."""
+    from paper_2604_21221_amd import pbsa
+    c, [(Q, K, V)] = _cache_and_chunks(1)
+    c.append_chunk(K, V, 0)
+    c.select(Q)
+    l_map, l_len, _ = c._device_maps()
+    print("[case] plain attention with a workspace", flush=True)
+    out = []
+    for ws in (None, torch.full((c._attn_bytes + 256,), 0x5A, dtype=torch.uint8, device=DEV)):
+        O = torch.empty_like(Q)
+        pbsa.pbsa_attention_fwd(c.params(Q=Q, O=O), Q, c.Kp, c.Vp, c.p_len, c.Kl, c.Vl, l_len, l_map, c.sel, O, None, ws)
+        out.append(O)
+    assert torch.equal(out[0].view(torch.int16), out[1].view(torch.int16))
+    assert bool((ws == 0x5A).all())
+
+
+def test_plain_attention_between_plan_and_apply_on_one_workspace():
+    """pbsa_memory_update_plan, pbsa_attention_fwd, pbsa_memory_update_apply, all with one workspace: the state of
+    pbsa_memory_update, bit for bit."""
+    from paper_2604_21221_amd import pbsa
+    a, chunks = _cache_and_chunks(4)
+    b, _ = _cache_and_chunks(4)
+    for g, (Q, K, V) in enumerate(chunks):
+        print(f"[case] one workspace, chunk {g}", flush=True)
+        for c in (a, b):
+            c.append_chunk(K, V, g)
+            c.select(Q)
+        a.update()
+        b.update_plan()
+        l_map, l_len, _ = b._device_maps()
+        O = torch.empty_like(Q)
+        pbsa.pbsa_attention_fwd(b.params(Q=Q, O=O), Q, b.Kp, b.Vp, b.p_len, b.Kl, b.Vl, l_len, l_map, b.sel, O, None, b.ws)
+        b.update_apply()
+        for name in ("Kp", "Vp", "Kc_p", "p_len", "p_id", "S_sum", "S_cnt", "slot_src"):
+            assert torch.equal(getattr(a, name), getattr(b, name)), (name, g)
