@@ -48,8 +48,8 @@ class PbsaCache:
         n_attn = pbsa.pbsa_attention_workspace_bytes(full) if attends else 0
         n_ws = pbsa.pbsa_workspace_bytes(full) if C <= pbsa.PBSA_MAX_C else 0
         self.ws = torch.empty(max(n_ws + n_attn, 256), dtype=torch.uint8, device=self.dev)
-        # the attention's share lies behind what an update in flight still needs
-        self._attn_ws = self.ws[n_ws:] if n_attn else None
+        # attention_with_plan()'s split takes the share behind what the update needs; attention() changes nothing of the
+        # cache and may be called from several streams at a time, so its scratch is each call's own
         self._attn_bytes = n_attn
         self.chunk_pos = []          # ring position of each chunk in the local region, oldest first
         self.chunk_ids = []          # global chunk index of each
@@ -191,8 +191,8 @@ class PbsaCache:
             O = torch.empty_like(Q)
         l_map, l_len, _ = self._device_maps()
         p = self.params(Q=Q, O=O)
-        pbsa.pbsa_attention_fwd_split(p, Q, self.Kp, self.Vp, self.p_len, self.Kl, self.Vl, l_len, l_map, self.sel, O, lse,
-                                      self._attn_ws)
+        ws = torch.empty(self._attn_bytes, dtype=torch.uint8, device=self.dev) if self._attn_bytes else None
+        pbsa.pbsa_attention_fwd_split(p, Q, self.Kp, self.Vp, self.p_len, self.Kl, self.Vl, l_len, l_map, self.sel, O, lse, ws)
         return O
 
     def _no_pending(self):

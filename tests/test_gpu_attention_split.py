@@ -36,7 +36,7 @@ def test_split_matches_whole(H, d, B, Nq, w, C, k, causal):
         c.set_persistent(2.0 * rnd(H, C, B, d), rnd(H, C, B, d), lens, torch.arange(C)[None].repeat(H, 1))
     Q = rnd(H, Nq, d)
     c.select(Q)
-    assert c._attn_ws is not None and c._attn_ws.numel() > 0, "this shape is meant to be split"
+    assert c._attn_bytes > 0, "this shape is meant to be split"
     lse, lse_w = (torch.empty(H, Nq, device=DEV) for _ in range(2))
     O = c.attention(Q, lse=lse)
     l_map, l_len, _ = c._device_maps()
@@ -98,3 +98,25 @@ def test_plain_attention_between_plan_and_apply_on_one_workspace():
         b.update_apply()
         for name in ("Kp", "Vp", "Kc_p", "p_len", "p_id", "S_sum", "S_cnt", "slot_src"):
             assert torch.equal(getattr(a, name), getattr(b, name)), (name, g)
+
+
+def test_attention_from_two_streams():
+    """Attention calls on one cache from two streams, each with its own Q and O, in a shape that is split: each gives what
+    it gives alone."""
+    c, chunks = _cache_and_chunks(2, Nq=2000, C=30, k=16)
+    for g, (_, K, V) in enumerate(chunks):
+        c.append_chunk(K, V, g)
+    Qs = [chunks[0][0], chunks[1][0]]
+    c.select(Qs[0])
+    want = [c.attention(Q) for Q in Qs]
+    O = [torch.empty_like(Q) for Q in Qs]
+    streams = [torch.cuda.Stream() for _ in Qs]
+    torch.cuda.synchronize()
+    print("[case] attention from two streams", flush=True)
+    for r in range(20):
+        for Q, o, s in zip(Qs, O, streams):
+            with torch.cuda.stream(s):
+                for _ in range(3):
+                    c.attention(Q, o)
+        torch.cuda.synchronize()
+        assert all(torch.equal(o, w) for o, w in zip(O, want)), r
