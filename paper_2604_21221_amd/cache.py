@@ -121,6 +121,8 @@ class PbsaCache:
 
     def append_chunk(self, K, V, chunk_id):
         """Copy a chunk's K/V ([H][Nq][d] bf16, token-major) into the next ring position, block-major."""
+        if K is None or V is None:
+            raise TypeError("append_chunk takes K and V (adopt_chunk declares a chunk that is in the ring already)")
         assert len(self.chunk_pos) <= self.w, "update() slides the window before the next append"
         pos = self.n_appended % self.ring
         self.chunk_pos.append(pos)
@@ -374,9 +376,9 @@ class PbsaCache:
         leaves its logits and the update maintains the slots, the update's decisions ride in the attention launch
         (step_fused, the same results bit for bit): four launches instead of six, 202.6 -> 189.4 us at 12 x 4680 x 128
         with 16 slots, 57 -> 49 us for two heads of 256 tokens."""
-        if self.Zl is not None and self.C <= pbsa.PBSA_MAX_C:
-            return self.step_fused(Q, K, V, chunk_id, O, lse)
         self.append_chunk(K, V, chunk_id)
+        if self.Zl is not None and self.C <= pbsa.PBSA_MAX_C:
+            return self.step_fused(Q, O=O, lse=lse)
         self.select(Q)
         O = self.attention(Q, O, lse)
         self.update()

@@ -37,3 +37,43 @@ def test_attention_shares_no_scratch(cache, monkeypatch):
     for name, t in vars(cache).items():
         if isinstance(t, torch.Tensor):
             assert not any(overlap(w, t) for w in ws), name
+
+
+CALLS = ("pbsa_append_chunk", "pbsa_select_blocks", "pbsa_attention_fwd_split", "pbsa_attention_fwd_plan",
+         "pbsa_attention_fwd_mass", "pbsa_memory_update", "pbsa_memory_update_apply", "pbsa_memory_update_fine")
+
+
+def record(monkeypatch):
+    calls = []
+    for name in CALLS:
+        monkeypatch.setattr(pbsa, name, lambda *a, name=name, **k: calls.append((name, a)))
+    return calls
+
+
+def books(c):
+    return list(c.chunk_pos), list(c.chunk_ids), c.n_appended, c.stale_from
+
+
+@pytest.mark.parametrize("call", ["append_chunk", "step", "step_fine", "step_fused", "step_chained"])
+@pytest.mark.parametrize("missing", ["K", "V", "KV"])
+def test_append_refuses_a_missing_tensor(cache, monkeypatch, call, missing):
+    """None for K or V is no chunk: refused, with nothing launched and nothing declared.  (step_fused and step_chained take
+    K = V = None for a chunk that has been adopted.)"""
+    if call in ("step_fused", "step_chained") and "K" in missing:
+        return
+    calls = record(monkeypatch)
+    kv = [None if n in missing else chunk() for n in "KV"]
+    before = books(cache)
+    with pytest.raises(TypeError):
+        getattr(cache, call)(*([] if call == "append_chunk" else [chunk()]), *kv, 0)
+    assert not calls and books(cache) == before
+
+
+def test_step_is_append_select_attention_update(cache, monkeypatch):
+    calls = record(monkeypatch)
+    cache.step(chunk(0), chunk(1), chunk(2), 0)
+    assert [n for n, _ in calls] == ["pbsa_append_chunk", "pbsa_select_blocks", "pbsa_attention_fwd_plan", "pbsa_memory_update_apply"]
+    cache.Zl = None                          # without the logits the decisions are taken behind the attention
+    del calls[:]
+    cache.step(chunk(0), chunk(1), chunk(2), 1)
+    assert [n for n, _ in calls] == ["pbsa_append_chunk", "pbsa_select_blocks", "pbsa_attention_fwd_split", "pbsa_memory_update"]
