@@ -43,6 +43,7 @@ class PbsaCache:
         self.slot_src = torch.full((H, max(C, 1)), -1, dtype=torch.int32, device=self.dev)
         self.scores = z(H, C + self.nqb, dt=torch.float32)
         full = pbsa.make_params(H, d, B, Nq, self.cap, self.cap, C, k, self.scale, n_sink, causal, n_evict=self.nqb)
+        self._full = full            # what an append is described by: the geometry, not how full the window is
         # with more slots than pbsa_memory_update maintains the cache can only be selected from and attended
         attends = C <= pbsa.PBSA_MAX_C_ATTEND and self.cap <= pbsa.PBSA_MAX_N_LOC and k <= pbsa.PBSA_MAX_K
         n_attn = pbsa.pbsa_attention_workspace_bytes(full) if attends else 0
@@ -125,11 +126,11 @@ class PbsaCache:
             raise TypeError("append_chunk takes K and V (adopt_chunk declares a chunk that is in the ring already)")
         assert len(self.chunk_pos) <= self.w, "update() slides the window before the next append"
         pos = self.n_appended % self.ring
+        self._write_chunk(pos, K, V, True)       # may refuse them: the chunk counts once it is there
         self.chunk_pos.append(pos)
         self.chunk_ids.append(chunk_id)
         self.n_appended += 1
         self.stale_from = min(self.stale_from, self.n_loc - self.nqb)
-        self._write_chunk(pos, K, V, True)
 
     def _in_place(self, x):
         """Whether pbsa_append_chunk takes tensor x as it is: bf16 on this GPU, whole, rows contiguous and aligned."""
@@ -143,7 +144,7 @@ class PbsaCache:
         if K is None and V is None:
             return
         if (K is None or self._in_place(K)) and (V is None or self._in_place(V)):
-            pbsa.pbsa_append_chunk(self.params(), K, V, pos * self.nqb, zero_tail, self.Kl, self.Vl, self.Kc_l)
+            pbsa.pbsa_append_chunk(self._full, K, V, pos * self.nqb, zero_tail, self.Kl, self.Vl, self.Kc_l)
             self._chunk_pooled = K is not None
             return
         for dst, src in ((self.Kl, K), (self.Vl, V)):

@@ -77,3 +77,30 @@ def test_step_is_append_select_attention_update(cache, monkeypatch):
     del calls[:]
     cache.step(chunk(0), chunk(1), chunk(2), 1)
     assert [n for n, _ in calls] == ["pbsa_append_chunk", "pbsa_select_blocks", "pbsa_attention_fwd_split", "pbsa_memory_update"]
+
+
+@pytest.mark.parametrize("call", ["append_chunk", "step", "step_fine", "step_fused", "step_chained"])
+@pytest.mark.parametrize("why", ["K", "V", "library"])
+def test_a_failed_append_declares_nothing(cache, monkeypatch, call, why):
+    """K or V of a shape that fits nowhere, or an error of the library: the cache stands where it stood, and the same call
+    with a good chunk goes through."""
+    calls = record(monkeypatch)
+    cache.append_chunk(chunk(0), chunk(1), 0)
+    cache.stale_from = cache.n_loc
+    before = books(cache)
+    bad = torch.zeros(H, NQ + 1, D, dtype=torch.bfloat16)
+    args = [] if call == "append_chunk" else [chunk(5)]
+
+    def refuse(*a):
+        raise pbsa.PbsaError(pbsa.PBSA_EINVAL)
+
+    with monkeypatch.context() as m:
+        if why == "library":
+            m.setattr(pbsa, "pbsa_append_chunk", refuse)
+        with pytest.raises(Exception):
+            getattr(cache, call)(*args, bad if why == "K" else chunk(2), bad if why == "V" else chunk(3), 1)
+    assert books(cache) == before
+    del calls[:]
+    cache.append_chunk(chunk(2), chunk(3), 1)
+    assert cache.chunk_ids == [0, 1] and cache.n_appended == 2 and cache.chunk_pos == [0, 1]
+    assert calls[0][1][0].n_loc >= calls[0][1][0].nqb          # which the library checks
