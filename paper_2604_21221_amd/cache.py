@@ -56,7 +56,6 @@ class PbsaCache:
         self.chunk_ids = []          # global chunk index of each
         self.n_appended = 0
         self.stale_from = 0
-        self._chunk_pooled = False   # the newest chunk's pooled keys were written together with its K
         self._maps = {}
         self._arange64 = None
         lens = torch.full((self.nqb,), B, dtype=torch.int32)
@@ -122,31 +121,37 @@ class PbsaCache:
 
     def append_chunk(self, K, V, chunk_id):
         """Copy a chunk's K/V ([H][Nq][d] bf16, token-major) into the next ring position, block-major."""
+        self._append(K, V, chunk_id, False)
+
+    def _append(self, K, V, chunk_id, pool):
+        """append_chunk; pool: the pooled keys are taken as the rows pass, for a selection that follows at once (whoever
+        appends by themselves may still change the rows in the ring, and the selection pools what it finds there).
+        Returns whether they were."""
         if K is None or V is None:
             raise TypeError("append_chunk takes K and V (adopt_chunk declares a chunk that is in the ring already)")
         assert len(self.chunk_pos) <= self.w, "update() slides the window before the next append"
         pos = self.n_appended % self.ring
-        self._write_chunk(pos, K, V, True)       # may refuse them: the chunk counts once it is there
+        pooled = self._write_chunk(pos, K, V, True, pool)       # may refuse them: the chunk counts once it is there
         self.chunk_pos.append(pos)
         self.chunk_ids.append(chunk_id)
         self.n_appended += 1
         self.stale_from = min(self.stale_from, self.n_loc - self.nqb)
+        return pooled
 
     def _in_place(self, x):
         """Whether pbsa_append_chunk takes tensor x as it is: bf16 on this GPU, whole, rows contiguous and aligned."""
         return (x.dtype is torch.bfloat16 and x.device == self.Kl.device and x.shape == (self.H, self.Nq, self.d) and x.stride(2) == 1
                 and x.stride(0) % 8 == 0 and x.stride(1) % 8 == 0 and x.stride(1) >= self.d and x.data_ptr() % 16 == 0)
 
-    def _write_chunk(self, pos, K, V, zero_tail):
-        """K and V (either may be None) into ring position `pos`: one launch that also writes the pooled keys; tensors
-        of another type, device or layout go through torch, and their keys are pooled by the next selection."""
-        self._chunk_pooled = False
+    def _write_chunk(self, pos, K, V, zero_tail, pool):
+        """K and V (either may be None) into ring position `pos` in one launch, with the pooled keys if asked for; tensors
+        of another type, device or layout go through torch.  Returns whether the pooled keys were written."""
         if K is None and V is None:
-            return
+            return False
         if (K is None or self._in_place(K)) and (V is None or self._in_place(V)):
-            pbsa.pbsa_append_chunk(self._full, K, V, pos * self.nqb, zero_tail, self.Kl, self.Vl, self.Kc_l)
-            self._chunk_pooled = K is not None
-            return
+            pool = pool and K is not None
+            pbsa.pbsa_append_chunk(self._full, K, V, pos * self.nqb, zero_tail, self.Kl, self.Vl, self.Kc_l if pool else None)
+            return pool
         for dst, src in ((self.Kl, K), (self.Vl, V)):
             if src is None:
                 continue
@@ -154,6 +159,7 @@ class PbsaCache:
             view[:, :self.Nq] = src
             if zero_tail and self.nqb * self.B > self.Nq:
                 view[:, self.Nq:] = 0
+        return False
 
     def rewrite_chunk(self, K=None, V=None):
         """Between the denoising passes of one chunk (Sec. 3.1: each chunk is denoised in T passes over the
@@ -161,7 +167,7 @@ class PbsaCache:
         with no arguments just note that the producer has.  The next selection then pools the chunk's
         blocks again; the pooled keys of the window stay cached."""
         assert self.chunk_pos, "no chunk to rewrite"
-        self._write_chunk(self.chunk_pos[-1], K, V, False)
+        self._write_chunk(self.chunk_pos[-1], K, V, False, False)
         self.stale_from = min(self.stale_from, self.n_loc - self.nqb)
 
     def adopt_chunk(self, chunk_id):
@@ -171,14 +177,16 @@ class PbsaCache:
         self.chunk_pos.append(self.n_appended % self.ring)
         self.chunk_ids.append(chunk_id)
         self.n_appended += 1
-        self._chunk_pooled = False
         self.stale_from = min(self.stale_from, self.n_loc - self.nqb)
 
     # -- the three calls ---------------------------------------------------------------------------
     def select(self, Q):
+        return self._select(Q, False)
+
+    def _select(self, Q, pooled):
+        """select; pooled: the newest chunk's pooled keys have just been written (anything older that is stale has not)."""
         l_map, l_len, _ = self._device_maps()
-        # the newest chunk's keys may have been pooled as they were written; anything older that is stale is not
-        fresh = self._chunk_pooled and self.stale_from == self.n_loc - self.nqb
+        fresh = pooled and self.stale_from == self.n_loc - self.nqb
         p = self.params(pool_from=self.n_loc if fresh else self.stale_from, Q=Q)
         if self._pending is not None:            # with the data movement of the previous chunk's update in its pooling launch
             pbsa.pbsa_select_blocks_apply(p, Q, self.Kl, l_len, l_map, self.Kc_l, self.Qc, self.sel, self.Zl, self._pending,
@@ -275,8 +283,7 @@ class PbsaCache:
 
     def step_fine(self, Q, K, V, chunk_id, O=None, lse=None):
         """The step with the fine-mass score: append, select, attend (recording the mass), update."""
-        self.append_chunk(K, V, chunk_id)
-        self.select(Q)
+        self._select(Q, self._append(K, V, chunk_id, True))
         O, Mt = self.attention_with_mass(Q, O, lse)
         self.update_fine(Mt)
         return O
@@ -335,9 +342,7 @@ class PbsaCache:
     def step_fused(self, Q, K=None, V=None, chunk_id=None, O=None, lse=None):
         """The step as two launches after the selection: attention with the update's decisions, then fold /
         promote.  K = V = None: the chunk has been adopted already."""
-        if K is not None:
-            self.append_chunk(K, V, chunk_id)
-        self.select(Q)
+        self._select(Q, K is not None and self._append(K, V, chunk_id, True))
         O = self.attention_with_plan(Q, O, lse)
         self.update_apply()
         return O
@@ -365,9 +370,7 @@ class PbsaCache:
     def step_chained(self, Q, K=None, V=None, chunk_id=None, O=None, lse=None):
         """Two library calls per step: selection (carrying the previous step's fold / promote), attention (carrying
         this step's decisions).  flush() after the last step.  K = V = None: the chunk has been adopted already."""
-        if K is not None:
-            self.append_chunk(K, V, chunk_id)
-        self.select(Q)
+        self._select(Q, K is not None and self._append(K, V, chunk_id, True))
         O = self.attention_with_plan(Q, O, lse)
         self.defer_apply()
         return O
@@ -377,10 +380,11 @@ class PbsaCache:
         leaves its logits and the update maintains the slots, the update's decisions ride in the attention launch
         (step_fused, the same results bit for bit): four launches instead of six, 202.6 -> 189.4 us at 12 x 4680 x 128
         with 16 slots, 57 -> 49 us for two heads of 256 tokens."""
-        self.append_chunk(K, V, chunk_id)
+        self._select(Q, self._append(K, V, chunk_id, True))
         if self.Zl is not None and self.C <= pbsa.PBSA_MAX_C:
-            return self.step_fused(Q, O=O, lse=lse)
-        self.select(Q)
+            O = self.attention_with_plan(Q, O, lse)
+            self.update_apply()
+            return O
         O = self.attention(Q, O, lse)
         self.update()
         return O

@@ -104,3 +104,41 @@ def test_a_failed_append_declares_nothing(cache, monkeypatch, call, why):
     cache.append_chunk(chunk(2), chunk(3), 1)
     assert cache.chunk_ids == [0, 1] and cache.n_appended == 2 and cache.chunk_pos == [0, 1]
     assert calls[0][1][0].n_loc >= calls[0][1][0].nqb          # which the library checks
+
+
+def test_who_pools_the_newest_chunk(cache, monkeypatch):
+    """A program that appends and selects by itself may change the rows in the ring in between: the selection pools what is
+    there.  A step takes the pooled keys with the append and its selection starts behind them -- unless the chunk went
+    through torch, or something older is stale as well."""
+    calls = record(monkeypatch)
+    nqb = cache.nqb
+
+    def pooling():                           # by the append; from which block by the selection; of how many
+        kc = [a[7] is not None for n, a in calls if n == "pbsa_append_chunk"]
+        sel = [(a[0].pool_from, a[0].n_loc) for n, a in calls if n == "pbsa_select_blocks"]
+        del calls[:]
+        return kc, sel
+
+    cache.append_chunk(chunk(0), chunk(1), 0)
+    cache.select(chunk(2))
+    assert pooling() == ([False], [(0, nqb)])
+    cache.rewrite_chunk(chunk(3), chunk(4))
+    cache.select(chunk(2))
+    assert pooling() == ([False], [(0, nqb)])
+    cache.step(chunk(0), chunk(1), chunk(2), 1)
+    assert pooling() == ([True], [(2 * nqb, 2 * nqb)])
+    for call in (cache.step_fused, cache.step_fine, cache.step):
+        call(chunk(0), chunk(1), chunk(2), 2)
+        assert pooling() == ([True], [(2 * nqb, 2 * nqb)])
+    cache.step(chunk(0), chunk(1).float(), chunk(2), 3)          # converted by torch
+    assert pooling() == ([], [(nqb, 2 * nqb)])
+    cache.stale_from = 0
+    cache.step(chunk(0), chunk(1), chunk(2), 4)
+    assert pooling() == ([True], [(0, 2 * nqb)])
+    # a step that ends between the two leaves nothing behind for the selection that follows
+    with monkeypatch.context() as m:
+        m.setattr(pbsa, "pbsa_select_blocks", lambda *a, **k: 1 / 0)
+        with pytest.raises(ZeroDivisionError):
+            cache.step(chunk(0), chunk(1), chunk(2), 5)
+    cache.select(chunk(2))
+    assert pooling() == ([True], [(nqb, 2 * nqb)])

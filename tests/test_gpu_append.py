@@ -41,6 +41,9 @@ def test_append_matches_copies_and_pooling(d, B, Nq, strided):
         c.append_chunk(K, V, g)
         put(want_K, g, K, True), put(want_V, g, V, True)
         assert same(c.Kl, want_K) and same(c.Vl, want_V)
+        assert torch.all(c.Kc_l[:, g * c.nqb:] == 7.0), "pooled before the selection has seen the rows"
+        pbsa.pbsa_append_chunk(c._full, K, V, g * c.nqb, True, c.Kl, c.Vl, c.Kc_l)
+        assert same(c.Kl, want_K) and same(c.Vl, want_V)
         assert torch.equal(c.Kc_l[:, g * c.nqb:(g + 1) * c.nqb], pooled(g)), "pooled keys"
         if g == 0:
             assert torch.all(c.Kc_l[:, c.nqb:] == 7.0), "another chunk's pooled keys were touched"
@@ -55,3 +58,21 @@ def test_append_matches_copies_and_pooling(d, B, Nq, strided):
     c.stale_from = 0
     c.select(Q)
     assert all(torch.equal(a, b) for a, b in zip(kept, (c.Kc_l, c.sel, c.Qc)))
+
+
+def test_selection_pools_the_rows_it_finds():
+    """Rows of the newest chunk that are changed in the ring between the append and the first selection count as changed."""
+    from paper_2604_21221_amd.cache import PbsaCache
+    H, d, B, Nq = 2, 64, 64, 200
+    gen = torch.Generator(device=DEV).manual_seed(3)
+    rnd = lambda: torch.randn(H, Nq, d, generator=gen, device=DEV).to(torch.bfloat16)
+    Q, K, V, K2 = rnd(), rnd(), rnd(), rnd()
+    print("[case] rows changed before the first selection", flush=True)
+    got = []
+    for first in (K, K2):
+        c = PbsaCache(H, d, B, Nq, 1, 2, 2, d ** -0.5, device=DEV)
+        c.append_chunk(first, V, 0)
+        c.Kl[:, :c.nqb].view(H, c.nqb * B, d)[:, :Nq] = K2
+        c.select(Q)
+        got.append((c.Kc_l, c.sel))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
