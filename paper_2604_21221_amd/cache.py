@@ -140,15 +140,29 @@ class PbsaCache:
 
     def _in_place(self, x):
         """Whether pbsa_append_chunk takes tensor x as it is: bf16 on this GPU, whole, rows contiguous and aligned."""
-        return (x.dtype is torch.bfloat16 and x.device == self.Kl.device and x.shape == (self.H, self.Nq, self.d) and x.stride(2) == 1
-                and x.stride(0) % 8 == 0 and x.stride(1) % 8 == 0 and x.stride(1) >= self.d and x.data_ptr() % 16 == 0)
+        return (type(x) is torch.Tensor and x.dtype is torch.bfloat16 and x.layout is torch.strided and x.device == self.Kl.device
+                and x.shape == (self.H, self.Nq, self.d) and x.stride(2) == 1 and x.stride(0) % 8 == 0 and x.stride(1) % 8 == 0
+                and x.stride(1) >= self.d and x.data_ptr() % 16 == 0 and not x.is_neg())
+
+    def _watched(self, K, V):
+        """Whether torch would record, transform or refuse a copy of K and V into the ring (gradients, forward mode, function
+        transforms, dispatch modes, tracing, inference tensors outside their mode): a launch would pass all of that by."""
+        if torch.is_grad_enabled() and (self.Kl.requires_grad or self.Vl.requires_grad or (K is not None and K.requires_grad)
+                                        or (V is not None and V.requires_grad)):
+            return True
+        return (torch.autograd.forward_ad._current_level >= 0 or torch._C._functorch.peek_interpreter_stack() is not None
+                or torch._C._len_torch_dispatch_stack() > 0 or torch._C._get_tracing_state() is not None
+                or torch.compiler.is_compiling() or (self.Kl.is_inference() and not torch.is_inference_mode_enabled()))
 
     def _write_chunk(self, pos, K, V, zero_tail, pool):
         """K and V (either may be None) into ring position `pos` in one launch, with the pooled keys if asked for; tensors
-        of another type, device or layout go through torch.  Returns whether the pooled keys were written."""
+        of another type, device or layout, and whatever autograd follows, go through torch.  Returns whether the pooled
+        keys were written."""
         if K is None and V is None:
             return False
-        if (K is None or self._in_place(K)) and (V is None or self._in_place(V)):
+        if (K is None or self._in_place(K)) and (V is None or self._in_place(V)) and not self._watched(K, V):
+            # as an in-place copy would, so that a backward which saved the ring notices
+            torch.autograd.graph.increment_version([dst for dst, src in ((self.Kl, K), (self.Vl, V)) if src is not None])
             pool = pool and K is not None
             pbsa.pbsa_append_chunk(self._full, K, V, pos * self.nqb, zero_tail, self.Kl, self.Vl, self.Kc_l if pool else None)
             return pool

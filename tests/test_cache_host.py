@@ -142,3 +142,95 @@ def test_who_pools_the_newest_chunk(cache, monkeypatch):
             cache.step(chunk(0), chunk(1), chunk(2), 5)
     cache.select(chunk(2))
     assert pooling() == ([True], [(nqb, 2 * nqb)])
+
+
+def rows(cache, t, pos=0):
+    return t[:, pos * cache.nqb:(pos + 1) * cache.nqb].view(H, cache.nqb * B, D)[:, :NQ]
+
+
+@pytest.mark.parametrize("which", ["K", "V"])
+def test_gradients_reach_an_appended_tensor(cache, monkeypatch, which):
+    """A copy into the ring is part of the graph: the gradient of the ring reaches K and V, and stops at rows that are
+    written over."""
+    calls = record(monkeypatch)
+    x, w = chunk(0).requires_grad_(), chunk(1).float()
+    cache.append_chunk(*((x, chunk(2)) if which == "K" else (chunk(2), x)), 0)
+    ring = cache.Kl if which == "K" else cache.Vl
+    assert not calls and torch.equal(rows(cache, ring).detach(), x.detach())
+    g, = torch.autograd.grad((rows(cache, ring).float() * w).sum(), x, retain_graph=True)
+    assert torch.equal(g, w.to(torch.bfloat16))
+    cache.rewrite_chunk(chunk(3), chunk(3))
+    assert not calls                         # the ring has a graph: the copy that cuts it off belongs there too
+    g, = torch.autograd.grad((rows(cache, cache.Kl if which == "K" else cache.Vl).float() * w).sum(), x)
+    assert not g.any()
+
+
+def test_no_graph_no_detour(cache, monkeypatch):
+    calls = record(monkeypatch)
+    with torch.no_grad():
+        cache.append_chunk(chunk(0).requires_grad_(), chunk(1), 0)
+    with torch.inference_mode():
+        cache.append_chunk(chunk(0), chunk(1), 1)
+    with torch.inference_mode():
+        c = PbsaCache(H, D, B, NQ, W, 3, 12, D ** -0.5, device="cpu")
+        c.append_chunk(chunk(0), chunk(1), 0)
+    assert len(calls) == 3
+    with pytest.raises(RuntimeError, match="inference tensor"):      # as of any change in place outside the mode
+        c.append_chunk(chunk(0), chunk(1), 1)
+    assert len(calls) == 3 and c.chunk_ids == [0]
+
+
+def test_what_follows_a_copy_sees_the_append(cache, monkeypatch):
+    """Forward mode, function transforms and dispatch modes are given a copy to look at."""
+    from torch.autograd import forward_ad
+    from torch.utils._python_dispatch import TorchDispatchMode
+    calls = record(monkeypatch)
+    with forward_ad.dual_level():
+        t = chunk(1)
+        cache.append_chunk(forward_ad.make_dual(chunk(0), t), chunk(2), 0)
+        assert torch.equal(rows(cache, forward_ad.unpack_dual(cache.Kl).tangent), t)
+    c2 = PbsaCache(H, D, B, NQ, W, 3, 12, D ** -0.5, device="cpu")
+    try:
+        torch.func.grad(lambda x: (c2.append_chunk(x, x, 0), x.float().sum())[1])(chunk(0))
+    except RuntimeError:
+        pass                                 # torch may refuse the copy; a launch would not
+
+    class Log(TorchDispatchMode):
+        seen = 0
+
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            self.seen += func is torch.ops.aten.copy_.default
+            return func(*args, **(kwargs or {}))
+
+    c3 = PbsaCache(H, D, B, NQ, W, 3, 12, D ** -0.5, device="cpu")
+    with Log() as log:
+        c3.append_chunk(chunk(0), chunk(1), 0)
+    assert log.seen >= 2 and not calls
+
+
+def test_a_launch_counts_as_a_change_in_place(cache, monkeypatch):
+    record(monkeypatch)
+    q = torch.randn(D, requires_grad=True)
+    y = (cache.Kl.float() @ q).sum() + (cache.Vl * q.to(torch.bfloat16)).float().sum()
+    before = cache.Kl._version, cache.Vl._version
+    cache.append_chunk(chunk(0), chunk(1), 0)
+    assert cache.Kl._version > before[0] and cache.Vl._version > before[1]
+    with pytest.raises(RuntimeError, match="modified by an inplace operation"):
+        y.backward()
+    v = cache.Vl._version
+    cache.rewrite_chunk(chunk(0))
+    assert cache.Vl._version == v
+
+
+def test_what_a_copy_takes_is_taken(cache, monkeypatch):
+    """Everything that can be assigned to the chunk's rows: other types, shapes that spread, numbers, lazily negated
+    tensors, subclasses."""
+    calls = record(monkeypatch)
+    x = chunk(0)
+    for src in (x.float(), x[:1], x[0], x.repeat(1, 1, 2)[:, :, 1:D + 1], torch._neg_view(x), torch.nn.Parameter(x, requires_grad=False)):
+        cache.rewrite_chunk(src, src) if cache.chunk_pos else cache.append_chunk(src, src, 0)
+        want = src.detach().to(torch.bfloat16).expand(H, NQ, D)
+        assert torch.equal(rows(cache, cache.Kl), want) and torch.equal(rows(cache, cache.Vl), want)
+    cache.rewrite_chunk(0.5, 2)
+    assert bool((rows(cache, cache.Kl) == 0.5).all()) and bool((rows(cache, cache.Vl) == 2).all())
+    assert not calls
