@@ -234,3 +234,16 @@ def test_what_a_copy_takes_is_taken(cache, monkeypatch):
     cache.rewrite_chunk(0.5, 2)
     assert bool((rows(cache, cache.Kl) == 0.5).all()) and bool((rows(cache, cache.Vl) == 2).all())
     assert not calls
+
+
+def test_rows_of_the_ring_are_copied_in_order(cache, monkeypatch):
+    """K from the rows of Vl that V is about to take: K is copied first, then V."""
+    calls = record(monkeypatch)
+    with torch.no_grad():
+        cache.Vl[:, :cache.nqb] = torch.randn(H, cache.nqb, B, D).to(torch.bfloat16)
+    old, v = rows(cache, cache.Vl).clone(), chunk(1)
+    cache.append_chunk(rows(cache, cache.Vl), v, 0)
+    assert torch.equal(rows(cache, cache.Kl), old) and torch.equal(rows(cache, cache.Vl), v)
+    k = chunk(2)
+    cache.rewrite_chunk(k, rows(cache, cache.Kl))
+    assert torch.equal(rows(cache, cache.Kl), k) and torch.equal(rows(cache, cache.Vl), k) and not calls
