@@ -141,6 +141,8 @@ class PbsaCache:
     def _in_place(self, x):
         """Whether pbsa_append_chunk takes tensor x as it is: bf16 on this GPU, whole, rows contiguous and aligned."""
         return (type(x) is torch.Tensor and x.dtype is torch.bfloat16 and x.layout is torch.strided and x.device == self.Kl.device
+                # the library launches on the current device
+                and (x.device.index is None or x.device.index == torch._C._cuda_getDevice())
                 and x.shape == (self.H, self.Nq, self.d) and x.stride(2) == 1 and x.stride(0) % 8 == 0 and x.stride(1) % 8 == 0
                 and x.stride(1) >= self.d and x.data_ptr() % 16 == 0 and not x.is_neg()
                 # rows of the ring itself: K is copied before V is, and a launch knows no such order

@@ -76,3 +76,18 @@ def test_selection_pools_the_rows_it_finds():
         c.select(Q)
         got.append((c.Kc_l, c.sel))
     assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
+def test_an_append_while_another_device_is_current(monkeypatch):
+    """The library launches on the current device's stream; a copy runs where its tensors are."""
+    from paper_2604_21221_amd import pbsa
+    from paper_2604_21221_amd.cache import PbsaCache
+    c = PbsaCache(2, 64, 64, 200, 1, 2, 2, 0.125, device=DEV)
+    K, V = (torch.randn(2, 200, 64, device=DEV).to(torch.bfloat16) for _ in range(2))
+    calls = []
+    with monkeypatch.context() as m:
+        m.setattr(pbsa, "pbsa_append_chunk", lambda *a, **k: calls.append(a))
+        m.setattr(torch._C, "_cuda_getDevice", lambda: 1)
+        c.append_chunk(K, V, 0)
+    rows = [t[:, :c.nqb].view(2, c.nqb * 64, 64)[:, :200] for t in (c.Kl, c.Vl)]
+    assert not calls and torch.equal(rows[0], K) and torch.equal(rows[1], V)
