@@ -1,6 +1,7 @@
 // Calls a libpbsa function with Python arguments: the marshalling of the binding (pbsa.py), in native code.  A call
 // takes up to two dozen tensors and a step makes four calls, which is what a small step costs on the host: 0.25 us per
 // tensor and 3 us for the stream in Python, against about 0.02 us per argument here.
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <cstdint>
@@ -49,6 +50,7 @@ bool convert(PyObject* o, int64_t& out) {
 // integer or a pointer; the calling convention of this platform lets a function be called with more of those than it
 // looks at (registers first, the caller cleans the stack), so one call expression serves all of them.
 PyObject* invoke(PyObject*, PyObject* const* args, Py_ssize_t n) {
+  HANDLE_TH_ERRORS                         // a tensor without memory of its own (of a function transform, say) throws
   if (n < 1 || n - 1 > kMaxArgs) {
     PyErr_SetString(PyExc_TypeError, "pbsa: wrong number of arguments");
     return nullptr;
@@ -66,6 +68,7 @@ PyObject* invoke(PyObject*, PyObject* const* args, Py_ssize_t n) {
                                     a[14], a[15], a[16], a[17], a[18], a[19], a[20], a[21], a[22], a[23], a[24], a[25]);
   Py_END_ALLOW_THREADS
   return PyLong_FromLong(rc);
+  END_HANDLE_TH_ERRORS
 }
 
 PyMethodDef methods[] = {
