@@ -8,86 +8,114 @@
 
 namespace {
 
-constexpr int kMaxArgs = 26;   // of pbsa_attention_fwd_plan, the longest, 25
+constexpr int kMaxArgs = 24;   // of pbsa_attention_fwd_plan, the longest
 
-PyObject* g_host_types = nullptr;   // (ctypes.Structure, ctypes.Array): what is passed by the address of its bytes
+PyObject* g_params = nullptr;       // the types of pbsa_params and pbsa_grid, set once
+PyObject* g_grid = nullptr;
+PyObject* g_array = nullptr;        // ctypes.Array
 
-// The value a C argument gets: a device address for a tensor, the address of its bytes for a ctypes structure or
-// array, an integer for itself, 0 for None.  False: a Python error is set.
-bool convert(PyObject* o, int64_t& out) {
-  if (o == Py_None) {
-    out = 0;
-  } else if (THPVariable_Check(o)) {
-    const at::Tensor& t = THPVariable_Unpack(o);
-    if (!t.is_cuda()) {
-      PyErr_SetString(PyExc_TypeError, "pbsa: tensor arguments must live on the GPU");
-      return false;
-    }
-    if (t.dim() < 3 && !t.is_contiguous()) {
-      PyErr_SetString(PyExc_TypeError, "pbsa: small tensors must be contiguous");
-      return false;
-    }
-    out = reinterpret_cast<int64_t>(t.data_ptr());
-  } else if (PyLong_Check(o)) {
-    out = static_cast<int64_t>(PyLong_AsUnsignedLongLongMask(o));
-    if (PyErr_Occurred()) return false;
-  } else if (PyObject_IsInstance(o, g_host_types) == 1) {
-    Py_buffer view;
-    if (PyObject_GetBuffer(o, &view, PyBUF_SIMPLE) != 0) return false;
-    out = reinterpret_cast<int64_t>(view.buf);   // the caller holds the object for the length of the call
-    PyBuffer_Release(&view);
-  } else {                                       // an integer of another kind; anything else is refused here
-    PyObject* i = PyNumber_Index(o);
-    if (!i) return false;
-    out = static_cast<int64_t>(PyLong_AsUnsignedLongLongMask(i));
-    Py_DECREF(i);
-    if (PyErr_Occurred()) return false;
-  }
-  return true;
+enum class Take { yes, no, error };  // no: not one of the plain cases, error: a Python error is set
+
+// The address of the bytes of a ctypes object; the caller holds it for the length of the call.
+Take bytes_of(PyObject* o, int64_t& out) {
+  Py_buffer view;
+  if (PyObject_GetBuffer(o, &view, PyBUF_SIMPLE) != 0) return Take::error;
+  out = reinterpret_cast<int64_t>(view.buf);
+  PyBuffer_Release(&view);
+  return Take::yes;
 }
 
-// invoke(function address, *arguments) -> the function's int result.  Every argument of the library's functions is an
-// integer or a pointer; the calling convention of this platform lets a function be called with more of those than it
-// looks at (registers first, the caller cleans the stack), so one call expression serves all of them.
+// The value of an argument of the given kind (pbsa.py's _SIGNATURES), in the plain cases.
+Take convert(char kind, PyObject* o, int64_t& out) {
+  switch (kind) {
+    case 'p': return Py_TYPE(o) == reinterpret_cast<PyTypeObject*>(g_params) ? bytes_of(o, out) : Take::no;
+    case 'g': return Py_TYPE(o) == reinterpret_cast<PyTypeObject*>(g_grid) ? bytes_of(o, out) : Take::no;
+    case 'P':
+    case 'L': {
+      const int is = PyObject_IsInstance(o, g_array);
+      return is < 0 ? Take::error : is ? bytes_of(o, out) : Take::no;
+    }
+    case 'i':
+    case 'l':
+    case 'z':
+      if (!PyLong_CheckExact(o)) return Take::no;
+      break;
+    case 't':
+      if (THPVariable_CheckExact(o)) {
+        const at::Tensor& t = THPVariable_Unpack(o);
+        if (!t.is_cuda() || (t.dim() < 3 && !t.is_contiguous())) return Take::no;
+        out = reinterpret_cast<int64_t>(t.data_ptr());
+        return Take::yes;
+      }
+      [[fallthrough]];
+    case 'w':
+      if (o == Py_None) {
+        out = 0;
+        return Take::yes;
+      }
+      if (!PyLong_Check(o)) return Take::no;
+      break;
+    default: return Take::no;
+  }
+  out = static_cast<int64_t>(PyLong_AsUnsignedLongLongMask(o));
+  return PyErr_Occurred() ? Take::error : Take::yes;
+}
+
+// invoke(function address, kinds, *arguments) -> the function's int result, or NotImplemented with nothing called where
+// an argument is not one of the plain cases of its kind.  Every argument of the library's functions is an integer or a
+// pointer; the calling convention of this platform lets a function be called with more of those than it looks at
+// (registers first, the caller cleans the stack), so one call expression serves all of them.
 PyObject* invoke(PyObject*, PyObject* const* args, Py_ssize_t n) {
   HANDLE_TH_ERRORS                         // a tensor without memory of its own (of a function transform, say) throws
-  if (n < 1 || n - 1 > kMaxArgs) {
+  if (n < 2 || n - 2 > kMaxArgs || !PyLong_CheckExact(args[0]) || !PyBytes_CheckExact(args[1]) || PyBytes_GET_SIZE(args[1]) != n - 2) {
     PyErr_SetString(PyExc_TypeError, "pbsa: wrong number of arguments");
     return nullptr;
   }
-  int64_t v[kMaxArgs + 1] = {};
-  for (Py_ssize_t i = 0; i < n; ++i)
-    if (!convert(args[i], v[i])) return nullptr;
+  const char* const kinds = PyBytes_AS_STRING(args[1]);
+  int64_t f, a[kMaxArgs] = {};
+  f = static_cast<int64_t>(PyLong_AsUnsignedLongLongMask(args[0]));
+  for (Py_ssize_t i = 0; i < n - 2; ++i) {
+    const Take t = convert(kinds[i], args[i + 2], a[i]);
+    if (t == Take::error) return nullptr;
+    if (t == Take::no) Py_RETURN_NOTIMPLEMENTED;
+  }
   typedef int (*fn_t)(int64_t, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t,
                       int64_t, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t,
-                      int64_t, int64_t, int64_t, int64_t);
-  const int64_t* a = v + 1;
+                      int64_t, int64_t);
   int rc;
   Py_BEGIN_ALLOW_THREADS
-  rc = reinterpret_cast<fn_t>(v[0])(a[0], a[1], a[2], a[3], a[4], a[5], a[6], a[7], a[8], a[9], a[10], a[11], a[12], a[13],
-                                    a[14], a[15], a[16], a[17], a[18], a[19], a[20], a[21], a[22], a[23], a[24], a[25]);
+  rc = reinterpret_cast<fn_t>(f)(a[0], a[1], a[2], a[3], a[4], a[5], a[6], a[7], a[8], a[9], a[10], a[11], a[12], a[13],
+                                    a[14], a[15], a[16], a[17], a[18], a[19], a[20], a[21], a[22], a[23]);
   Py_END_ALLOW_THREADS
   return PyLong_FromLong(rc);
   END_HANDLE_TH_ERRORS
 }
 
+// setup(type of pbsa_params, type of pbsa_grid, ctypes.Array)
+PyObject* setup(PyObject*, PyObject* const* args, Py_ssize_t n) {
+  if (n != 3 || !PyType_Check(args[0]) || !PyType_Check(args[1]) || !PyType_Check(args[2])) {
+    PyErr_SetString(PyExc_TypeError, "pbsa: setup takes three types");
+    return nullptr;
+  }
+  PyObject** const to[3] = {&g_params, &g_grid, &g_array};
+  for (int i = 0; i < 3; ++i) {
+    Py_INCREF(args[i]);
+    Py_XDECREF(*to[i]);
+    *to[i] = args[i];
+  }
+  Py_RETURN_NONE;
+}
+
+template <typename F>
+constexpr PyCFunction fast(F f) {
+  return reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(f));
+}
 PyMethodDef methods[] = {
-    {"invoke", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(invoke)), METH_FASTCALL,
-     "invoke(function address, *arguments) -> int"},
+    {"invoke", fast(invoke), METH_FASTCALL, "invoke(function address, kinds, *arguments) -> int or NotImplemented"},
+    {"setup", fast(setup), METH_FASTCALL, "setup(pbsa_params, pbsa_grid, ctypes.Array)"},
     {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_pbsa_host", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__pbsa_host() {
-  PyObject* ct = PyImport_ImportModule("ctypes");
-  if (!ct) return nullptr;
-  PyObject* s = PyObject_GetAttrString(ct, "Structure");
-  PyObject* a = PyObject_GetAttrString(ct, "Array");
-  Py_DECREF(ct);
-  if (!s || !a) return nullptr;
-  g_host_types = PyTuple_Pack(2, s, a);
-  Py_DECREF(s);
-  Py_DECREF(a);
-  return g_host_types ? PyModule_Create(&module) : nullptr;
-}
+PyMODINIT_FUNC PyInit__pbsa_host() { return PyModule_Create(&module); }

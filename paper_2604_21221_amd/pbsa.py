@@ -19,14 +19,6 @@ PBSA_MAX_N_LOC, PBSA_MAX_C, PBSA_MAX_C_ATTEND, PBSA_MAX_K = 672, 64, 336, 672
 PBSA_MAX_N_LOC_AUX, PBSA_MAX_C_AUX, PBSA_MAX_K_AUX = 512, 192, 512
 PBSA_STATIC_WS_BYTES = 4 << 20
 
-EXPORTS = ("pbsa_workspace_bytes", "pbsa_pool_blocks", "pbsa_summary_view", "pbsa_append_chunk", "pbsa_attention_workspace_bytes", "pbsa_select_blocks", "pbsa_attention_fwd",
-           "pbsa_attention_fwd_split", "pbsa_memory_update", "pbsa_memory_update_static", "pbsa_memory_update_plan", "pbsa_memory_update_apply", "pbsa_attention_fwd_plan",
-           "pbsa_select_blocks_apply",
-           "pbsa_attention_mass", "pbsa_mass_workspace_bytes", "pbsa_attention_fwd_mass",
-           "pbsa_memory_update_fine", "pbsa_bwd_workspace_bytes", "pbsa_attention_bwd", "pbsa_blockify",
-           "pbsa_unblockify", "pbsa_strerror", "pbsa_version")
-
-
 class pbsa_params(ctypes.Structure):
     _fields_ = [("size", ctypes.c_uint32), ("H", ctypes.c_int32), ("d", ctypes.c_int32), ("B", ctypes.c_int32),
                 ("Nq", ctypes.c_int32), ("nqb", ctypes.c_int32), ("n_loc", ctypes.c_int32),
@@ -61,6 +53,35 @@ class PbsaError(RuntimeError):
         super().__init__(f"pbsa error {code}: {pbsa_strerror(code)}")
 
 
+# The library's functions and the kinds of their arguments: p / g a pbsa_params / pbsa_grid by reference, t a tensor (or a
+# device address, or None), i / l / z an int32 / int64 / size, w an address that is none of a tensor's (workspace, stream),
+# P / L a host array of pointers / of int64, o a size to be filled in.
+_SIGNATURES = {
+    "pbsa_workspace_bytes": "po",
+    "pbsa_attention_workspace_bytes": "po",
+    "pbsa_mass_workspace_bytes": "po",
+    "pbsa_bwd_workspace_bytes": "po",
+    "pbsa_pool_blocks": "pttitw",
+    "pbsa_summary_view": "p" + 5 * "t" + "w",
+    "pbsa_append_chunk": "pttlllliitttw",
+    "pbsa_select_blocks": "p" + 8 * "t" + "wzw",
+    "pbsa_select_blocks_apply": "p" + 8 * "t" + "p" + 6 * "t" + "wzw",
+    "pbsa_attention_fwd": "p" + 11 * "t" + "wzw",
+    "pbsa_attention_fwd_split": "p" + 11 * "t" + "wzw",
+    "pbsa_attention_fwd_plan": "p" + 20 * "t" + "wzw",
+    "pbsa_attention_fwd_mass": "p" + 12 * "t" + "wzw",
+    "pbsa_attention_mass": "p" + 9 * "t" + "w",
+    "pbsa_attention_bwd": "p" + 17 * "t" + "wzw",
+    "pbsa_memory_update": "p" + 17 * "t" + "wzw",
+    "pbsa_memory_update_static": "p" + 17 * "t" + "w",
+    "pbsa_memory_update_plan": "p" + 12 * "t" + "wzw",
+    "pbsa_memory_update_apply": "p" + 7 * "t" + "wzw",
+    "pbsa_memory_update_fine": "p" + 16 * "t" + "wzw",
+    "pbsa_blockify": "giPPLw",
+    "pbsa_unblockify": "gtltw",
+}
+EXPORTS = (*_SIGNATURES, "pbsa_strerror", "pbsa_version")
+
 _lib = None
 
 
@@ -72,41 +93,17 @@ def lib() -> ctypes.CDLL:
             raise ImportError(f"{LIB_PATH} is missing: build it with `python -m paper_2604_21221_amd.build` "
                               "(there is no CPU fallback)")
         L = ctypes.CDLL(LIB_PATH)
-        vp, i32, sz = ctypes.c_void_p, ctypes.c_int32, ctypes.c_size_t
-        pp = ctypes.POINTER(pbsa_params)
         L.pbsa_version.restype = ctypes.c_int
         L.pbsa_version.argtypes = []
         L.pbsa_strerror.restype = ctypes.c_char_p
         L.pbsa_strerror.argtypes = [ctypes.c_int]
-        L.pbsa_workspace_bytes.argtypes = [pp, ctypes.POINTER(sz)]
-        L.pbsa_attention_workspace_bytes.argtypes = [pp, ctypes.POINTER(sz)]
-        L.pbsa_pool_blocks.argtypes = [pp, vp, vp, i32, vp, vp]
-        L.pbsa_summary_view.argtypes = [pp] + [vp] * 6
-        i64 = ctypes.c_int64
-        L.pbsa_append_chunk.argtypes = [pp, vp, vp, i64, i64, i64, i64, i32, i32, vp, vp, vp, vp]
-        L.pbsa_select_blocks.argtypes = [pp] + [vp] * 9 + [sz, vp]
-        L.pbsa_attention_fwd.argtypes = L.pbsa_attention_fwd_split.argtypes = [pp] + [vp] * 12 + [sz, vp]
-        L.pbsa_memory_update.argtypes = [pp] + [vp] * 18 + [sz, vp]
-        L.pbsa_memory_update_static.argtypes = [pp] + [vp] * 18
-        L.pbsa_memory_update_plan.argtypes = [pp] + [vp] * 13 + [sz, vp]
-        L.pbsa_memory_update_apply.argtypes = [pp] + [vp] * 8 + [sz, vp]
-        L.pbsa_attention_fwd_plan.argtypes = [pp] + [vp] * 21 + [sz, vp]
-        L.pbsa_select_blocks_apply.argtypes = [pp] + [vp] * 8 + [pp] + [vp] * 7 + [sz, vp]
-        L.pbsa_attention_mass.argtypes = [pp] + [vp] * 10
-        L.pbsa_mass_workspace_bytes.argtypes = [pp, ctypes.POINTER(sz)]
-        L.pbsa_attention_fwd_mass.argtypes = [pp] + [vp] * 13 + [sz, vp]
-        L.pbsa_memory_update_fine.argtypes = [pp] + [vp] * 17 + [sz, vp]
-        L.pbsa_bwd_workspace_bytes.argtypes = [pp, ctypes.POINTER(sz)]
-        L.pbsa_attention_bwd.argtypes = [pp] + [vp] * 18 + [sz, vp]
-        pg = ctypes.POINTER(pbsa_grid)
-        L.pbsa_blockify.argtypes = [pg, i32, ctypes.POINTER(vp), ctypes.POINTER(vp), ctypes.POINTER(ctypes.c_int64), vp]
-        L.pbsa_unblockify.argtypes = [pg, vp, ctypes.c_int64, vp, vp]
-        for name in ("pbsa_workspace_bytes", "pbsa_pool_blocks", "pbsa_summary_view", "pbsa_append_chunk", "pbsa_attention_workspace_bytes", "pbsa_select_blocks",
-                     "pbsa_attention_fwd", "pbsa_attention_fwd_split", "pbsa_memory_update", "pbsa_memory_update_static", "pbsa_memory_update_plan", "pbsa_memory_update_apply",
-                     "pbsa_attention_fwd_plan", "pbsa_select_blocks_apply", "pbsa_attention_mass", "pbsa_mass_workspace_bytes",
-                     "pbsa_attention_fwd_mass", "pbsa_memory_update_fine", "pbsa_bwd_workspace_bytes",
-                     "pbsa_attention_bwd", "pbsa_blockify", "pbsa_unblockify"):
-            getattr(L, name).restype = ctypes.c_int
+        ref = ctypes.POINTER
+        types = dict(p=ref(pbsa_params), g=ref(pbsa_grid), t=ctypes.c_void_p, w=ctypes.c_void_p, i=ctypes.c_int32, l=ctypes.c_int64,
+                     z=ctypes.c_size_t, o=ref(ctypes.c_size_t), P=ref(ctypes.c_void_p), L=ref(ctypes.c_int64))
+        for name, kinds in _SIGNATURES.items():
+            fn = getattr(L, name)
+            fn.restype = ctypes.c_int
+            fn.argtypes = [types[k] for k in kinds]
         _lib = L
     return _lib
 
@@ -137,30 +134,49 @@ def _ws(ws):
     if ws is None:
         return None, 0
     if isinstance(ws, tuple):
-        return ws
-    return ws.data_ptr(), ws.nbytes
+        return ws[0], ws[1]
+    return ws.data_ptr(), ws.numel() * ws.element_size()
 
 
-class _Addresses(dict):
-    """Address of each library function, looked up (and the library loaded) on first use."""
+class _Functions(dict):
+    """Address and argument kinds of each library function, looked up (and the library loaded) on first use."""
 
     def __missing__(self, name):
-        self[name] = a = ctypes.cast(getattr(lib(), name), ctypes.c_void_p).value
-        return a
+        self[name] = f = (ctypes.cast(getattr(lib(), name), ctypes.c_void_p).value, _SIGNATURES[name].encode())
+        return f
 
 
-_A = _Addresses()
+_F = _Functions()
 
 
 def _invoke(*args):
-    """Calls the function at address args[0] with the rest: tensors, integers, ctypes structures or None (csrc/pbsa_host.cpp)."""
+    """Calls the function at address args[0] with the rest (csrc/pbsa_host.cpp)."""
     global _invoke
     try:
-        from ._pbsa_host import invoke
+        from ._pbsa_host import invoke, setup
     except ImportError as e:
         raise ImportError("the binding's native half is missing: build it with `python -m paper_2604_21221_amd.build`") from e
+    setup(pbsa_params, pbsa_grid, ctypes.Array)
     _invoke = invoke
     return invoke(*args)
+
+
+def _through_ctypes(name, args):
+    """The call for what the native half leaves alone: anything but plain tensors, integers and the structures themselves.
+    ctypes and _ptr take it or refuse it."""
+    conv = dict(p=ctypes.byref, g=ctypes.byref, t=_ptr, w=ctypes.c_void_p)
+    return getattr(lib(), name)(*[conv[k](a) if k in conv else a for k, a in zip(_SIGNATURES[name], args)])
+
+
+def _call(name, *args):
+    rc = _invoke(*_F[name], *args)
+    _check(_through_ctypes(name, args) if rc is NotImplemented else rc)
+
+
+def _size(name, p):
+    out = ctypes.c_size_t(0)
+    _check(getattr(lib(), name)(ctypes.byref(p), ctypes.byref(out)))
+    return out.value
 
 
 def _check(rc: int):
@@ -177,121 +193,110 @@ def pbsa_strerror(code: int) -> str:
 
 
 def pbsa_workspace_bytes(p: pbsa_params) -> int:
-    out = ctypes.c_size_t(0)
-    _check(_invoke(_A["pbsa_workspace_bytes"], p, ctypes.addressof(out)))
-    return out.value
+    return _size("pbsa_workspace_bytes", p)
 
 
 def pbsa_attention_workspace_bytes(p: pbsa_params) -> int:
-    out = ctypes.c_size_t(0)
-    _check(_invoke(_A["pbsa_attention_workspace_bytes"], p, ctypes.addressof(out)))
-    return out.value
+    return _size("pbsa_attention_workspace_bytes", p)
 
 
 def pbsa_pool_blocks(p, X, length, n_blocks, out, stream=None):
-    _check(_invoke(_A["pbsa_pool_blocks"], p, X, length, n_blocks, out, _stream(stream)))
+    _call("pbsa_pool_blocks", p, X, length, n_blocks, out, _stream(stream))
 
 
 def pbsa_summary_view(p, S_sum, S_cnt, Kp, Vp, p_len, stream=None):
-    _check(_invoke(_A["pbsa_summary_view"], p, S_sum, S_cnt, Kp, Vp, p_len, _stream(stream)))
+    _call("pbsa_summary_view", p, S_sum, S_cnt, Kp, Vp, p_len, _stream(stream))
 
 
 def pbsa_append_chunk(p, K, V, slot0, zero_tail, Kl, Vl, Kc_l=None, stream=None):
     """K, V: [H][Nq][d] bf16 with a contiguous last dimension, or None."""
     ks, vs = (x.stride() if x is not None else (0, 0, 1) for x in (K, V))
-    _check(_invoke(_A["pbsa_append_chunk"], p, K, V, ks[0], ks[1], vs[0], vs[1], slot0, int(zero_tail), Kl, Vl, Kc_l,
-                   _stream(stream)))
+    _call("pbsa_append_chunk", p, K, V, ks[0], ks[1], vs[0], vs[1], slot0, int(zero_tail), Kl, Vl, Kc_l, _stream(stream))
 
 
 def pbsa_select_blocks(p, Q, Kl, l_len, l_map, Kc_l, Qc, sel, Zl=None, ws=None, stream=None):
     w, wb = _ws(ws)
-    _check(_invoke(_A["pbsa_select_blocks"], p, Q, Kl, l_len, l_map, Kc_l, Qc, sel, Zl, w, wb, _stream(stream)))
+    _call("pbsa_select_blocks", p, Q, Kl, l_len, l_map, Kc_l, Qc, sel, Zl, w, wb, _stream(stream))
 
 
 def pbsa_select_blocks_apply(p, Q, Kl, l_len, l_map, Kc_l, Qc, sel, Zl, p_upd, Kp, Vp, p_len, S_sum, S_cnt, Vl, ws,
                              stream=None):
     w, wb = _ws(ws)
-    _check(_invoke(_A["pbsa_select_blocks_apply"], p, Q, Kl, l_len, l_map, Kc_l, Qc, sel, Zl, p_upd, Kp, Vp, p_len, S_sum,
-                   S_cnt, Vl, w, wb, _stream(stream)))
+    _call("pbsa_select_blocks_apply", p, Q, Kl, l_len, l_map, Kc_l, Qc, sel, Zl, p_upd, Kp, Vp, p_len, S_sum, S_cnt, Vl, w,
+          wb, _stream(stream))
 
 
 def pbsa_attention_fwd(p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse=None, ws=None, stream=None):
     w, wb = _ws(ws)
-    _check(_invoke(_A["pbsa_attention_fwd"], p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse, w, wb, _stream(stream)))
+    _call("pbsa_attention_fwd", p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse, w, wb, _stream(stream))
 
 
 def pbsa_attention_fwd_split(p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse, ws, stream=None):
     """pbsa_attention_fwd with pbsa_attention_workspace_bytes(p) bytes of scratch."""
     w, wb = _ws(ws)
-    _check(_invoke(_A["pbsa_attention_fwd_split"], p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse, w, wb,
-                   _stream(stream)))
+    _call("pbsa_attention_fwd_split", p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse, w, wb, _stream(stream))
 
 
 def pbsa_memory_update(p, Qc, Kc_l, Zl, Kp, Vp, Kc_p, p_len, p_id, S_sum, S_cnt, Kl, Vl, l_len, l_map, l_id, scores,
                        slot_src, ws, stream=None):
     w, wb = _ws(ws)
-    _check(_invoke(_A["pbsa_memory_update"], p, Qc, Kc_l, Zl, Kp, Vp, Kc_p, p_len, p_id, S_sum, S_cnt, Kl, Vl, l_len, l_map,
-                   l_id, scores, slot_src, w, wb, _stream(stream)))
+    _call("pbsa_memory_update", p, Qc, Kc_l, Zl, Kp, Vp, Kc_p, p_len, p_id, S_sum, S_cnt, Kl, Vl, l_len, l_map, l_id, scores,
+          slot_src, w, wb, _stream(stream))
 
 
 def pbsa_memory_update_static(p, Qc, Kc_l, Zl, Kp, Vp, Kc_p, p_len, p_id, S_sum, S_cnt, Kl, Vl, l_len, l_map, l_id, scores,
                               slot_src, stream=None):
-    _check(_invoke(_A["pbsa_memory_update_static"], p, Qc, Kc_l, Zl, Kp, Vp, Kc_p, p_len, p_id, S_sum, S_cnt, Kl, Vl, l_len,
-                   l_map, l_id, scores, slot_src, _stream(stream)))
+    _call("pbsa_memory_update_static", p, Qc, Kc_l, Zl, Kp, Vp, Kc_p, p_len, p_id, S_sum, S_cnt, Kl, Vl, l_len, l_map, l_id,
+          scores, slot_src, _stream(stream))
 
 
 def pbsa_memory_update_plan(p, Qc, Kc_l, Zl, Kc_p, p_len, p_id, S_cnt, l_len, l_map, l_id, scores, slot_src, ws,
                             stream=None):
     w, wb = _ws(ws)
-    _check(_invoke(_A["pbsa_memory_update_plan"], p, Qc, Kc_l, Zl, Kc_p, p_len, p_id, S_cnt, l_len, l_map, l_id, scores,
-                   slot_src, w, wb, _stream(stream)))
+    _call("pbsa_memory_update_plan", p, Qc, Kc_l, Zl, Kc_p, p_len, p_id, S_cnt, l_len, l_map, l_id, scores, slot_src, w, wb,
+          _stream(stream))
 
 
 def pbsa_attention_fwd_plan(p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse, Qc, Kc_l, Zl, Kc_p, p_id, S_cnt, l_id,
                             scores, slot_src, ws, stream=None):
     w, wb = _ws(ws)
-    _check(_invoke(_A["pbsa_attention_fwd_plan"], p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse, Qc, Kc_l, Zl, Kc_p,
-                   p_id, S_cnt, l_id, scores, slot_src, w, wb, _stream(stream)))
+    _call("pbsa_attention_fwd_plan", p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse, Qc, Kc_l, Zl, Kc_p, p_id, S_cnt,
+          l_id, scores, slot_src, w, wb, _stream(stream))
 
 
 def pbsa_memory_update_apply(p, Kp, Vp, p_len, S_sum, S_cnt, Kl, Vl, ws, stream=None):
     w, wb = _ws(ws)
-    _check(_invoke(_A["pbsa_memory_update_apply"], p, Kp, Vp, p_len, S_sum, S_cnt, Kl, Vl, w, wb, _stream(stream)))
+    _call("pbsa_memory_update_apply", p, Kp, Vp, p_len, S_sum, S_cnt, Kl, Vl, w, wb, _stream(stream))
 
 
 def pbsa_attention_mass(p, Q, Kp, p_len, Kl, l_len, l_map, sel, lse, Mt, stream=None):
-    _check(_invoke(_A["pbsa_attention_mass"], p, Q, Kp, p_len, Kl, l_len, l_map, sel, lse, Mt, _stream(stream)))
+    _call("pbsa_attention_mass", p, Q, Kp, p_len, Kl, l_len, l_map, sel, lse, Mt, _stream(stream))
 
 
 def pbsa_mass_workspace_bytes(p: pbsa_params) -> int:
-    out = ctypes.c_size_t(0)
-    _check(_invoke(_A["pbsa_mass_workspace_bytes"], p, ctypes.addressof(out)))
-    return out.value
+    return _size("pbsa_mass_workspace_bytes", p)
 
 
 def pbsa_attention_fwd_mass(p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse, Mt, ws, stream=None):
     w, wb = _ws(ws)
-    _check(_invoke(_A["pbsa_attention_fwd_mass"], p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse, Mt, w, wb,
-                   _stream(stream)))
+    _call("pbsa_attention_fwd_mass", p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse, Mt, w, wb, _stream(stream))
 
 
 def pbsa_memory_update_fine(p, Mt, Kc_l, Kp, Vp, Kc_p, p_len, p_id, S_sum, S_cnt, Kl, Vl, l_len, l_map, l_id, scores,
                             slot_src, ws, stream=None):
     w, wb = _ws(ws)
-    _check(_invoke(_A["pbsa_memory_update_fine"], p, Mt, Kc_l, Kp, Vp, Kc_p, p_len, p_id, S_sum, S_cnt, Kl, Vl, l_len, l_map,
-                   l_id, scores, slot_src, w, wb, _stream(stream)))
+    _call("pbsa_memory_update_fine", p, Mt, Kc_l, Kp, Vp, Kc_p, p_len, p_id, S_sum, S_cnt, Kl, Vl, l_len, l_map, l_id,
+          scores, slot_src, w, wb, _stream(stream))
 
 
 def pbsa_bwd_workspace_bytes(p: pbsa_params) -> int:
-    out = ctypes.c_size_t(0)
-    _check(_invoke(_A["pbsa_bwd_workspace_bytes"], p, ctypes.addressof(out)))
-    return out.value
+    return _size("pbsa_bwd_workspace_bytes", p)
 
 
 def pbsa_attention_bwd(p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, dO, lse, dQ, dKp, dVp, dKl, dVl, ws, stream=None):
     w, wb = _ws(ws)
-    _check(_invoke(_A["pbsa_attention_bwd"], p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, dO, lse, dQ, dKp, dVp, dKl,
-                   dVl, w, wb, _stream(stream)))
+    _call("pbsa_attention_bwd", p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, dO, lse, dQ, dKp, dVp, dKl, dVl, w, wb,
+          _stream(stream))
 
 
 def pbsa_blockify(g, X, Xblk, blk_stride_h, stream=None):
@@ -300,8 +305,8 @@ def pbsa_blockify(g, X, Xblk, blk_stride_h, stream=None):
     xs = (ctypes.c_void_p * n)(*[_ptr(x) for x in X])
     bs = (ctypes.c_void_p * n)(*[_ptr(x) for x in Xblk])
     st = (ctypes.c_int64 * n)(*[int(v) for v in blk_stride_h])
-    _check(_invoke(_A["pbsa_blockify"], g, n, xs, bs, st, _stream(stream)))
+    _call("pbsa_blockify", g, n, xs, bs, st, _stream(stream))
 
 
 def pbsa_unblockify(g, Xblk, blk_stride_h, X, stream=None):
-    _check(_invoke(_A["pbsa_unblockify"], g, Xblk, int(blk_stride_h), X, _stream(stream)))
+    _call("pbsa_unblockify", g, Xblk, int(blk_stride_h), X, _stream(stream))
