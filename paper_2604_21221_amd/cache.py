@@ -138,25 +138,30 @@ class PbsaCache:
         self.stale_from = min(self.stale_from, self.n_loc - self.nqb)
         return pooled
 
-    def _in_place(self, x):
-        """Whether pbsa_append_chunk takes tensor x as it is: bf16 on this GPU, whole, rows contiguous and aligned."""
-        return (type(x) is torch.Tensor and x.dtype is torch.bfloat16 and x.layout is torch.strided and x.device == self.Kl.device
-                # the library launches on the current device
-                and (x.device.index is None or x.device.index == torch._C._cuda_getDevice())
-                and x.shape == (self.H, self.Nq, self.d) and x.stride(2) == 1 and x.stride(0) % 8 == 0 and x.stride(1) % 8 == 0
-                and x.stride(1) >= self.d and x.data_ptr() % 16 == 0 and not x.is_neg()
-                # rows of the ring itself: K is copied before V is, and a launch knows no such order
-                and x.untyped_storage()._cdata not in (self.Kl.untyped_storage()._cdata, self.Vl.untyped_storage()._cdata))
-
-    def _watched(self, K, V):
-        """Whether torch would record, transform or refuse a copy of K and V into the ring (gradients, forward mode, function
-        transforms, dispatch modes, tracing, inference tensors outside their mode): a launch would pass all of that by."""
-        if torch.is_grad_enabled() and (self.Kl.requires_grad or self.Vl.requires_grad or (K is not None and K.requires_grad)
-                                        or (V is not None and V.requires_grad)):
-            return True
-        return (torch.autograd.forward_ad._current_level >= 0 or torch._C._functorch.peek_interpreter_stack() is not None
-                or torch._C._len_torch_dispatch_stack() > 0 or torch._C._get_tracing_state() is not None
-                or torch.compiler.is_compiling() or (self.Kl.is_inference() and not torch.is_inference_mode_enabled()))
+    def _in_place(self, K, V):
+        """Whether pbsa_append_chunk takes K and V (or None) as they are and nothing but their bytes counts: bf16 on this GPU,
+        whole, rows contiguous and aligned; nothing that torch would record, transform or refuse in a copy (gradients,
+        forward mode, function transforms, dispatch modes, tracing, inference tensors outside their mode); and not rows of
+        the ring itself: K is copied before V is, and a launch knows no such order."""
+        Kl, Vl = self.Kl, self.Vl
+        dev, shape = Kl.device, (self.H, self.Nq, self.d)
+        ring = Kl.untyped_storage()._cdata, Vl.untyped_storage()._cdata
+        watched = torch.is_grad_enabled()
+        if watched and (Kl.requires_grad or Vl.requires_grad):
+            return False
+        for x in (K, V):
+            if x is None:
+                continue
+            if (type(x) is not torch.Tensor or x.dtype is not torch.bfloat16 or x.layout is not torch.strided or x.device != dev
+                    or x.shape != shape or (watched and x.requires_grad) or x.is_neg() or x.untyped_storage()._cdata in ring):
+                return False
+            sh, st, one = x.stride()
+            if one != 1 or sh % 8 or st % 8 or st < self.d or x.data_ptr() % 16:
+                return False
+        return ((dev.index is None or dev.index == torch._C._cuda_getDevice())       # the library launches on the current device
+                and torch.autograd.forward_ad._current_level < 0 and torch._C._functorch.peek_interpreter_stack() is None
+                and torch._C._len_torch_dispatch_stack() == 0 and torch._C._get_tracing_state() is None
+                and not torch.compiler.is_compiling() and (not Kl.is_inference() or torch.is_inference_mode_enabled()))
 
     def _write_chunk(self, pos, K, V, zero_tail, pool):
         """K and V (either may be None) into ring position `pos` in one launch, with the pooled keys if asked for; tensors
@@ -164,7 +169,7 @@ class PbsaCache:
         keys were written."""
         if K is None and V is None:
             return False
-        if (K is None or self._in_place(K)) and (V is None or self._in_place(V)) and not self._watched(K, V):
+        if self._in_place(K, V):
             # as an in-place copy would, so that a backward which saved the ring notices
             torch.autograd.graph.increment_version([dst for dst, src in ((self.Kl, K), (self.Vl, V)) if src is not None])
             pool = pool and K is not None
