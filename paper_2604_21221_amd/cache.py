@@ -45,9 +45,15 @@ class PbsaCache:
         full = pbsa.make_params(H, d, B, Nq, self.cap, self.cap, C, k, self.scale, n_sink, causal, n_evict=self.nqb)
         self._full = full            # what an append is described by: the geometry, not how full the window is
         # with more slots than pbsa_memory_update maintains the cache can only be selected from and attended
-        attends = C <= pbsa.PBSA_MAX_C_ATTEND and self.cap <= pbsa.PBSA_MAX_N_LOC and k <= pbsa.PBSA_MAX_K
-        n_attn = pbsa.pbsa_attention_workspace_bytes(full) if attends else 0
         n_ws = pbsa.pbsa_workspace_bytes(full) if C <= pbsa.PBSA_MAX_C else 0
+        # what the kernels do not take can be stored all the same (no GPU call: the library looks at the geometry alone)
+        try:
+            pbsa.pbsa_append_chunk(full, None, None, 0, True, None, None, stream=0)
+            self._by_launch = True
+        except pbsa.PbsaError:
+            self._by_launch = False
+        attends = self._by_launch and C <= pbsa.PBSA_MAX_C_ATTEND and self.cap <= pbsa.PBSA_MAX_N_LOC and k <= pbsa.PBSA_MAX_K
+        n_attn = pbsa.pbsa_attention_workspace_bytes(full) if attends else 0
         self.ws = torch.empty(max(n_ws + n_attn, 256), dtype=torch.uint8, device=self.dev)
         # attention_with_plan()'s split takes the share behind what the update needs; attention() changes nothing of the
         # cache and may be called from several streams at a time, so its scratch is each call's own
@@ -169,7 +175,7 @@ class PbsaCache:
         keys were written."""
         if K is None and V is None:
             return False
-        if self._in_place(K, V):
+        if self._by_launch and self._in_place(K, V):
             # as an in-place copy would, so that a backward which saved the ring notices
             torch.autograd.graph.increment_version([dst for dst, src in ((self.Kl, K), (self.Vl, V)) if src is not None])
             pool = pool and K is not None

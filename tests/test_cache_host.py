@@ -44,9 +44,10 @@ CALLS = ("pbsa_append_chunk", "pbsa_select_blocks", "pbsa_attention_fwd_split", 
 
 
 def record(monkeypatch):
+    """The library's calls from here on (but for the one by which a new cache asks what its geometry can do)."""
     calls = []
     for name in CALLS:
-        monkeypatch.setattr(pbsa, name, lambda *a, name=name, **k: calls.append((name, a)))
+        monkeypatch.setattr(pbsa, name, lambda *a, name=name, **k: a[1:3] == (None, None) or calls.append((name, a)))
     return calls
 
 
@@ -247,3 +248,19 @@ def test_rows_of_the_ring_are_copied_in_order(cache, monkeypatch):
     k = chunk(2)
     cache.rewrite_chunk(k, rows(cache, cache.Kl))
     assert torch.equal(rows(cache, cache.Kl), k) and torch.equal(rows(cache, cache.Vl), k) and not calls
+
+
+@pytest.mark.parametrize("kw", [dict(d=32), dict(B=32), dict(n_sink=101), dict(causal=2), dict(scale=0.0), dict(H=65536, d=32)],
+                         ids=lambda kw: next(iter(kw)))
+def test_a_geometry_no_kernel_takes_can_be_stored(monkeypatch, kw):
+    """With more slots than the update maintains nothing of the library is asked when a cache is made: whatever the kernels
+    would refuse holds chunks all the same."""
+    a = dict(H=2, d=64, B=64, Nq=3, window_chunks=1, C=100, k=2, scale=0.1)
+    a.update(kw)
+    if a["H"] > 1000:
+        a.update(C=65, Nq=1, B=1, window_chunks=0, fold=False, pass_logits=False)
+    c = PbsaCache(**a, device="cpu")
+    k, v = (torch.randn(a["H"], a["Nq"], a["d"]).to(torch.bfloat16) for _ in range(2))
+    c.append_chunk(k, v, 0)
+    for t, x in ((c.Kl, k), (c.Vl, v)):
+        assert torch.equal(t[:, :c.nqb].reshape(a["H"], -1, a["d"])[:, :a["Nq"]], x)
