@@ -42,22 +42,12 @@ class PbsaCache:
         self.sel = torch.full((H, self.nqb, max(k, 1)), -1, dtype=torch.int32, device=self.dev)
         self.slot_src = torch.full((H, max(C, 1)), -1, dtype=torch.int32, device=self.dev)
         self.scores = z(H, C + self.nqb, dt=torch.float32)
-        full = pbsa.make_params(H, d, B, Nq, self.cap, self.cap, C, k, self.scale, n_sink, causal, n_evict=self.nqb)
-        self._full = full            # what an append is described by: the geometry, not how full the window is
+        self._derive()
         # with more slots than pbsa_memory_update maintains the cache can only be selected from and attended
-        n_ws = pbsa.pbsa_workspace_bytes(full) if C <= pbsa.PBSA_MAX_C else 0
-        # what the kernels do not take can be stored all the same (no GPU call: the library looks at the geometry alone)
-        try:
-            pbsa.pbsa_append_chunk(full, None, None, 0, True, None, None, stream=0)
-            self._by_launch = True
-        except pbsa.PbsaError:
-            self._by_launch = False
-        attends = self._by_launch and C <= pbsa.PBSA_MAX_C_ATTEND and self.cap <= pbsa.PBSA_MAX_N_LOC and k <= pbsa.PBSA_MAX_K
-        n_attn = pbsa.pbsa_attention_workspace_bytes(full) if attends else 0
-        self.ws = torch.empty(max(n_ws + n_attn, 256), dtype=torch.uint8, device=self.dev)
+        n_ws = pbsa.pbsa_workspace_bytes(self._full) if C <= pbsa.PBSA_MAX_C else 0
         # attention_with_plan()'s split takes the share behind what the update needs; attention() changes nothing of the
         # cache and may be called from several streams at a time, so its scratch is each call's own
-        self._attn_bytes = n_attn
+        self.ws = torch.empty(max(n_ws + self._attn_bytes, 256), dtype=torch.uint8, device=self.dev)
         self.chunk_pos = []          # ring position of each chunk in the local region, oldest first
         self.chunk_ids = []          # global chunk index of each
         self.n_appended = 0
@@ -67,6 +57,28 @@ class PbsaCache:
         lens = torch.full((self.nqb,), B, dtype=torch.int32)
         lens[-1] = Nq - (self.nqb - 1) * B
         self._chunk_lens = lens
+
+    def _derive(self):
+        """What follows from the geometry: its description for an append (which does not depend on how full the window is),
+        whether the library takes it, the scratch of an attention call."""
+        self._full = full = pbsa.make_params(self.H, self.d, self.B, self.Nq, self.cap, self.cap, self.C, self.k, self.scale,
+                                             self.n_sink, self.causal, n_evict=self.nqb)
+        # what the kernels do not take can be stored all the same (no GPU call: the library looks at the geometry alone)
+        try:
+            pbsa.pbsa_append_chunk(full, None, None, 0, True, None, None, stream=0)
+            self._by_launch = True
+        except pbsa.PbsaError:
+            self._by_launch = False
+        attends = (self._by_launch and self.C <= pbsa.PBSA_MAX_C_ATTEND and self.cap <= pbsa.PBSA_MAX_N_LOC
+                   and self.k <= pbsa.PBSA_MAX_K)
+        self._attn_bytes = pbsa.pbsa_attention_workspace_bytes(full) if attends else 0
+
+    def __setstate__(self, state):
+        """A saved cache, also one saved before these were kept; scratch with nothing in it is made again when asked for."""
+        self.__dict__.update(state)
+        for name in ("_bwd_ws", "_mass_ws"):
+            self.__dict__.pop(name, None)
+        self._derive()
 
     @property
     def n_loc(self):

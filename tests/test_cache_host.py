@@ -40,7 +40,8 @@ def test_attention_shares_no_scratch(cache, monkeypatch):
 
 
 CALLS = ("pbsa_append_chunk", "pbsa_select_blocks", "pbsa_attention_fwd_split", "pbsa_attention_fwd_plan",
-         "pbsa_attention_fwd_mass", "pbsa_memory_update", "pbsa_memory_update_apply", "pbsa_memory_update_fine")
+         "pbsa_attention_fwd_mass", "pbsa_attention_bwd", "pbsa_memory_update", "pbsa_memory_update_apply",
+         "pbsa_memory_update_fine")
 
 
 def record(monkeypatch):
@@ -264,3 +265,25 @@ def test_a_geometry_no_kernel_takes_can_be_stored(monkeypatch, kw):
     c.append_chunk(k, v, 0)
     for t, x in ((c.Kl, k), (c.Vl, v)):
         assert torch.equal(t[:, :c.nqb].reshape(a["H"], -1, a["d"])[:, :a["Nq"]], x)
+
+
+def test_a_saved_cache_goes_on(cache, monkeypatch):
+    """Saved and loaded, with scratch of whatever size it had, and from a file that holds only what a cache was first made
+    of."""
+    import copy
+    import pickle
+    calls = record(monkeypatch)
+    cache.append_chunk(chunk(0), chunk(1), 0)
+    cache._bwd_ws = cache._mass_ws = torch.empty(16, dtype=torch.uint8)
+    old = copy.copy(cache)
+    old.__dict__ = {k: v for k, v in vars(cache).items() if k not in ("_full", "_by_launch", "_attn_bytes")}
+    for c in (pickle.loads(pickle.dumps(cache)), copy.deepcopy(cache), pickle.loads(pickle.dumps(old))):
+        assert c.chunk_ids == [0] and c._attn_bytes == cache._attn_bytes > 0
+        assert not hasattr(c, "_bwd_ws") and not hasattr(c, "_mass_ws")
+        del calls[:]
+        c.attention(chunk(3))
+        c.append_chunk(chunk(0), chunk(1), 1)
+        c.attention_bwd(chunk(3), chunk(3), chunk(3), torch.zeros(H, NQ))
+        assert [n for n, _ in calls] == ["pbsa_attention_fwd_split", "pbsa_append_chunk", "pbsa_attention_bwd"]
+        need = pbsa.pbsa_bwd_workspace_bytes(c.params())
+        assert calls[-1][1][-1].numel() == need and calls[0][1][-1].numel() == c._attn_bytes
