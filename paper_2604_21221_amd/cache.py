@@ -52,6 +52,7 @@ class PbsaCache:
         self.chunk_ids = []          # global chunk index of each
         self.n_appended = 0
         self.stale_from = 0
+        self._installed = 0          # slots that set_persistent() may have filled
         self._maps = {}
         self._arange64 = None
         lens = torch.full((self.nqb,), B, dtype=torch.int32)
@@ -72,10 +73,25 @@ class PbsaCache:
         attends = (self._by_launch and self.C <= pbsa.PBSA_MAX_C_ATTEND and self.cap <= pbsa.PBSA_MAX_N_LOC
                    and self.k <= pbsa.PBSA_MAX_K)
         self._attn_bytes = pbsa.pbsa_attention_workspace_bytes(full) if attends else 0
+        self._pays = {}
+
+    def _split_pays(self):
+        """Whether an attention call is to split its last round.  The library's rule goes by the shape alone; on the first
+        chunks of a roll-out, whose slots are empty, a query tile is two or three tiles of a walk long and the second launch
+        costs more than it gives (select + attend: 31.8 -> 34.8 us at 4 x 1024 x 128 with 32 empty slots).  So the same rule
+        is asked about the blocks there may be: those in the window, and in the slots what has been installed and
+        what has left the window.  That is the state of the cache: calls of all kinds on it agree."""
+        held = min(self.C, self._installed + (self.n_appended - len(self.chunk_pos)) * self.nqb)
+        pays = self._pays.get((held, self.n_loc))
+        if pays is None:
+            p = pbsa.make_params(self.H, self.d, self.B, self.Nq, self.n_loc, self.n_loc, held, self.k, self.scale)
+            pays = self._pays[held, self.n_loc] = pbsa.pbsa_attention_workspace_bytes(p) > 0
+        return pays
 
     def __setstate__(self, state):
         """A saved cache, also one saved before these were kept; scratch with nothing in it is made again when asked for."""
         self.__dict__.update(state)
+        self.__dict__.setdefault("_installed", self.C)
         for name in ("_bwd_ws", "_mass_ws"):
             self.__dict__.pop(name, None)
         self._derive()
@@ -120,6 +136,7 @@ class PbsaCache:
     def set_persistent(self, Kp, Vp, lens, ids):
         """Install blocks ([H][c][B][d] bf16) in the first slots; pooled keys come from pbsa_pool_blocks."""
         c = Kp.shape[1]
+        self._installed = max(self._installed, c)
         self.Kp[:, :c] = Kp
         self.Vp[:, :c] = Vp
         self.p_len[:, :c] = lens
@@ -243,8 +260,11 @@ class PbsaCache:
             O = torch.empty_like(Q)
         l_map, l_len, _ = self._device_maps()
         p = self.params(Q=Q, O=O)
-        ws = torch.empty(self._attn_bytes, dtype=torch.uint8, device=self.dev) if self._attn_bytes else None
-        pbsa.pbsa_attention_fwd_split(p, Q, self.Kp, self.Vp, self.p_len, self.Kl, self.Vl, l_len, l_map, self.sel, O, lse, ws)
+        args = p, Q, self.Kp, self.Vp, self.p_len, self.Kl, self.Vl, l_len, l_map, self.sel, O, lse
+        if self._attn_bytes and self._split_pays():
+            pbsa.pbsa_attention_fwd_split(*args, torch.empty(self._attn_bytes, dtype=torch.uint8, device=self.dev))
+        else:
+            pbsa.pbsa_attention_fwd(*args)
         return O
 
     def _no_pending(self):
@@ -305,8 +325,11 @@ class PbsaCache:
         Mt = self._mass_buffer()
         l_map, l_len, _ = self._device_maps()
         p = self.params(Q=Q, O=O)
+        ws = self._mass_ws
+        if self._attn_bytes and not self._split_pays():
+            ws = ws.data_ptr(), pbsa.pbsa_mass_workspace_bytes(p)        # no room beyond what it needs: nothing is split
         pbsa.pbsa_attention_fwd_mass(p, Q, self.Kp, self.Vp, self.p_len, self.Kl, self.Vl, l_len, l_map, self.sel, O,
-                                     lse, Mt, self._mass_ws)
+                                     lse, Mt, ws)
         return O, Mt
 
     def update_fine(self, Mt):
@@ -375,9 +398,12 @@ class PbsaCache:
             O = torch.empty_like(Q)
         l_map, l_len, l_id = self._device_maps(want_ids=True)
         self._plan_p = self.params(n_evict=self.n_evict_now(), Q=Q, O=O)
+        ws = self.ws
+        if self._attn_bytes and not self._split_pays():
+            ws = ws.data_ptr(), pbsa.pbsa_workspace_bytes(self._plan_p)  # no room beyond what it needs: nothing is split
         pbsa.pbsa_attention_fwd_plan(self._plan_p, Q, self.Kp, self.Vp, self.p_len, self.Kl, self.Vl, l_len, l_map, self.sel,
                                      O, lse, self.Qc, self.Kc_l, self.Zl, self.Kc_p, self.p_id, self.S_cnt, l_id,
-                                     self.scores, self.slot_src, self.ws)
+                                     self.scores, self.slot_src, ws)
         return O
 
     def step_fused(self, Q, K=None, V=None, chunk_id=None, O=None, lse=None):

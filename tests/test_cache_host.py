@@ -11,7 +11,9 @@ H, D, B, NQ, W = 2, 64, 64, 200, 1
 
 @pytest.fixture
 def cache():
-    return PbsaCache(H, D, B, NQ, W, 3, 12, D ** -0.5, device="cpu")
+    c = PbsaCache(H, D, B, NQ, W, 3, 12, D ** -0.5, device="cpu")
+    c._installed = 3                         # as by set_persistent()
+    return c
 
 
 def chunk(seed=0):
@@ -29,6 +31,7 @@ def test_attention_shares_no_scratch(cache, monkeypatch):
     calls = []
     monkeypatch.setattr(pbsa, "pbsa_attention_fwd_split", lambda *a, **k: calls.append(a))
     cache.adopt_chunk(0)
+    cache.adopt_chunk(1)
     for _ in range(2):
         cache.attention(chunk())
     ws = [a[12] for a in calls]
@@ -39,7 +42,7 @@ def test_attention_shares_no_scratch(cache, monkeypatch):
             assert not any(overlap(w, t) for w in ws), name
 
 
-CALLS = ("pbsa_append_chunk", "pbsa_select_blocks", "pbsa_attention_fwd_split", "pbsa_attention_fwd_plan",
+CALLS = ("pbsa_append_chunk", "pbsa_select_blocks", "pbsa_pool_blocks", "pbsa_attention_fwd", "pbsa_attention_fwd_split", "pbsa_attention_fwd_plan",
          "pbsa_attention_fwd_mass", "pbsa_attention_bwd", "pbsa_memory_update", "pbsa_memory_update_apply",
          "pbsa_memory_update_fine")
 
@@ -276,14 +279,50 @@ def test_a_saved_cache_goes_on(cache, monkeypatch):
     cache.append_chunk(chunk(0), chunk(1), 0)
     cache._bwd_ws = cache._mass_ws = torch.empty(16, dtype=torch.uint8)
     old = copy.copy(cache)
-    old.__dict__ = {k: v for k, v in vars(cache).items() if k not in ("_full", "_by_launch", "_attn_bytes")}
+    old.__dict__ = {k: v for k, v in vars(cache).items() if k not in ("_full", "_by_launch", "_attn_bytes", "_installed", "_pays")}
     for c in (pickle.loads(pickle.dumps(cache)), copy.deepcopy(cache), pickle.loads(pickle.dumps(old))):
         assert c.chunk_ids == [0] and c._attn_bytes == cache._attn_bytes > 0
         assert not hasattr(c, "_bwd_ws") and not hasattr(c, "_mass_ws")
         del calls[:]
-        c.attention(chunk(3))
         c.append_chunk(chunk(0), chunk(1), 1)
+        c.attention(chunk(3))
         c.attention_bwd(chunk(3), chunk(3), chunk(3), torch.zeros(H, NQ))
-        assert [n for n, _ in calls] == ["pbsa_attention_fwd_split", "pbsa_append_chunk", "pbsa_attention_bwd"]
+        assert [n for n, _ in calls] == ["pbsa_append_chunk", "pbsa_attention_fwd_split", "pbsa_attention_bwd"]
         need = pbsa.pbsa_bwd_workspace_bytes(c.params())
-        assert calls[-1][1][-1].numel() == need and calls[0][1][-1].numel() == c._attn_bytes
+        assert calls[-1][1][-1].numel() == need and calls[1][1][-1].numel() == c._attn_bytes
+
+
+def test_no_split_for_what_is_not_there_yet(monkeypatch):
+    """64 slots and a selection of one block: nothing to share out until blocks have been installed in the slots or have left
+    the window for them; attention, attention with decisions and attention with mass agree at every chunk."""
+    calls = record(monkeypatch)
+    make = lambda: PbsaCache(H, D, B, 512, 1, 64, 1, D ** -0.5, device="cpu")
+    x = torch.zeros(H, 512, D, dtype=torch.bfloat16)
+
+    def splits(c):
+        del calls[:]
+        c.select(x)
+        c.attention(x)
+        c.attention_with_mass(x)
+        c.attention_with_plan(x)
+        (plain, a), (_, m), (_, f) = [(n, a) for n, a in calls if n.startswith("pbsa_attention")]
+        split = plain == "pbsa_attention_fwd_split"
+        assert not split or a[-1].numel() == c._attn_bytes
+        need = pbsa.pbsa_mass_workspace_bytes(m[0]), pbsa.pbsa_workspace_bytes(f[0])
+        room = [w[1] if isinstance(w, tuple) else w.numel() for w in (m[-1], f[-1])]
+        assert [r >= n + c._attn_bytes for r, n in zip(room, need)] == [split, split] and (split or room == list(need))
+        c.update_apply()
+        return split
+
+    c = make()
+    assert c._attn_bytes > 0
+    seen = []
+    for g in range(12):
+        c.append_chunk(x, x, g)
+        seen.append(splits(c))
+    assert seen == sorted(seen) and not any(seen[:3]) and seen[-1]      # from some chunk on, once 8 blocks a chunk have left
+    c = make()
+    c.set_persistent(torch.zeros(H, 64, B, D, dtype=torch.bfloat16), torch.zeros(H, 64, B, D, dtype=torch.bfloat16),
+                     torch.full((H, 64), B, dtype=torch.int32), torch.arange(64)[None].repeat(H, 1))
+    c.append_chunk(x, x, 0)
+    assert splits(c)

@@ -36,7 +36,7 @@ def test_split_matches_whole(H, d, B, Nq, w, C, k, causal):
         c.set_persistent(2.0 * rnd(H, C, B, d), rnd(H, C, B, d), lens, torch.arange(C)[None].repeat(H, 1))
     Q = rnd(H, Nq, d)
     c.select(Q)
-    assert c._attn_bytes > 0, "this shape is meant to be split"
+    assert c._attn_bytes > 0 and c._split_pays(), "this shape is meant to be split"
     lse, lse_w = (torch.empty(H, Nq, device=DEV) for _ in range(2))
     O = c.attention(Q, lse=lse)
     l_map, l_len, _ = c._device_maps()
@@ -108,6 +108,7 @@ def test_attention_from_two_streams():
         c.append_chunk(K, V, g)
     Qs = [chunks[0][0], chunks[1][0]]
     c.select(Qs[0])
+    assert c._split_pays()
     want = [c.attention(Q) for Q in Qs]
     O = [torch.empty_like(Q) for Q in Qs]
     streams = [torch.cuda.Stream() for _ in Qs]
