@@ -1,10 +1,12 @@
-"""The attention launch whose last round of workgroups is shared out over the keys, against the same call without scratch
-(every query tile walked whole): parts with no tile of a class, ragged and empty slots, rows without keys, whole rounds
-ahead of the split one.
+"""The attention launch whose last round of workgroups is shared out over the keys, and the same call with every query tile
+walked whole, against fp64: parts with no tile of a class, ragged and empty slots, rows without keys, whole rounds ahead of
+the split one.
 
-Bound: both sides round every probability to bf16 (2^-9 relative, in numerator and normaliser alike) relative to
-references that differ, so an output differs by at most 2 (2^-9 + 2^-9) max|V| before it is rounded to bf16 itself
-(2^-9 |O| <= 2^-9 max|V| on either side): 3 * 2^-8 max|V|; lse by twice -log(1 - 2^-9)."""
+Bound, for both: a probability p_j is rounded to bf16 (8 bits of significand), (1 + e_j) p_j with |e_j| <= 2^-8 and, over many
+keys, e_j independent with root mean square at most 2^-8 / sqrt(3); the normaliser is the sum of the rounded ones.  To first
+order O is then off by sum_j p_j e_j (v_j - O), of standard deviation 2^-8 / sqrt(3) sqrt(sum_j p_j^2 (v_j - O)^2), and lse by
+sum_j p_j e_j.  Eight standard deviations (|e_j| <= sqrt(3) of one, so a row of one key is inside too), 2^-8 |O| for O's own
+rounding, and fp32: 1e-5 of the largest |v|, 2e-5 (1 + |lse|)."""
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -13,18 +15,49 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-@pytest.mark.parametrize("H,d,B,Nq,w,C,k,causal", [
-    (2, 64, 64, 256, 3, 2, 12, 1),         # more parts than most classes have tiles
-    (1, 128, 128, 300, 0, 30, 1, 1),       # nearly everything persistent
-    (3, 128, 64, 1000, 2, 5, 17, 1),       # two query blocks per workgroup: solo tiles
-    (3, 64, 64, 999, 1, 0, 20, 0),         # no slots but the (empty) summary
-    (5, 64, 128, 1000, 3, 5, 7, 0),
-    (1, 64, 64, 640, 1, 40, 0, 1),         # nothing selected
-    (40, 64, 64, 1664, 1, 3, 9, 1),        # 520 query tiles: 512 whole, 8 split
+def exact_rows(c, Q, h, i, lens, sel, l_map, l_len):
+    """Query block i of head h in fp64: O, lse, the standard deviations of both (see above), and (key block, mass) pairs."""
+    rows, u = [], []
+    for slot in range(c.C + 1):
+        rows.append((c.Kp[h, slot, :lens[h][slot]], c.Vp[h, slot, :lens[h][slot]]))
+        u.append(slot)
+    for l in sel[h][i][:c.k]:
+        if l >= 0:
+            rows.append((c.Kl[h, l_map[l], :l_len[l]], c.Vl[h, l_map[l], :l_len[l]]))
+            u.append(c.C + 1 + l)
+    K, V = (torch.cat([r[n] for r in rows]).double() for n in (0, 1))
+    q = Q[h, i * c.B:(i + 1) * c.B].double()
+    if K.shape[0] == 0:
+        zero = torch.zeros(q.shape[0], dtype=torch.float64, device=DEV)
+        return torch.zeros_like(q), zero - float("inf"), torch.zeros_like(q), zero, []
+    z = torch.mm(q, K.t().contiguous()) * c.scale
+    lse = torch.logsumexp(z, 1)
+    P = torch.exp(z - lse[:, None])
+    O = torch.mm(P, V)
+    P2 = P * P
+    var = torch.mm(P2, V * V) - 2 * O * torch.mm(P2, V) + O * O * P2.sum(1, keepdim=True)
+    e = 2.0 ** -8 / 3 ** 0.5
+    at, mass = 0, []
+    for n, (k_rows, _) in zip(u, rows):
+        mass.append((n, float(P[:, at:at + k_rows.shape[0]].sum())))
+        at += k_rows.shape[0]
+    return O, lse, e * var.clamp_min(0).sqrt(), e * P2.sum(1).sqrt(), mass
+
+
+@pytest.mark.parametrize("H,d,B,Nq,w,C,k,causal,empty", [
+    (2, 64, 64, 256, 3, 2, 12, 1, False),  # more parts than most classes have tiles
+    (1, 128, 128, 300, 0, 30, 1, 1, False),  # nearly everything persistent
+    (3, 128, 64, 1000, 2, 5, 17, 1, False),  # two query blocks per workgroup: solo tiles
+    (3, 64, 64, 999, 1, 0, 20, 0, False),  # no slots but the (empty) summary
+    (5, 64, 128, 1000, 3, 5, 7, 0, False),
+    (2, 64, 64, 640, 1, 40, 0, 1, True),   # nothing selected, and a head whose slots are empty: rows without keys
+    (3, 128, 128, 300, 1, 40, 0, 1, True),
+    (40, 64, 64, 1664, 1, 3, 9, 1, False),   # 520 query tiles: 512 whole, 8 split
 ])
-def test_split_matches_whole(H, d, B, Nq, w, C, k, causal):
+def test_split_and_whole_match_fp64(H, d, B, Nq, w, C, k, causal, empty):
     from paper_2604_21221_amd import pbsa
     from paper_2604_21221_amd.cache import PbsaCache
+    from tests.test_gpu_parity_fine_mass import MASS_ATOL, MASS_RTOL
     gen = torch.Generator(device=DEV).manual_seed(H + d + Nq)
     rnd = lambda *s: torch.randn(*s, generator=gen, device=DEV).to(torch.bfloat16)
     c = PbsaCache(H, d, B, Nq, w, C, k, d ** -0.5, causal=causal, device=DEV)
@@ -33,23 +66,48 @@ def test_split_matches_whole(H, d, B, Nq, w, C, k, causal):
         c.append_chunk(2.0 * rnd(H, Nq, d), rnd(H, Nq, d), g)
     if C:
         lens = torch.randint(0, B + 1, (H, C), generator=gen, device=DEV, dtype=torch.int32)
+        if empty:
+            lens[0] = 0
         c.set_persistent(2.0 * rnd(H, C, B, d), rnd(H, C, B, d), lens, torch.arange(C)[None].repeat(H, 1))
     Q = rnd(H, Nq, d)
     c.select(Q)
     assert c._attn_bytes > 0 and c._split_pays(), "this shape is meant to be split"
-    lse, lse_w = (torch.empty(H, Nq, device=DEV) for _ in range(2))
-    O = c.attention(Q, lse=lse)
     l_map, l_len, _ = c._device_maps()
+    lse, lse_w, lse_m, lse_mw = (torch.empty(H, Nq, device=DEV) for _ in range(4))
+    O = c.attention(Q, lse=lse)
     O_w = torch.empty_like(Q)
-    pbsa.pbsa_attention_fwd(c.params(Q=Q, O=O_w), Q, c.Kp, c.Vp, c.p_len, c.Kl, c.Vl, l_len, l_map, c.sel, O_w, lse_w)
-    fin = torch.isfinite(lse_w)
-    assert torch.equal(torch.isfinite(lse), fin) and torch.equal(lse[~fin], lse_w[~fin])
-    assert float((lse - lse_w)[fin].abs().max() if fin.any() else 0.0) <= 2 * 1.96e-3
+    args = Q, c.Kp, c.Vp, c.p_len, c.Kl, c.Vl, l_len, l_map, c.sel
+    pbsa.pbsa_attention_fwd(c.params(Q=Q, O=O_w), *args, O_w, lse_w)
+    assert not torch.equal(O, O_w) or empty, "not split after all"
+    # the variant that records the mass takes the same parts, or none
+    O_m, Mt = c.attention_with_mass(Q, lse=lse_m)
+    O_mw, Mt_w = torch.empty_like(Q), torch.empty_like(Mt)
+    p = c.params(Q=Q, O=O_mw)
+    pbsa.pbsa_attention_fwd_mass(p, *args, O_mw, lse_mw, Mt_w, (c._mass_ws.data_ptr(), pbsa.pbsa_mass_workspace_bytes(p)))
+    for a, b in ((O, O_m), (O_w, O_mw)):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+    assert torch.equal(lse, lse_m) and torch.equal(lse_w, lse_mw)
+    host = c.p_len.tolist(), c.sel.tolist(), l_map.tolist(), l_len.tolist()
     v_max = max(float(c.Vl.abs().max()), float(c.Vp.abs().max()))
-    assert float((O.float() - O_w.float()).abs().max()) <= 3 * 2.0 ** -8 * v_max
-    # the variant that records the mass takes the same parts
-    O_m, _ = c.attention_with_mass(Q)
-    assert torch.equal(O_m.view(torch.int16), O.view(torch.int16))
+    no_key, worst = 0, {}
+    for h in sorted({0, 1, H // 2, H - 2, H - 1} & set(range(H))):
+        for i in range(c.nqb):
+            want, want_lse, sd, sd_lse, mass = exact_rows(c, Q, h, i, *host)
+            at = slice(i * B, min((i + 1) * B, Nq))
+            for name, o, l, M in (("split", O, lse, Mt), ("whole", O_w, lse_w, Mt_w)):
+                if not mass:
+                    assert not o[h, at].any() and bool((l[h, at] == float("-inf")).all())
+                    no_key += 1
+                    continue
+                off = (o[h, at].double() - want).abs() / (8 * sd + 2.0 ** -8 * want.abs() + 1e-5 * v_max)
+                off_lse = (l[h, at].double() - want_lse).abs() / (8 * sd_lse + 2e-5 * (1 + want_lse.abs()))
+                worst[name] = max(worst.get(name, 0.0), float(off.max()), float(off_lse.max()))
+                got = M[h, :, i].tolist()
+                for u, m in mass:
+                    assert abs(got[u] - m) <= MASS_RTOL * m + MASS_ATOL, (name, h, i, u)
+    print(f"[case] worst error over its bound: {worst}", flush=True)
+    assert all(v <= 1.0 for v in worst.values())
+    assert (no_key > 0) == empty
 
 
 def _cache_and_chunks(n, H=5, d=64, B=128, Nq=1000, w=1, C=5, k=7):

@@ -3,11 +3,11 @@
 Bar (floating point, no integer decisions): for each of dQ, dK, dV the error against the fp64 oracle is bounded,
 element by element, relative to the size of the tensor's entries: max-abs <= GRAD_MAX * max|ref| and mean-abs <=
 GRAD_MEAN * mean|ref|.  The kernel's roundings: P = exp(z - lse) inherits the forward's lse (within 4e-3 of exact,
-so every probability of a row is off by the same factor up to 4e-3), P and dZ are rounded to bf16 (2^-9 relative)
-before the second products, D = dO . O uses the forward's bf16 O; sums are fp32.  A gradient entry is a sum of
+so every probability of a row is off by the same factor up to 4e-3), P and dZ are rounded to bf16 (2^-8 relative
+at most) before the second products, D = dO . O uses the forward's bf16 O; sums are fp32.  A gradient entry is a sum of
 hundreds to thousands of such terms with mixed signs, so the systematic part (the lse factor, <= 4e-3 of the
 entry's scale) plus the bf16 rounding (2e-3) bounds the mean at 6e-3 of the mean entry, and the max is allowed 1e-2
-of the largest entry (worst seen: 5.7e-3 and 4.3e-3).
+of the largest entry (worst seen: 6.4e-3 and 4.2e-3).
 """
 import math
 
