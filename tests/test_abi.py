@@ -267,6 +267,30 @@ def test_attention_with_plan_argument_checks(L):
         assert e.value.code == code, kw
 
 
+def test_append_argument_checks(L):
+    """pbsa_append_chunk: the slot range is what keeps it inside the ring."""
+    p = good()                               # 4 blocks per chunk, 16 slots
+    dense = (200 * 128, 128)
+
+    def append(p=p, K=P, V=P, ks=dense, vs=dense, slot0=0, Kl=P, Vl=P, Kc_l=P):
+        rc = L.pbsa_append_chunk(ctypes.byref(p), K, V, *ks, *vs, slot0, 1, Kl, Vl, Kc_l, None)
+        assert rc != pbsa.PBSA_OK
+        return rc
+
+    for kw, code in [(dict(slot0=-1), pbsa.PBSA_EINVAL), (dict(slot0=13), pbsa.PBSA_EINVAL), (dict(slot0=2 ** 31 - 1), pbsa.PBSA_EINVAL),
+                     (dict(Kl=None), pbsa.PBSA_EINVAL), (dict(Vl=None), pbsa.PBSA_EINVAL),
+                     (dict(ks=(200 * 128, 120)), pbsa.PBSA_EINVAL), (dict(vs=(200 * 128, 120)), pbsa.PBSA_EINVAL),
+                     (dict(ks=(-128, 128)), pbsa.PBSA_EINVAL), (dict(ks=(200 * 132, 132)), pbsa.PBSA_EALIGN),
+                     (dict(vs=(200 * 128 + 4, 128)), pbsa.PBSA_EALIGN), (dict(K=P + 2), pbsa.PBSA_EALIGN),
+                     (dict(V=P + 8), pbsa.PBSA_EALIGN), (dict(Kl=P + 8), pbsa.PBSA_EALIGN), (dict(Vl=P + 8), pbsa.PBSA_EALIGN),
+                     (dict(Kc_l=P + 4), pbsa.PBSA_EALIGN), (dict(p=good(d=96)), pbsa.PBSA_ESHAPE),
+                     (dict(p=good(B=32)), pbsa.PBSA_ESHAPE), (dict(p=good(n_loc=2)), pbsa.PBSA_EINVAL)]:
+        assert append(**kw) == code, kw
+    # neither tensor: nothing to do, and nothing is looked at but the parameters and the slot
+    for slot0, code in ((0, pbsa.PBSA_OK), (12, pbsa.PBSA_OK), (13, pbsa.PBSA_EINVAL)):
+        assert L.pbsa_append_chunk(ctypes.byref(p), None, None, 0, 0, 0, 0, slot0, 1, None, None, None, None) == code
+
+
 def test_split_attention_argument_checks(L):
     """pbsa_attention_fwd_split validates like pbsa_attention_fwd and wants pbsa_attention_workspace_bytes."""
     p = good(k=12)                           # 4 query tiles of 17 key tiles each: shared out

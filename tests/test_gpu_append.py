@@ -91,3 +91,33 @@ def test_an_append_while_another_device_is_current(monkeypatch):
         c.append_chunk(K, V, 0)
     rows = [t[:, :c.nqb].view(2, c.nqb * 64, 64)[:, :200] for t in (c.Kl, c.Vl)]
     assert not calls and torch.equal(rows[0], K) and torch.equal(rows[1], V)
+
+
+def test_chunks_that_go_through_torch():
+    """Tensors that the launch does not take as they are (fp32, rows at an odd address, spread over the heads) end as the same
+    rows, pooled keys, selection and output as their dense bf16 copies; so does V rewritten alone."""
+    from paper_2604_21221_amd.cache import PbsaCache
+    H, d, B, Nq = 3, 128, 64, 333
+    gen = torch.Generator(device=DEV).manual_seed(17)
+    rnd = lambda *s: torch.randn(*s, generator=gen, device=DEV).to(torch.bfloat16)
+    odd = rnd(H * Nq * d + 1)[1:].view(H, Nq, d)
+    forms = {"fp32": rnd(H, Nq, d).float(), "odd address": odd, "one head for all": rnd(1, Nq, d)}
+    assert odd.data_ptr() % 16 == 2
+    for name, x in forms.items():
+        print(f"[case] append through torch: {name}", flush=True)
+        dense = x.to(torch.bfloat16).expand(H, Nq, d).clone()
+        V, V2, Q = rnd(H, Nq, d), rnd(H, Nq, d), rnd(H, Nq, d)
+        got = []
+        for K in (x, dense):
+            c = PbsaCache(H, d, B, Nq, 1, 2, 3, d ** -0.5, device=DEV)
+            O = c.step(Q, K, V, 0)
+            c.append_chunk(V, K, 1)
+            c.select(Q)
+            first = c.Kc_l.clone()
+            c.rewrite_chunk(V=V2)
+            c.select(Q)
+            assert torch.equal(first, c.Kc_l), "V alone changed the pooled keys"
+            got.append((O, c.Kl, c.Vl, c.Kc_l, c.sel, c.attention(Q)))
+        assert all(torch.equal(a, b) for a, b in zip(*got))
+        rows = got[0][2][:, c.nqb:].view(H, c.nqb * B, d)
+        assert torch.equal(rows[:, :Nq], V2) and not rows[:, Nq:].any()
