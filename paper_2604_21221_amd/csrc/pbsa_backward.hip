@@ -19,11 +19,10 @@
 //   second products are transposing LDS reads of the streamed tiles with the same enumeration:
 //          dq:  dQ^T += K^T dZ^T          dkv: dK^T += Q^T dZ,  dV^T += dO^T P
 // Tiles go from global memory straight to LDS (global_load_lds), half a tile (32 streamed rows) per ring entry; the
-// 16-byte chunks of a row are permuted by the row number so that the row-wise operand reads are
-// free of bank conflicts and a transposing one has two cycles of them (a permutation without any changed no time).  Rows past a tile's valid length are never loaded: their lanes fetch the last
-// valid row, and a -inf in the place of its score or its lse makes their P an exact zero.  dq holds 64 fixed rows per wave, so every
-// fragment read from LDS feeds two MFMAs; dkv cannot at d = 128 (two outputs: 256 accumulator registers for 64
-// keys) and holds 32 per wave: it reads one fragment per MFMA.
+// 16-byte chunks of a row are permuted by the row number (swz).  Rows past a tile's valid length are never loaded: their
+// lanes fetch the last valid row, and a -inf in the place of its score or its lse makes their P an exact zero.  dq holds 64
+// fixed rows per wave, so every fragment read from LDS feeds two MFMAs; dkv cannot at d = 128 (two outputs: 256
+// accumulator registers for 64 keys) and holds 32 per wave: it reads one fragment per MFMA.
 #include <type_traits>
 
 #include "pbsa_internal.h"
@@ -89,17 +88,16 @@ __device__ __forceinline__ void dma4(const void* base, uint32_t lane_off, uint32
                : "memory", "m0");
 }
 
-template <int LDS_IMM>
-__device__ __forceinline__ void dma16x4(const void* base, uint32_t o0, uint32_t o1, uint32_t o2, uint32_t o3, uint32_t lds_base) {
+__device__ __forceinline__ void dma16x4(const void* base, uint32_t o0, uint32_t o1, uint32_t o2, uint32_t o3, uint32_t lds_off) {
   // four loads 1 KiB apart in LDS and in memory alike: the instruction's offset moves both addresses
-  asm volatile("s_add_u32 m0, %0, %6\n\ts_nop 0\n\t"
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
                "global_load_lds_dwordx4 %1, %5\n\t"
                "global_load_lds_dwordx4 %2, %5 offset:1024\n\t"
                "global_load_lds_dwordx4 %3, %5 offset:2048\n\t"
                "global_load_lds_dwordx4 %4, %5 offset:3072"
                :
-               : "s"(lds_base), "v"(o0), "v"(o1), "v"(o2), "v"(o3), "s"(base), "n"(LDS_IMM)
-               : "memory", "scc", "m0");
+               : "s"(lds_off), "v"(o0), "v"(o1), "v"(o2), "v"(o3), "s"(base)
+               : "memory", "m0");
 }
 __device__ __forceinline__ void dma16x2(const void* base, uint32_t o0, uint32_t o1, uint32_t lds_off) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
@@ -110,10 +108,13 @@ __device__ __forceinline__ void dma16x2(const void* base, uint32_t o0, uint32_t 
                : "memory", "m0");
 }
 
-// Where the 16-byte chunks of a tile row sit in LDS: logical chunk c of row r at chunk c ^ swz(r).  The row-wise
-// operand reads (16 consecutive rows, one logical chunk) need swz distinct over 16 consecutive rows (8 when a row
-// has 8 chunks); the transposing reads (4 consecutive rows from a multiple of 4, two adjacent chunks c, c + 1 with
-// c even, each) need swz(r) >> 1 distinct over those rows.  The row number rotated left by one bit does both.
+// Where the 16-byte chunks of a tile row sit in LDS: logical chunk c of row r at chunk c ^ swz(r), the row number rotated
+// left by one bit.  That is distinct over 16 consecutive rows (8 when a row has 8 chunks), which the row-wise operand reads
+// need (16 consecutive rows, one logical chunk).  The transposing reads go through the banks 32 lanes at a time, four
+// consecutive rows with four adjacent chunks each, and would need swz(r) >> 2 distinct over those rows; at d = 128 rows 0
+// and 1 share theirs, and rows 2 and 3: two conflict cycles per read, by the counters the only ones (a permutation without
+// them measured 0.998 to 1.004 of the time: not taken).  At d = 64, where a row is half a pass over the banks, the counters
+// say 4.1 cycles per pair of a row-wise and a transposing read (3 heads x 1500 rows).
 template <int CH>
 __device__ __forceinline__ int swz(int r) {
   if constexpr (CH == 16) return ((r & 7) << 1) | ((r >> 3) & 1);
@@ -124,18 +125,8 @@ typedef __attribute__((address_space(3))) const bf16x8* lds_b128_t;
 typedef __attribute__((address_space(3))) bf16x4* lds_tr_t;
 typedef __attribute__((address_space(3))) const f32x4* lds_f4_t;
 __device__ __forceinline__ bf16x8 lds_read_row(uint32_t addr) { return *(lds_b128_t)(uintptr_t)addr; }
-// transposed fragment of 16 streamed rows: two transposing reads, rows r and r + 8 of the 16.  HI_XOR: what the
-// row permutation does to the byte address when the row goes up by 8.
-// off: this lane's byte offset inside the tile (the permutation acts on it), base: LDS address of the tile plus a
-// whole number of 16-row groups.
-template <int ROW, int HI_XOR>
-__device__ __forceinline__ bf16x8 lds_read_tr(uint32_t base, uint32_t off) {
-  const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_tr_t)(uintptr_t)(base + off));
-  const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_tr_t)(uintptr_t)(base + (off ^ HI_XOR) + 8 * ROW));
-  return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-}
-// the same from the two addresses
-__device__ __forceinline__ bf16x8 lds_read_tr2(uint32_t at_lo, uint32_t at_hi) {
+// transposed fragment of 16 streamed rows: two transposing reads, of rows r and r + 8 of the 16
+__device__ __forceinline__ bf16x8 lds_read_tr(uint32_t at_lo, uint32_t at_hi) {
   const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_tr_t)(uintptr_t)at_lo);
   const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_tr_t)(uintptr_t)at_hi);
   return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
@@ -433,8 +424,8 @@ __global__ void __launch_bounds__(kThreads) bwd_dkv_kernel(BwdArgs a) {
       s1 += (size_t)(32 * mg) * st1;
       s2 += (size_t)(32 * mg) * st2;
       if constexpr (NH == 4) {
-        dma16x4<0>(s1, so1[0], so1[1], so1[2], so1[3], dst);
-        dma16x4<0>(s2, so2[0], so2[1], so2[2], so2[3], dst + HALF);
+        dma16x4(s1, so1[0], so1[1], so1[2], so1[3], dst);
+        dma16x4(s2, so2[0], so2[1], so2[2], so2[3], dst + HALF);
       } else {
         dma16x2(s1, so1[0], so1[1], dst);
         dma16x2(s2, so2[0], so2[1], dst + HALF);
@@ -547,7 +538,7 @@ __global__ void __launch_bounds__(kThreads) bwd_dkv_kernel(BwdArgs a) {
         for (int q = 0; q < 2; ++q) {
           const int i = 2 * (sl - NS / 4) + q, tensor = i / (2 * DT), j = (i / DT) % 2, dt = i % DT;
           const uint32_t at = (uint32_t)(mg * TILE + tensor * HALF + 16 * j * ROW);
-          tf[i] = lds_read_tr2(tl[dt] + at, th[dt] + at);
+          tf[i] = lds_read_tr(tl[dt] + at, th[dt] + at);
         }
       }
 #pragma unroll
@@ -644,7 +635,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1)))
   constexpr int CH = D / 8, RPI = 64 / CH;          // 16-byte chunks per row, rows per load instruction
   constexpr int NW = (32 / RPI) / 4;                // windows of four load instructions per tensor and half tile: 2 or 1
   constexpr int HI_XOR = CH == 16 ? 16 : 0;
-  constexpr int NS = 2 * KS, EPS = 16 / NS;         // slices behind the first products, elements per slice
+  constexpr int NS = 2 * KS;                        // slices behind the first products
   extern __shared__ __align__(1024) unsigned char smem[];
   // ring: entry e holds 32 rows of K at e * TILE and 32 rows of V behind them
   int* lst_a = reinterpret_cast<int*>(smem + 2 * TILE);
@@ -776,8 +767,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1)))
     if (last >= 32 * mg + 31) {
 #pragma unroll
       for (int w = 0; w < NW; ++w) {
-        dma16x4<0>(s1 + 32 * mg * ROW + w * 4096, so[0], so[1], so[2], so[3], dst + w * 4096);
-        dma16x4<0>(s2 + 32 * mg * ROW + w * 4096, so[0], so[1], so[2], so[3], dst + HALF + w * 4096);
+        dma16x4(s1 + 32 * mg * ROW + w * 4096, so[0], so[1], so[2], so[3], dst + w * 4096);
+        dma16x4(s2 + 32 * mg * ROW + w * 4096, so[0], so[1], so[2], so[3], dst + HALF + w * 4096);
       }
     } else {                               // rows past the last one that exists are not touched: that row again
 #pragma unroll
@@ -904,7 +895,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1)))
           for (int r = 0; r < 2; ++r) {
             const int i = 2 * (sl - NS / 4) + r;
             const uint32_t at = at0 + (uint32_t)(16 * (i / DT) * ROW);
-            tf[i] = lds_read_tr2(tl[i % DT] + at, th[i % DT] + at);
+            tf[i] = lds_read_tr(tl[i % DT] + at, th[i % DT] + at);
           }
         }
       });

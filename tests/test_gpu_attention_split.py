@@ -87,6 +87,10 @@ def test_split_and_whole_match_fp64(H, d, B, Nq, w, C, k, causal, empty):
     for a, b in ((O, O_m), (O_w, O_mw)):
         assert torch.equal(a.view(torch.int16), b.view(torch.int16))
     assert torch.equal(lse, lse_m) and torch.equal(lse_w, lse_mw)
+    # and so does the one that takes the update's decisions
+    lse_p = torch.empty_like(lse)
+    O_p = c.attention_with_plan(Q, lse=lse_p)
+    assert torch.equal(O_p.view(torch.int16), O.view(torch.int16)) and torch.equal(lse_p, lse)
     host = c.p_len.tolist(), c.sel.tolist(), l_map.tolist(), l_len.tolist()
     v_max = max(float(c.Vl.abs().max()), float(c.Vp.abs().max()))
     no_key, worst = 0, {}
