@@ -1307,7 +1307,7 @@ __global__ void __launch_bounds__(kCombineThreads) combine_kernel(AttnArgs a) {
 // of n query tiles lasts ceil(n / kPlaces) rounds and its last round may be nearly empty: a chunk of 5 heads x 1000 rows
 // is 40 workgroups on 512 places.  The tiles of that last round are split over as many workgroups as it has places for,
 // as long as a shorter walk gains more than the second launch and the partial results cost.  Depends on the shape
-// alone, so that every call of a shape -- with decisions, with mass, plain -- takes the same parts.
+// alone, so that every call of a shape that is given the scratch -- with decisions, with mass, neither -- takes the same parts.
 AttnSplit attn_split(const pbsa_params& p) {
   constexpr int kPlaces = 512;
   AttnSplit sp{0, 1, 0, 0, 0};

@@ -113,7 +113,7 @@ __global__ void __launch_bounds__(kThreads) pool_kernel(PoolArgs a) {
 // blocks (Eq. 6) from the rows as they pass.  One workgroup = one block of K or of V; a thread moves 16 bytes per
 // sweep, all sweeps in flight together.  For K the rows also go to LDS, where D / 2 threads add them in ascending
 // order (the pinned order of the pooling), two dimensions each: 64 consecutive words per row, free of bank conflicts.
-// Bound by HBM: each byte is read once and written once, and the selection that follows does not read K again: 11.1 us
+// Bound by HBM: each byte is read once and written once, and a selection that follows need not read K again: 11.1 us
 // for a chunk of 12 x 4680 x 128 (57.5 MB moved, 5.2 TB/s), where four tensor copies took 27 us and the selection's
 // own pooling launch another 8.7.
 // ------------------------------------------------------------------------------------------------
