@@ -183,3 +183,30 @@ def test_attention_from_two_streams():
                     c.attention(Q, o)
         torch.cuda.synchronize()
         assert all(torch.equal(o, w) for o, w in zip(O, want)), r
+
+
+def test_split_attention_in_a_graph():
+    """Captured, with its scratch from the graph's own memory: every replay gives what the eager call gives, with eager calls
+    on the same cache in between and two graphs of one capture stream."""
+    c, chunks = _cache_and_chunks(2, C=30, k=16)
+    for g, (_, K, V) in enumerate(chunks):
+        c.append_chunk(K, V, g)
+    Q, other = chunks[0][0].clone(), chunks[1][0]
+    O = [torch.empty_like(Q) for _ in range(2)]
+    c.select(Q)
+    assert c._split_pays()
+    c.attention(Q, O[0])
+    torch.cuda.synchronize()
+    print("[case] split attention in a graph", flush=True)
+    graphs = [torch.cuda.CUDAGraph() for _ in O]
+    for g, o in zip(graphs, O):
+        with torch.cuda.graph(g):
+            c.attention(Q, o)
+    for r in range(4):
+        Q.copy_(chunks[r % 2][r % 3])
+        for g in graphs:
+            g.replay()
+        eager = c.attention(other)
+        torch.cuda.synchronize()
+        want = c.attention(Q)
+        assert torch.equal(O[0], want) and torch.equal(O[1], want) and torch.equal(eager, c.attention(other)), r
