@@ -83,7 +83,7 @@ extern "C" {
 #define PBSA_MAX_C_ATTEND 336 /* persistent slots that pbsa_attention_fwd can attend (pbsa_select_blocks does not
                                * look at them); above PBSA_MAX_C the caller maintains the set itself */
 /* Limits of every other entry point (the memory update in all its forms, pbsa_select_blocks_apply,
- * pbsa_attention_fwd_plan, pbsa_attention_fwd_mass, pbsa_attention_mass, pbsa_attention_bwd): */
+ * pbsa_attention_fwd_plan, pbsa_attention_fwd_mass, their _split forms, pbsa_attention_mass, pbsa_attention_bwd): */
 #define PBSA_MAX_N_LOC_AUX 512
 #define PBSA_MAX_K_AUX     512
 #define PBSA_MAX_C_AUX     192 /* slots attended, where the call attends                      */
@@ -167,8 +167,7 @@ int pbsa_attention_fwd(const pbsa_params* p, const void* Q, const void* Kp, cons
  * another order of summation, decided by p alone.  ws: pbsa_attention_workspace_bytes(p) bytes (0 where nothing is
  * shared out; ws may be NULL then), 256-byte aligned, contents not kept.  It is written: it must not overlap a
  * workspace that holds a plan still to be applied (pbsa_memory_update_plan, pbsa_attention_fwd_plan), nor the ws of a
- * call that may run at the same time.  pbsa_attention_fwd_plan and pbsa_attention_fwd_mass share out in the same way
- * when the workspace they take is that much larger than they need (the share lies behind their own part). */
+ * call that may run at the same time. */
 int pbsa_attention_workspace_bytes(const pbsa_params* p, size_t* out);
 int pbsa_attention_fwd_split(const pbsa_params* p, const void* Q, const void* Kp, const void* Vp, const int32_t* p_len,
                              const void* Kl, const void* Vl, const int32_t* l_len, const int32_t* l_map,
@@ -241,17 +240,23 @@ int pbsa_select_blocks_apply(const pbsa_params* p, const void* Q, const void* Kl
 /* pbsa_attention_fwd and pbsa_memory_update_plan of the same chunk as ONE launch (Alg. 1 with the update's
  * decisions, Eq. 7-9, taken while the fine stage of Eq. 3-5 runs): the attention's grid gets H more workgroups, one
  * per head, that do the plan call's work.  Nothing they read is written by the attention part and the other way
- * round, so the results are those of the two calls, bit for bit (with the share of pbsa_attention_workspace_bytes(p)
- * behind the workspace: those of pbsa_attention_fwd_split); a launch whose attention workgroups do not fill
+ * round, so the results are those of the two calls, bit for bit; a launch whose attention workgroups do not fill
  * the GPU (two workgroups of 128 query rows per compute unit) has the plan's work for free.  Arguments: those of
  * pbsa_attention_fwd (p->C <= PBSA_MAX_C here), then those of pbsa_memory_update_plan that it does not have yet;
  * Zl is required (PBSA_EINVAL without), ws as for pbsa_memory_update.  pbsa_memory_update_apply completes the
- * update. */
+ * update.  pbsa_attention_fwd_plan_split: the same with the attention as pbsa_attention_fwd_split does it; split_ws is
+ * that call's ws, apart from the plan's. */
 int pbsa_attention_fwd_plan(const pbsa_params* p, const void* Q, const void* Kp, const void* Vp, const int32_t* p_len,
                             const void* Kl, const void* Vl, const int32_t* l_len, const int32_t* l_map,
                             const int32_t* sel, void* O, float* lse, const float* Qc, const float* Kc_l,
                             const float* Zl, float* Kc_p, int64_t* p_id, int32_t* S_cnt, const int64_t* l_id,
                             float* scores, int32_t* slot_src, void* ws, size_t ws_bytes, void* hip_stream);
+int pbsa_attention_fwd_plan_split(const pbsa_params* p, const void* Q, const void* Kp, const void* Vp, const int32_t* p_len,
+                                  const void* Kl, const void* Vl, const int32_t* l_len, const int32_t* l_map,
+                                  const int32_t* sel, void* O, float* lse, const float* Qc, const float* Kc_l,
+                                  const float* Zl, float* Kc_p, int64_t* p_id, int32_t* S_cnt, const int64_t* l_id,
+                                  float* scores, int32_t* slot_src, void* ws, size_t ws_bytes, void* split_ws,
+                                  size_t split_bytes, void* hip_stream);
 
 /* Attention mass per key block (the fine-grained counterpart of Eq. 7: the attention of Eq. 3-5 as it was
  * actually paid, mask included, summed block by block).  Key blocks are numbered u = slot for the persistent
@@ -273,12 +278,18 @@ int pbsa_attention_mass(const pbsa_params* p, const void* Q, const void* Kp, con
  * over pbsa_attention_fwd where pbsa_attention_mass repeats the whole first product.  O, lse (required here)
  * and every argument before them are those of pbsa_attention_fwd; the masses are those of the bf16-rounded
  * probabilities the second product used, so a query block's masses add up to its number of tokens to fp32
- * rounding.  ws: pbsa_mass_workspace_bytes(p) bytes of device scratch, 256-byte aligned, contents not kept. */
+ * rounding.  ws: pbsa_mass_workspace_bytes(p) bytes of device scratch, 256-byte aligned, contents not kept.
+ * pbsa_attention_fwd_mass_split: the same with the attention as pbsa_attention_fwd_split does it; split_ws is that
+ * call's ws, apart from the records'. */
 int pbsa_mass_workspace_bytes(const pbsa_params* p, size_t* out);
 int pbsa_attention_fwd_mass(const pbsa_params* p, const void* Q, const void* Kp, const void* Vp, const int32_t* p_len,
                             const void* Kl, const void* Vl, const int32_t* l_len, const int32_t* l_map,
                             const int32_t* sel, void* O, float* lse, float* Mt, void* ws, size_t ws_bytes,
                             void* hip_stream);
+int pbsa_attention_fwd_mass_split(const pbsa_params* p, const void* Q, const void* Kp, const void* Vp, const int32_t* p_len,
+                                  const void* Kl, const void* Vl, const int32_t* l_len, const int32_t* l_map,
+                                  const int32_t* sel, void* O, float* lse, float* Mt, void* ws, size_t ws_bytes,
+                                  void* split_ws, size_t split_bytes, void* hip_stream);
 
 /* pbsa_memory_update with the persistence score taken from the attention mass instead of Eq. 7-8's
  * block-level softmax: the score of key block u is its mass per query token,

@@ -45,9 +45,7 @@ class PbsaCache:
         self._derive()
         # with more slots than pbsa_memory_update maintains the cache can only be selected from and attended
         n_ws = pbsa.pbsa_workspace_bytes(self._full) if C <= pbsa.PBSA_MAX_C else 0
-        # attention_with_plan()'s split takes the share behind what the update needs; attention() changes nothing of the
-        # cache and may be called from several streams at a time, so its scratch is each call's own
-        self.ws = torch.empty(max(n_ws + self._attn_bytes, 256), dtype=torch.uint8, device=self.dev)
+        self.ws = torch.empty(max(n_ws, 256), dtype=torch.uint8, device=self.dev)
         self.chunk_pos = []          # ring position of each chunk in the local region, oldest first
         self.chunk_ids = []          # global chunk index of each
         self.n_appended = 0
@@ -75,6 +73,20 @@ class PbsaCache:
         self._attn_bytes = pbsa.pbsa_attention_workspace_bytes(full) if attends else 0
         self._pays = {}
 
+    def _split_ws(self):
+        """Scratch for the split of one attention call, or None: nothing is split."""
+        return torch.empty(self._attn_bytes, dtype=torch.uint8, device=self.dev) if self._attn_bytes and self._split_pays() else None
+
+    def _kept_split_ws(self, name):
+        """The same for a call that has a workspace of the cache's to itself anyway: kept beside that."""
+        if not (self._attn_bytes and self._split_pays()):
+            return None
+        ws = getattr(self, name, None)
+        if ws is None:
+            ws = torch.empty(self._attn_bytes, dtype=torch.uint8, device=self.dev)
+            setattr(self, name, ws)
+        return ws
+
     def _split_pays(self):
         """Whether an attention call is to split its last round.  The library's rule goes by the shape alone; on the first
         chunks of a roll-out, whose slots are empty, a query tile is two or three tiles of a walk long and the second launch
@@ -92,7 +104,7 @@ class PbsaCache:
         """A saved cache, also one saved before these were kept; scratch with nothing in it is made again when asked for."""
         self.__dict__.update(state)
         self.__dict__.setdefault("_installed", self.C)
-        for name in ("_bwd_ws", "_mass_ws"):
+        for name in ("_bwd_ws", "_mass_ws", "_mass_split_ws", "_plan_split_ws"):
             self.__dict__.pop(name, None)
         self._derive()
 
@@ -261,8 +273,10 @@ class PbsaCache:
         l_map, l_len, _ = self._device_maps()
         p = self.params(Q=Q, O=O)
         args = p, Q, self.Kp, self.Vp, self.p_len, self.Kl, self.Vl, l_len, l_map, self.sel, O, lse
-        if self._attn_bytes and self._split_pays():
-            pbsa.pbsa_attention_fwd_split(*args, torch.empty(self._attn_bytes, dtype=torch.uint8, device=self.dev))
+        # attention changes nothing of the cache and may be called from several streams at a time: scratch of its own
+        split_ws = self._split_ws()
+        if split_ws is not None:
+            pbsa.pbsa_attention_fwd_split(*args, split_ws)
         else:
             pbsa.pbsa_attention_fwd(*args)
         return O
@@ -321,15 +335,16 @@ class PbsaCache:
             lse = self._lse
         if getattr(self, "_mass_ws", None) is None:
             full = pbsa.make_params(self.H, self.d, self.B, self.Nq, self.cap, self.cap, self.C, self.k, self.scale)
-            self._mass_ws = torch.empty(pbsa.pbsa_mass_workspace_bytes(full) + self._attn_bytes, dtype=torch.uint8, device=self.dev)
+            self._mass_ws = torch.empty(pbsa.pbsa_mass_workspace_bytes(full), dtype=torch.uint8, device=self.dev)
         Mt = self._mass_buffer()
         l_map, l_len, _ = self._device_maps()
         p = self.params(Q=Q, O=O)
-        ws = self._mass_ws
-        if self._attn_bytes and not self._split_pays():
-            ws = ws.data_ptr(), pbsa.pbsa_mass_workspace_bytes(p)        # no room beyond what it needs: nothing is split
-        pbsa.pbsa_attention_fwd_mass(p, Q, self.Kp, self.Vp, self.p_len, self.Kl, self.Vl, l_len, l_map, self.sel, O,
-                                     lse, Mt, ws)
+        args = p, Q, self.Kp, self.Vp, self.p_len, self.Kl, self.Vl, l_len, l_map, self.sel, O, lse, Mt, self._mass_ws
+        split_ws = self._kept_split_ws("_mass_split_ws")
+        if split_ws is not None:
+            pbsa.pbsa_attention_fwd_mass_split(*args, split_ws)
+        else:
+            pbsa.pbsa_attention_fwd_mass(*args)
         return O, Mt
 
     def update_fine(self, Mt):
@@ -398,12 +413,13 @@ class PbsaCache:
             O = torch.empty_like(Q)
         l_map, l_len, l_id = self._device_maps(want_ids=True)
         self._plan_p = self.params(n_evict=self.n_evict_now(), Q=Q, O=O)
-        ws = self.ws
-        if self._attn_bytes and not self._split_pays():
-            ws = ws.data_ptr(), pbsa.pbsa_workspace_bytes(self._plan_p)  # no room beyond what it needs: nothing is split
-        pbsa.pbsa_attention_fwd_plan(self._plan_p, Q, self.Kp, self.Vp, self.p_len, self.Kl, self.Vl, l_len, l_map, self.sel,
-                                     O, lse, self.Qc, self.Kc_l, self.Zl, self.Kc_p, self.p_id, self.S_cnt, l_id,
-                                     self.scores, self.slot_src, ws)
+        args = (self._plan_p, Q, self.Kp, self.Vp, self.p_len, self.Kl, self.Vl, l_len, l_map, self.sel, O, lse, self.Qc,
+                self.Kc_l, self.Zl, self.Kc_p, self.p_id, self.S_cnt, l_id, self.scores, self.slot_src, self.ws)
+        split_ws = self._kept_split_ws("_plan_split_ws")
+        if split_ws is not None:
+            pbsa.pbsa_attention_fwd_plan_split(*args, split_ws)
+        else:
+            pbsa.pbsa_attention_fwd_plan(*args)
         return O
 
     def step_fused(self, Q, K=None, V=None, chunk_id=None, O=None, lse=None):

@@ -47,11 +47,15 @@ int check_strides(int64_t sh, int64_t st, const pbsa_params* p) {
 
 size_t workspace_bytes(const pbsa_params& p) { return pbsa::carve_update_ws(p, nullptr).bytes; }
 
-// Scratch for the split of an attention launch: what lies `used` bytes into a workspace, or nullptr where that is not
-// enough (nothing is split then).  `used` is a multiple of 256.
-void* split_scratch(const pbsa_params& p, void* ws, size_t ws_bytes, size_t used) {
-  if (!ws || (reinterpret_cast<uintptr_t>(ws) & 255u) || ws_bytes < used + pbsa::attn_split(p).bytes) return nullptr;
-  return static_cast<char*>(ws) + used;
+// Scratch that the caller gives for the split of an attention launch; out = nullptr where nothing is split.
+int split_scratch(const pbsa_params* p, void* ws, size_t ws_bytes, void** out) {
+  const size_t need = pbsa::attn_split(*p).bytes;
+  *out = nullptr;
+  if (need == 0) return PBSA_OK;
+  if (!ws || ws_bytes < need) return PBSA_EWS;
+  if (reinterpret_cast<uintptr_t>(ws) & 255u) return PBSA_EALIGN;
+  *out = ws;
+  return PBSA_OK;
 }
 
 }  // namespace
@@ -243,14 +247,13 @@ int pbsa_attention_fwd_split(const pbsa_params* p, const void* Q, const void* Kp
                              const int32_t* sel, void* O, float* lse, void* ws, size_t ws_bytes, void* hip_stream) {
   int rc = check_attention(p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O);
   if (rc) return rc;
-  const size_t need = pbsa::attn_split(*p).bytes;
-  if (need > 0 && (!ws || ws_bytes < need)) return PBSA_EWS;
-  if (need > 0 && (reinterpret_cast<uintptr_t>(ws) & 255u)) return PBSA_EALIGN;
+  void* scratch = nullptr;
+  if ((rc = split_scratch(p, ws, ws_bytes, &scratch))) return rc;
   hipError_t e = pbsa::launch_attention(
       *p, static_cast<const pbsa::bf16_t*>(Q), static_cast<const pbsa::bf16_t*>(Kp),
       static_cast<const pbsa::bf16_t*>(Vp), p_len, static_cast<const pbsa::bf16_t*>(Kl),
       static_cast<const pbsa::bf16_t*>(Vl), l_len, l_map, sel, static_cast<pbsa::bf16_t*>(O), lse, nullptr,
-      need > 0 ? ws : nullptr, static_cast<hipStream_t>(hip_stream));
+      scratch, static_cast<hipStream_t>(hip_stream));
   return e == hipSuccess ? PBSA_OK : hip_fail(e);
 }
 
@@ -262,10 +265,10 @@ int pbsa_mass_workspace_bytes(const pbsa_params* p, size_t* out) {
   return PBSA_OK;
 }
 
-int pbsa_attention_fwd_mass(const pbsa_params* p, const void* Q, const void* Kp, const void* Vp, const int32_t* p_len,
-                            const void* Kl, const void* Vl, const int32_t* l_len, const int32_t* l_map,
-                            const int32_t* sel, void* O, float* lse, float* Mt, void* ws, size_t ws_bytes,
-                            void* hip_stream) {
+static int attention_fwd_mass(const pbsa_params* p, const void* Q, const void* Kp, const void* Vp, const int32_t* p_len,
+                              const void* Kl, const void* Vl, const int32_t* l_len, const int32_t* l_map,
+                              const int32_t* sel, void* O, float* lse, float* Mt, void* ws, size_t ws_bytes,
+                              bool split, void* split_ws, size_t split_bytes, void* hip_stream) {
   int rc = check_common(p, PBSA_MAX_C_AUX);
   if (rc) return rc;
   if (!Q || !Kp || !Vp || !p_len || !Kl || !Vl || !l_len || !l_map || !O || !lse || !Mt) return PBSA_EINVAL;
@@ -279,16 +282,34 @@ int pbsa_attention_fwd_mass(const pbsa_params* p, const void* Q, const void* Kp,
     return PBSA_EALIGN;
   if (!ws || ws_bytes < pbsa::carve_mass_ws(*p, nullptr).bytes) return PBSA_EWS;
   if (reinterpret_cast<uintptr_t>(ws) & 255u) return PBSA_EALIGN;
+  void* scratch = nullptr;
+  if (split && (rc = split_scratch(p, split_ws, split_bytes, &scratch))) return rc;
   const pbsa::MassRows rows = pbsa::carve_mass_ws(*p, ws);
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   hipError_t e = pbsa::launch_attention(
       *p, static_cast<const pbsa::bf16_t*>(Q), static_cast<const pbsa::bf16_t*>(Kp),
       static_cast<const pbsa::bf16_t*>(Vp), p_len, static_cast<const pbsa::bf16_t*>(Kl),
       static_cast<const pbsa::bf16_t*>(Vl), l_len, l_map, sel, static_cast<pbsa::bf16_t*>(O), lse, &rows,
-      split_scratch(*p, ws, ws_bytes, rows.bytes), stream);
+      scratch, stream);
   if (e != hipSuccess) return hip_fail(e);
   e = pbsa::launch_mass_reduce(*p, rows, lse, Mt, stream);
   return e == hipSuccess ? PBSA_OK : hip_fail(e);
+}
+
+int pbsa_attention_fwd_mass(const pbsa_params* p, const void* Q, const void* Kp, const void* Vp, const int32_t* p_len,
+                            const void* Kl, const void* Vl, const int32_t* l_len, const int32_t* l_map,
+                            const int32_t* sel, void* O, float* lse, float* Mt, void* ws, size_t ws_bytes,
+                            void* hip_stream) {
+  return attention_fwd_mass(p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse, Mt, ws, ws_bytes, false,
+                            nullptr, 0, hip_stream);
+}
+
+int pbsa_attention_fwd_mass_split(const pbsa_params* p, const void* Q, const void* Kp, const void* Vp, const int32_t* p_len,
+                                  const void* Kl, const void* Vl, const int32_t* l_len, const int32_t* l_map,
+                                  const int32_t* sel, void* O, float* lse, float* Mt, void* ws, size_t ws_bytes,
+                                  void* split_ws, size_t split_bytes, void* hip_stream) {
+  return attention_fwd_mass(p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse, Mt, ws, ws_bytes, true,
+                            split_ws, split_bytes, hip_stream);
 }
 
 int pbsa_memory_update(const pbsa_params* p, const float* Qc, const float* Kc_l, const float* Zl, void* Kp,
@@ -354,11 +375,12 @@ int pbsa_memory_update_plan(const pbsa_params* p, const float* Qc, const float* 
   return e == hipSuccess ? PBSA_OK : hip_fail(e);
 }
 
-int pbsa_attention_fwd_plan(const pbsa_params* p, const void* Q, const void* Kp, const void* Vp, const int32_t* p_len,
-                            const void* Kl, const void* Vl, const int32_t* l_len, const int32_t* l_map,
-                            const int32_t* sel, void* O, float* lse, const float* Qc, const float* Kc_l,
-                            const float* Zl, float* Kc_p, int64_t* p_id, int32_t* S_cnt, const int64_t* l_id,
-                            float* scores, int32_t* slot_src, void* ws, size_t ws_bytes, void* hip_stream) {
+static int attention_fwd_plan(const pbsa_params* p, const void* Q, const void* Kp, const void* Vp, const int32_t* p_len,
+                              const void* Kl, const void* Vl, const int32_t* l_len, const int32_t* l_map,
+                              const int32_t* sel, void* O, float* lse, const float* Qc, const float* Kc_l,
+                              const float* Zl, float* Kc_p, int64_t* p_id, int32_t* S_cnt, const int64_t* l_id,
+                              float* scores, int32_t* slot_src, void* ws, size_t ws_bytes,
+                              bool split, void* split_ws, size_t split_bytes, void* hip_stream) {
   int rc = check_common(p);
   if (rc) return rc;
   if (!Q || !Kp || !Vp || !p_len || !Kl || !Vl || !l_len || !l_map || !O) return PBSA_EINVAL;
@@ -374,14 +396,35 @@ int pbsa_attention_fwd_plan(const pbsa_params* p, const void* Q, const void* Kp,
     return PBSA_EALIGN;
   if (!ws || ws_bytes < workspace_bytes(*p)) return PBSA_EWS;
   if (reinterpret_cast<uintptr_t>(ws) & 255u) return PBSA_EALIGN;
+  void* scratch = nullptr;
+  if (split && (rc = split_scratch(p, split_ws, split_bytes, &scratch))) return rc;
   const pbsa::UpdateWs w = pbsa::carve_update_ws(*p, ws);
   hipError_t e = pbsa::launch_attention_plan(
       *p, static_cast<const pbsa::bf16_t*>(Q), static_cast<const pbsa::bf16_t*>(Kp),
       static_cast<const pbsa::bf16_t*>(Vp), p_len, static_cast<const pbsa::bf16_t*>(Kl),
       static_cast<const pbsa::bf16_t*>(Vl), l_len, l_map, sel, static_cast<pbsa::bf16_t*>(O), lse, Qc, Kc_l, Zl, Kc_p,
-      p_id, S_cnt, S_cnt != nullptr, l_id, scores, slot_src, w, split_scratch(*p, ws, ws_bytes, w.bytes),
+      p_id, S_cnt, S_cnt != nullptr, l_id, scores, slot_src, w, scratch,
       static_cast<hipStream_t>(hip_stream));
   return e == hipSuccess ? PBSA_OK : hip_fail(e);
+}
+
+int pbsa_attention_fwd_plan(const pbsa_params* p, const void* Q, const void* Kp, const void* Vp, const int32_t* p_len,
+                            const void* Kl, const void* Vl, const int32_t* l_len, const int32_t* l_map,
+                            const int32_t* sel, void* O, float* lse, const float* Qc, const float* Kc_l,
+                            const float* Zl, float* Kc_p, int64_t* p_id, int32_t* S_cnt, const int64_t* l_id,
+                            float* scores, int32_t* slot_src, void* ws, size_t ws_bytes, void* hip_stream) {
+  return attention_fwd_plan(p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse, Qc, Kc_l, Zl, Kc_p, p_id, S_cnt, l_id,
+                            scores, slot_src, ws, ws_bytes, false, nullptr, 0, hip_stream);
+}
+
+int pbsa_attention_fwd_plan_split(const pbsa_params* p, const void* Q, const void* Kp, const void* Vp, const int32_t* p_len,
+                                  const void* Kl, const void* Vl, const int32_t* l_len, const int32_t* l_map,
+                                  const int32_t* sel, void* O, float* lse, const float* Qc, const float* Kc_l,
+                                  const float* Zl, float* Kc_p, int64_t* p_id, int32_t* S_cnt, const int64_t* l_id,
+                                  float* scores, int32_t* slot_src, void* ws, size_t ws_bytes,
+                                  void* split_ws, size_t split_bytes, void* hip_stream) {
+  return attention_fwd_plan(p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse, Qc, Kc_l, Zl, Kc_p, p_id, S_cnt, l_id,
+                            scores, slot_src, ws, ws_bytes, true, split_ws, split_bytes, hip_stream);
 }
 
 int pbsa_memory_update_apply(const pbsa_params* p, void* Kp, void* Vp, int32_t* p_len, float* S_sum, const int32_t* S_cnt,

@@ -8,7 +8,7 @@
 
 namespace {
 
-constexpr int kMaxArgs = 24;   // of pbsa_attention_fwd_plan, the longest
+constexpr int kMaxArgs = 26;   // of pbsa_attention_fwd_plan_split, the longest
 
 PyObject* g_params = nullptr;       // the types of pbsa_params and pbsa_grid, set once
 PyObject* g_grid = nullptr;
@@ -81,11 +81,11 @@ PyObject* invoke(PyObject*, PyObject* const* args, Py_ssize_t n) {
   }
   typedef int (*fn_t)(int64_t, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t,
                       int64_t, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t,
-                      int64_t, int64_t);
+                      int64_t, int64_t, int64_t, int64_t);
   int rc;
   Py_BEGIN_ALLOW_THREADS
   rc = reinterpret_cast<fn_t>(f)(a[0], a[1], a[2], a[3], a[4], a[5], a[6], a[7], a[8], a[9], a[10], a[11], a[12], a[13],
-                                    a[14], a[15], a[16], a[17], a[18], a[19], a[20], a[21], a[22], a[23]);
+                                    a[14], a[15], a[16], a[17], a[18], a[19], a[20], a[21], a[22], a[23], a[24], a[25]);
   Py_END_ALLOW_THREADS
   return PyLong_FromLong(rc);
   END_HANDLE_TH_ERRORS

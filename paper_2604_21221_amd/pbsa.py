@@ -69,7 +69,9 @@ _SIGNATURES = {
     "pbsa_attention_fwd": "p" + 11 * "t" + "wzw",
     "pbsa_attention_fwd_split": "p" + 11 * "t" + "wzw",
     "pbsa_attention_fwd_plan": "p" + 20 * "t" + "wzw",
+    "pbsa_attention_fwd_plan_split": "p" + 20 * "t" + "wzwzw",
     "pbsa_attention_fwd_mass": "p" + 12 * "t" + "wzw",
+    "pbsa_attention_fwd_mass_split": "p" + 12 * "t" + "wzwzw",
     "pbsa_attention_mass": "p" + 9 * "t" + "w",
     "pbsa_attention_bwd": "p" + 17 * "t" + "wzw",
     "pbsa_memory_update": "p" + 17 * "t" + "wzw",
@@ -264,6 +266,14 @@ def pbsa_attention_fwd_plan(p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, l
           l_id, scores, slot_src, w, wb, _stream(stream))
 
 
+def pbsa_attention_fwd_plan_split(p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse, Qc, Kc_l, Zl, Kc_p, p_id, S_cnt,
+                                  l_id, scores, slot_src, ws, split_ws, stream=None):
+    w, wb = _ws(ws)
+    v, vb = _ws(split_ws)
+    _call("pbsa_attention_fwd_plan_split", p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse, Qc, Kc_l, Zl, Kc_p, p_id,
+          S_cnt, l_id, scores, slot_src, w, wb, v, vb, _stream(stream))
+
+
 def pbsa_memory_update_apply(p, Kp, Vp, p_len, S_sum, S_cnt, Kl, Vl, ws, stream=None):
     w, wb = _ws(ws)
     _call("pbsa_memory_update_apply", p, Kp, Vp, p_len, S_sum, S_cnt, Kl, Vl, w, wb, _stream(stream))
@@ -280,6 +290,13 @@ def pbsa_mass_workspace_bytes(p: pbsa_params) -> int:
 def pbsa_attention_fwd_mass(p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse, Mt, ws, stream=None):
     w, wb = _ws(ws)
     _call("pbsa_attention_fwd_mass", p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse, Mt, w, wb, _stream(stream))
+
+
+def pbsa_attention_fwd_mass_split(p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse, Mt, ws, split_ws, stream=None):
+    w, wb = _ws(ws)
+    v, vb = _ws(split_ws)
+    _call("pbsa_attention_fwd_mass_split", p, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, lse, Mt, w, wb, v, vb,
+          _stream(stream))
 
 
 def pbsa_memory_update_fine(p, Mt, Kc_l, Kp, Vp, Kc_p, p_len, p_id, S_sum, S_cnt, Kl, Vl, l_len, l_map, l_id, scores,

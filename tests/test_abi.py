@@ -313,6 +313,22 @@ def test_split_attention_argument_checks(L):
             split(**kw)
         assert e.value.code == code, kw
 
+    # the two forms that do more: their own workspace and the split's are two
+    def plan(Q=P, Zl=P, ws=(0x10000, 1 << 30), split_ws=(0x10000, 1 << 30)):
+        pbsa.pbsa_attention_fwd_plan_split(p, Q, P, P, P, P, P, P, P, P, P, None, P, P, Zl, P, P, P, P, None, P, ws, split_ws,
+                                           stream=0)
+
+    def mass(Q=P, lse=P, ws=(0x10000, 1 << 40), split_ws=(0x10000, 1 << 30)):
+        pbsa.pbsa_attention_fwd_mass_split(p, Q, P, P, P, P, P, P, P, P, P, lse, P, ws, split_ws, stream=0)
+
+    for call, kw, code in [(plan, dict(Q=None), pbsa.PBSA_EINVAL), (plan, dict(Zl=None), pbsa.PBSA_EINVAL),
+                           (mass, dict(lse=None), pbsa.PBSA_EINVAL), (mass, dict(Q=P + 2), pbsa.PBSA_EALIGN)] + \
+            [(call, dict([(name, ws)]), code) for call in (plan, mass) for name, small in (("ws", 255), ("split_ws", need - 1))
+             for ws, code in ((None, pbsa.PBSA_EWS), ((0x10000, small), pbsa.PBSA_EWS), ((0x10010, 1 << 40), pbsa.PBSA_EALIGN))]:
+        with pytest.raises(pbsa.PbsaError) as e:
+            call(**kw)
+        assert e.value.code == code, (call.__name__, kw)
+
 
 def test_select_with_pending_apply_argument_checks(L):
     """pbsa_select_blocks_apply validates both halves and that the two parameter blocks describe the same cache."""

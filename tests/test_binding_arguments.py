@@ -152,6 +152,6 @@ def test_signatures_match_the_header():
             arg = " ".join(arg.split())
             want = ("p" if "pbsa_params" in arg else "g" if "pbsa_grid" in arg else "P" if "* const*" in arg else
                     "o" if arg.startswith("size_t*") else "L" if arg == "const int64_t* blk_stride_h" and "giPPL" in kinds else
-                    "w" if arg in ("void* ws", "void* hip_stream") else "t" if "*" in arg else
+                    "w" if arg in ("void* ws", "void* split_ws", "void* hip_stream") else "t" if "*" in arg else
                     {"int32_t": "i", "int64_t": "l", "size_t": "z"}[arg.split()[0]])
             assert kind == want, (name, arg)

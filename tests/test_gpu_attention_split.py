@@ -162,6 +162,32 @@ def test_plain_attention_between_plan_and_apply_on_one_workspace():
             assert torch.equal(getattr(a, name), getattr(b, name)), (name, g)
 
 
+def test_room_in_a_workspace_changes_nothing():
+    """pbsa_attention_fwd_plan and pbsa_attention_fwd_mass give pbsa_attention_fwd's output bit for bit however large their
+    workspace is, and use no more of it than they say."""
+    from paper_2604_21221_amd import pbsa
+    c, [(Q, K, V)] = _cache_and_chunks(1)
+    c.append_chunk(K, V, 0)
+    c.select(Q)
+    l_map, l_len, l_id = c._device_maps(want_ids=True)
+    p = c.params(Q=Q, O=Q)
+    need = pbsa.pbsa_workspace_bytes(p), pbsa.pbsa_mass_workspace_bytes(p)
+    args = Q, c.Kp, c.Vp, c.p_len, c.Kl, c.Vl, l_len, l_map, c.sel
+    O = torch.empty_like(Q)
+    lse = torch.empty(c.H, c.Nq, device=DEV)
+    pbsa.pbsa_attention_fwd(p, *args, O, lse)
+    print("[case] large workspaces", flush=True)
+    for n, call in zip(need, (
+            lambda O, lse, ws: pbsa.pbsa_attention_fwd_plan(p, *args, O, lse, c.Qc, c.Kc_l, c.Zl, c.Kc_p, c.p_id, c.S_cnt, l_id,
+                                                            c.scores, c.slot_src, ws),
+            lambda O, lse, ws: pbsa.pbsa_attention_fwd_mass(p, *args, O, lse, c._mass_buffer(), ws))):
+        ws = torch.full((n + 2 * c._attn_bytes,), 0x5A, dtype=torch.uint8, device=DEV)
+        O2, lse2 = torch.empty_like(O), torch.empty_like(lse)
+        call(O2, lse2, ws)
+        assert torch.equal(O.view(torch.int16), O2.view(torch.int16)) and torch.equal(lse, lse2)
+        assert bool((ws[n:] == 0x5A).all())
+
+
 def test_attention_from_two_streams():
     """Attention calls on one cache from two streams, each with its own Q and O, in a shape that is split: each gives what
     it gives alone."""
