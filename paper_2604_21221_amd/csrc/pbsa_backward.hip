@@ -3,10 +3,12 @@
 //     dV = P^T dO        dP = dO V^T        dZ = P o (dP - D),  D[q] = dO[q] . O[q]
 //     dQ = scale dZ K    dK = scale dZ^T Q
 // P is recomputed from the forward's log-sum-exp: exp2(z c2 - lse log2 e); nothing of the forward's
-// probabilities is stored.  Three kernels, no atomics, every output element written by exactly one lane:
+// probabilities is stored.  A launch of prep, then one of dq and dkv together (bwd_walk_kernel), no atomics, every output
+// element written by exactly one lane:
 //   prep   per row -lse log2 e and -D (fp32, D from the bf16 tensors); per local block the query blocks that attend it
-//   dq     one single-wave workgroup per 64 query rows: their Q and dO fragments stay in registers, the 64-key tiles
-//          they attend (persistent slots, then the blocks of their row of sel) stream through LDS
+//   dq     one wave per 64 query rows: their Q and dO fragments stay in registers, the 64-key tiles they attend
+//          (persistent slots, then the blocks of their row of sel) stream through LDS; where there are few such waves, two
+//          share a walk
 //   dkv    one two-wave workgroup per 64-key tile: its K and V fragments stay in registers, the 64-row tiles of the
 //          query blocks that attend it (all of them for a persistent slot; those whose row of sel names the block
 //          otherwise, which prep has written down) stream through LDS
@@ -23,6 +25,7 @@
 // lanes fetch the last valid row, and a -inf in the place of its score or its lse makes their P an exact zero.  dq holds 64
 // fixed rows per wave, so every fragment read from LDS feeds two MFMAs; dkv cannot at d = 128 (two outputs: 256
 // accumulator registers for 64 keys) and holds 32 per wave: it reads one fragment per MFMA.
+#include <algorithm>
 #include <type_traits>
 
 #include "pbsa_internal.h"
@@ -43,6 +46,7 @@ constexpr float kLog2e = 1.4426950408889634f;
 
 struct BwdArgs {
   int H, Nq, nqb, n_loc, n_loc_cap, C, k, B;
+  int dq_split;       // dq: the two waves of a workgroup share a row tile's walk, else each has a row tile
   float scale;
   long q_stride_h, q_stride_t, o_stride_h, o_stride_t;
   const bf16_t* Q;
@@ -247,12 +251,11 @@ __global__ void __launch_bounds__(256) bwd_prep_kernel(BwdArgs a) {
 // dkv: one workgroup (two waves) per 64-key tile
 // ------------------------------------------------------------------------------------------------
 template <int D>
-__global__ void __launch_bounds__(kThreads) bwd_dkv_kernel(BwdArgs a) {
+__device__ __forceinline__ void dkv_body(const BwdArgs& a, const int block, unsigned char* smem) {
   constexpr int KS = D / 16, DT = D / 32, ROW = D * 2, TILE = kTile * ROW;
   constexpr int CH = D / 8, RPI = 64 / CH;          // 16-byte chunks per row, rows per load instruction
   constexpr int NI = 32 / RPI;                      // load instructions per wave per tile (its 32 rows)
   constexpr int HI_XOR = CH == 16 ? 16 : 0;         // row + 8 flips the lowest bit of the chunk permutation when it has 4 bits
-  extern __shared__ __align__(1024) unsigned char smem[];
   __shared__ int cnt_s[2 * 8];
   __shared__ __align__(256) float rows_f[4 * 64];   // per ring entry, the scalars of the half tile's rows (BwdArgs::rows)
   // ring: entry e holds T1 at e * 2 TILE and T2 behind it
@@ -272,7 +275,7 @@ __global__ void __launch_bounds__(kThreads) bwd_dkv_kernel(BwdArgs a) {
   // 128 264 -> 225 us.
   const int n_pers = (a.C + 1) * SUB, n_ranks = n_pers + a.n_loc * SUB, n_cand = a.nqb * SUB;
   int h, rank;
-  head_item((int)blockIdx.x, a.H, h, rank);
+  head_item(block, a.H, h, rank);
   if (rank >= n_ranks) return;             // the last eight ranks of a head need not be full
   const bool kv_local = rank >= n_pers;
   int fixed_len = 0, kv_slot_tile = 0;
@@ -619,47 +622,52 @@ __global__ void __launch_bounds__(kThreads) bwd_dkv_kernel(BwdArgs a) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// dq with 64 query rows per wave.  One workgroup = one wave = 64 query rows (two MFMA column groups of 32), so that every
-// K or V fragment read from LDS -- row-wise for the first products, transposed for the second -- feeds two MFMAs.  The
-// wave stages its own half tiles (32 keys of K and of V per ring entry, two entries) and is the only one to read them: no
-// barrier anywhere.  Q and dO fragments and the dQ^T accumulators fill the accumulator half of the register file
+// dq with 64 query rows per wave (two MFMA column groups of 32), so that every K or V fragment read from LDS -- row-wise
+// for the first products, transposed for the second -- feeds two MFMAs.  The wave stages its own half tiles (32 keys of K
+// and of V per ring entry, two entries) and is the only one to read them: no barrier in the walk.  The two waves of a
+// workgroup (PAIR) have a row tile each or, dq_split, half of one row tile's walk each: the two sums meet in LDS at the end,
+// in the same order whichever wave adds.  Q and dO fragments and the dQ^T accumulators fill the accumulator half of the register file
 // (128 + 128 registers at d = 128).  Bound at 12 x 4680 x 128: matrix and vector work in one wave per SIMD at the clock the
 // chip holds under it (222 GFLOP in 215 us, 1.03 PFLOP/s; a library product of 8192^3 reaches 1.19).  The elementwise stages
 // are spread over 40 of a turn's 48 MFMAs; over 28 of them: 712.8 against 708.3 us for select, forward and backward, 89.8
 // against 88.2 at 3 x 1500 x 64.  Two waves to a workgroup that share the tiles both attend (half the traffic with
 // 128-token blocks, three half tiles on their way): 217 us, and 35.3 against 32.6 at 3 x 1500 x 64, where it lost.
 // ------------------------------------------------------------------------------------------------
-template <int D>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1))) bwd_dq_kernel(BwdArgs a) {
+template <int D, bool PAIR>
+__device__ __forceinline__ void dq_body(const BwdArgs& a, const int block, unsigned char* smem_wg) {
   constexpr int KS = D / 16, DT = D / 32, ROW = D * 2, TILE = kTile * ROW, HALF = TILE / 2;
   constexpr int CH = D / 8, RPI = 64 / CH;          // 16-byte chunks per row, rows per load instruction
   constexpr int NW = (32 / RPI) / 4;                // windows of four load instructions per tensor and half tile: 2 or 1
   constexpr int HI_XOR = CH == 16 ? 16 : 0;
   constexpr int NS = 2 * KS;                        // slices behind the first products
-  extern __shared__ __align__(1024) unsigned char smem[];
-  // ring: entry e holds 32 rows of K at e * TILE and 32 rows of V behind them
-  int* lst_a = reinterpret_cast<int*>(smem + 2 * TILE);
   const int SUB = a.B / kTile;
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int qn = lane & 31, half = lane >> 5;
+  const int n_pers = (a.C + 1) * SUB, n_cand = n_pers + a.k * SUB;
+  // each wave has a ring of its own -- entry e holds 32 rows of K at e * TILE and 32 rows of V behind them -- and, behind
+  // the rings, a list
+  constexpr int NWV = PAIR ? 2 : 1;        // waves of the workgroup
+  unsigned char* const smem = smem_wg + wave * (2 * TILE);
+  uint32_t* const lst = reinterpret_cast<uint32_t*>(smem_wg + NWV * 2 * TILE) + wave * n_cand;
   int h, r_tile;
-  head_item((int)blockIdx.x, a.H, h, r_tile);
+  head_item(block, a.H, h, r_tile);
+  if (!(PAIR && a.dq_split)) r_tile = NWV * r_tile + wave;
   if (r_tile * kTile >= a.Nq) return;
   const float c2 = a.scale * kLog2e;
   const int i_blk = r_tile * kTile / a.B;
-  const int n_pers = (a.C + 1) * SUB, n_cand = n_pers + a.k * SUB;
-  int* lst_b = lst_a + n_cand;
   const int fixed_len = min(kTile, a.Nq - r_tile * kTile);
 
   // ---- the tiles these rows attend: persistent slots, then the blocks of their row of sel -----------------
   int n_tiles = 0;
   for (int i0 = 0; i0 < n_cand; i0 += 64) {
     const int i = i0 + lane;
-    int where = 0, rows = 0;
+    uint32_t where = 0;                    // bit 31 local, bits 24.. rows - 1, the tile in the cache's tensor
+    int rows = 0;
     if (i < n_pers) {
       const int c = i / SUB, sub = i % SUB;
       rows = min(max(min(max(a.p_len[(size_t)h * (a.C + 1) + c], 0), a.B) - sub * kTile, 0), kTile);
-      where = i;
+      where = (uint32_t)i;
     } else if (i < n_cand) {
       const int jj = (i - n_pers) / SUB, sub = (i - n_pers) % SUB;
       const int l = a.sel[((size_t)h * a.nqb + i_blk) * a.k + jj];
@@ -667,19 +675,20 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1)))
         const int slot = a.l_map[l];
         if (slot >= 0 && slot < a.n_loc_cap) {
           rows = min(max(min(max(a.l_len[l], 0), a.B) - sub * kTile, 0), kTile);
-          where = (int)(0x80000000u | (uint32_t)(slot * SUB + sub));
+          where = 0x80000000u | (uint32_t)(slot * SUB + sub);
         }
       }
     }
     const unsigned long long m = __ballot(rows > 0);
-    if (rows > 0) {
-      const int pos = n_tiles + lanes_below(m);
-      lst_a[pos] = where;
-      lst_b[pos] = rows;
-    }
+    if (rows > 0) lst[n_tiles + lanes_below(m)] = where | (uint32_t)(rows - 1) << 24;
     n_tiles += __popcll(m);
   }
   n_tiles = __builtin_amdgcn_readfirstlane(n_tiles);
+  int t_first = 0;                         // the wave's share of the list
+  if (PAIR && a.dq_split) {
+    t_first = wave * ((n_tiles + 1) / 2);
+    n_tiles = wave ? n_tiles : (n_tiles + 1) / 2;
+  }
 
   // ---- fixed fragments (B operands) of both column groups: row 32 n + lane % 32, dims 16 ks + 8 (lane / 32) .. + 8 ----
   bf16x8 f1[2][KS], f2[2][KS];
@@ -758,9 +767,9 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1)))
   const unsigned char* vp = reinterpret_cast<const unsigned char*>(a.Vp) + hp;
   auto stage = [&](int u, int entry) {
     const int t = u >> 1, mg = u & 1;
-    const int where = __builtin_amdgcn_readfirstlane(lst_a[t]);
-    const int last = __builtin_amdgcn_readfirstlane(lst_b[t]) - 1;
-    const size_t off = (size_t)(where & 0x7FFFFFFF) * TILE;
+    const int where = __builtin_amdgcn_readfirstlane((int)lst[t]);
+    const int last = (where >> 24) & 63;
+    const size_t off = (size_t)(where & 0xFFFFFF) * TILE;
     const unsigned char* s1 = (where < 0 ? kl : kp) + off;
     const unsigned char* s2 = (where < 0 ? vl : vp) + off;
     const uint32_t dst = ring_s + (uint32_t)(entry * TILE);
@@ -800,9 +809,9 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1)))
   for (int v = 0; v < 16; ++v) km[v] = 0.0f;
   bool km_clear = true;
   const int n_half = 2 * n_tiles;
-  if (n_half > 0) {
-    stage(0, 0);
-    stage(1, 1);
+  if (t_first < n_tiles) {
+    stage(2 * t_first, 0);
+    stage(2 * t_first + 1, 1);
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(8 * NW) : "memory");
 #pragma unroll
     for (int i = 0; i < NS; ++i) x[i] = lds_read_row(rd[i / 2] + (i % 2) * HALF);
@@ -871,7 +880,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1)))
   auto turn = [&](auto MG, int t) {
     constexpr int mg = decltype(MG)::value;                 // two turns per tile: the ring entry is the half
     const int u = 2 * t + mg;
-    const int rows = __builtin_amdgcn_readfirstlane(lst_b[t]);
+    const int rows = ((__builtin_amdgcn_readfirstlane((int)lst[t]) >> 24) & 63) + 1;
     // accumulator element v: key 32 mg + 8 (v / 4) + 4 half + v % 4, query row 32 n + lane % 32.  Keys past the
     // tile's length hold a copy of its last row; a query row that does not exist has nl = -inf.
     if (rows < 32 * mg + 32) {
@@ -920,8 +929,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1)))
   }
 #pragma unroll
   for (int i = 0; i < 2 * DT; ++i) tf[i] = bf16x8{};
-  if (n_tiles > 0) {
-    for (int t = 0; t < n_tiles; ++t) {
+  if (t_first < n_tiles) {
+    for (int t = t_first; t < n_tiles; ++t) {
       turn(std::integral_constant<int, 0>{}, t);
       turn(std::integral_constant<int, 1>{}, t);
     }
@@ -933,10 +942,35 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1)))
   for (int n = 0; n < 2; ++n)
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) asm volatile("s_nop 15\n\ts_nop 15" : "+a"(out[n][dt]));
+  if (PAIR && a.dq_split) {
+    // each wave leaves the other's column group in its own ring, which nobody reads any more, and adds what it finds for
+    // its group in the other's: the same two numbers added, whichever wave does it
+    auto swap = [&](int mine, int other) {
+      float4* const give = reinterpret_cast<float4*>(smem) + lane;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int v4 = 0; v4 < 4; ++v4)
+          give[(4 * dt + v4) * 64] = make_float4(out[other][dt][4 * v4], out[other][dt][4 * v4 + 1], out[other][dt][4 * v4 + 2],
+                                                 out[other][dt][4 * v4 + 3]);
+      __syncthreads();
+      const float4* const take = reinterpret_cast<const float4*>(smem_wg + (wave ^ 1) * (2 * TILE)) + lane;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int v4 = 0; v4 < 4; ++v4) {
+          const float4 o = take[(4 * dt + v4) * 64];
+          out[mine][dt][4 * v4] += o.x; out[mine][dt][4 * v4 + 1] += o.y;
+          out[mine][dt][4 * v4 + 2] += o.z; out[mine][dt][4 * v4 + 3] += o.w;
+        }
+    };
+    if (wave == 0) swap(0, 1);
+    else swap(1, 0);
+  }
 #pragma unroll
   for (int n = 0; n < 2; ++n) {
     const int frow = 32 * n + qn;
-    if (frow < fixed_len) {
+    if (frow < fixed_len && (!(PAIR && a.dq_split) || n == wave)) {
       float* o = a.dQ + ((size_t)h * a.Nq + (size_t)r_tile * kTile + frow) * D;
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)
@@ -949,11 +983,26 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1)))
   }
 }
 
-template <typename K>
-hipError_t launch_with_lds(K kernel, const BwdArgs& a, dim3 grid, int threads, size_t lds, hipStream_t stream) {
+// dq and dkv as one launch (neither needs what the other writes) or as a launch each.  A launch's time ends with its longest
+// walks; as one launch the two kernels' ends and beginnings overlap, and the places dq leaves empty (888 waves on 1024
+// places at 12 heads x 4680 rows) are dkv's from the start.  The dq workgroups, whose walks are the longest, come first.
+// Select, forward and backward, two launches -> one (with dq_split where it applies): 712 -> 696 us at 12 x 4680 x 128 with
+// 32 + 48 blocks of 64, 446 -> 433 with 8 + 16 blocks of 128, 227 -> 134 at 4 x 3000 x 128, 88 -> 57 at 3 x 1500 x 64.
+constexpr int kDq = 1, kDkv = 2;
+template <int D, int PARTS>
+__global__ void __launch_bounds__(PARTS == kDq ? 64 : kThreads) __attribute__((amdgpu_waves_per_eu(PARTS == kDkv ? 2 : 1)))
+    bwd_walk_kernel(BwdArgs a, int n_dq) {
+  extern __shared__ __align__(1024) unsigned char smem[];
+  if (PARTS == kDq || (PARTS != kDkv && (int)blockIdx.x < n_dq)) dq_body<D, PARTS != kDq>(a, (int)blockIdx.x, smem);
+  else dkv_body<D>(a, (int)blockIdx.x - n_dq, smem);
+}
+
+template <int D, int PARTS>
+hipError_t launch_walk(const BwdArgs& a, unsigned n_dq, unsigned n_dkv, size_t lds, hipStream_t stream) {
+  const auto kernel = bwd_walk_kernel<D, PARTS>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kernel, grid, dim3(threads), lds, stream, a);
+  hipLaunchKernelGGL(kernel, dim3(n_dq + n_dkv), dim3(PARTS == kDq ? 64 : kThreads), lds, stream, a, (int)n_dq);
   return hipGetLastError();
 }
 
@@ -978,7 +1027,7 @@ hipError_t launch_attention_bwd(const pbsa_params& p, const bf16_t* Q, const bf1
                                 const int32_t* l_map, const int32_t* sel, const bf16_t* O, const bf16_t* dO,
                                 const float* lse, float* dQ, float* dKp, float* dVp, float* dKl, float* dVl, void* ws,
                                 hipStream_t stream) {
-  BwdArgs a{p.H, p.Nq, p.nqb, p.n_loc, p.n_loc_cap, p.C, p.k, p.B, p.scale, p.q_stride_h, p.q_stride_t, p.o_stride_h,
+  BwdArgs a{p.H, p.Nq, p.nqb, p.n_loc, p.n_loc_cap, p.C, p.k, p.B, 0, p.scale, p.q_stride_h, p.q_stride_t, p.o_stride_h,
             p.o_stride_t, Q, Kp, Vp, p_len, Kl, Vl, l_len, l_map, sel, O, dO, lse, static_cast<float*>(ws),
             reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + bwd_workspace(p).att),
             reinterpret_cast<int4*>(static_cast<char*>(ws) + bwd_workspace(p).order), dQ, dKp, dVp, dKl, dVl};
@@ -990,23 +1039,30 @@ hipError_t launch_attention_bwd(const pbsa_params& p, const bf16_t* Q, const bf1
   else hipLaunchKernelGGL(bwd_prep_kernel<64>, pgrid, dim3(256), plan_lds, stream, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const size_t ring = (size_t)4 * kTile * p.d * 2;
-  {
-    const size_t n_cand = (size_t)(p.C + 1 + p.k) * sub;
-    const dim3 grid(head_items((p.Nq + kTile - 1) / kTile, p.H));
-    const size_t lds = (size_t)2 * kTile * p.d * 2 + n_cand * 8 + 16;
-    e = p.d == 128 ? launch_with_lds(bwd_dq_kernel<128>, a, grid, 64, lds, stream)
-                   : launch_with_lds(bwd_dq_kernel<64>, a, grid, 64, lds, stream);
+  const int n_row_tiles = (p.Nq + kTile - 1) / kTile, n_tiles = p.H * n_row_tiles;
+  const int n_cand = (p.C + 1 + p.k) * sub;                  // of a dq walk: its list
+  const size_t tile = (size_t)kTile * p.d * 2;
+  const unsigned n_dkv = head_items((p.C + 1 + p.n_loc) * sub, p.H);
+  const size_t lds_dkv = 4 * tile + (size_t)4 * sub * p.nqb + 16;
+  // Where the line lies between one launch and two: at d = 128 both bodies need a SIMD's whole register file per wave, and
+  // one launch is never slower.  At d = 64 dkv by itself runs two waves per SIMD, beside dq one, which costs it more than
+  // the shared launch saves where dq's walks are long and its waves fill the last round of 1024 places, the time dkv could
+  // have had anyway: 12 x 4680 rows with 32 + 48 blocks of 64 (888 waves) 414 us as two launches and 422 as one, 13 x 4800 441
+  // and 459; but 11 x 4680 (814 waves) 400 and 393, 16 x 4000 with 4 + 8 blocks 145 and 132, 12 x 4680 with 16 + 24 blocks 272
+  // and 248, 8 x 2000 with 6 + 8 blocks 95 and 71.
+  const int rounds = (n_tiles + 1023) / 1024;
+  if (p.d == 64 && n_cand >= 64 && 5 * n_tiles >= 4 * 1024 * rounds) {
+    e = launch_walk<64, kDq>(a, head_items(n_row_tiles, p.H), 0, 2 * tile + (size_t)4 * n_cand + 16, stream);
     if (e != hipSuccess) return e;
+    return launch_walk<64, kDkv>(a, 0, n_dkv, lds_dkv, stream);
   }
-  {
-    const size_t n_cand = (size_t)p.nqb * sub;
-    const dim3 grid(head_items((p.C + 1 + p.n_loc) * sub, p.H));
-    const size_t lds = ring + n_cand * 4 + 16;
-    e = p.d == 128 ? launch_with_lds(bwd_dkv_kernel<128>, a, grid, kThreads, lds, stream)
-                   : launch_with_lds(bwd_dkv_kernel<64>, a, grid, kThreads, lds, stream);
-  }
-  return e;
+  // Two waves share a walk where the row tiles are at most as many as the compute units: each walk has a unit to itself, and
+  // half of it ends earlier (4 x 3000 x 128, 188 row tiles: 134 us split).  With 512 (16 x 2048 x 128) a row tile per wave
+  // takes 165 us and the split, which loads the fixed fragments twice, 175; with 888 433 and 441.
+  a.dq_split = n_tiles <= 256;
+  const unsigned n_dq = head_items(a.dq_split ? n_row_tiles : (n_row_tiles + 1) / 2, p.H);
+  const size_t lds = std::max(lds_dkv, 4 * tile + (size_t)8 * n_cand + 16);
+  return p.d == 128 ? launch_walk<128, kDq | kDkv>(a, n_dq, n_dkv, lds, stream) : launch_walk<64, kDq | kDkv>(a, n_dq, n_dkv, lds, stream);
 }
 
 }  // namespace pbsa

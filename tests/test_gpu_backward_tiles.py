@@ -1,7 +1,7 @@
 """Backward where its kernels' tiles, lists and workgroup order can go wrong, every element against the fp64 oracle: a last
 row tile of 1, 31, 32, 33 and 63 rows (half tiles with no row, one row, all but one), one, three and nine heads (fewer and
 more than the eight dies the grid is dealt over), more query blocks than one word of the turned-around selection holds,
-blocks that every row, few rows and no row selected.  Bounds: those of test_gpu_parity_grad.py, derived there."""
+blocks that every row, few rows and no row selected, and either side of the lines at which the launch is set up differently.  Bounds: those of test_gpu_parity_grad.py, derived there."""
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -21,6 +21,14 @@ CASES = [
     ("rows63",     9, 128, 64,  127,  0, 1, 1, 0, 1, [32]),
     ("two_words",  1, 64,  64,  2113, 0, 1, 3, 0, 0, [64]),
     ("three_words", 2, 128, 64, 4100, 0, 1, 2, 0, 1, [64]),
+    # up to 256 row tiles in all, two waves share a row tile's walk: a walk of one tile leaves one of them nothing
+    ("one_tile",   1, 128, 64,  70,   0, 1, 1, 0, 1, [0]),
+    ("three_tiles", 2, 64, 64,  130,  0, 2, 1, 0, 0, [64, 3]),
+    # more than 256: a row tile per wave, an odd number of them per head
+    ("pairs_128",  9, 128, 64,  1800, 0, 1, 2, 0, 1, [64]),
+    ("pairs_64",   9, 64,  128, 1830, 0, 1, 1, 0, 0, [70]),
+    # d = 64, at least 820 row tiles and 64 tiles to walk (most slots empty): dq and dkv as a launch each
+    ("two_launches", 13, 64, 64, 4100, 0, 62, 1, 0, 1, [64] + [0] * 60 + [7]),
 ]
 
 
