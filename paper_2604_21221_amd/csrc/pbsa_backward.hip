@@ -27,6 +27,7 @@
 // accumulator registers for 64 keys) and holds 32 per wave: it reads one fragment per MFMA.
 #include <algorithm>
 #include <type_traits>
+#include <utility>
 
 #include "pbsa_internal.h"
 
@@ -84,7 +85,16 @@ __device__ __forceinline__ void dma16(const void* base, uint32_t lane_off, uint3
                : "memory", "m0");
 }
 
-// the same with 4 bytes per lane: LDS bytes [lds_off, lds_off + 256)
+// the same, OFF bytes further on in LDS and in memory alike (the instruction's offset moves both addresses)
+template <int OFF>
+__device__ __forceinline__ void dma16_at(const void* base, uint32_t lane_off, uint32_t lds_off) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3"
+               :
+               : "s"(lds_off), "v"(lane_off), "s"(base), "n"(OFF)
+               : "memory", "m0");
+}
+
+// the same as dma16 with 4 bytes per lane: LDS bytes [lds_off, lds_off + 256)
 __device__ __forceinline__ void dma4(const void* base, uint32_t lane_off, uint32_t lds_off) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
                :
@@ -101,14 +111,6 @@ __device__ __forceinline__ void dma16x4(const void* base, uint32_t o0, uint32_t 
                "global_load_lds_dwordx4 %4, %5 offset:3072"
                :
                : "s"(lds_off), "v"(o0), "v"(o1), "v"(o2), "v"(o3), "s"(base)
-               : "memory", "m0");
-}
-__device__ __forceinline__ void dma16x2(const void* base, uint32_t o0, uint32_t o1, uint32_t lds_off) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
-               "global_load_lds_dwordx4 %1, %3\n\t"
-               "global_load_lds_dwordx4 %2, %3 offset:1024"
-               :
-               : "s"(lds_off), "v"(o0), "v"(o1), "s"(base)
                : "memory", "m0");
 }
 
@@ -137,6 +139,11 @@ __device__ __forceinline__ bf16x8 lds_read_tr(uint32_t at_lo, uint32_t at_hi) {
 }
 __device__ __forceinline__ void acc_mfma(f32x16& acc, const bf16x8& a, const bf16x8& b) {
   asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+}
+// f(0), f(1), .. with the number as a constant
+template <typename F, int... I>
+__device__ __forceinline__ void unroll(F f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
 }
 __device__ __forceinline__ uint32_t pack2(float a, float b) {
   bf16x2 pk;
@@ -400,58 +407,64 @@ __device__ __forceinline__ void dkv_body(const BwdArgs& a, const int block, unsi
   // entry of four.  Wave w brings rows 16 w .. 16 w + 15 of the half.  Every wave issues the same number of loads per
   // half tile, so that one count serves the wait; past the end of the list the last half tile is fetched again into an
   // entry whose contents are never used.
-  constexpr int HALF = TILE / 2, RING = 4, NH = NI / 2;    // NH: load instructions per wave, tensor and half tile
+  constexpr int HALF = TILE / 2, NH = NI / 2;    // NH: load instructions per wave, tensor and half tile
   constexpr int PER = 2 * NH + 1;               // loads per wave and half tile
   const int rl = lane / CH;
-  const int n_half = 2 * n_tiles;
   const long st1 = a.q_stride_t * 2, st2 = a.o_stride_t * 2;     // row strides of the streamed tensors in bytes
-  const unsigned char* const b1 = reinterpret_cast<const unsigned char*>(a.Q + (size_t)h * a.q_stride_h);
-  const unsigned char* const b2 = reinterpret_cast<const unsigned char*>(a.dO + (size_t)h * a.o_stride_h);
+  // A load's address: tile base + the lane's offset within the tile, and its instruction offset k 1024 on top, which the
+  // lane's offset takes back; both are moved by 3 KiB against each other so that the offset is not below zero.
+  constexpr int BIAS = 3072;
+  const unsigned char* const b1 = reinterpret_cast<const unsigned char*>(a.Q + (size_t)h * a.q_stride_h) - BIAS;
+  const unsigned char* const b2 = reinterpret_cast<const unsigned char*>(a.dO + (size_t)h * a.o_stride_h) - BIAS;
   const float* const rows_g = a.rows + (size_t)h * row_blocks(a.Nq) * 64;
-  // per-lane source offsets of the wave's instructions within a half tile whose 32 rows all exist, less what the
-  // instruction's own offset adds (a row's stride is at least its d elements: never below zero)
-  uint32_t so1[NH], so2[NH];
+  uint32_t so1[2][NH], so2[2][NH];         // [half][load]
+  auto set_offsets = [&](int last) {       // rows past `last`: that row again
 #pragma unroll
-  for (int k = 0; k < NH; ++k) {
-    const int r = 16 * wave + RPI * k + rl;
-    const uint32_t chunk = (uint32_t)(((lane % CH) ^ swz<CH>(r)) << 4);
-    so1[k] = (uint32_t)(r * st1) + chunk - (uint32_t)(k * 1024);
-    so2[k] = (uint32_t)(r * st2) + chunk - (uint32_t)(k * 1024);
-  }
-  auto stage = [&](int where, int mg, int entry) {
-    const int last = min(kTile, a.Nq - where * kTile) - 1;
-    const unsigned char* s1 = b1 + (size_t)where * kTile * st1;
-    const unsigned char* s2 = b2 + (size_t)where * kTile * st2;
-    const uint32_t dst = ring_s + (uint32_t)(entry * TILE + wave * (HALF / 2));
-    if (last >= 32 * mg + 31) {
-      s1 += (size_t)(32 * mg) * st1;
-      s2 += (size_t)(32 * mg) * st2;
-      if constexpr (NH == 4) {
-        dma16x4(s1, so1[0], so1[1], so1[2], so1[3], dst);
-        dma16x4(s2, so2[0], so2[1], so2[2], so2[3], dst + HALF);
-      } else {
-        dma16x2(s1, so1[0], so1[1], dst);
-        dma16x2(s2, so2[0], so2[1], dst + HALF);
-      }
-    } else {                               // rows past the last one that exists are not touched: that row again
+    for (int mg = 0; mg < 2; ++mg)
 #pragma unroll
       for (int k = 0; k < NH; ++k) {
         const int r = 16 * wave + RPI * k + rl, src_row = min(32 * mg + r, last);
-        const uint32_t chunk = (uint32_t)(((lane % CH) ^ swz<CH>(r)) << 4);
-        dma16(s1, (uint32_t)(src_row * st1) + chunk, dst + k * 1024);
-        dma16(s2, (uint32_t)(src_row * st2) + chunk, dst + HALF + k * 1024);
+        const uint32_t chunk = (uint32_t)(((lane % CH) ^ swz<CH>(r)) << 4) + (uint32_t)(BIAS - k * 1024);
+        so1[mg][k] = (uint32_t)(src_row * st1) + chunk;
+        so2[mg][k] = (uint32_t)(src_row * st2) + chunk;
       }
-    }
-    // the scalars of the half's 32 rows (both waves bring the same)
-    dma4(rows_g + (size_t)(2 * where + mg) * 64, (uint32_t)lane * 4u, rows_s + (uint32_t)(entry * 256));
   };
+  set_offsets(kTile - 1);
+  // a head's last row tile need not be full; it is the last of every list it is in, so the offsets change once
+  const int ragged = a.Nq % kTile ? a.Nq / kTile : -1;
+  const unsigned char* s1 = b1;            // the tile that is being fetched
+  const unsigned char* s2 = b2;
+  uint32_t rows_off = 0;
+  auto stage_tile = [&](int where) {
+    s1 = b1 + (size_t)where * kTile * st1;
+    s2 = b2 + (size_t)where * kTile * st2;
+    rows_off = (uint32_t)lane * 4u + (uint32_t)(where * 512);
+  };
+  // load i of a half: Q and dO in turn, then the scalars of the half's 32 rows (both waves bring the same)
+  auto stage_one = [&](auto MG, auto I, uint32_t ring_at, uint32_t rows_at) {
+    constexpr int mg = decltype(MG)::value, i = decltype(I)::value, k = i / 2;
+    if constexpr (i < 2 * NH) {
+      if constexpr (i % 2 == 0) dma16_at<k * 1024>(s1, so1[mg][k], ring_at + mg * TILE);
+      else dma16_at<k * 1024>(s2, so2[mg][k], ring_at + mg * TILE + HALF);
+    } else {
+      dma4(rows_g + 64 * mg, rows_off, rows_at + mg * 256);
+    }
+  };
+  auto stage_half = [&](auto MG, uint32_t ring_at, uint32_t rows_at) {
+    unroll([&](auto I) { stage_one(MG, I, ring_at, rows_at); }, std::make_integer_sequence<int, PER>{});
+  };
+  uint32_t ring_at = ring_s + (uint32_t)(wave * (HALF / 2)), rows_at = rows_s;    // of the pair of entries of tile t
 
   // ---- the walk: a software pipeline over half tiles ---------------------------------------------------
   // Turn u, in two phases.  First: the first products of half tile u + 1 (2 KS MFMAs, their row fragments already in
   // registers), each with a slice of half tile u's elementwise stage behind it and, over the middle slices, the
   // transposing reads of half tile u.  Then a wait and the turn's one barrier: half tile u + 2 has landed, and nobody
   // reads half tile u any more.  Second: the second products of half tile u (4 DT MFMAs), each with a row fragment of
-  // half tile u + 2 read behind it; half tile u + 4 is sent for, into the entry u has left.
+  // half tile u + 2 read behind it; half tile u + 4 is sent for, into the entry u has left, a load behind each product.
+  // (The loads in bursts of four, their addresses computed there and then, held the wave up for some 150 cycles a turn: with
+  // that, and addresses moved to the other ring entries where they were last used instead of behind the turn, 57.3 -> 53.1 us
+  // at 3 x 1500 x 64, 133.7 -> 125.6 at 4 x 3000 x 128, 432.5 -> 425.5 at 12 x 4680 x 128 with 8 + 16 blocks of 128.  The large
+  // ones are held by power: with zeros for data the same walks take 20 % less, at a higher clock.)
   // The compiler orders instructions without side effects as it likes: left alone it issued all the elementwise work
   // behind the last MFMA, and a
   // turn took 2700 cycles for 1024 cycles of matrix work, on a compute unit of its own too (12 heads x 4680 x 128 with
@@ -477,12 +490,16 @@ __device__ __forceinline__ void dkv_body(const BwdArgs& a, const int block, unsi
 #pragma unroll
     for (int g = 0; g < 4; ++g) read_dn4(addr, g);
   };
-  if (n_half > 0) {
-#pragma unroll
-    for (int j = 0; j < RING; ++j) {
-      const int u = min(j, n_half - 1);
-      stage(__builtin_amdgcn_readfirstlane(lst_a[u >> 1]), u & 1, j);
+  int v_where = 0;                         // the tile after the one that is being fetched
+  if (n_tiles > 0) {
+    for (int j = 0; j < 2; ++j) {          // two tiles (the last one again where there is only one)
+      const int where = __builtin_amdgcn_readfirstlane(lst_a[min(j, n_tiles - 1)]);
+      if (where == ragged) set_offsets(a.Nq - where * kTile - 1);
+      stage_tile(where);
+      stage_half(std::integral_constant<int, 0>{}, ring_at + j * 2 * TILE, rows_at + j * 512);
+      stage_half(std::integral_constant<int, 1>{}, ring_at + j * 2 * TILE, rows_at + j * 512);
     }
+    v_where = lst_a[min(2, n_tiles - 1)];
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * PER) : "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -502,11 +519,20 @@ __device__ __forceinline__ void dkv_body(const BwdArgs& a, const int block, unsi
     nl0 = read_scalar4(sc_own);
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) rd[ks] += 2 * TILE;     // the turns of tile t read the rows of tile t + 1
+    // all here before the loop: inside it, only as much is waited for as the loop itself has outstanding
+#pragma unroll
+    for (int i = 0; i < NS; ++i) asm volatile("" : "+v"(x[i]));
+    asm volatile("" : "+v"(dn), "+v"(nl0), "+v"(v_where));
   }
+  uint32_t step = 2 * TILE, sc_step = 512;                  // to the other pair of ring entries and back
   // Two turns per tile, so that the accumulator sets trade places by name (no copies) and the half is a constant.
   auto turn = [&](auto MG, int t, f32x16& c1, f32x16& c2a, f32x16& n1, f32x16& n2) {
     constexpr int mg = decltype(MG)::value;
-    int v_where = lst_a[min(t + 2, n_tiles - 1)];
+    int where = 0;
+    if constexpr (mg == 0) {
+      where = __builtin_amdgcn_readfirstlane(v_where);
+      if (where == ragged) set_offsets(a.Nq - where * kTile - 1);
+    }
     float nl[16], ex[16], zz[16];
     nl[0] = nl0.x; nl[1] = nl0.y; nl[2] = nl0.z; nl[3] = nl0.w;
     u32x4 eP[2], eZ[2];
@@ -542,8 +568,13 @@ __device__ __forceinline__ void dkv_body(const BwdArgs& a, const int block, unsi
           const int i = 2 * (sl - NS / 4) + q, tensor = i / (2 * DT), j = (i / DT) % 2, dt = i % DT;
           const uint32_t at = (uint32_t)(mg * TILE + tensor * HALF + 16 * j * ROW);
           tf[i] = lds_read_tr(tl[dt] + at, th[dt] + at);
+          if (mg == 1 && tensor == 1 && j == 1) {           // the last use this tile
+            tl[dt] += step;
+            th[dt] += step;
+          }
         }
       }
+      if (mg == 0 && sl == 1) stage_tile(where);
 #pragma unroll
       for (int q = 0; q < EPS; ++q) {
         const int v = sl * EPS + q;
@@ -558,40 +589,36 @@ __device__ __forceinline__ void dkv_body(const BwdArgs& a, const int block, unsi
     }
 #pragma unroll
     for (int q = 0; q < EPS; ++q) finish((NS - 1) * EPS + q);
-    const int where = __builtin_amdgcn_readfirstlane(v_where);
     // this wave's rows of half tile u + 2 are in and its reads of half tile u done; then everybody's
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER) : "memory");
     __builtin_amdgcn_s_waitcnt(0xC07F);    // lgkmcnt(0), in the form the compiler counts
     __builtin_amdgcn_s_barrier();
     asm volatile("s_nop 4" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int i = 0; i < NTF; ++i) {
-      const int tensor = i % 2, j = i / (2 * DT), dt = (i / 2) % DT;
+    unroll([&](auto I) {
+      constexpr int i = decltype(I)::value, tensor = i % 2, j = i / (2 * DT), dt = (i / 2) % DT;
       acc_mfma(tensor ? out2[dt] : out1[dt], tf[(2 * tensor + j) * DT + dt], as_bf16x8(tensor ? eP[j] : eZ[j]));
       __builtin_amdgcn_sched_barrier(0);
       x[i] = lds_read_row(rd[i / 2] + mg * TILE + (i % 2) * HALF);
-      if (i == 1) stage(where, mg, 2 * (t & 1) + mg);
-      if (i >= NTF / 2 - 2 && i < NTF / 2 + 2) read_dn4(sc_next + 256 * mg, i - (NTF / 2 - 2));
-      if (i == NTF / 2 + 2) nl0 = read_scalar4(mg ? sc_next : sc_own + 256);
+      if constexpr (mg == 1 && i % 2 == 1) rd[i / 2] -= step;
+      if constexpr (i >= 1 && i <= PER) stage_one(MG, std::integral_constant<int, i - 1>{}, ring_at, rows_at);
+      if constexpr (i >= NTF / 2 - 2 && i < NTF / 2 + 2) read_dn4(sc_next + 256 * mg, i - (NTF / 2 - 2));
+      if constexpr (i == NTF / 2 + 2) nl0 = read_scalar4(mg ? sc_next : sc_own + 256);
+      if constexpr (mg == 1 && i == NTF / 2 + 3) {
+        v_where = lst_a[min(t + 3, n_tiles - 1)];
+        sc_own += sc_step;
+        sc_next -= sc_step;
+      }
       __builtin_amdgcn_sched_barrier(0);
-    }
+    }, std::make_integer_sequence<int, NTF>{});
   };
   {
     f32x16 d1, d2;                         // the other accumulator set
-    uint32_t step = 2 * TILE, sc_step = 512;                // to the other pair of ring entries and back
     for (int t = 0; t < n_tiles; ++t) {
       turn(std::integral_constant<int, 0>{}, t, c1, c2a, d1, d2);
       turn(std::integral_constant<int, 1>{}, t, d1, d2, c1, c2a);
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) rd[ks] -= step;
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt) {
-        tl[dt] += step;
-        th[dt] += step;
-      }
-      sc_own += sc_step;
-      sc_next -= sc_step;
+      ring_at += step;
+      rows_at += sc_step;
       step = 0u - step;
       sc_step = 0u - sc_step;
     }
