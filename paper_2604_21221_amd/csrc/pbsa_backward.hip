@@ -76,16 +76,9 @@ __device__ __forceinline__ int lanes_below(unsigned long long mask) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-// One wave-wide global -> LDS load of 16 bytes per lane: LDS bytes [lds_off, lds_off + 1024) receive lane i's
-// 16 bytes at lds_off + 16 i.  Completion is tracked by the issuing wave's vmcnt.
-__device__ __forceinline__ void dma16(const void* base, uint32_t lane_off, uint32_t lds_off) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-               :
-               : "s"(lds_off), "v"(lane_off), "s"(base)
-               : "memory", "m0");
-}
-
-// the same, OFF bytes further on in LDS and in memory alike (the instruction's offset moves both addresses)
+// One wave-wide global -> LDS load of 16 bytes per lane: LDS bytes [lds_off + OFF, + 1024) receive lane i's 16 bytes, fetched
+// from base + lane_off + OFF, at 16 i (the instruction's offset moves both addresses).  Completion is tracked by the issuing
+// wave's vmcnt.
 template <int OFF>
 __device__ __forceinline__ void dma16_at(const void* base, uint32_t lane_off, uint32_t lds_off) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3"
@@ -94,23 +87,11 @@ __device__ __forceinline__ void dma16_at(const void* base, uint32_t lane_off, ui
                : "memory", "m0");
 }
 
-// the same as dma16 with 4 bytes per lane: LDS bytes [lds_off, lds_off + 256)
+// the same with 4 bytes per lane: LDS bytes [lds_off, lds_off + 256)
 __device__ __forceinline__ void dma4(const void* base, uint32_t lane_off, uint32_t lds_off) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
                :
                : "s"(lds_off), "v"(lane_off), "s"(base)
-               : "memory", "m0");
-}
-
-__device__ __forceinline__ void dma16x4(const void* base, uint32_t o0, uint32_t o1, uint32_t o2, uint32_t o3, uint32_t lds_off) {
-  // four loads 1 KiB apart in LDS and in memory alike: the instruction's offset moves both addresses
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
-               "global_load_lds_dwordx4 %1, %5\n\t"
-               "global_load_lds_dwordx4 %2, %5 offset:1024\n\t"
-               "global_load_lds_dwordx4 %3, %5 offset:2048\n\t"
-               "global_load_lds_dwordx4 %4, %5 offset:3072"
-               :
-               : "s"(lds_off), "v"(o0), "v"(o1), "v"(o2), "v"(o3), "s"(base)
                : "memory", "m0");
 }
 
@@ -780,41 +761,47 @@ __device__ __forceinline__ void dq_body(const BwdArgs& a, const int block, unsig
   }
 
   // ---- staging: the wave brings whole half tiles (32 rows of K and of V, dense rows) ---------------------
-  const int rl = lane / CH;
-  uint32_t so[4];                          // per-lane source offsets of the four instructions of a window
+  // in windows of 4 KiB (four loads of K, four of V).  A load's address: its window's base + the lane's offset in it + the
+  // instruction's own offset, which the lane's offset takes back; the offsets are moved up by BIAS and the bases down, so
+  // that a lane that fetches an earlier row than its own does not go below zero.
+  constexpr int WROWS = 4 * RPI;           // rows of a window (the permutation repeats within them)
+  constexpr uint32_t BIAS = 16384;
+  static_assert((kTile - WROWS) * ROW + 3072 <= (int)BIAS, "no lane's offset is below zero");
+  uint32_t so[4];
+  auto set_offsets = [&](int first, int last) {             // rows first .. of the tile; past `last`: that row again
+    int ln = lane;
+    asm volatile("" : "+v"(ln));           // worked out here, not kept in registers throughout the walk
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int r = RPI * k + rl;            // the permutation repeats every 16 rows (8 when a row has 8 chunks)
-    so[k] = (uint32_t)(r * ROW) + (uint32_t)(((lane % CH) ^ swz<CH>(r)) << 4) - (uint32_t)(k * 1024);
-  }
-  const size_t hl = (size_t)h * a.n_loc_cap * a.B * D * 2, hp = (size_t)h * (a.C + 1) * a.B * D * 2;
-  const unsigned char* kl = reinterpret_cast<const unsigned char*>(a.Kl) + hl;
-  const unsigned char* vl = reinterpret_cast<const unsigned char*>(a.Vl) + hl;
-  const unsigned char* kp = reinterpret_cast<const unsigned char*>(a.Kp) + hp;
-  const unsigned char* vp = reinterpret_cast<const unsigned char*>(a.Vp) + hp;
-  auto stage = [&](int u, int entry) {
-    const int t = u >> 1, mg = u & 1;
-    const int where = __builtin_amdgcn_readfirstlane((int)lst[t]);
-    const int last = (where >> 24) & 63;
-    const size_t off = (size_t)(where & 0xFFFFFF) * TILE;
-    const unsigned char* s1 = (where < 0 ? kl : kp) + off;
-    const unsigned char* s2 = (where < 0 ? vl : vp) + off;
-    const uint32_t dst = ring_s + (uint32_t)(entry * TILE);
-    if (last >= 32 * mg + 31) {
-#pragma unroll
-      for (int w = 0; w < NW; ++w) {
-        dma16x4(s1 + 32 * mg * ROW + w * 4096, so[0], so[1], so[2], so[3], dst + w * 4096);
-        dma16x4(s2 + 32 * mg * ROW + w * 4096, so[0], so[1], so[2], so[3], dst + HALF + w * 4096);
-      }
-    } else {                               // rows past the last one that exists are not touched: that row again
-#pragma unroll
-      for (int k = 0; k < 4 * NW; ++k) {
-        const int r = RPI * k + rl, src_row = min(32 * mg + r, last);
-        const uint32_t chunk = (uint32_t)(((lane % CH) ^ swz<CH>(r)) << 4);
-        dma16(s1, (uint32_t)(src_row * ROW) + chunk, dst + k * 1024);
-        dma16(s2, (uint32_t)(src_row * ROW) + chunk, dst + HALF + k * 1024);
-      }
+    for (int k = 0; k < 4; ++k) {
+      const int r = RPI * k + ln / CH;
+      so[k] = (uint32_t)((min(first + r, last) - first) * ROW + (((ln % CH) ^ swz<CH>(r)) << 4) + (int)BIAS - k * 1024);
     }
+  };
+  set_offsets(0, kTile);
+  const size_t hl = (size_t)h * a.n_loc_cap * a.B * D * 2 - BIAS, hp = (size_t)h * (a.C + 1) * a.B * D * 2 - BIAS;
+  const unsigned char* const kl = reinterpret_cast<const unsigned char*>(a.Kl) + hl;
+  const unsigned char* const vl = reinterpret_cast<const unsigned char*>(a.Vl) + hl;
+  const unsigned char* const kp = reinterpret_cast<const unsigned char*>(a.Kp) + hp;
+  const unsigned char* const vp = reinterpret_cast<const unsigned char*>(a.Vp) + hp;
+  const unsigned char* s1 = kl;            // the tile that is being fetched
+  const unsigned char* s2 = vl;
+  int s_last = 0;                          // its last row
+  auto stage_tile = [&](int word) {
+    const size_t off = (size_t)(word & 0xFFFFFF) * TILE;
+    s1 = (word < 0 ? kl : kp) + off;
+    s2 = (word < 0 ? vl : vp) + off;
+    s_last = (word >> 24) & 63;
+  };
+  // load i of half MG of that tile, into ring entry MG: window by window, K and V in turn.  A tile that is not full has
+  // its offsets set before each window and set back behind the last.
+  auto stage_one = [&](auto MG, auto I) {
+    constexpr int mg = decltype(MG)::value, i = decltype(I)::value, w = i / 8, k = i % 8 / 2;
+    constexpr int first = 32 * mg + WROWS * w;
+    if constexpr (i % 8 == 0)
+      if (s_last < first + WROWS - 1) set_offsets(first, s_last);
+    dma16_at<k * 1024>((i % 2 ? s2 : s1) + first * ROW, so[k], ring_s + (uint32_t)(mg * TILE + (i % 2) * HALF + w * 4096));
+    if constexpr (i == 8 * NW - 1)
+      if (s_last < 32 * mg + 31) set_offsets(0, kTile);
   };
 
   // ---- the walk ------------------------------------------------------------------------------------------
@@ -823,26 +810,33 @@ __device__ __forceinline__ void dq_body(const BwdArgs& a, const int block, unsig
   //   2  the second products of group 1, u - 1           (2 DT)
   //   3  the first products of group 1                   (2 KS), behind them the elementwise stage of group 0 and the
   //                                                      transposing reads of u
-  //      then half tile u + 1 has landed (it was sent for a turn ago), and u + 2 is sent for, into the entry of u
-  //   4  the second products of group 0                  (2 DT), behind them the row reads of u + 1
+  //      then half tile u + 1 has landed (it was sent for a turn ago)
+  //   4  the second products of group 0                  (2 DT), behind them the row reads of u + 1 and, two loads
+  //                                                      behind each product, the fetching of u + 2
   // The last quarter of an elementwise stage runs behind the first DT of the second products that follow it: those need
   // its first half only.  Per element: fma, exp2, multiply, half of a conversion; -D is what the dP accumulators start
-  // from, and a key past the tile's length has -inf in the score accumulator's start (the scale is positive), so its P is
-  // an exact zero.  The empty asm statements keep MFMAs and slices where they stand; without them the compiler issues
-  // all the elementwise work behind the last MFMA of its phase.
+  // from, and in a tile that is not full a key past the end has -inf in the score accumulator's start (the scale is positive),
+  // so its P is an exact zero; a full tile's accumulators start from the constant 0.  The empty asm statements keep MFMAs
+  // and slices where they stand; without them the compiler issues all the elementwise work behind the last MFMA of its phase.
+  // Select, forward and backward with the loads in bursts of four and the score accumulators' start kept in registers,
+  // against this: 657.9 -> 653.3 us at 12 x 4680 x 128 with 32 + 48 blocks of 64, 409.5 -> 406.7 with 8 + 16 blocks of 128,
+  // 389.4 -> 381.5 at 12 x 4680 x 64, 159.4 -> 157.8 at 16 x 2048 x 128.
   bf16x8 x[NS];                            // row fragments: x[2 ks] of K, x[2 ks + 1] of V
-  f32x16 km;                               // 0 or, for a key that does not exist, -inf, in accumulator order
-#pragma unroll
-  for (int v = 0; v < 16; ++v) km[v] = 0.0f;
-  bool km_clear = true;
-  const int n_half = 2 * n_tiles;
+  // the list's words of the tile of the turn and of the tile that is fetched meanwhile, and, still on its way, the next one's
+  int w_own = 0, w_next = 0, v_word = 0;
   if (t_first < n_tiles) {
-    stage(2 * t_first, 0);
-    stage(2 * t_first + 1, 1);
+    w_own = __builtin_amdgcn_readfirstlane((int)lst[t_first]);
+    w_next = __builtin_amdgcn_readfirstlane((int)lst[min(t_first + 1, n_tiles - 1)]);
+    stage_tile(w_own);
+    unroll([&](auto I) { stage_one(std::integral_constant<int, 0>{}, I); }, std::make_integer_sequence<int, 8 * NW>{});
+    unroll([&](auto I) { stage_one(std::integral_constant<int, 1>{}, I); }, std::make_integer_sequence<int, 8 * NW>{});
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(8 * NW) : "memory");
 #pragma unroll
     for (int i = 0; i < NS; ++i) x[i] = lds_read_row(rd[i / 2] + (i % 2) * HALF);
+#pragma unroll
+    for (int i = 0; i < NS; ++i) asm volatile("" : "+v"(x[i]));
   }
+  const f32x16 zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
   f32x16 a1[2], a2[2];
   u32x4 eZ[2][2];
   bf16x8 tf[2 * DT];                       // transposed fragments: 16 keys j, 32 dims dt at j DT + dt
@@ -865,16 +859,25 @@ __device__ __forceinline__ void dq_body(const BwdArgs& a, const int block, unsig
 #pragma unroll
     for (int v = lo; v < hi; ++v) asm volatile("" : "+v"(ex[n][v]));
   };
-  const auto nothing = [](int) {};
+  const auto nothing = [](auto) {};
   // the first products of group n and, behind them, elements 0 .. E1 - 1 of the other group's elementwise stage
-  auto run_phase = [&](int n, auto PRODUCTS, auto behind) {
+  // accumulator element v: key 32 mg + 8 (v / 4) + 4 half + v % 4, query row 32 n + lane % 32.  Keys past the tile's
+  // length hold a copy of its last row (`keys` of the half tile's exist); a query row that does not exist has nl = -inf.
+  auto run_phase = [&](int n, auto PRODUCTS, int keys, auto behind) {
     const auto at = [](int sl) { return sl < 0 ? 0 : E1 * sl / NS; };
 #pragma unroll
     for (int sl = 0; sl < NS; ++sl) {
       if constexpr (decltype(PRODUCTS)::value) {
         const int ks = sl / 2;
-        if (sl % 2 == 0) {
-          a1[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[sl], f1[n][ks], ks == 0 ? km : a1[n], 0, 0, 0);
+        if (sl == 0 && keys < 32) {
+          f32x16 km;
+          const int lim = keys - 4 * half;
+#pragma unroll
+          for (int v = 0; v < 16; ++v) km[v] = 8 * (v / 4) + (v % 4) < lim ? 0.0f : -INFINITY;
+          a1[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], f1[n][0], km, 0, 0, 0);
+          asm volatile("" : "+v"(a1[n]));
+        } else if (sl % 2 == 0) {
+          a1[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[sl], f1[n][ks], ks == 0 ? zero : a1[n], 0, 0, 0);
           asm volatile("" : "+v"(a1[n]));
         } else {
           a2[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[sl], f2[n][ks], ks == 0 ? dn[n] : a2[n], 0, 0, 0);
@@ -891,41 +894,33 @@ __device__ __forceinline__ void dq_body(const BwdArgs& a, const int block, unsig
     asm volatile("s_nop 4" ::: "memory");
   };
   // the second products of group n, the rest of its elementwise stage behind the first DT of them
-  auto second_products = [&](int n, auto behind) {
+  auto second_products = [&](auto N, auto behind) {
+    constexpr int n = decltype(N)::value;
     constexpr int LAST = E1 * (NS - 1) / NS;                // begun in the last slice, not finished
     const auto at = [](int i) { return E1 + (16 - E1) * i / (DT - 1); };
-#pragma unroll
-    for (int i = 0; i < 2 * DT; ++i) {
+    unroll([&](auto I) {
+      constexpr int i = decltype(I)::value;
       if (i == DT) asm volatile("s_nop 4" ::: "memory");
       acc_mfma(out[n][i % DT], tf[i], as_bf16x8(eZ[n][i / DT]));
       __builtin_amdgcn_sched_barrier(0);
-      behind(i);
+      behind(I);
       if (i < DT) slice(n, i == 0 ? LAST : at(i - 1), i < DT - 1 ? at(i) : 16, i < DT - 1 ? at(i + 1) : 16);
       __builtin_amdgcn_sched_barrier(0);
-    }
+    }, std::make_integer_sequence<int, 2 * DT>{});
   };
   auto turn = [&](auto MG, int t) {
     constexpr int mg = decltype(MG)::value;                 // two turns per tile: the ring entry is the half
-    const int u = 2 * t + mg;
-    const int rows = ((__builtin_amdgcn_readfirstlane((int)lst[t]) >> 24) & 63) + 1;
-    // accumulator element v: key 32 mg + 8 (v / 4) + 4 half + v % 4, query row 32 n + lane % 32.  Keys past the
-    // tile's length hold a copy of its last row; a query row that does not exist has nl = -inf.
-    if (rows < 32 * mg + 32) {
-      const int lim = rows - 32 * mg - 4 * half;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) km[v] = 8 * (v / 4) + (v % 4) < lim ? 0.0f : -INFINITY;
-      km_clear = false;
-    } else if (!km_clear) {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) km[v] = 0.0f;
-      km_clear = true;
+    if constexpr (mg == 0) {
+      stage_tile(w_next);                  // past the end of the list the last tile again: nobody reads it
+      v_word = (int)lst[min(t + 2, n_tiles - 1)];
     }
+    const int keys = ((w_own >> 24) & 63) + 1 - 32 * mg;
     __builtin_amdgcn_sched_barrier(0);
-    run_phase(0, std::true_type{}, nothing);
-    second_products(1, nothing);
+    run_phase(0, std::true_type{}, keys, nothing);
+    second_products(std::integral_constant<int, 1>{}, nothing);
     {
       const uint32_t at0 = (uint32_t)(mg * TILE);
-      run_phase(1, std::true_type{}, [&](int sl) {
+      run_phase(1, std::true_type{}, keys, [&](int sl) {
         if (sl >= NS / 4 && sl < NS / 4 + DT) {
 #pragma unroll
           for (int r = 0; r < 2; ++r) {
@@ -938,15 +933,22 @@ __device__ __forceinline__ void dq_body(const BwdArgs& a, const int block, unsig
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // half tile u + 1 is in
     __builtin_amdgcn_s_waitcnt(0xC07F);                     // lgkmcnt(0): and u read (nobody else uses the ring)
-    if (u + 2 < n_half) stage(u + 2, mg);
     __builtin_amdgcn_sched_barrier(0);
-    second_products(0, [&](int i) {
+    second_products(std::integral_constant<int, 0>{}, [&](auto I) {
+      constexpr int i = decltype(I)::value;
+      static_assert(8 * NW == 4 * DT, "two loads behind each product");
+      stage_one(MG, std::integral_constant<int, 2 * i>{});
 #pragma unroll
       for (int r = 0; r < 2; ++r) {
         const int f = 2 * i + r;
         x[f] = lds_read_row(rd[f / 2] + (mg ^ 1) * TILE + (f % 2) * HALF);
       }
+      stage_one(MG, std::integral_constant<int, 2 * i + 1>{});
     });
+    if constexpr (mg == 1) {
+      w_own = w_next;
+      w_next = __builtin_amdgcn_readfirstlane(v_word);
+    }
   };
   // before the first half tile: a stage of group 1 that adds nothing
 #pragma unroll
@@ -961,8 +963,9 @@ __device__ __forceinline__ void dq_body(const BwdArgs& a, const int block, unsig
       turn(std::integral_constant<int, 0>{}, t);
       turn(std::integral_constant<int, 1>{}, t);
     }
-    run_phase(0, std::false_type{}, nothing);               // group 1 of the last half tile
-    second_products(1, nothing);
+    run_phase(0, std::false_type{}, 32, nothing);               // group 1 of the last half tile
+    second_products(std::integral_constant<int, 1>{}, nothing);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // the trailing loads land before the ring is used otherwise
   }
   // the compiler does not see the matrix instructions that wrote the output accumulators: let the pipe drain
 #pragma unroll
