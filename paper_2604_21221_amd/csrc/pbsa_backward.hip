@@ -235,6 +235,31 @@ __global__ void __launch_bounds__(256) bwd_prep_kernel(BwdArgs a) {
   }
 }
 
+// The 32 rows of an output whose transpose a wave holds in its accumulators (element v of tile dt is dim 32 dt + 8 (v / 4)
+// + 4 (lane / 32) + v % 4 of row lane % 32), times `scale`, to memory, rows [0, n_rows) of them, through 32 D floats of LDS
+// that nobody else uses: a lane's 16 bytes of a row go to LDS at chunk c ^ row and leave in instructions of 1 KiB.  Straight
+// from the accumulators an instruction would write 32 bytes of each of 32 rows: 691.8 -> 685.5 us for select, forward and
+// backward at 12 x 4680 x 128 with 32 + 48 blocks of 64, 430.4 -> 426.0 with 8 + 16 blocks of 128, 165.1 -> 162.7 at 16 x 2048 x 128.
+template <int D>
+__device__ __forceinline__ void store_rows(float* dst, const f32x16 (&o)[D / 32], float scale, int n_rows, unsigned char* scratch) {
+  constexpr int CHUNKS = D / 4, RPS = 64 / CHUNKS;         // 16-byte chunks per row, rows per store instruction
+  const int lane = threadIdx.x & 63, row = lane & 31, half = lane >> 5;
+  float4* const lds = reinterpret_cast<float4*>(scratch);
+#pragma unroll
+  for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+    for (int v4 = 0; v4 < 4; ++v4)
+      lds[row * CHUNKS + ((8 * dt + 2 * v4 + half) ^ (row & (CHUNKS - 1)))] =
+          make_float4(o[dt][4 * v4] * scale, o[dt][4 * v4 + 1] * scale, o[dt][4 * v4 + 2] * scale, o[dt][4 * v4 + 3] * scale);
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // other lanes' writes
+#pragma unroll
+  for (int i = 0; i < 32 / RPS; ++i) {
+    const int r = RPS * i + lane / CHUNKS, c = lane % CHUNKS;
+    const float4 v = lds[r * CHUNKS + (c ^ (r & (CHUNKS - 1)))];
+    if (r < n_rows) *reinterpret_cast<float4*>(dst + (size_t)r * D + 4 * c) = v;
+  }
+}
+
 // ------------------------------------------------------------------------------------------------
 // dkv: one workgroup (two waves) per 64-key tile
 // ------------------------------------------------------------------------------------------------
@@ -612,21 +637,12 @@ __device__ __forceinline__ void dkv_body(const BwdArgs& a, const int block, unsi
     asm volatile("" : "+a"(out2[dt]));
   }
 
-  // ---- outputs: element v of tile dt is dim 32 dt + 8 (v / 4) + 4 half + v % 4 of fixed row 32 w + lane % 32 ----
-  const int frow = 32 * wave + qn;
+  // ---- outputs -------------------------------------------------------------------------------------
   // every row of the tile's slot is written: zeros past the valid length and for a block nobody attends
-  float* ok_ = dk + (size_t)frow * D;
-  float* ov_ = dv + (size_t)frow * D;
-  const float sc = frow < fixed_len ? a.scale : 0.0f, one = frow < fixed_len ? 1.0f : 0.0f;
-#pragma unroll
-  for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-    for (int v4 = 0; v4 < 4; ++v4) {
-      *reinterpret_cast<float4*>(ok_ + 32 * dt + 8 * v4 + 4 * half) =
-          make_float4(out1[dt][4 * v4] * sc, out1[dt][4 * v4 + 1] * sc, out1[dt][4 * v4 + 2] * sc, out1[dt][4 * v4 + 3] * sc);
-      *reinterpret_cast<float4*>(ov_ + 32 * dt + 8 * v4 + 4 * half) =
-          make_float4(out2[dt][4 * v4] * one, out2[dt][4 * v4 + 1] * one, out2[dt][4 * v4 + 2] * one, out2[dt][4 * v4 + 3] * one);
-    }
+  __syncthreads();                         // the ring is dead: what either wave fetched last has landed
+  const bool exists = 32 * wave + qn < fixed_len;
+  store_rows<D>(dk + (size_t)(32 * wave) * D, out1, exists ? a.scale : 0.0f, 32, smem + wave * (2 * TILE));
+  store_rows<D>(dv + (size_t)(32 * wave) * D, out2, exists ? 1.0f : 0.0f, 32, smem + wave * (2 * TILE) + TILE);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -996,21 +1012,13 @@ __device__ __forceinline__ void dq_body(const BwdArgs& a, const int block, unsig
     };
     if (wave == 0) swap(0, 1);
     else swap(1, 0);
+    __syncthreads();                       // both have taken theirs
   }
 #pragma unroll
-  for (int n = 0; n < 2; ++n) {
-    const int frow = 32 * n + qn;
-    if (frow < fixed_len && (!(PAIR && a.dq_split) || n == wave)) {
-      float* o = a.dQ + ((size_t)h * a.Nq + (size_t)r_tile * kTile + frow) * D;
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int v4 = 0; v4 < 4; ++v4)
-          *reinterpret_cast<float4*>(o + 32 * dt + 8 * v4 + 4 * half) =
-              make_float4(out[n][dt][4 * v4] * a.scale, out[n][dt][4 * v4 + 1] * a.scale, out[n][dt][4 * v4 + 2] * a.scale,
-                          out[n][dt][4 * v4 + 3] * a.scale);
-    }
-  }
+  for (int n = 0; n < 2; ++n)
+    if (!(PAIR && a.dq_split) || n == wave)
+      store_rows<D>(a.dQ + ((size_t)h * a.Nq + (size_t)r_tile * kTile + 32 * n) * D, out[n], a.scale, fixed_len - 32 * n,
+                    smem + n * TILE);
 }
 
 // dq and dkv as one launch (neither needs what the other writes) or as a launch each.  A launch's time ends with its longest
