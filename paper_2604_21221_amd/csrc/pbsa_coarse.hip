@@ -9,6 +9,9 @@
 // This file is compiled with -ffp-contract=off: every fp32 operation below is exactly the one
 // written (the arithmetic that decides block sets and slots is specified operation by operation
 // in pbsa.h so that an independent implementation reproduces the integers bit for bit).
+#include <type_traits>
+#include <utility>
+
 #include "pbsa_internal.h"
 #include "pbsa_plan_device.h"
 
@@ -19,6 +22,14 @@ using namespace plan_dev;
 
 constexpr int kThreads = 256;
 constexpr int kXC = 32;   // pooled-key dimensions staged through LDS per step
+
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+// f(0), f(1), .. with the number as a constant
+template <typename F, int... I>
+__device__ __forceinline__ void unroll(F f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
 
 __device__ __forceinline__ float bf_lo(uint32_t u) { return __uint_as_float(u << 16); }
 __device__ __forceinline__ float bf_hi(uint32_t u) { return __uint_as_float(u & 0xFFFF0000u); }
@@ -32,8 +43,40 @@ __device__ __forceinline__ uint32_t f2bf_rne(float f) {
 
 // ------------------------------------------------------------------------------------------------
 // Pooling.  One job = one block; D/2 threads per job, each owning 2 dimensions (one 4-byte load per
-// token) and adding the tokens in ascending order.  The loads of 64 tokens are in flight together.
+// token) and adding the tokens in ascending order.  The loads of a block are in flight together.
 // ------------------------------------------------------------------------------------------------
+// Adds min(N, len) tokens (two dimensions of them) to acc0 / acc1 in ascending order, all N loads in flight together.  The
+// address walks from token to token: as a product of the token's number and the pitch, 64 bits wide, the addresses took
+// longer than the sums.  Unless FULL, a load past the last token takes that one again and counts as zero (a sum that starts
+// from +0 is never -0, so +0 leaves it as it is).
+template <int N, bool FULL, typename PITCH>
+__device__ __forceinline__ void pool_rows(const bf16_t* p, PITCH pitch, int len, float& acc0, float& acc1) {
+  uint32_t v[N];
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    v[u] = *reinterpret_cast<const uint32_t*>(p);
+    p += FULL || u + 1 < len ? (long)pitch : 0;
+  }
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    const uint32_t w = FULL || u < len ? v[u] : 0u;
+    acc0 = acc0 + bf_lo(w);
+    acc1 = acc1 + bf_hi(w);
+  }
+}
+// len tokens, at most 128 (none: nothing is read).  The wave takes one way through: its lanes may have two blocks.
+template <typename PITCH>
+__device__ __forceinline__ void pool_block(const bf16_t* p, PITCH pitch, int len, float& acc0, float& acc1) {
+  if (len <= 0) return;
+  if (__any(len > 64)) {
+    if (__all(len == 128)) pool_rows<128, true>(p, pitch, len, acc0, acc1);
+    else pool_rows<128, false>(p, pitch, len, acc0, acc1);
+  } else {
+    if (__all(len == 64)) pool_rows<64, true>(p, pitch, len, acc0, acc1);
+    else pool_rows<64, false>(p, pitch, len, acc0, acc1);
+  }
+}
+
 struct PoolArgs {
   int mode;                 // 0: generic blocks, 1: select (local key blocks, then query blocks)
   int n_jobs;
@@ -54,47 +97,32 @@ __device__ __forceinline__ void pool_body(const PoolArgs& a, const int bx) {
   const int c = threadIdx.x % TPJ;
   if (job >= a.n_jobs) return;
   const bf16_t* src;
-  long pitch = D;
   int len;
   float* dst;
-  if (a.mode == 0) {
-    src = a.X + (size_t)job * a.B * D;
-    len = a.len[job];
-    dst = a.out + (size_t)job * D;
+  float acc0 = 0.0f, acc1 = 0.0f;
+  // jobs [0, H*nk) of mode 1 pool local key blocks, the rest pool the chunk's query blocks
+  const int nk = a.n_kjobs_per_head;
+  if (a.mode == 1 && job >= a.H * nk) {
+    const int jq = job - a.H * nk;
+    const int h = jq / a.nqb, i = jq % a.nqb;
+    len = min(a.B, a.Nq - i * a.B);
+    dst = a.Qc + ((size_t)h * a.nqb + i) * D;
+    pool_block(a.Q + (size_t)h * a.q_stride_h + (size_t)i * a.B * a.q_stride_t + 2 * c, a.q_stride_t, len, acc0, acc1);
   } else {
-    // jobs [0, H*nk) pool local key blocks, the rest pool the chunk's query blocks
-    const int nk = a.n_kjobs_per_head;
-    if (job < a.H * nk) {
+    if (a.mode == 0) {
+      src = a.X + (size_t)job * a.B * D;
+      len = a.len[job];
+      dst = a.out + (size_t)job * D;
+    } else {
       const int h = job / nk, l = a.pool_from + job % nk;
       const int slot = a.l_map[l];
       if (slot < 0 || slot >= a.n_loc_cap) return;
       src = a.X + ((size_t)h * a.n_loc_cap + slot) * a.B * D;
       len = a.len[l];
       dst = a.out + ((size_t)h * a.n_loc_cap + slot) * D;
-    } else {
-      const int jq = job - a.H * nk;
-      const int h = jq / a.nqb, i = jq % a.nqb;
-      src = a.Q + (size_t)h * a.q_stride_h + (size_t)i * a.B * a.q_stride_t;
-      pitch = a.q_stride_t;
-      len = min(a.B, a.Nq - i * a.B);
-      dst = a.Qc + ((size_t)h * a.nqb + i) * D;
     }
-  }
-  len = max(0, min(len, a.B));
-  float acc0 = 0.0f, acc1 = 0.0f;
-  const bf16_t* p = src + c * 2;
-  for (int t0 = 0; t0 < len; t0 += 64) {
-    uint32_t v[64];
-#pragma unroll
-    for (int u = 0; u < 64; ++u)
-      v[u] = *reinterpret_cast<const uint32_t*>(p + (size_t)min(t0 + u, len - 1) * pitch);
-#pragma unroll
-    for (int u = 0; u < 64; ++u) {
-      if (t0 + u < len) {
-        acc0 = acc0 + bf_lo(v[u]);
-        acc1 = acc1 + bf_hi(v[u]);
-      }
-    }
+    len = max(0, min(len, a.B));
+    pool_block(src + 2 * c, std::integral_constant<long, D>{}, len, acc0, acc1);
   }
   const float fl = (float)len;
   float2 o;
@@ -241,43 +269,51 @@ __device__ __forceinline__ void dma16(const void* base, uint32_t voff, uint32_t 
                : "memory", "m0");
 }
 
-// Adds up to N tokens (two dimensions of them) to acc0 / acc1 in ascending order, all N loads in flight together.
-template <int N>
-__device__ __forceinline__ void pool_rows(const bf16_t* p, long pitch, int len, float& acc0, float& acc1) {
-  uint32_t v[N];
-#pragma unroll
-  for (int u = 0; u < N; ++u) v[u] = *reinterpret_cast<const uint32_t*>(p + (size_t)min(u, len - 1) * pitch);
-#pragma unroll
-  for (int u = 0; u < N; ++u) {
-    if (u < len) {
-      acc0 = acc0 + bf_lo(v[u]);
-      acc1 = acc1 + bf_hi(v[u]);
-    }
-  }
+// v_mfma_f32_4x4x1_16b_f32: sixteen 4 x 4 products of one contraction index.  With A of block X broadcast to all blocks (cbsz
+// 4), lane L's element r of the result is fma(a of lane 4 X + r, b of lane L, c of element r): rounded once, denormals,
+// infinities and NaN patterns as v_fma_f32 has them (131072 chains of 128 each for seven mixes of values, every bit).
+template <int X>
+__device__ __forceinline__ f32x4 fma_4_rows(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 4, X, 0);
 }
+
+template <int D, int NM>
+struct SelectGeo {
+  static constexpr int DX = NM <= 8 ? 32 : 16;                                  // dimensions per round
+  static constexpr int NR = D / DX, BUF = NM * 64 * DX * 4;                     // rounds, bytes of a round
+  static constexpr int REST = 4 * D * 4 + 4 * NM * 64 * 4;                      // the queries and the logits
+  static constexpr int FIT = (160 * 1024 - REST) / BUF;
+  static constexpr int NBUF = FIT < NR ? FIT : NR;                              // rounds in LDS at a time
+  static constexpr int LDS = NBUF * BUF + REST;
+  static_assert(NBUF >= 2, "a round arrives while another one is multiplied");
+};
 
 // Selection (Eq. 10-11).  A workgroup handles 4 query blocks of one head; its NM waves split the local
 // blocks: lane `lane` of wave w owns column j = 64 w + lane and runs the four chains
-// acc_r = fma(q_r[x], k_j[x], acc_r), x ascending.  The pooled keys reach LDS by direct global -> LDS
-// loads, DX dimensions (4 DX bytes per column) per round, double buffered; a wave stages exactly the 64
+// acc_r = fma(q_r[x], k_j[x], acc_r), x ascending, as four rows of one matrix instruction per x: the instruction takes
+// the queries from registers, where vector instructions had to read each of them from LDS for every 64 columns and the
+// workgroup's LDS reads were what the chains waited for.  The pooled keys reach LDS by direct global -> LDS loads, DX
+// dimensions (4 DX bytes per column) per round, as many rounds at a time as fit; a wave stages exactly the 64
 // columns it consumes, so the rounds need no workgroup barrier.  Within a column's round the 16-byte
 // chunks are permuted (logical chunk c of column j sits at c ^ ((j / 2) % (DX / 4))), which spreads the
 // per-lane 16-byte reads of consecutive columns over the bank groups.  The logits then go to LDS and wave
 // r ranks row r.  DX = 32 up to 8 waves; 16 beyond, where two rounds of 32 would not fit in LDS.  A query block is
 // looked at by exactly one workgroup, so that one pools it (Eq. 6, D / 2 threads per block, tokens added in ascending
-// order) while its first pooled keys arrive (11.1 us at 12 x 37 blocks of 128 tokens and 111 columns, against 8.5 us
-// behind a pooling launch of 9.6); at least four waves, so that the four blocks are pooled and ranked side by side
-// whatever NM is.
-template <int D, int NM, int DX>
+// order) while its pooled keys arrive; at least four waves, so that the four blocks are pooled and ranked side by side
+// whatever NM is.  Latency bound, a chain of phases; inside a
+// workgroup, by time stamps, against 64-bit products for the queries' addresses, chains of v_fma_f32 over two rounds in LDS
+// and all 32 bits of the threshold: pooling 2.5 -> 1.3 us, logits 1.2 -> 0.5, threshold 1.2 -> 0.8 at 2 heads x 4 blocks of 64
+// (16 columns of 64 dimensions); 3.7 -> 2.6, 2.7 -> 1.4, 2.6 -> 1.4 at 12 x 37 blocks of 128 (148 columns of 128).
+template <int D, int NM>
 __device__ __forceinline__ void select_body(const SelectArgs& a, const int bx, const int h, unsigned char* smem) {
+  using G = SelectGeo<D, NM>;
   constexpr int NCP = NM * 64;                        // padded columns
-  constexpr int BUF = NCP * DX * 4;                   // one round of every column
-  constexpr int NR = D / DX;
+  constexpr int DX = G::DX, BUF = G::BUF, NR = G::NR, NBUF = G::NBUF;
   constexpr int CPC = DX / 4;                         // 16-byte chunks per column and round
   constexpr int NI = 64 * CPC / 64;                   // load instructions per wave and round (64 columns)
   constexpr int CPI = 64 / CPC;                       // columns per instruction
   constexpr int NW = NM < 4 ? 4 : NM, NT = 64 * NW;   // waves, threads
-  float* qs = reinterpret_cast<float*>(smem + 2 * BUF);                         // [4][D]
+  float* qs = reinterpret_cast<float*>(smem + NBUF * BUF);                      // [4][D]
   float* zs = qs + 4 * D;                                                       // [4][NCP]
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int i0 = bx * 4;
@@ -300,10 +336,10 @@ __device__ __forceinline__ void select_body(const SelectArgs& a, const int bx, c
   const unsigned char* kbase = reinterpret_cast<const unsigned char*>(a.Kc_l);
 #define PBSA_STAGE(R_)                                                                                 \
   _Pragma("unroll") for (int n_ = 0; n_ < NI; ++n_)                                                     \
-      dma16(kbase + (R_) * (DX * 4), goff[n_], wave_lds + ((R_) & 1) * BUF + n_ * 1024);
+      dma16(kbase + (R_) * (DX * 4), goff[n_], wave_lds + ((R_) % NBUF) * BUF + n_ * 1024);
   if (has_cols) {
-    PBSA_STAGE(0)
-    if (NR > 1) PBSA_STAGE(1)
+#pragma unroll
+    for (int r = 0; r < NBUF; ++r) PBSA_STAGE(r)
   }
 
   if (a.Q) {
@@ -313,11 +349,11 @@ __device__ __forceinline__ void select_body(const SelectArgs& a, const int bx, c
       if (i < a.nqb) {
         const int len = min(a.B, a.Nq - i * a.B);
         const bf16_t* p = a.Q + (size_t)h * a.q_stride_h + (size_t)i * a.B * a.q_stride_t + 2 * c;
-        if (len > 64 && NM <= 8) {
-          pool_rows<128>(p, a.q_stride_t, len, acc0, acc1);
+        if constexpr (NM <= 8) {
+          pool_block(p, a.q_stride_t, len, acc0, acc1);
         } else {
-          pool_rows<64>(p, a.q_stride_t, min(len, 64), acc0, acc1);
-          if (len > 64) pool_rows<64>(p + 64 * a.q_stride_t, a.q_stride_t, len - 64, acc0, acc1);
+          pool_rows<64, false>(p, a.q_stride_t, min(len, 64), acc0, acc1);
+          if (len > 64) pool_rows<64, false>(p + 64 * a.q_stride_t, a.q_stride_t, len - 64, acc0, acc1);
         }
         const float fl = (float)len;
         acc0 = acc0 / fl;
@@ -334,33 +370,31 @@ __device__ __forceinline__ void select_body(const SelectArgs& a, const int bx, c
   }
   __syncthreads();
 
-  float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  // The logits: lane = column; element r of acc runs the chain of query block r.  a_q[m] holds dimensions 16 m .. 16 m + 15 of
+  // the four queries, as the instruction wants them.
+  f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
   const int jcol = 64 * wave + lane;
   const int sw = (jcol >> 1) % CPC;
-  if (has_cols)
-#pragma unroll 1
-  for (int r0 = 0; r0 < NR; ++r0) {
-    if (r0 + 1 < NR) {
-      if constexpr (NI == 8) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-      else asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-    } else {
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    }
-    const unsigned char* kb = smem + (r0 & 1) * BUF + jcol * (DX * 4);
+  if (has_cols) {
+    float a_q[D / 16];
 #pragma unroll
-    for (int c = 0; c < CPC; ++c) {
-      const float4 k4 = *reinterpret_cast<const float4*>(kb + ((c ^ sw) << 4));
+    for (int m = 0; m < D / 16; ++m) a_q[m] = qs[(lane & 3) * D + 16 * m + (lane >> 2)];
+    unroll([&](auto R) {
+      constexpr int r0 = decltype(R)::value, later = (r0 + NBUF <= NR ? NBUF : NR - r0) - 1;   // rounds on their way behind r0
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(later * NI) : "memory");
+      const unsigned char* kb = smem + (r0 % NBUF) * BUF + jcol * (DX * 4);
+      float4 k4[CPC];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float4 q4 = *reinterpret_cast<const float4*>(qs + r * D + r0 * DX + 4 * c);
-        acc[r] = __builtin_fmaf(q4.x, k4.x, acc[r]);
-        acc[r] = __builtin_fmaf(q4.y, k4.y, acc[r]);
-        acc[r] = __builtin_fmaf(q4.z, k4.z, acc[r]);
-        acc[r] = __builtin_fmaf(q4.w, k4.w, acc[r]);
-      }
-      if (c % 2 == 1) __builtin_amdgcn_sched_barrier(0);   // keep the operand reads close to their use
-    }
-    if (r0 + 2 < NR) PBSA_STAGE(r0 + 2)
+      for (int c = 0; c < CPC; ++c) k4[c] = *reinterpret_cast<const float4*>(kb + ((c ^ sw) << 4));
+      unroll([&](auto C) {
+        constexpr int c = decltype(C)::value, x = r0 * DX + 4 * c;
+        acc = fma_4_rows<(x + 0) % 16>(a_q[x / 16], k4[c].x, acc);
+        acc = fma_4_rows<(x + 1) % 16>(a_q[x / 16], k4[c].y, acc);
+        acc = fma_4_rows<(x + 2) % 16>(a_q[x / 16], k4[c].z, acc);
+        acc = fma_4_rows<(x + 3) % 16>(a_q[x / 16], k4[c].w, acc);
+      }, std::make_integer_sequence<int, CPC>{});
+      if constexpr (r0 + NBUF < NR) PBSA_STAGE(r0 + NBUF)
+    }, std::make_integer_sequence<int, NR>{});
   }
 #undef PBSA_STAGE
 
@@ -391,6 +425,7 @@ __device__ __forceinline__ void select_body(const SelectArgs& a, const int bx, c
     int32_t* out = a.sel + ((size_t)h * a.nqb + i) * a.k;
     if (kk > 0) {
       // T = kk-th largest key, found bit by bit: the largest T with #{key >= T} >= kk
+      // (once exactly kk keys are at or above T, lower bits of it take none of them away)
       uint32_t T = 0;
       for (int bit = 31; bit >= 0; --bit) {
         const uint32_t cand = T | (1u << bit);
@@ -398,6 +433,7 @@ __device__ __forceinline__ void select_body(const SelectArgs& a, const int bx, c
 #pragma unroll
         for (int m = 0; m < NM; ++m) cnt += __popcll(__ballot(key[m] >= cand));
         if (cnt >= kk) T = cand;
+        if (cnt == kk) break;
       }
       int n_gt = 0;
 #pragma unroll
@@ -419,11 +455,10 @@ __device__ __forceinline__ void select_body(const SelectArgs& a, const int bx, c
   }
 }
 
-template <int D, int NM, int DX>
+template <int D, int NM>
 __global__ void __launch_bounds__(64 * (NM < 4 ? 4 : NM)) select_kernel(SelectArgs a) {
-  static_assert(DX == 32 || DX == 16, "a round is 8 or 4 load instructions per wave");
   extern __shared__ __align__(1024) unsigned char smem[];
-  select_body<D, NM, DX>(a, blockIdx.x, blockIdx.y, smem);
+  select_body<D, NM>(a, blockIdx.x, blockIdx.y, smem);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -809,13 +844,12 @@ hipError_t launch_summary_view(const pbsa_params& p, const float* S_sum, const i
   return hipGetLastError();
 }
 
-template <int D, int NM, int DX = 32>
+template <int D, int NM>
 static hipError_t launch_select_t(const SelectArgs& a, hipStream_t stream) {
-  constexpr size_t lds = (size_t)2 * NM * 64 * DX * 4 + (size_t)4 * D * 4 + (size_t)4 * NM * 64 * 4;
-  static_assert(lds <= 160 * 1024, "two rounds of every column, the queries and the logits must fit in LDS");
-  hipError_t e = allow_lds(select_kernel<D, NM, DX>, lds);
+  constexpr size_t lds = SelectGeo<D, NM>::LDS;
+  hipError_t e = allow_lds(select_kernel<D, NM>, lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((select_kernel<D, NM, DX>), dim3((a.nqb + 3) / 4, a.H), dim3(64 * (NM < 4 ? 4 : NM)), lds, stream, a);
+  hipLaunchKernelGGL((select_kernel<D, NM>), dim3((a.nqb + 3) / 4, a.H), dim3(64 * (NM < 4 ? 4 : NM)), lds, stream, a);
   return hipGetLastError();
 }
 
@@ -888,13 +922,13 @@ static hipError_t launch_select_logits(const pbsa_params& p, const bf16_t* Q, co
     if (nm <= 2) return launch_select_t<128, 2>(a, stream);
     if (nm <= 5) return launch_select_t<128, 5>(a, stream);
     if (nm <= 8) return launch_select_t<128, 8>(a, stream);
-    return launch_select_t<128, 11, 16>(a, stream);
+    return launch_select_t<128, 11>(a, stream);
   }
   static_assert(PBSA_MAX_N_LOC <= 11 * 64, "one lane per local block");
   if (nm <= 2) return launch_select_t<64, 2>(a, stream);
   if (nm <= 5) return launch_select_t<64, 5>(a, stream);
   if (nm <= 8) return launch_select_t<64, 8>(a, stream);
-  return launch_select_t<64, 11, 16>(a, stream);
+  return launch_select_t<64, 11>(a, stream);
 }
 
 template <int D, int NM>

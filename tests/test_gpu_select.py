@@ -1,0 +1,63 @@
+"""Selection where its instances and its pooling can go wrong, bit for bit against the oracle: 1 to 672 local blocks (each of the
+kernel's column counts, its smallest and its largest), the newest chunk's last block of 1 token to a whole one (at d = 64 two
+blocks share a wave: a whole and a short one together), pooled by the selection and in its own launch, and values whose
+logits overflow, are denormal or tie.  A logit is a chain of fused multiply-adds in one fixed order, so every bit is fixed."""
+import math
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from harness import synth  # noqa: E402
+from oracle.rollout import OracleState  # noqa: E402
+from tests.test_gpu_parity import DEV, compare_select, gpu, rnd  # noqa: E402,F401
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # d, B, query blocks, tokens of the last one, window chunks, k
+    (64, 64, 1, 1, 0, 1), (64, 64, 3, 63, 1, 2), (64, 128, 4, 64, 0, 4), (64, 128, 5, 65, 2, 3), (64, 128, 2, 127, 1, 9),
+    (128, 64, 2, 33, 2, 3), (128, 128, 3, 1, 0, 2), (128, 128, 4, 104, 1, 5), (128, 128, 6, 128, 0, 6),
+    (64, 64, 43, 64, 2, 17), (128, 64, 43, 7, 2, 40), (128, 64, 81, 64, 3, 12), (64, 64, 81, 31, 3, 324),
+    (64, 64, 161, 50, 1, 9), (128, 64, 161, 64, 3, 33),
+]
+
+
+def logits_and_sets(gpu, d, B, nqb, tail, w, k, scale_qk, values):  # noqa: F811
+    H, Nq, scale = 2, (nqb - 1) * B + tail, np.float32(1.0 / math.sqrt(d))
+    C = 1 if (w + 1) * nqb <= gpu["pbsa"].PBSA_MAX_N_LOC_AUX else gpu["pbsa"].PBSA_MAX_C + 1      # beyond: no update's workspace
+    st = OracleState(H, d, B, Nq, w, C, k, scale, fold=False)
+    c = gpu["cache"].PbsaCache(H, d, B, Nq, w, C, k, scale, fold=False, device=DEV)
+    lens = np.full(nqb, B, np.int32)
+    lens[-1] = tail
+    for g in range(w + 1):
+        Q, K, V = values(500 + 3 * g, H, Nq, d, scale_qk), values(501 + 3 * g, H, Nq, d, scale_qk), rnd(502 + 3 * g, H, Nq, d)
+        st.append_chunk(synth.to_blocks(K, B), synth.to_blocks(V, B), lens, g * nqb + np.arange(nqb))
+        c.append_chunk(gpu["wl"].bf16_tensor(K, DEV), gpu["wl"].bf16_tensor(V, DEV), g)
+    _, Z = st.select(Q, want_logits=True)
+    c.select(gpu["wl"].bf16_tensor(Q, DEV))
+    what = f"d{d} B{B} {nqb} blocks, last {tail}, window {w}, k {k}"
+    compare_select(c, st, what)
+    if c.Zl is not None:
+        got = c.Zl.view(-1)[:Z.size].cpu().numpy().reshape(Z.shape)
+        seen = np.arange(st.n_loc)[None] <= st.n_loc - nqb + np.arange(nqb)[:, None]     # the oracle leaves the others out
+        assert np.array_equal(got.view(np.uint32)[:, seen], Z.view(np.uint32)[:, seen]), f"{what}: logits differ"
+
+
+@pytest.mark.parametrize("case", CASES, ids=[f"d{c[0]}_B{c[1]}_{c[2]}x{c[4] + 1}_last{c[3]}_k{c[5]}" for c in CASES])
+def test_selection_every_bit(gpu, case):  # noqa: F811
+    logits_and_sets(gpu, *case, 1.0, lambda key, H, Nq, d, s: rnd(key, H, Nq, d, scale=s))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("kind", ["denormal", "overflow", "ties"])
+def test_selection_of_unusual_values(gpu, d, kind):  # noqa: F811
+    if kind == "ties":                       # few distinct values: many logits are equal, many are zero of either sign
+        values = lambda key, H, Nq, dd, s: synth.to_bf16_bits(np.round(synth.normals(synth.stream_key(9, "misc", key), H * Nq * dd)).reshape(H, Nq, dd) * 0)  # noqa: E731
+        logits_and_sets(gpu, d, 64, 7, 64, 1, 5, 1.0, values)
+        values = lambda key, H, Nq, dd, s: synth.to_bf16_bits(np.repeat(np.sign(synth.normals(synth.stream_key(9, "misc", key), H * Nq)).reshape(H, Nq, 1), dd, 2))  # noqa: E731
+        logits_and_sets(gpu, d, 64, 7, 64, 1, 5, 1.0, values)
+    else:
+        s = 2.0 ** -68 if kind == "denormal" else 2.0 ** 62      # products around the smallest normal; sums near the largest number
+        logits_and_sets(gpu, d, 64, 9, 60, 2, 6, s, lambda key, H, Nq, dd, sc: rnd(key, H, Nq, dd, scale=sc))
