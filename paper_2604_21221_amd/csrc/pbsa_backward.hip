@@ -8,8 +8,8 @@
 //   prep   per row -lse log2 e and -D (fp32, D from the bf16 tensors); per local block the query blocks that attend it
 //   dq     one wave per 64 query rows: their Q and dO fragments stay in registers, the 64-key tiles they attend
 //          (persistent slots, then the blocks of their row of sel) stream through LDS; where there are few such waves, two
-//          share a walk
-//   dkv    one two-wave workgroup per 64-key tile: its K and V fragments stay in registers, the 64-row tiles of the
+//          or four share a walk
+//   dkv    two waves per 64-key tile, or twice two where there are few, each pair with half of the walk: its K and V fragments stay in registers, the 64-row tiles of the
 //          query blocks that attend it (all of them for a persistent slot; those whose row of sel names the block
 //          otherwise, which prep has written down) stream through LDS
 // Both have a fixed side in registers (MFMA B operands) and a streamed side in LDS (A operands):
@@ -41,7 +41,6 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
-constexpr int kThreads = 128;
 constexpr int kTile = 64;
 constexpr float kLog2e = 1.4426950408889634f;
 
@@ -235,18 +234,19 @@ __global__ void __launch_bounds__(256) bwd_prep_kernel(BwdArgs a) {
   }
 }
 
-// The 32 rows of an output whose transpose a wave holds in its accumulators (element v of tile dt is dim 32 dt + 8 (v / 4)
-// + 4 (lane / 32) + v % 4 of row lane % 32), times `scale`, to memory, rows [0, n_rows) of them, through 32 D floats of LDS
-// that nobody else uses: a lane's 16 bytes of a row go to LDS at chunk c ^ row and leave in instructions of 1 KiB.  Straight
-// from the accumulators an instruction would write 32 bytes of each of 32 rows: 691.8 -> 685.5 us for select, forward and
-// backward at 12 x 4680 x 128 with 32 + 48 blocks of 64, 430.4 -> 426.0 with 8 + 16 blocks of 128, 165.1 -> 162.7 at 16 x 2048 x 128.
-template <int D>
-__device__ __forceinline__ void store_rows(float* dst, const f32x16 (&o)[D / 32], float scale, int n_rows, unsigned char* scratch) {
-  constexpr int CHUNKS = D / 4, RPS = 64 / CHUNKS;         // 16-byte chunks per row, rows per store instruction
+// 32 rows of an output, NT tiles of 32 dimensions each, whose transpose a wave holds in its accumulators (element v of tile
+// dt is dim 32 dt + 8 (v / 4) + 4 (lane / 32) + v % 4 of row lane % 32), times `scale`, to memory, rows [0, n_rows) of them,
+// through 32 NT KiB / 8 of LDS that nobody else uses: a lane's 16 bytes of a row go to LDS at chunk c ^ row and leave in
+// instructions of 1 KiB.  Straight from the accumulators an instruction would write 32 bytes of each of 32 rows: 691.8 ->
+// 685.5 us for select, forward and backward at 12 x 4680 x 128 with 32 + 48 blocks of 64, 430.4 -> 426.0 with 8 + 16 blocks of
+// 128, 165.1 -> 162.7 at 16 x 2048 x 128.
+template <int NT>
+__device__ __forceinline__ void store_rows(float* dst, int pitch, const f32x16* o, float scale, int n_rows, unsigned char* scratch) {
+  constexpr int CHUNKS = 8 * NT, RPS = 64 / CHUNKS;        // 16-byte chunks per row, rows per store instruction
   const int lane = threadIdx.x & 63, row = lane & 31, half = lane >> 5;
   float4* const lds = reinterpret_cast<float4*>(scratch);
 #pragma unroll
-  for (int dt = 0; dt < D / 32; ++dt)
+  for (int dt = 0; dt < NT; ++dt)
 #pragma unroll
     for (int v4 = 0; v4 < 4; ++v4)
       lds[row * CHUNKS + ((8 * dt + 2 * v4 + half) ^ (row & (CHUNKS - 1)))] =
@@ -256,26 +256,55 @@ __device__ __forceinline__ void store_rows(float* dst, const f32x16 (&o)[D / 32]
   for (int i = 0; i < 32 / RPS; ++i) {
     const int r = RPS * i + lane / CHUNKS, c = lane % CHUNKS;
     const float4 v = lds[r * CHUNKS + (c ^ (r & (CHUNKS - 1)))];
-    if (r < n_rows) *reinterpret_cast<float4*>(dst + (size_t)r * D + 4 * c) = v;
+    if (r < n_rows) *reinterpret_cast<float4*>(dst + (size_t)r * pitch + 4 * c) = v;
   }
 }
 
+// Partial sums change hands through LDS: a wave's accumulator tiles, one KiB per four elements and wave instruction.
+template <int NT>
+__device__ __forceinline__ void give_tiles(const f32x16* o, unsigned char* to) {
+  float4* const lds = reinterpret_cast<float4*>(to) + (threadIdx.x & 63);
+#pragma unroll
+  for (int dt = 0; dt < NT; ++dt)
+#pragma unroll
+    for (int v4 = 0; v4 < 4; ++v4)
+      lds[(4 * dt + v4) * 64] = make_float4(o[dt][4 * v4], o[dt][4 * v4 + 1], o[dt][4 * v4 + 2], o[dt][4 * v4 + 3]);
+}
+template <int NT>
+__device__ __forceinline__ void add_tiles(f32x16* o, const unsigned char* from) {
+  const float4* const lds = reinterpret_cast<const float4*>(from) + (threadIdx.x & 63);
+#pragma unroll
+  for (int dt = 0; dt < NT; ++dt)
+#pragma unroll
+    for (int v4 = 0; v4 < 4; ++v4) {
+      const float4 x = lds[(4 * dt + v4) * 64];
+      o[dt][4 * v4] += x.x;
+      o[dt][4 * v4 + 1] += x.y;
+      o[dt][4 * v4 + 2] += x.z;
+      o[dt][4 * v4 + 3] += x.w;
+    }
+}
+
 // ------------------------------------------------------------------------------------------------
-// dkv: one workgroup (two waves) per 64-key tile
+// dkv: one workgroup per 64-key tile, NP pairs of waves with 1 / NP of its walk each; in a pair a wave has 32 keys
 // ------------------------------------------------------------------------------------------------
-template <int D>
-__device__ __forceinline__ void dkv_body(const BwdArgs& a, const int block, unsigned char* smem) {
+template <int D, int NP>
+__device__ __forceinline__ void dkv_body(const BwdArgs& a, const int block, unsigned char* smem_wg) {
+  constexpr int kThreads = 128 * NP;
   constexpr int KS = D / 16, DT = D / 32, ROW = D * 2, TILE = kTile * ROW;
   constexpr int CH = D / 8, RPI = 64 / CH;          // 16-byte chunks per row, rows per load instruction
   constexpr int NI = 32 / RPI;                      // load instructions per wave per tile (its 32 rows)
   constexpr int HI_XOR = CH == 16 ? 16 : 0;         // row + 8 flips the lowest bit of the chunk permutation when it has 4 bits
   __shared__ int cnt_s[2 * 8];
-  __shared__ __align__(256) float rows_f[4 * 64];   // per ring entry, the scalars of the half tile's rows (BwdArgs::rows)
-  // ring: entry e holds T1 at e * 2 TILE and T2 behind it
-  int* lst_a = reinterpret_cast<int*>(smem + 4 * TILE);   // per streamed tile: where it is
+  __shared__ __align__(256) float rows_wg[NP * 4 * 64];   // per ring entry, the scalars of the half tile's rows (BwdArgs::rows)
+  // a ring for each pair of waves -- entry e holds a half of T1 at e TILE and of T2 behind it -- and, behind the rings, per
+  // streamed tile: where it is
+  int* lst_a = reinterpret_cast<int*>(smem_wg + NP * 4 * TILE);
   const int SUB = a.B / kTile;
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave_wg = __builtin_amdgcn_readfirstlane(tid >> 6), pair = wave_wg >> 1, wave = wave_wg & 1;
+  unsigned char* const smem = smem_wg + pair * (4 * TILE);
+  float* const rows_f = rows_wg + pair * 256;
   const int qn = lane & 31, half = lane >> 5;
   const float c2 = a.scale * kLog2e;
 
@@ -340,7 +369,7 @@ __device__ __forceinline__ void dkv_body(const BwdArgs& a, const int block, unsi
     where = i;                                      // row tile i covers tokens 64 i ..
     return a.Nq - i * kTile > 0;
   };
-  constexpr int kMaxRounds = 8;            // 512 query blocks of two tiles / 128 threads
+  constexpr int kMaxRounds = 8 / NP;       // 512 query blocks of two tiles / threads
   const int n_rounds = min((n_cand + kThreads - 1) / kThreads, kMaxRounds);
   // every candidate is looked at once (a look is a chain of dependent loads); what it found stays in registers
   // until the counts of all rounds are known
@@ -351,20 +380,23 @@ __device__ __forceinline__ void dkv_body(const BwdArgs& a, const int block, unsi
     c_where[r] = 0;
     const bool on = r < n_rounds && classify(r * kThreads + tid, c_where[r]);
     c_mask[r] = __ballot(on);
-    if (r < n_rounds && lane == 0) cnt_s[r * 2 + wave] = __popcll(c_mask[r]);
+    if (r < n_rounds && lane == 0) cnt_s[r * 2 * NP + wave_wg] = __popcll(c_mask[r]);
   }
   __syncthreads();
-  int n_tiles = 0;
-  for (int q = 0; q < 2 * n_rounds; ++q) n_tiles += cnt_s[q];
+  int n_listed = 0;
+  for (int q = 0; q < 2 * NP * n_rounds; ++q) n_listed += cnt_s[q];
 #pragma unroll
   for (int r = 0; r < kMaxRounds; ++r) {
     if (r < n_rounds && ((c_mask[r] >> lane) & 1)) {
       int pos = lanes_below(c_mask[r]);
-      for (int q = 0; q < r * 2 + wave; ++q) pos += cnt_s[q];
+      for (int q = 0; q < r * 2 * NP + wave_wg; ++q) pos += cnt_s[q];
       lst_a[pos] = c_where[r];
     }
   }
   __syncthreads();
+  // this pair's share of the list
+  const int n_most = (n_listed + NP - 1) / NP, t_first = pair * n_most, n_tiles = min(n_most, n_listed - t_first);
+  lst_a += t_first;
 
   // they have arrived before the walk starts: no wait for them inside it, where one would also wait for the tiles
 #pragma unroll
@@ -629,7 +661,9 @@ __device__ __forceinline__ void dkv_body(const BwdArgs& a, const int block, unsi
       sc_step = 0u - sc_step;
     }
   }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // the trailing loads land before the workgroup goes
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // the trailing loads land before the ring is used otherwise
+  if constexpr (NP > 1)                    // a pair with a shorter share meets the other's barriers
+    for (int i = 2 * max(n_tiles, 0) + (n_tiles > 0); i < 2 * n_most + (n_most > 0); ++i) __builtin_amdgcn_s_barrier();
   // the compiler does not see the matrix instructions that wrote the output accumulators: let the pipe drain
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) {
@@ -639,25 +673,43 @@ __device__ __forceinline__ void dkv_body(const BwdArgs& a, const int block, unsi
 
   // ---- outputs -------------------------------------------------------------------------------------
   // every row of the tile's slot is written: zeros past the valid length and for a block nobody attends
-  __syncthreads();                         // the ring is dead: what either wave fetched last has landed
+  __syncthreads();                         // the rings are dead: what any wave fetched last has landed
   const bool exists = 32 * wave + qn < fixed_len;
-  store_rows<D>(dk + (size_t)(32 * wave) * D, out1, exists ? a.scale : 0.0f, 32, smem + wave * (2 * TILE));
-  store_rows<D>(dv + (size_t)(32 * wave) * D, out2, exists ? 1.0f : 0.0f, 32, smem + wave * (2 * TILE) + TILE);
+  unsigned char* const mine = smem + wave * (2 * TILE);
+  const size_t row0 = (size_t)(32 * wave) * D;
+  const float k_scale = exists ? a.scale : 0.0f, v_scale = exists ? 1.0f : 0.0f;
+  if constexpr (NP == 1) {
+    store_rows<DT>(dk + row0, D, out1, k_scale, 32, mine);
+    store_rows<DT>(dv + row0, D, out2, v_scale, 32, mine + TILE);
+  } else {
+    // the first pair finishes dK, the second dV
+    const unsigned char* const theirs = smem_wg + (pair ^ 1) * (4 * TILE) + wave * (2 * TILE);
+    if (pair == 0) give_tiles<DT>(out2, mine);
+    else give_tiles<DT>(out1, mine);
+    __syncthreads();
+    if (pair == 0) {
+      add_tiles<DT>(out1, theirs);
+      store_rows<DT>(dk + row0, D, out1, k_scale, 32, mine + TILE);
+    } else {
+      add_tiles<DT>(out2, theirs);
+      store_rows<DT>(dv + row0, D, out2, v_scale, 32, mine + TILE);
+    }
+  }
 }
 
 // ------------------------------------------------------------------------------------------------
 // dq with 64 query rows per wave (two MFMA column groups of 32), so that every K or V fragment read from LDS -- row-wise
 // for the first products, transposed for the second -- feeds two MFMAs.  The wave stages its own half tiles (32 keys of K
 // and of V per ring entry, two entries) and is the only one to read them: no barrier in the walk.  The two waves of a
-// workgroup (PAIR) have a row tile each or, dq_split, half of one row tile's walk each: the two sums meet in LDS at the end,
-// in the same order whichever wave adds.  Q and dO fragments and the dQ^T accumulators fill the accumulator half of the register file
+// workgroup have a row tile each or, dq_split, half of one row tile's walk each, four a quarter of it: the sums meet in LDS
+// at the end and are added in the order of the waves.  Q and dO fragments and the dQ^T accumulators fill the accumulator half of the register file
 // (128 + 128 registers at d = 128).  Bound at 12 x 4680 x 128: matrix and vector work in one wave per SIMD at the clock the
 // chip holds under it (222 GFLOP in 215 us, 1.03 PFLOP/s; a library product of 8192^3 reaches 1.19).  The elementwise stages
 // are spread over 40 of a turn's 48 MFMAs; over 28 of them: 712.8 against 708.3 us for select, forward and backward, 89.8
 // against 88.2 at 3 x 1500 x 64.  Two waves to a workgroup that share the tiles both attend (half the traffic with
 // 128-token blocks, three half tiles on their way): 217 us, and 35.3 against 32.6 at 3 x 1500 x 64, where it lost.
 // ------------------------------------------------------------------------------------------------
-template <int D, bool PAIR>
+template <int D, int NWV>
 __device__ __forceinline__ void dq_body(const BwdArgs& a, const int block, unsigned char* smem_wg) {
   constexpr int KS = D / 16, DT = D / 32, ROW = D * 2, TILE = kTile * ROW, HALF = TILE / 2;
   constexpr int CH = D / 8, RPI = 64 / CH;          // 16-byte chunks per row, rows per load instruction
@@ -671,12 +723,12 @@ __device__ __forceinline__ void dq_body(const BwdArgs& a, const int block, unsig
   const int n_pers = (a.C + 1) * SUB, n_cand = n_pers + a.k * SUB;
   // each wave has a ring of its own -- entry e holds 32 rows of K at e * TILE and 32 rows of V behind them -- and, behind
   // the rings, a list
-  constexpr int NWV = PAIR ? 2 : 1;        // waves of the workgroup
   unsigned char* const smem = smem_wg + wave * (2 * TILE);
   uint32_t* const lst = reinterpret_cast<uint32_t*>(smem_wg + NWV * 2 * TILE) + wave * n_cand;
   int h, r_tile;
   head_item(block, a.H, h, r_tile);
-  if (!(PAIR && a.dq_split)) r_tile = NWV * r_tile + wave;
+  const bool share = NWV == 4 || (NWV == 2 && a.dq_split);  // the waves share one row tile's walk
+  if (!share) r_tile = NWV * r_tile + wave;
   if (r_tile * kTile >= a.Nq) return;
   const float c2 = a.scale * kLog2e;
   const int i_blk = r_tile * kTile / a.B;
@@ -709,9 +761,10 @@ __device__ __forceinline__ void dq_body(const BwdArgs& a, const int block, unsig
   }
   n_tiles = __builtin_amdgcn_readfirstlane(n_tiles);
   int t_first = 0;                         // the wave's share of the list
-  if (PAIR && a.dq_split) {
-    t_first = wave * ((n_tiles + 1) / 2);
-    n_tiles = wave ? n_tiles : (n_tiles + 1) / 2;
+  if (share) {
+    const int n_most = (n_tiles + NWV - 1) / NWV;
+    t_first = wave * n_most;
+    n_tiles = min(n_tiles, t_first + n_most);
   }
 
   // ---- fixed fragments (B operands) of both column groups: row 32 n + lane % 32, dims 16 ks + 8 (lane / 32) .. + 8 ----
@@ -988,37 +1041,33 @@ __device__ __forceinline__ void dq_body(const BwdArgs& a, const int block, unsig
   for (int n = 0; n < 2; ++n)
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) asm volatile("s_nop 15\n\ts_nop 15" : "+a"(out[n][dt]));
-  if (PAIR && a.dq_split) {
-    // each wave leaves the other's column group in its own ring, which nobody reads any more, and adds what it finds for
-    // its group in the other's: the same two numbers added, whichever wave does it
-    auto swap = [&](int mine, int other) {
-      float4* const give = reinterpret_cast<float4*>(smem) + lane;
+  if constexpr (NWV > 1) {
+    if (share) {
+      // every wave leaves its sums in its own ring, which nobody reads any more, and adds up its part of the tiles, in the
+      // order of the waves: a column group (two waves), half of one (four)
+      constexpr int NT = NWV == 4 ? DT / 2 : DT;
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int v4 = 0; v4 < 4; ++v4)
-          give[(4 * dt + v4) * 64] = make_float4(out[other][dt][4 * v4], out[other][dt][4 * v4 + 1], out[other][dt][4 * v4 + 2],
-                                                 out[other][dt][4 * v4 + 3]);
+      for (int n = 0; n < 2; ++n) give_tiles<DT>(out[n], smem + n * TILE);
       __syncthreads();
-      const float4* const take = reinterpret_cast<const float4*>(smem_wg + (wave ^ 1) * (2 * TILE)) + lane;
+      const int n = wave & 1, dt0 = (wave >> 1) * NT;
+      const unsigned char* const from = smem_wg + n * TILE + dt0 * 4096;
+      f32x16 sum[NT];
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
+      for (int dt = 0; dt < NT; ++dt)
 #pragma unroll
-        for (int v4 = 0; v4 < 4; ++v4) {
-          const float4 o = take[(4 * dt + v4) * 64];
-          out[mine][dt][4 * v4] += o.x; out[mine][dt][4 * v4 + 1] += o.y;
-          out[mine][dt][4 * v4 + 2] += o.z; out[mine][dt][4 * v4 + 3] += o.w;
-        }
-    };
-    if (wave == 0) swap(0, 1);
-    else swap(1, 0);
-    __syncthreads();                       // both have taken theirs
+        for (int v = 0; v < 16; ++v) sum[dt][v] = 0.0f;
+#pragma unroll
+      for (int w = 0; w < NWV; ++w) add_tiles<NT>(sum, from + w * (2 * TILE));
+      __syncthreads();                     // everybody has taken theirs
+      store_rows<NT>(a.dQ + ((size_t)h * a.Nq + (size_t)r_tile * kTile + 32 * n) * D + 32 * dt0, D, sum, a.scale,
+                     fixed_len - 32 * n, smem);
+      return;
+    }
   }
 #pragma unroll
   for (int n = 0; n < 2; ++n)
-    if (!(PAIR && a.dq_split) || n == wave)
-      store_rows<D>(a.dQ + ((size_t)h * a.Nq + (size_t)r_tile * kTile + 32 * n) * D, out[n], a.scale, fixed_len - 32 * n,
-                    smem + n * TILE);
+    store_rows<DT>(a.dQ + ((size_t)h * a.Nq + (size_t)r_tile * kTile + 32 * n) * D, D, out[n], a.scale, fixed_len - 32 * n,
+                   smem + n * TILE);
 }
 
 // dq and dkv as one launch (neither needs what the other writes) or as a launch each.  A launch's time ends with its longest
@@ -1027,20 +1076,24 @@ __device__ __forceinline__ void dq_body(const BwdArgs& a, const int block, unsig
 // Select, forward and backward, two launches -> one (with dq_split where it applies): 712 -> 696 us at 12 x 4680 x 128 with
 // 32 + 48 blocks of 64, 446 -> 433 with 8 + 16 blocks of 128, 227 -> 134 at 4 x 3000 x 128, 88 -> 57 at 3 x 1500 x 64.
 constexpr int kDq = 1, kDkv = 2;
-template <int D, int PARTS>
-__global__ void __launch_bounds__(PARTS == kDq ? 64 : kThreads) __attribute__((amdgpu_waves_per_eu(PARTS == kDkv ? 2 : 1)))
+template <int D, int PARTS, int NWV>
+__global__ void __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(PARTS == kDkv ? 2 : 1)))
     bwd_walk_kernel(BwdArgs a, int n_dq) {
   extern __shared__ __align__(1024) unsigned char smem[];
-  if (PARTS == kDq || (PARTS != kDkv && (int)blockIdx.x < n_dq)) dq_body<D, PARTS != kDq>(a, (int)blockIdx.x, smem);
-  else dkv_body<D>(a, (int)blockIdx.x - n_dq, smem);
+  if constexpr (PARTS == kDq) {
+    dq_body<D, NWV>(a, (int)blockIdx.x, smem);
+  } else {
+    if (PARTS != kDkv && (int)blockIdx.x < n_dq) dq_body<D, NWV>(a, (int)blockIdx.x, smem);
+    else dkv_body<D, NWV / 2>(a, (int)blockIdx.x - n_dq, smem);
+  }
 }
 
-template <int D, int PARTS>
+template <int D, int PARTS, int NWV>
 hipError_t launch_walk(const BwdArgs& a, unsigned n_dq, unsigned n_dkv, size_t lds, hipStream_t stream) {
-  const auto kernel = bwd_walk_kernel<D, PARTS>;
+  const auto kernel = bwd_walk_kernel<D, PARTS, NWV>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kernel, dim3(n_dq + n_dkv), dim3(PARTS == kDq ? 64 : kThreads), lds, stream, a, (int)n_dq);
+  hipLaunchKernelGGL(kernel, dim3(n_dq + n_dkv), dim3(64 * NWV), lds, stream, a, (int)n_dq);
   return hipGetLastError();
 }
 
@@ -1090,9 +1143,20 @@ hipError_t launch_attention_bwd(const pbsa_params& p, const bf16_t* Q, const bf1
   // and 248, 8 x 2000 with 6 + 8 blocks 95 and 71.
   const int rounds = (n_tiles + 1023) / 1024;
   if (p.d == 64 && n_cand >= 64 && 5 * n_tiles >= 4 * 1024 * rounds) {
-    e = launch_walk<64, kDq>(a, head_items(n_row_tiles, p.H), 0, 2 * tile + (size_t)4 * n_cand + 16, stream);
+    e = launch_walk<64, kDq, 1>(a, head_items(n_row_tiles, p.H), 0, 2 * tile + (size_t)4 * n_cand + 16, stream);
     if (e != hipSuccess) return e;
-    return launch_walk<64, kDkv>(a, 0, n_dkv, lds_dkv, stream);
+    return launch_walk<64, kDkv, 2>(a, 0, n_dkv, lds_dkv, stream);
+  }
+  // Four waves share a walk where there are few walks: a workgroup of four has a compute unit to itself, and at up to 448
+  // workgroups the longest walks, which come first, end half as late (2 waves -> 4: 52 -> 45 us at 3 x 1500 x 64, 309
+  // workgroups; 99 -> 90 at 3 x 2000 x 128, 438; 140 -> 112 at 1 x 4680 x 128, 403; but 73 -> 74 at 6 x 1200 x 128, 510,
+  // 86 -> 92 at 4 x 3000 x 64, 836).  Walks of fewer than eight row tiles gain less than the meeting of the sums costs
+  // (50.0 -> 50.4 at 12 x 300 x 128, five row tiles).
+  const size_t lds4 = 8 * tile + (size_t)4 * std::max(4 * n_cand, sub * p.nqb) + 16;
+  if (n_tiles + p.H * (p.C + 1 + p.n_loc) * sub <= 448 && n_row_tiles >= 8 && lds4 <= 156 * 1024) {
+    const unsigned n_dq = head_items(n_row_tiles, p.H);
+    return p.d == 128 ? launch_walk<128, kDq | kDkv, 4>(a, n_dq, n_dkv, lds4, stream)
+                      : launch_walk<64, kDq | kDkv, 4>(a, n_dq, n_dkv, lds4, stream);
   }
   // Two waves share a walk where the row tiles are at most as many as the compute units: each walk has a unit to itself, and
   // half of it ends earlier (4 x 3000 x 128, 188 row tiles: 134 us split).  With 512 (16 x 2048 x 128) a row tile per wave
@@ -1100,7 +1164,8 @@ hipError_t launch_attention_bwd(const pbsa_params& p, const bf16_t* Q, const bf1
   a.dq_split = n_tiles <= 256;
   const unsigned n_dq = head_items(a.dq_split ? n_row_tiles : (n_row_tiles + 1) / 2, p.H);
   const size_t lds = std::max(lds_dkv, 4 * tile + (size_t)8 * n_cand + 16);
-  return p.d == 128 ? launch_walk<128, kDq | kDkv>(a, n_dq, n_dkv, lds, stream) : launch_walk<64, kDq | kDkv>(a, n_dq, n_dkv, lds, stream);
+  return p.d == 128 ? launch_walk<128, kDq | kDkv, 2>(a, n_dq, n_dkv, lds, stream)
+                    : launch_walk<64, kDq | kDkv, 2>(a, n_dq, n_dkv, lds, stream);
 }
 
 }  // namespace pbsa

@@ -21,9 +21,16 @@ CASES = [
     ("rows63",     9, 128, 64,  127,  0, 1, 1, 0, 1, [32]),
     ("two_words",  1, 64,  64,  2113, 0, 1, 3, 0, 0, [64]),
     ("three_words", 2, 128, 64, 4100, 0, 1, 2, 0, 1, [64]),
-    # up to 256 row tiles in all, two waves share a row tile's walk: a walk of one tile leaves one of them nothing
+    # up to 256 row tiles in all and fewer than eight per head, two waves share a row tile's walk: a walk of one tile leaves
+    # one of them nothing
     ("one_tile",   1, 128, 64,  70,   0, 1, 1, 0, 1, [0]),
     ("three_tiles", 2, 64, 64,  130,  0, 2, 1, 0, 0, [64, 3]),
+    # up to 448 workgroups of row tiles and key tiles, eight row tiles or more per head: four waves share a walk, of one tile,
+    # of a few, of many, the last one ragged; just above, two share it again
+    ("four_one",   1, 64,  64,  520,  0, 1, 1, 0, 1, [0]),
+    ("four_few",   2, 128, 128, 1100, 0, 2, 1, 0, 0, [128, 5]),
+    ("four_many",  1, 128, 64,  650,  1, 3, 9, 0, 1, [64, 1, 0]),
+    ("two_above",  9, 64,  64,  1600, 0, 1, 1, 0, 1, [64]),
     # more than 256: a row tile per wave, an odd number of them per head
     ("pairs_128",  9, 128, 64,  1800, 0, 1, 2, 0, 1, [64]),
     ("pairs_64",   9, 64,  128, 1830, 0, 1, 1, 0, 0, [70]),
