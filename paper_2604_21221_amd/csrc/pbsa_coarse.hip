@@ -854,9 +854,11 @@ static hipError_t launch_select_t(const SelectArgs& a, hipStream_t stream) {
 }
 
 // Whether the selection launch pools the query blocks itself.  Not when nothing is selected and no logits are wanted
-// (there is none).  launch_select_apply leaves the queries in its pooling launch: the fold sets that launch's length
+// (there is none), and not when key blocks are to be pooled first: that launch takes the queries along (a denoising pass
+// of 12 x 4680 x 128: 511.7 -> 503.9 us for four; of 2 x 600 x 128: 151 -> 140 for four, of 3 x 1500 x 64 140 -> 130 for three).
+// launch_select_apply leaves the queries in its pooling launch: the fold sets that launch's length
 // and hides their 14 MB (186.3 us per chained step against 187.8 at H = 12, 4680 rows of 128, blocks of 64).
-static bool select_pools_queries(const pbsa_params& p, const float* Zl) { return p.k > 0 || Zl; }
+static bool select_pools_queries(const pbsa_params& p, const float* Zl) { return (p.k > 0 || Zl) && p.pool_from >= p.n_loc; }
 
 static PoolArgs select_pool_args(const pbsa_params& p, const bf16_t* Q, const bf16_t* Kl, const int32_t* l_len,
                                  const int32_t* l_map, float* Kc_l, float* Qc, bool with_queries) {
@@ -881,7 +883,8 @@ static hipError_t launch_select_logits(const pbsa_params& p, const bf16_t* Q, co
 hipError_t launch_select(const pbsa_params& p, const bf16_t* Q, const bf16_t* Kl, const int32_t* l_len,
                          const int32_t* l_map, float* Kc_l, float* Qc, int32_t* sel, float* Zl,
                          hipStream_t stream) {
-  const PoolArgs pa = select_pool_args(p, Q, Kl, l_len, l_map, Kc_l, Qc, !select_pools_queries(p, Zl));
+  const bool in_select = select_pools_queries(p, Zl);
+  const PoolArgs pa = select_pool_args(p, Q, Kl, l_len, l_map, Kc_l, Qc, !in_select);
   if (pa.n_jobs > 0) {
     const int jpw = kThreads / (p.d / 2);
     const dim3 grid((pa.n_jobs + jpw - 1) / jpw);
@@ -890,7 +893,7 @@ hipError_t launch_select(const pbsa_params& p, const bf16_t* Q, const bf16_t* Kl
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  return launch_select_logits(p, Q, l_map, Kc_l, Qc, sel, Zl, stream);
+  return launch_select_logits(p, in_select ? Q : nullptr, l_map, Kc_l, Qc, sel, Zl, stream);
 }
 
 hipError_t launch_select_apply(const pbsa_params& p, const bf16_t* Q, const bf16_t* Kl, const int32_t* l_len,
