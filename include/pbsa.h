@@ -141,6 +141,12 @@ int pbsa_append_chunk(const pbsa_params* p, const void* K, const void* V, int64_
                       int64_t v_stride_h, int64_t v_stride_t, int32_t slot0, int32_t zero_tail, void* Kl, void* Vl,
                       float* Kc_l, void* hip_stream);
 
+/* pbsa_append_chunk that also pools the queries of the chunk (Q [H][Nq][d] bf16 with the element strides given, last dimension
+ * contiguous; Q and Qc both or neither) into Qc [H][nqb][d] fp32, the bits pbsa_select_blocks would write there. */
+int pbsa_append_chunk_pool(const pbsa_params* p, const void* K, const void* V, int64_t k_stride_h, int64_t k_stride_t,
+                           int64_t v_stride_h, int64_t v_stride_t, int32_t slot0, int32_t zero_tail, void* Kl, void* Vl,
+                           float* Kc_l, const void* Q, int64_t q_stride_h, int64_t q_stride_t, float* Qc, void* hip_stream);
+
 /* Coarse routing inside the local region (Eq. 10-11).  Pools the chunk's queries into Qc, refreshes
  * the pooled keys Kc_l of logical blocks >= pool_from, scores every visible local block of every
  * query block with dot(Qc_i, Kc_l) (the argument of Eq. 10's softmax, which is monotone per row)
@@ -150,6 +156,11 @@ int pbsa_append_chunk(const pbsa_params* p, const void* K, const void* V, int64_
 int pbsa_select_blocks(const pbsa_params* p, const void* Q, const void* Kl, const int32_t* l_len,
                        const int32_t* l_map, float* Kc_l, float* Qc, int32_t* sel, float* Zl, void* ws,
                        size_t ws_bytes, void* hip_stream);
+
+/* pbsa_select_blocks where everything has been pooled already: Qc and the pooled keys Kc_l of all n_loc blocks are given
+ * (pool_from is not looked at).  The same block sets and logits, bit for bit. */
+int pbsa_select_pooled(const pbsa_params* p, const int32_t* l_map, const float* Kc_l, const float* Qc, int32_t* sel, float* Zl,
+                       void* hip_stream);
 
 /* PBSA fine stage (Eq. 3-5): for each query token one softmax, scaled by p->scale, over every
  * valid token of every non-empty persistent slot 0..C (summary included) and every valid token of

@@ -13,6 +13,9 @@ import torch
 from . import pbsa
 
 
+_KEYS, _KEYS_AND_QUERIES = 1, 2              # what an append pooled
+
+
 class PbsaCache:
     def __init__(self, H, d, B, Nq, window_chunks, C, k, scale, n_sink=0, causal=1, fold=True, device="cuda:0",
                  pass_logits=True, ring_chunks=None):
@@ -115,8 +118,8 @@ class PbsaCache:
     def _device_maps(self, want_ids=False):
         """l_map / l_len (and on request l_id) device tensors of the current ring arrangement.  The map
         and the lengths depend only on the ring positions and are cached per arrangement; ids of
-        consecutive chunks are a window of one device-resident arange, so the steady state issues no
-        copy and no kernel here."""
+        consecutive chunks are a window of one device-resident arange (its address, for the call that
+        follows), so the steady state issues no copy and no kernel here."""
         key = tuple(self.chunk_pos)
         m = self._maps.get(key)
         if m is None:
@@ -128,19 +131,19 @@ class PbsaCache:
         if not want_ids:
             return m[0], m[1], None
         ids = self.chunk_ids
-        if ids[0] >= 0 and all(b == a + 1 for a, b in zip(ids, ids[1:])):
+        if ids[0] >= 0 and ids == list(range(ids[0], ids[0] + len(ids))):
             lo, hi = ids[0] * self.nqb, (ids[-1] + 1) * self.nqb
             if self._arange64 is None or self._arange64.numel() < hi:
                 self._arange64 = torch.arange(max(2 * hi, 64 * self.cap), dtype=torch.int64, device=self.dev)
-            l_id = self._arange64[lo:hi]
+            l_id = self._arange64.data_ptr() + 8 * lo           # a slice of it, without the tensor object
         else:
             ar = torch.arange(self.nqb)
             l_id = torch.cat([g * self.nqb + ar for g in ids]).to(torch.int64).to(self.dev)
         return m[0], m[1], l_id
 
     def params(self, n_evict=0, pool_from=0, Q=None, O=None):
-        qs = (Q.stride(0), Q.stride(1)) if Q is not None else None
-        os_ = (O.stride(0), O.stride(1)) if O is not None else None
+        qs = Q.stride() if Q is not None else None
+        os_ = O.stride() if O is not None else None
         return pbsa.make_params(self.H, self.d, self.B, self.Nq, self.n_loc, self.cap, self.C, self.k, self.scale,
                                 self.n_sink, self.causal, n_evict, pool_from, qs, os_)
 
@@ -170,58 +173,57 @@ class PbsaCache:
         """Copy a chunk's K/V ([H][Nq][d] bf16, token-major) into the next ring position, block-major."""
         self._append(K, V, chunk_id, False)
 
-    def _append(self, K, V, chunk_id, pool):
+    def _append(self, K, V, chunk_id, pool, Q=None):
         """append_chunk; pool: the pooled keys are taken as the rows pass, for a selection that follows at once (whoever
-        appends by themselves may still change the rows in the ring, and the selection pools what it finds there).
-        Returns whether they were."""
+        appends by themselves may still change the rows in the ring, and the selection pools what it finds there), and with
+        Q, where that is of use, the queries are pooled along.
+        Returns whether they were: nothing, _KEYS, or _KEYS_AND_QUERIES."""
         if K is None or V is None:
             raise TypeError("append_chunk takes K and V (adopt_chunk declares a chunk that is in the ring already)")
         assert len(self.chunk_pos) <= self.w, "update() slides the window before the next append"
         pos = self.n_appended % self.ring
-        pooled = self._write_chunk(pos, K, V, True, pool)       # may refuse them: the chunk counts once it is there
+        pooled = self._write_chunk(pos, K, V, True, pool, Q)    # may refuse them: the chunk counts once it is there
         self.chunk_pos.append(pos)
         self.chunk_ids.append(chunk_id)
         self.n_appended += 1
         self.stale_from = min(self.stale_from, self.n_loc - self.nqb)
         return pooled
 
-    def _in_place(self, K, V):
-        """Whether pbsa_append_chunk takes K and V (or None) as they are and nothing but their bytes counts: bf16 on this GPU,
+    def _in_place(self, *tensors):
+        """Whether pbsa_append_chunk takes K and V (or None, and the queries) as they are and nothing but their bytes counts: bf16 on this GPU,
         whole, rows contiguous and aligned; nothing that torch would record, transform or refuse in a copy (gradients,
         forward mode, function transforms, dispatch modes, tracing, inference tensors outside their mode); and not rows of
         the ring itself: K is copied before V is, and a launch knows no such order."""
         Kl, Vl = self.Kl, self.Vl
-        dev, shape = Kl.device, (self.H, self.Nq, self.d)
-        ring = Kl.untyped_storage()._cdata, Vl.untyped_storage()._cdata
         watched = torch.is_grad_enabled()
         if watched and (Kl.requires_grad or Vl.requires_grad):
             return False
-        for x in (K, V):
-            if x is None:
-                continue
-            if (type(x) is not torch.Tensor or x.dtype is not torch.bfloat16 or x.layout is not torch.strided or x.device != dev
-                    or x.shape != shape or (watched and x.requires_grad) or x.is_neg() or x.untyped_storage()._cdata in ring):
-                return False
-            sh, st, one = x.stride()
-            if one != 1 or sh % 8 or st % 8 or st < self.d or x.data_ptr() % 16:
-                return False
+        if not pbsa.plain_rows(Kl, Vl, self.H, self.Nq, self.d, watched, *tensors):
+            return False
+        dev = Kl.device
         return ((dev.index is None or dev.index == torch._C._cuda_getDevice())       # the library launches on the current device
                 and torch.autograd.forward_ad._current_level < 0 and torch._C._functorch.peek_interpreter_stack() is None
                 and torch._C._len_torch_dispatch_stack() == 0 and torch._C._get_tracing_state() is None
                 and not torch.compiler.is_compiling() and (not Kl.is_inference() or torch.is_inference_mode_enabled()))
 
-    def _write_chunk(self, pos, K, V, zero_tail, pool):
-        """K and V (either may be None) into ring position `pos` in one launch, with the pooled keys if asked for; tensors
-        of another type, device or layout, and whatever autograd follows, go through torch.  Returns whether the pooled
-        keys were written."""
+    def _write_chunk(self, pos, K, V, zero_tail, pool, Q=None):
+        """K and V (either may be None) into ring position `pos` in one launch, with the pooled keys and queries if asked for;
+        tensors of another type, device or layout, and whatever autograd follows, go through torch.  Returns what was pooled
+        (_append)."""
         if K is None and V is None:
-            return False
+            return 0
         if self._by_launch and self._in_place(K, V):
             # as an in-place copy would, so that a backward which saved the ring notices
             torch.autograd.graph.increment_version([dst for dst, src in ((self.Kl, K), (self.Vl, V)) if src is not None])
             pool = pool and K is not None
-            pbsa.pbsa_append_chunk(self._full, K, V, pos * self.nqb, zero_tail, self.Kl, self.Vl, self.Kc_l if pool else None)
-            return pool
+            args = self._full, K, V, pos * self.nqb, zero_tail, self.Kl, self.Vl, self.Kc_l if pool else None
+            # up to two workgroups per compute unit the queries' blocks cost the launch nothing
+            if (pool and Q is not None and self._pending is None and self.H * self.nqb <= 170
+                    and pbsa.plain_rows(self.Kl, self.Vl, self.H, self.Nq, self.d, torch.is_grad_enabled(), Q)):
+                pbsa.pbsa_append_chunk(*args, None, Q, self.Qc)
+                return _KEYS_AND_QUERIES
+            pbsa.pbsa_append_chunk(*args)
+            return _KEYS if pool else 0
         for dst, src in ((self.Kl, K), (self.Vl, V)):
             if src is None:
                 continue
@@ -229,7 +231,7 @@ class PbsaCache:
             view[:, :self.Nq] = src
             if zero_tail and self.nqb * self.B > self.Nq:
                 view[:, self.Nq:] = 0
-        return False
+        return 0
 
     def rewrite_chunk(self, K=None, V=None):
         """Between the denoising passes of one chunk (Sec. 3.1: each chunk is denoised in T passes over the
@@ -254,7 +256,7 @@ class PbsaCache:
         return self._select(Q, False)
 
     def _select(self, Q, pooled):
-        """select; pooled: the newest chunk's pooled keys have just been written (anything older that is stale has not)."""
+        """select; pooled: what of the newest chunk has just been pooled (_append); anything older that is stale has not."""
         l_map, l_len, _ = self._device_maps()
         fresh = pooled and self.stale_from == self.n_loc - self.nqb
         p = self.params(pool_from=self.n_loc if fresh else self.stale_from, Q=Q)
@@ -262,6 +264,8 @@ class PbsaCache:
             pbsa.pbsa_select_blocks_apply(p, Q, self.Kl, l_len, l_map, self.Kc_l, self.Qc, self.sel, self.Zl, self._pending,
                                           self.Kp, self.Vp, self.p_len, self.S_sum, self.S_cnt, self.Vl, self.ws)
             self._pending = None
+        elif fresh and pooled == _KEYS_AND_QUERIES:
+            pbsa.pbsa_select_blocks(p, Q, self.Kl, l_len, l_map, self.Kc_l, self.Qc, self.sel, self.Zl, pooled=True)
         else:
             pbsa.pbsa_select_blocks(p, Q, self.Kl, l_len, l_map, self.Kc_l, self.Qc, self.sel, self.Zl)
         self.stale_from = self.n_loc
@@ -362,7 +366,7 @@ class PbsaCache:
 
     def step_fine(self, Q, K, V, chunk_id, O=None, lse=None):
         """The step with the fine-mass score: append, select, attend (recording the mass), update."""
-        self._select(Q, self._append(K, V, chunk_id, True))
+        self._select(Q, self._append(K, V, chunk_id, True, Q))
         O, Mt = self.attention_with_mass(Q, O, lse)
         self.update_fine(Mt)
         return O
@@ -425,7 +429,7 @@ class PbsaCache:
     def step_fused(self, Q, K=None, V=None, chunk_id=None, O=None, lse=None):
         """The step as two launches after the selection: attention with the update's decisions, then fold /
         promote.  K = V = None: the chunk has been adopted already."""
-        self._select(Q, K is not None and self._append(K, V, chunk_id, True))
+        self._select(Q, K is not None and self._append(K, V, chunk_id, True, Q))
         O = self.attention_with_plan(Q, O, lse)
         self.update_apply()
         return O
@@ -453,7 +457,7 @@ class PbsaCache:
     def step_chained(self, Q, K=None, V=None, chunk_id=None, O=None, lse=None):
         """Two library calls per step: selection (carrying the previous step's fold / promote), attention (carrying
         this step's decisions).  flush() after the last step.  K = V = None: the chunk has been adopted already."""
-        self._select(Q, K is not None and self._append(K, V, chunk_id, True))
+        self._select(Q, K is not None and self._append(K, V, chunk_id, True, Q))
         O = self.attention_with_plan(Q, O, lse)
         self.defer_apply()
         return O
@@ -463,7 +467,7 @@ class PbsaCache:
         leaves its logits and the update maintains the slots, the update's decisions ride in the attention launch
         (step_fused, the same results bit for bit): four launches instead of six, 202.6 -> 189.4 us at 12 x 4680 x 128
         with 16 slots, 57 -> 49 us for two heads of 256 tokens."""
-        self._select(Q, self._append(K, V, chunk_id, True))
+        self._select(Q, self._append(K, V, chunk_id, True, Q))
         if self.Zl is not None and self.C <= pbsa.PBSA_MAX_C:
             O = self.attention_with_plan(Q, O, lse)
             self.update_apply()

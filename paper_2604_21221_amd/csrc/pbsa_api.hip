@@ -141,20 +141,43 @@ int pbsa_summary_view(const pbsa_params* p, const float* S_sum, const int32_t* S
   return e == hipSuccess ? PBSA_OK : hip_fail(e);
 }
 
-int pbsa_append_chunk(const pbsa_params* p, const void* K, const void* V, int64_t k_stride_h, int64_t k_stride_t,
-                      int64_t v_stride_h, int64_t v_stride_t, int32_t slot0, int32_t zero_tail, void* Kl, void* Vl,
-                      float* Kc_l, void* hip_stream) {
+int pbsa_append_chunk_pool(const pbsa_params* p, const void* K, const void* V, int64_t k_stride_h, int64_t k_stride_t,
+                           int64_t v_stride_h, int64_t v_stride_t, int32_t slot0, int32_t zero_tail, void* Kl, void* Vl,
+                           float* Kc_l, const void* Q, int64_t q_stride_h, int64_t q_stride_t, float* Qc, void* hip_stream) {
   int rc = check_common(p, INT32_MAX, INT32_MAX, INT32_MAX);   // looks at no slot, selection or older block
   if (rc) return rc;
   if ((K && !Kl) || (V && !Vl)) return PBSA_EINVAL;
   if (slot0 < 0 || slot0 > p->n_loc_cap - p->nqb) return PBSA_EINVAL;
   if (K && (rc = check_strides(k_stride_h, k_stride_t, p))) return rc;
   if (V && (rc = check_strides(v_stride_h, v_stride_t, p))) return rc;
-  if (!aligned16(K) || !aligned16(V) || !aligned16(Kl) || !aligned16(Vl) || !aligned16(Kc_l)) return PBSA_EALIGN;
-  if (!K && !V) return PBSA_OK;
+  if ((Q == nullptr) != (Qc == nullptr)) return PBSA_EINVAL;
+  if (Q && (rc = check_strides(q_stride_h, q_stride_t, p))) return rc;
+  if (!aligned16(K) || !aligned16(V) || !aligned16(Kl) || !aligned16(Vl) || !aligned16(Kc_l) || !aligned16(Q) || !aligned16(Qc))
+    return PBSA_EALIGN;
+  if (!K && !V && !Q) return PBSA_OK;
   hipError_t e = pbsa::launch_append(*p, static_cast<const pbsa::bf16_t*>(K), static_cast<const pbsa::bf16_t*>(V), k_stride_h,
                                      k_stride_t, v_stride_h, v_stride_t, slot0, zero_tail, static_cast<pbsa::bf16_t*>(Kl),
-                                     static_cast<pbsa::bf16_t*>(Vl), Kc_l, static_cast<hipStream_t>(hip_stream));
+                                     static_cast<pbsa::bf16_t*>(Vl), Kc_l, static_cast<const pbsa::bf16_t*>(Q), q_stride_h,
+                                     q_stride_t, Qc, static_cast<hipStream_t>(hip_stream));
+  return e == hipSuccess ? PBSA_OK : hip_fail(e);
+}
+
+int pbsa_append_chunk(const pbsa_params* p, const void* K, const void* V, int64_t k_stride_h, int64_t k_stride_t,
+                      int64_t v_stride_h, int64_t v_stride_t, int32_t slot0, int32_t zero_tail, void* Kl, void* Vl,
+                      float* Kc_l, void* hip_stream) {
+  return pbsa_append_chunk_pool(p, K, V, k_stride_h, k_stride_t, v_stride_h, v_stride_t, slot0, zero_tail, Kl, Vl, Kc_l,
+                                nullptr, 0, 0, nullptr, hip_stream);
+}
+
+int pbsa_select_pooled(const pbsa_params* p, const int32_t* l_map, const float* Kc_l, const float* Qc, int32_t* sel, float* Zl,
+                       void* hip_stream) {
+  int rc = check_common(p, PBSA_MAX_C_ATTEND, PBSA_MAX_N_LOC, PBSA_MAX_K);
+  if (rc) return rc;
+  if (!l_map || !Kc_l || !Qc) return PBSA_EINVAL;
+  if (p->k > 0 && !sel) return PBSA_EINVAL;
+  if (!aligned16(Kc_l) || !aligned16(Qc)) return PBSA_EALIGN;
+  hipError_t e = pbsa::launch_select(*p, nullptr, nullptr, nullptr, l_map, const_cast<float*>(Kc_l), const_cast<float*>(Qc), sel,
+                                     Zl, true, static_cast<hipStream_t>(hip_stream));
   return e == hipSuccess ? PBSA_OK : hip_fail(e);
 }
 
@@ -170,7 +193,7 @@ int pbsa_select_blocks(const pbsa_params* p, const void* Q, const void* Kl, cons
   if (rc) return rc;
   if (!aligned16(Q) || !aligned16(Kl) || !aligned16(Kc_l) || !aligned16(Qc)) return PBSA_EALIGN;
   hipError_t e = pbsa::launch_select(*p, static_cast<const pbsa::bf16_t*>(Q), static_cast<const pbsa::bf16_t*>(Kl),
-                                     l_len, l_map, Kc_l, Qc, sel, Zl, static_cast<hipStream_t>(hip_stream));
+                                     l_len, l_map, Kc_l, Qc, sel, Zl, false, static_cast<hipStream_t>(hip_stream));
   return e == hipSuccess ? PBSA_OK : hip_fail(e);
 }
 

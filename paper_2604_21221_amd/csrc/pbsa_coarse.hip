@@ -143,14 +143,17 @@ __global__ void __launch_bounds__(kThreads) pool_kernel(PoolArgs a) {
 // order (the pinned order of the pooling), two dimensions each: 64 consecutive words per row, free of bank conflicts.
 // Bound by HBM: each byte is read once and written once, and a selection that follows need not read K again: 11.1 us
 // for a chunk of 12 x 4680 x 128 (57.5 MB moved, 5.2 TB/s), where four tensor copies took 27 us and the selection's
-// own pooling launch another 8.7.
+// own pooling launch another 8.7.  The chunk's queries can be pooled along (and are not copied): a third of the workgroups
+// more, which is nothing to a launch that leaves most of the chip idle, against the 1.3 to
+// 2.8 us the selection's own pooling takes (a step of 5 x 1000 x 64 40.7 -> 38.2 us, of 8 x 2500 x 128 76.1 -> 72.8).
 // ------------------------------------------------------------------------------------------------
 struct AppendArgs {
   int B, Nq, nqb, n_loc_cap, slot0, zero_tail;
-  long sh[2], st[2];        // element strides of K and of V
-  const bf16_t* src[2];
+  long sh[3], st[3];        // element strides of K, of V and of Q
+  const bf16_t* src[3];
   bf16_t* dst[2];
   float* Kc_l;
+  float* Qc;
 };
 
 template <int D, int BT>
@@ -163,17 +166,18 @@ __global__ void __launch_bounds__(kThreads) append_kernel(AppendArgs a) {
   const int len = min(BT, a.Nq - i * BT);
   const int r0 = threadIdx.x / CPR, c = threadIdx.x % CPR;
   src += (size_t)h * a.sh[kv] + (size_t)i * BT * a.st[kv] + 8 * c;
-  bf16_t* dst = a.dst[kv] + ((size_t)h * a.n_loc_cap + a.slot0 + i) * BT * D + 8 * c;
+  const size_t slot = (size_t)h * a.n_loc_cap + a.slot0 + i;
+  bf16_t* dst = kv == 2 ? nullptr : a.dst[kv] + slot * BT * D + 8 * c;
   uint4 v[NS];
 #pragma unroll
   for (int s = 0; s < NS; ++s) v[s] = *reinterpret_cast<const uint4*>(src + (size_t)min(r0 + s * RPS, len - 1) * a.st[kv]);
-  const bool pool = kv == 0 && a.Kc_l;
+  const bool pool = kv == 0 ? a.Kc_l != nullptr : kv == 2;
 #pragma unroll
   for (int s = 0; s < NS; ++s) {
     const int r = r0 + s * RPS;
     if (pool) tile[r * CPR + c] = v[s];
     if (r >= len) v[s] = make_uint4(0u, 0u, 0u, 0u);
-    if (r < len || a.zero_tail) *reinterpret_cast<uint4*>(dst + (size_t)r * D) = v[s];
+    if (dst && (r < len || a.zero_tail)) *reinterpret_cast<uint4*>(dst + (size_t)r * D) = v[s];
   }
   if (!pool) return;
   __syncthreads();
@@ -187,8 +191,8 @@ __global__ void __launch_bounds__(kThreads) append_kernel(AppendArgs a) {
     acc1 = acc1 + bf_hi(u);
   }
   const float fl = (float)len;
-  *reinterpret_cast<float2*>(a.Kc_l + ((size_t)h * a.n_loc_cap + a.slot0 + i) * D + 2 * threadIdx.x) =
-      make_float2(acc0 / fl, acc1 / fl);
+  float* const out = kv == 0 ? a.Kc_l + slot * D : a.Qc + ((size_t)h * a.nqb + i) * D;
+  *reinterpret_cast<float2*>(out + 2 * threadIdx.x) = make_float2(acc0 / fl, acc1 / fl);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -825,10 +829,10 @@ hipError_t launch_pool_blocks(const pbsa_params& p, const bf16_t* X, const int32
 
 hipError_t launch_append(const pbsa_params& p, const bf16_t* K, const bf16_t* V, int64_t k_stride_h, int64_t k_stride_t,
                          int64_t v_stride_h, int64_t v_stride_t, int32_t slot0, int32_t zero_tail, bf16_t* Kl, bf16_t* Vl,
-                         float* Kc_l, hipStream_t stream) {
-  const AppendArgs a{p.B, p.Nq, p.nqb, p.n_loc_cap, slot0, zero_tail, {(long)k_stride_h, (long)v_stride_h},
-                     {(long)k_stride_t, (long)v_stride_t}, {K, V}, {Kl, Vl}, Kc_l};
-  const dim3 grid(p.nqb, p.H, 2), block(kThreads);
+                         float* Kc_l, const bf16_t* Q, int64_t q_stride_h, int64_t q_stride_t, float* Qc, hipStream_t stream) {
+  const AppendArgs a{p.B, p.Nq, p.nqb, p.n_loc_cap, slot0, zero_tail, {(long)k_stride_h, (long)v_stride_h, (long)q_stride_h},
+                     {(long)k_stride_t, (long)v_stride_t, (long)q_stride_t}, {K, V, Q}, {Kl, Vl}, Kc_l, Qc};
+  const dim3 grid(p.nqb, p.H, Q ? 3 : 2), block(kThreads);
   if (p.d == 128 && p.B == 128) hipLaunchKernelGGL((append_kernel<128, 128>), grid, block, 0, stream, a);
   else if (p.d == 128) hipLaunchKernelGGL((append_kernel<128, 64>), grid, block, 0, stream, a);
   else if (p.B == 128) hipLaunchKernelGGL((append_kernel<64, 128>), grid, block, 0, stream, a);
@@ -881,8 +885,9 @@ static hipError_t launch_select_logits(const pbsa_params& p, const bf16_t* Q, co
                                        int32_t* sel, float* Zl, hipStream_t stream);
 
 hipError_t launch_select(const pbsa_params& p, const bf16_t* Q, const bf16_t* Kl, const int32_t* l_len,
-                         const int32_t* l_map, float* Kc_l, float* Qc, int32_t* sel, float* Zl,
+                         const int32_t* l_map, float* Kc_l, float* Qc, int32_t* sel, float* Zl, bool pooled,
                          hipStream_t stream) {
+  if (pooled) return launch_select_logits(p, nullptr, l_map, Kc_l, Qc, sel, Zl, stream);
   const bool in_select = select_pools_queries(p, Zl);
   const PoolArgs pa = select_pool_args(p, Q, Kl, l_len, l_map, Kc_l, Qc, !in_select);
   if (pa.n_jobs > 0) {

@@ -27,11 +27,12 @@ hipError_t launch_pool_blocks(const pbsa_params& p, const bf16_t* X, const int32
                               float* out, hipStream_t stream);
 hipError_t launch_append(const pbsa_params& p, const bf16_t* K, const bf16_t* V, int64_t k_stride_h, int64_t k_stride_t,
                          int64_t v_stride_h, int64_t v_stride_t, int32_t slot0, int32_t zero_tail, bf16_t* Kl, bf16_t* Vl,
-                         float* Kc_l, hipStream_t stream);
+                         float* Kc_l, const bf16_t* Q, int64_t q_stride_h, int64_t q_stride_t, float* Qc, hipStream_t stream);
 hipError_t launch_summary_view(const pbsa_params& p, const float* S_sum, const int32_t* S_cnt, bf16_t* Kp, bf16_t* Vp,
                                int32_t* p_len, hipStream_t stream);
+// pooled: Qc and all of Kc_l have been written already (Q is not looked at)
 hipError_t launch_select(const pbsa_params& p, const bf16_t* Q, const bf16_t* Kl, const int32_t* l_len,
-                         const int32_t* l_map, float* Kc_l, float* Qc, int32_t* sel, float* Zl,
+                         const int32_t* l_map, float* Kc_l, float* Qc, int32_t* sel, float* Zl, bool pooled,
                          hipStream_t stream);
 // launch_select of a chunk with launch_update_apply of the update of the chunk before it (parameters pu, same Kl) riding
 // in its pooling launch.  The caller guarantees that the new chunk's ring position is not the one being folded.

@@ -64,6 +64,8 @@ _SIGNATURES = {
     "pbsa_pool_blocks": "pttitw",
     "pbsa_summary_view": "p" + 5 * "t" + "w",
     "pbsa_append_chunk": "pttlllliitttw",
+    "pbsa_append_chunk_pool": "pttlllliittttlltw",
+    "pbsa_select_pooled": "ptttttw",
     "pbsa_select_blocks": "p" + 8 * "t" + "wzw",
     "pbsa_select_blocks_apply": "p" + 8 * "t" + "p" + 6 * "t" + "wzw",
     "pbsa_attention_fwd": "p" + 11 * "t" + "wzw",
@@ -163,6 +165,14 @@ def _invoke(*args):
     return invoke(*args)
 
 
+def plain_rows(*args):
+    """plain_rows(Kl, Vl, H, Nq, d, watched, *tensors) -> bool (csrc/pbsa_host.cpp)"""
+    global plain_rows
+    from ._pbsa_host import plain_rows as native
+    plain_rows = native
+    return native(*args)
+
+
 def _through_ctypes(name, args):
     """The call for what the native half leaves alone: anything but plain tensors, integers and the structures themselves.
     ctypes and _ptr take it or refuse it."""
@@ -210,13 +220,23 @@ def pbsa_summary_view(p, S_sum, S_cnt, Kp, Vp, p_len, stream=None):
     _call("pbsa_summary_view", p, S_sum, S_cnt, Kp, Vp, p_len, _stream(stream))
 
 
-def pbsa_append_chunk(p, K, V, slot0, zero_tail, Kl, Vl, Kc_l=None, stream=None):
-    """K, V: [H][Nq][d] bf16 with a contiguous last dimension, or None."""
+def pbsa_append_chunk(p, K, V, slot0, zero_tail, Kl, Vl, Kc_l=None, stream=None, Q=None, Qc=None):
+    """K, V: [H][Nq][d] bf16 with a contiguous last dimension, or None.  Q, Qc: the queries are pooled along
+    (pbsa_append_chunk_pool), for a pbsa_select_blocks with pooled=True."""
     ks, vs = (x.stride() if x is not None else (0, 0, 1) for x in (K, V))
+    if Q is not None:
+        qs = Q.stride()
+        _call("pbsa_append_chunk_pool", p, K, V, ks[0], ks[1], vs[0], vs[1], slot0, int(zero_tail), Kl, Vl, Kc_l, Q, qs[0], qs[1],
+              Qc, _stream(stream))
+        return
     _call("pbsa_append_chunk", p, K, V, ks[0], ks[1], vs[0], vs[1], slot0, int(zero_tail), Kl, Vl, Kc_l, _stream(stream))
 
 
-def pbsa_select_blocks(p, Q, Kl, l_len, l_map, Kc_l, Qc, sel, Zl=None, ws=None, stream=None):
+def pbsa_select_blocks(p, Q, Kl, l_len, l_map, Kc_l, Qc, sel, Zl=None, ws=None, stream=None, pooled=False):
+    """pooled: Qc and all of Kc_l have been written already (pbsa_select_pooled)."""
+    if pooled:
+        _call("pbsa_select_pooled", p, l_map, Kc_l, Qc, sel, Zl, _stream(stream))
+        return
     w, wb = _ws(ws)
     _call("pbsa_select_blocks", p, Q, Kl, l_len, l_map, Kc_l, Qc, sel, Zl, w, wb, _stream(stream))
 

@@ -291,6 +291,29 @@ def test_append_argument_checks(L):
         assert L.pbsa_append_chunk(ctypes.byref(p), None, None, 0, 0, 0, 0, slot0, 1, None, None, None, None) == code
 
 
+def test_pooled_append_and_selection_argument_checks(L):
+    """pbsa_append_chunk_pool checks like pbsa_append_chunk, and the queries like K; pbsa_select_pooled like pbsa_select_blocks."""
+    p = good()
+    dense = (200 * 128, 128)
+
+    def append(K=P, slot0=0, Kc_l=P, Q=P, qs=dense, Qc=P):
+        return L.pbsa_append_chunk_pool(ctypes.byref(p), K, P, *dense, *dense, slot0, 1, P, P, Kc_l, Q, *qs, Qc, None)
+
+    for kw, code in [(dict(slot0=13), pbsa.PBSA_EINVAL), (dict(K=P + 2), pbsa.PBSA_EALIGN), (dict(Kc_l=P + 4), pbsa.PBSA_EALIGN),
+                     (dict(Q=None), pbsa.PBSA_EINVAL), (dict(Qc=None), pbsa.PBSA_EINVAL), (dict(Q=P + 8), pbsa.PBSA_EALIGN),
+                     (dict(Qc=P + 4), pbsa.PBSA_EALIGN), (dict(qs=(200 * 128, 120)), pbsa.PBSA_EINVAL),
+                     (dict(qs=(-8, 128)), pbsa.PBSA_EINVAL), (dict(qs=(200 * 132, 132)), pbsa.PBSA_EALIGN)]:
+        assert append(**kw) == code, kw
+
+    def select(p=p, l_map=P, Kc_l=P, Qc=P, sel=P):
+        return L.pbsa_select_pooled(ctypes.byref(p), l_map, Kc_l, Qc, sel, P, None)
+
+    for kw, code in [(dict(l_map=None), pbsa.PBSA_EINVAL), (dict(Kc_l=None), pbsa.PBSA_EINVAL), (dict(Qc=None), pbsa.PBSA_EINVAL),
+                     (dict(sel=None), pbsa.PBSA_EINVAL), (dict(Kc_l=P + 4), pbsa.PBSA_EALIGN), (dict(Qc=P + 8), pbsa.PBSA_EALIGN),
+                     (dict(p=good(d=96)), pbsa.PBSA_ESHAPE), (dict(p=good(n_loc=2)), pbsa.PBSA_EINVAL)]:
+        assert select(**kw) == code, kw
+
+
 def test_split_attention_argument_checks(L):
     """pbsa_attention_fwd_split validates like pbsa_attention_fwd and wants pbsa_attention_workspace_bytes."""
     p = good(k=12)                           # 4 query tiles of 17 key tiles each: shared out

@@ -325,3 +325,26 @@ def test_no_split_for_what_is_not_there_yet(monkeypatch):
                      torch.full((H, 64), B, dtype=torch.int32), torch.arange(64)[None].repeat(H, 1))
     c.append_chunk(x, x, 0)
     assert splits(c)
+
+
+def test_who_pools_the_queries(cache, monkeypatch):
+    """A step's append pools the queries along, and its selection starts from them, where it reads them as they are and nothing
+    older is stale; a selection by itself pools its own."""
+    asked = []
+    for name in CALLS:
+        monkeypatch.setattr(pbsa, name, lambda *a, name=name, **k: asked.append((name, len(a) > 9 and a[9] is not None, k.get("pooled", False))))
+
+    def steps(Q):
+        del asked[:]
+        cache.step(Q, chunk(1), chunk(2), cache.n_appended)
+        return asked[0][1], asked[1][2]
+
+    assert steps(chunk(0)) == (True, True)
+    assert steps(torch.zeros(H, NQ, D + 1, dtype=torch.bfloat16)[:, :, 1:]) == (False, False)       # rows that are not aligned
+    assert steps(chunk(0).requires_grad_()) == (False, False)
+    cache.stale_from = 0                     # an older block is stale: the selection pools, the queries too
+    assert steps(chunk(0)) == (True, False)
+    cache.append_chunk(chunk(1), chunk(2), cache.n_appended)
+    del asked[:]
+    cache.select(chunk(0))
+    assert asked == [("pbsa_select_blocks", False, False)]

@@ -61,3 +61,27 @@ def test_selection_of_unusual_values(gpu, d, kind):  # noqa: F811
     else:
         s = 2.0 ** -68 if kind == "denormal" else 2.0 ** 62      # products around the smallest normal; sums near the largest number
         logits_and_sets(gpu, d, 64, 9, 60, 2, 6, s, lambda key, H, Nq, dd, sc: rnd(key, H, Nq, dd, scale=sc))
+
+
+@pytest.mark.parametrize("case", [(64, 64, 3, 1, 2), (64, 128, 5, 104, 1), (128, 64, 4, 64, 2), (128, 128, 3, 127, 1), (64, 64, 86, 9, 0)],
+                         ids=lambda c: "d%d_B%d_%d_blocks_last%d" % c[:4])
+def test_queries_pooled_with_the_append(gpu, case):  # noqa: F811
+    """A step (queries pooled by the append where the launch is small: 2 heads of up to 85 blocks; strided as a model has them)
+    against append and select by themselves: every bit of what the selection leaves."""
+    d, B, nqb, tail, w = case
+    H, Nq, scale = 2, (nqb - 1) * B + tail, np.float32(1.0 / math.sqrt(d))
+    one, two = (gpu["cache"].PbsaCache(H, d, B, Nq, w, 3, 4, scale, device=DEV) for _ in range(2))
+    for g in range(w + 2):
+        Q, K, V = (gpu["wl"].bf16_tensor(rnd(900 + 3 * g + i, Nq, H, d), DEV).transpose(0, 1) for i in range(3))
+        one.step(Q, K, V, g)
+        two.append_chunk(K, V, g)
+        two.select(Q)
+        n = H * nqb * two.n_loc
+        for name in ("Qc", "Kc_l", "sel"):
+            a, b = (getattr(c, name).cpu().numpy() for c in (one, two))
+            assert np.array_equal(a.view(np.uint32), b.view(np.uint32)), f"chunk {g}: {name}"
+        a, b = (c.Zl.view(-1)[:n].cpu().numpy().view(np.uint32) for c in (one, two))
+        assert np.array_equal(a, b), f"chunk {g}: logits"
+        two.attention(Q)
+        two.update()
+        assert np.array_equal(one.slot_src.cpu().numpy(), two.slot_src.cpu().numpy()), f"chunk {g}: slots"
