@@ -217,8 +217,10 @@ class PbsaCache:
             torch.autograd.graph.increment_version([dst for dst, src in ((self.Kl, K), (self.Vl, V)) if src is not None])
             pool = pool and K is not None
             args = self._full, K, V, pos * self.nqb, zero_tail, self.Kl, self.Vl, self.Kc_l if pool else None
-            # up to two workgroups per compute unit the queries' blocks cost the launch nothing
-            if (pool and Q is not None and self._pending is None and self.H * self.nqb <= 170
+            # Up to 400 blocks the launch has room for the queries' (step without -> with them: 76.1 -> 72.8 us at 8 heads x 20
+            # blocks of 128, 128.4 -> 125.6 at 8 x 32, 72.3 -> 69.8 at 16 x 24 of 64; 88.1 -> 88.5 at 6 x 38 of 64); beyond, their
+            # bytes take it as long as they take the selection (187.3 -> 187.5 at 12 x 37 of 128, 181.6 -> 181.3 at 16 x 42).
+            if (pool and Q is not None and self._pending is None and self.H * self.nqb <= 400
                     and pbsa.plain_rows(self.Kl, self.Vl, self.H, self.Nq, self.d, torch.is_grad_enabled(), Q)):
                 pbsa.pbsa_append_chunk(*args, None, Q, self.Qc)
                 return _KEYS_AND_QUERIES
