@@ -21,6 +21,9 @@ namespace {
 using namespace plan_dev;
 
 constexpr int kThreads = 256;
+// Of the fold's workgroups: with 256 threads there are 192 of them at 12 heads of 64 x 128 positions, and a quarter of the chip
+// has none (128 -> 256 threads: fold 12.9 -> 14.1 us there, 4.8 -> 5.4 at two heads of 64 x 64; 64 threads: 14.0, 4.7).
+constexpr int kFoldThreads = 128;
 constexpr int kXC = 32;   // pooled-key dimensions staged through LDS per step
 
 typedef __attribute__((ext_vector_type(4))) float f32x4;
@@ -90,10 +93,10 @@ struct PoolArgs {
   float* Qc;
 };
 
-template <int D>
+template <int D, int NT = kThreads>
 __device__ __forceinline__ void pool_body(const PoolArgs& a, const int bx) {
   constexpr int TPJ = D / 2;
-  const int job = bx * (kThreads / TPJ) + threadIdx.x / TPJ;
+  const int job = bx * (NT / TPJ) + threadIdx.x / TPJ;
   const int c = threadIdx.x % TPJ;
   if (job >= a.n_jobs) return;
   const bf16_t* src;
@@ -768,18 +771,18 @@ __global__ void __launch_bounds__(kThreads) summary_view_kernel(int H, int B, in
   *reinterpret_cast<uint2*>((kv ? Vp : Kp) + ((size_t)h * C1 + C) * blk + rowoff) = w;
 }
 
-__global__ void __launch_bounds__(kThreads) fold_promote_kernel(FoldArgs a) {
-  fold_promote_body<kThreads>(a, blockIdx.x, blockIdx.y);
+__global__ void __launch_bounds__(kFoldThreads) fold_promote_kernel(FoldArgs a) {
+  fold_promote_body<kFoldThreads>(a, blockIdx.x, blockIdx.y);
 }
 
 // The pooling of one chunk's selection call and the fold / promote of the update of the chunk before it, as one
 // launch: the two touch disjoint data when the new chunk does not sit in the ring position whose blocks are being
 // folded, and each is too short to fill the GPU for long.  The n_fold_x * H fold workgroups come first.
 template <int D>
-__global__ void __launch_bounds__(kThreads) pool_fold_kernel(PoolArgs pa, FoldArgs fa, int n_fold_x) {
+__global__ void __launch_bounds__(kFoldThreads) pool_fold_kernel(PoolArgs pa, FoldArgs fa, int n_fold_x) {
   const int n_fold = n_fold_x * fa.H, b = (int)blockIdx.x;      // the fold's workgroups run longest: they start first
-  if (b >= n_fold) pool_body<D>(pa, b - n_fold);
-  else fold_promote_body<kThreads>(fa, b % n_fold_x, b / n_fold_x);
+  if (b >= n_fold) pool_body<D, kFoldThreads>(pa, b - n_fold);
+  else fold_promote_body<kFoldThreads>(fa, b % n_fold_x, b / n_fold_x);
 }
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -909,11 +912,11 @@ hipError_t launch_select_apply(const pbsa_params& p, const bf16_t* Q, const bf16
   const FoldArgs fa = fold_args(pu, Kp, Vp, p_len, S_sum, S_cnt, Kl, Vl, ws);
   // the fold / promote workgroups ride in the pooling launch: its workgroups have the same size and no LDS of their
   // own (in the logits launch, 80 KB of LDS per workgroup, they would wait for places: measured slower)
-  const int jpw = kThreads / (p.d / 2), rows_per_wg = kThreads / (pu.d / 4);
+  const int jpw = kFoldThreads / (p.d / 2), rows_per_wg = kFoldThreads / (pu.d / 4);
   const int n_fold_x = (2 * pu.B + rows_per_wg - 1) / rows_per_wg;
   const dim3 grid(n_fold_x * pu.H + (pa.n_jobs + jpw - 1) / jpw);
-  if (p.d == 128) hipLaunchKernelGGL(pool_fold_kernel<128>, grid, dim3(kThreads), 0, stream, pa, fa, n_fold_x);
-  else hipLaunchKernelGGL(pool_fold_kernel<64>, grid, dim3(kThreads), 0, stream, pa, fa, n_fold_x);
+  if (p.d == 128) hipLaunchKernelGGL(pool_fold_kernel<128>, grid, dim3(kFoldThreads), 0, stream, pa, fa, n_fold_x);
+  else hipLaunchKernelGGL(pool_fold_kernel<64>, grid, dim3(kFoldThreads), 0, stream, pa, fa, n_fold_x);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return launch_select_logits(p, nullptr, l_map, Kc_l, Qc, sel, Zl, stream);
@@ -1003,8 +1006,8 @@ hipError_t launch_update_apply(const pbsa_params& p, bf16_t* Kp, bf16_t* Vp, int
                                const int32_t* S_cnt, const bf16_t* Kl, const bf16_t* Vl, const UpdateWs& ws,
                                hipStream_t stream) {
   const FoldArgs fa = fold_args(p, Kp, Vp, p_len, S_sum, S_cnt, Kl, Vl, ws);
-  const int rows_per_wg = kThreads / (p.d / 4);
-  hipLaunchKernelGGL(fold_promote_kernel, dim3((2 * p.B + rows_per_wg - 1) / rows_per_wg, p.H), dim3(kThreads), 0,
+  const int rows_per_wg = kFoldThreads / (p.d / 4);
+  hipLaunchKernelGGL(fold_promote_kernel, dim3((2 * p.B + rows_per_wg - 1) / rows_per_wg, p.H), dim3(kFoldThreads), 0,
                      stream, fa);
   return hipGetLastError();
 }
