@@ -724,7 +724,7 @@ attention_kernel(AttnArgs a, PlanArgs<PLAN> pl) {
   constexpr int CH = D / 8, RPI = 64 / CH;          // 16-byte chunks per row, rows per wave instruction
   constexpr int NIW = (kTile / RPI) / 2;            // global_load_lds instructions per wave per tile
   constexpr int SMEM = 4 * TILE;                    // K ring (2 tiles), V ring (2 tiles)
-  static_assert((3 * PBSA_MAX_N_LOC + PBSA_MAX_C_ATTEND + 1) * 4 <= SMEM, "setup scratch must fit");
+  static_assert(PBSA_MAX_N_LOC * 8 + (PBSA_MAX_C_ATTEND + 1 + 8) * 4 <= SMEM, "setup scratch must fit");
   // the plain call takes the larger limits and keeps the list within two workgroups' share of a CU's LDS by
   // storing 16-bit descriptors (the mass variant's carry the key block as well)
   constexpr bool kAux = MASS || PLAN;
@@ -735,7 +735,9 @@ attention_kernel(AttnArgs a, PlanArgs<PLAN> pl) {
   __shared__ __align__(1024) unsigned char smem[SMEM];
   __shared__ int t_src[kTilesMax];         // bit 31: local, bits 0..: (slot * SUB + sub)
   __shared__ meta_t t_meta[kTilesMax];     // valid keys (bits 0..7) | waves that attend (bits 8, 9)
-  int* lflag = reinterpret_cast<int*>(smem);        // setup scratch, dead before the first tile is staged
+  // setup scratch, dead before the first tile is staged: per local block its physical slot and, in one word, its length
+  // (0: it is nowhere) and from bit 16 the waves that attend it; the slots' lengths; each wave's counts
+  int2* lblk = reinterpret_cast<int2*>(smem);
 
   // XCD-aware mapping: consecutive workgroup ids go round-robin to the 8 XCDs, so give XCD x the
   // contiguous range [x * per, (x+1) * per) of (head, query tile) pairs: neighbours share K/V in L2.
@@ -784,28 +786,33 @@ attention_kernel(AttnArgs a, PlanArgs<PLAN> pl) {
   // Everything the list needs is fetched from global memory in one parallel round into LDS scratch:
   // per local block the set of waves whose query block selected it, its length and its physical slot;
   // per persistent slot its length.  The candidates -- the 64-key tiles of the persistent slots, then
-  // of the local blocks, in ascending order -- are then classified by every wave, candidate i by lane
-  // i mod 64 in round i / 64: full tiles of both waves, ragged tiles, full tiles of wave 0 only, of
-  // wave 1 only.  Every part of the list is in ascending candidate order.
-  int* llen_s = lflag + kLocMax;
-  int* lmap_s = llen_s + kLocMax;
-  int* plen_s = lmap_s + kLocMax;
-  for (int l = tid; l < a.n_loc; l += kThreads) {
-    lflag[l] = 0;
-    llen_s[l] = a.l_len[l];
-    lmap_s[l] = a.l_map[l];
-  }
-  for (int c = tid; c <= a.C; c += kThreads) plen_s[c] = a.p_len[(size_t)h * (a.C + 1) + c];
-  // the selections of this workgroup's query blocks, fetched now (loads return in order: anything asked
-  // for after the queries would wait for them) and turned into flags once the flags are zeroed
-  constexpr int kSelPer = (2 * (kAux ? PBSA_MAX_K_AUX : PBSA_MAX_K) + kThreads - 1) / kThreads;
-  int selv[kSelPer];
+  // of the local blocks, in ascending order -- are then classified 64 at a time, the first half of them by wave 0: full
+  // tiles of both waves, ragged tiles, full tiles of wave 0 only, of wave 1 only.  Every part of the list is in ascending
+  // candidate order.  With each wave sweeping all candidates, three LDS words each, and a division per selected block in a
+  // loop unrolled for the largest shape the list took 3.4 us of a launch of 12 heads x 4680 rows, now 2.1 (four denoising
+  // passes at 8 + 16 blocks of 128 497.9 -> 485.7 us, a chained step 111.3 -> 109.7, select, forward and backward of
+  // 3 x 1500 x 64 44.8 -> 43.4; a chained step at 32 + 48 blocks of 64 175.0 -> 175.5).
+  int* plen_s = reinterpret_cast<int*>(lblk + kLocMax);
+  int* cnt_s = plen_s + PBSA_MAX_C_ATTEND + 1;
+  // The first of each are fetched together (up to 384 local blocks, 128 slots, 256 selected blocks); the rest, at shapes beyond
+  // those, in loops of their own: this code runs once per workgroup, and instructions that have to be fetched cost more than
+  // the loads they issue (the same list with everything unrolled gained nothing, and a step of 2 x 256 x 64 lost 1 us).
+  constexpr int kLocPer = 3, kSelPer = 2;
+  const int n_sel = G * a.k;
+  const int32_t* const sel_wg = a.sel + ((size_t)h * a.nqb + i0) * a.k;         // the rows lie one behind the other
+  const int32_t* const plen_h = a.p_len + (size_t)h * (a.C + 1);
+  const int n_sel_here = G == 1 || i0 + 1 < a.nqb ? n_sel : a.k;
+  int llen_v[kLocPer], lmap_v[kLocPer], selv[kSelPer];
+  // (loads return in order: anything asked for after the queries would wait for them)
 #pragma unroll
-  for (int u = 0; u < kSelPer; ++u) {
-    const int idx = tid + u * kThreads;
-    const int g = idx / max(a.k, 1), j = idx % max(a.k, 1);
-    selv[u] = idx < G * a.k && i0 + g < a.nqb ? a.sel[((size_t)h * a.nqb + i0 + g) * a.k + j] : -1;
+  for (int u = 0; u < kLocPer; ++u) {
+    const int l = min(tid + u * kThreads, a.n_loc - 1);
+    llen_v[u] = a.l_len[l];
+    lmap_v[u] = a.l_map[l];
   }
+  const int plen_v = plen_h[min(tid, a.C)];
+#pragma unroll
+  for (int u = 0; u < kSelPer; ++u) selv[u] = tid + u * kThreads < n_sel_here ? sel_wg[tid + u * kThreads] : -1;
 
   // ---- Q fragments (B operand of S^T = K Q^T): row group g, query row lane % 32, dims 16 ks + 8 (lane/32) ..+8.
   // Issued after the few loads the tile list waits for and not touched until the list is built: the
@@ -819,13 +826,24 @@ attention_kernel(AttnArgs a, PlanArgs<PLAN> pl) {
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) qf[g][ks] = *reinterpret_cast<const bf16x8*>(qrow + 16 * ks);
   }
-  __syncthreads();
+  auto put_block = [&](int l, int slot, int len) {
+    if (l < a.n_loc) lblk[l] = make_int2(slot, (unsigned)slot < (unsigned)a.n_loc_cap ? min(max(len, 0), B) : 0);
+  };
 #pragma unroll
-  for (int u = 0; u < kSelPer; ++u) {
-    const int l = selv[u], g = (tid + u * kThreads) / max(a.k, 1);
-    // with one query block per workgroup both waves belong to it
-    if (l >= 0 && l < a.n_loc) atomicOr(&lflag[l], G == 1 ? 3 : 1 << g);
-  }
+  for (int u = 0; u < kLocPer; ++u) put_block(tid + u * kThreads, lmap_v[u], llen_v[u]);
+#pragma unroll 1
+  for (int l = tid + kLocPer * kThreads; l < a.n_loc; l += kThreads) put_block(l, a.l_map[l], a.l_len[l]);
+  if (tid <= a.C) plen_s[tid] = min(max(plen_v, 0), B);
+#pragma unroll 1
+  for (int c = tid + kThreads; c <= a.C; c += kThreads) plen_s[c] = min(max(plen_h[c], 0), B);
+  __syncthreads();
+  auto flag = [&](int idx, int l) {        // with one query block per workgroup both waves belong to it
+    if (l >= 0 && l < a.n_loc) atomicOr(&lblk[l].y, (G == 1 ? 3 : idx < a.k ? 1 : 2) << 16);
+  };
+#pragma unroll
+  for (int u = 0; u < kSelPer; ++u) flag(tid + u * kThreads, selv[u]);
+#pragma unroll 1
+  for (int idx = tid + kSelPer * kThreads; idx < n_sel_here; idx += kThreads) flag(idx, sel_wg[idx]);
   __syncthreads();
   const int n_pers = (a.C + 1) * SUB, n_cand = n_pers + a.n_loc * SUB;
   // candidate i -> its class (-1: no tile) and its list entry
@@ -833,31 +851,42 @@ attention_kernel(AttnArgs a, PlanArgs<PLAN> pl) {
     if (i >= n_cand) return -1;
     if (i < n_pers) {
       const int c = i / SUB, sub = i % SUB;
-      const int tl = min(max(min(max(plen_s[c], 0), B) - sub * kTile, 0), kTile);
+      const int tl = min(max(plen_s[c] - sub * kTile, 0), kTile);
       src = i;
       meta = tl | (3 << 8);
       if constexpr (MASS) meta |= (c << 10) | (sub << 20);       // the key block the tile belongs to, and which tile of it
       return tl == 0 ? -1 : tl == kTile ? 0 : 1;
     }
     const int l = (i - n_pers) / SUB, sub = (i - n_pers) % SUB;
-    const int f = lflag[l], slot = lmap_s[l];
-    if (f == 0 || slot < 0 || slot >= a.n_loc_cap) return -1;
-    const int tl = min(max(min(max(llen_s[l], 0), B) - sub * kTile, 0), kTile);
-    src = (int)(0x80000000u | (uint32_t)(slot * SUB + sub));
+    const int2 blk = lblk[l];
+    const int f = blk.y >> 16, tl = min(max((blk.y & 0xFFFF) - sub * kTile, 0), kTile);
+    src = (int)(0x80000000u | (uint32_t)(blk.x * SUB + sub));
     meta = tl | (f << 8);
     if constexpr (MASS) meta |= ((a.C + 1 + l) << 10) | (sub << 20);
-    return tl == 0 ? -1 : tl < kTile ? 1 : f == 3 ? 0 : f + 1;      // f is 1 or 2 otherwise
+    return f == 0 || tl == 0 ? -1 : tl < kTile ? 1 : f == 3 ? 0 : f + 1;      // f is 1 or 2 otherwise
   };
-  // Every wave classifies every candidate, 64 per round, twice: the first sweep gives the sizes of the four parts, the
-  // second the places, with the running counts in scalar registers (ballots only: no barrier and no LDS traffic
-  // between the sweeps).  The waves take turns writing the rounds.
-  const int n_rounds = (n_cand + 63) / 64;
+  // A wave classifies its candidates twice: the first sweep gives the sizes of the four parts, the second the places, with
+  // the running counts in scalar registers (ballots).
+  const int n_rounds = (n_cand + 63) / 64, r_mid = (n_rounds + 1) / 2;
+  const int r_begin = wave == 0 ? 0 : r_mid, r_end = wave == 0 ? r_mid : n_rounds;
   int tot[4] = {0, 0, 0, 0};
-  for (int r = 0; r < n_rounds; ++r) {
+#pragma unroll 1
+  for (int r = r_begin; r < r_end; ++r) {
     int src, meta;
     const int cls = classify(r * 64 + lane, src, meta);
 #pragma unroll
     for (int c = 0; c < 4; ++c) tot[c] += __popcll(__ballot(cls == c));
+  }
+  if (lane == 0)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) cnt_s[4 * wave + c] = tot[c];
+  __syncthreads();
+  int before[4];                           // what the candidates of wave 0 put ahead of this wave's
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const int other = __builtin_amdgcn_readfirstlane(cnt_s[4 * (wave ^ 1) + c]);
+    before[c] = wave == 0 ? 0 : other;
+    tot[c] += other;
   }
   // this workgroup's tiles of each class: all of them, or ranks lo .. lo + num - 1 (the classes take the parts in opposite
   // orders, so that the remainders do not meet in one part)
@@ -872,16 +901,15 @@ attention_kernel(AttnArgs a, PlanArgs<PLAN> pl) {
   }
   const int first[4] = {0, num[0], num[0] + num[1], num[0] + num[1] + num[2]};
   const int cls_end[4] = {first[1], first[2], first[3], first[3] + num[3]};
-  int base[4] = {first[0] - lo[0], first[1] - lo[1], first[2] - lo[2], first[3] - lo[3]};
+  int base[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) base[c] = first[c] - lo[c] + before[c];
   int32_t* mass_list = MASS ? a.Rlist + (size_t)logical * a.list_cap : nullptr;
-  for (int r = 0; r < n_rounds; ++r) {
-    int src = 0, meta = 0;
-    const int cls = classify(r * 64 + lane, src, meta);
-    const bool mine = (r & 1) == wave;
+  auto place = [&](int cls, int src, int meta) {
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       const unsigned long long m = __ballot(cls == c);
-      if (cls == c && mine) {
+      if (cls == c) {
         const int pos = base[c] + lanes_below(m);
         if (!SPLIT || (pos >= first[c] && pos < cls_end[c])) {
           t_src[pos] = src;
@@ -894,6 +922,12 @@ attention_kernel(AttnArgs a, PlanArgs<PLAN> pl) {
       }
       base[c] += __popcll(m);
     }
+  };
+#pragma unroll 1
+  for (int r = r_begin; r < r_end; ++r) {
+    int src = 0, meta = 0;
+    const int cls = classify(r * 64 + lane, src, meta);
+    place(cls, src, meta);
   }
   __syncthreads();
   // The Q fragments are only ever MFMA operands, which may come from the accumulator half of the
