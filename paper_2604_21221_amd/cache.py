@@ -8,6 +8,8 @@ ring bookkeeping (which physical slot holds which logical block).
 """
 from __future__ import annotations
 
+from operator import index
+
 import torch
 
 from . import pbsa
@@ -130,9 +132,10 @@ class PbsaCache:
             self._maps[key] = m
         if not want_ids:
             return m[0], m[1], None
-        ids = self.chunk_ids
-        if ids[0] >= 0 and ids == list(range(ids[0], ids[0] + len(ids))):
-            lo, hi = ids[0] * self.nqb, (ids[-1] + 1) * self.nqb
+        ids = self.chunk_ids                 # numbers of the caller's, of whatever type
+        if ids[0] >= 0 and (ids == list(range(ids[0], ids[0] + len(ids))) if type(ids[0]) is int
+                            else all(b == a + 1 for a, b in zip(ids, ids[1:]))):
+            lo, hi = index(ids[0]) * self.nqb, (index(ids[-1]) + 1) * self.nqb
             if self._arange64 is None or self._arange64.numel() < hi:
                 self._arange64 = torch.arange(max(2 * hi, 64 * self.cap), dtype=torch.int64, device=self.dev)
             l_id = self._arange64.data_ptr() + 8 * lo           # a slice of it, without the tensor object

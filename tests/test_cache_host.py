@@ -348,3 +348,30 @@ def test_who_pools_the_queries(cache, monkeypatch):
     del asked[:]
     cache.select(chunk(0))
     assert asked == [("pbsa_select_blocks", False, False)]
+
+
+@pytest.mark.parametrize("kind", [int, "int64", "int32", "int16", "tensor", float])
+def test_chunk_ids_of_any_integer_type(cache, kind):
+    """Whatever type of number a program counts its chunks with, consecutive or not: the update is given the blocks' ids as
+    64-bit integers, where they are consecutive by a plain address."""
+    import ctypes
+    import numpy as np
+    make = kind if kind in (int, float) else torch.tensor if kind == "tensor" else getattr(np, kind)
+    nqb = cache.nqb
+
+    def ids(first, second):
+        cache.chunk_pos, cache.chunk_ids = [], []
+        for g in (first, second):
+            cache.adopt_chunk(make(g))
+        return cache._device_maps(want_ids=True)[2]
+
+    if kind is float:                        # not a number of a chunk, but gaps have always been taken
+        with pytest.raises(TypeError):
+            ids(6, 7)
+    else:
+        at = ids(6, 7)
+        assert type(at) is int and 0 <= at - cache._arange64.data_ptr() <= 8 * (cache._arange64.numel() - 2 * nqb)
+        assert list((ctypes.c_int64 * (2 * nqb)).from_address(at)) == list(range(6 * nqb, 8 * nqb))
+    for first, second in ((6, 8), (7, 6), (-1, 0)):
+        got = ids(first, second)
+        assert got.dtype == torch.int64 and got.tolist() == [g * nqb + i for g in (first, second) for i in range(nqb)]
