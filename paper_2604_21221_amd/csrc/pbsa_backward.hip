@@ -735,10 +735,13 @@ __device__ __forceinline__ void dq_body(const BwdArgs& a, const int block, unsig
   const int fixed_len = min(kTile, a.Nq - r_tile * kTile);
 
   // ---- the tiles these rows attend: persistent slots, then the blocks of their row of sel -----------------
+  // the library takes rings of H * n_loc_cap * d * 4 < 2^32, with blocks of up to two tiles
+  constexpr int kTileBits = 25;
+  static_assert(2 * ((1ll << 32) / (64 * 4)) <= 1ll << kTileBits && kTile <= 1 << (31 - kTileBits), "one word per tile");
   int n_tiles = 0;
   for (int i0 = 0; i0 < n_cand; i0 += 64) {
     const int i = i0 + lane;
-    uint32_t where = 0;                    // bit 31 local, bits 24.. rows - 1, the tile in the cache's tensor
+    uint32_t where = 0;                    // bit 31 local, bits 25 .. 30 rows - 1, the tile in the cache's tensor
     int rows = 0;
     if (i < n_pers) {
       const int c = i / SUB, sub = i % SUB;
@@ -756,7 +759,7 @@ __device__ __forceinline__ void dq_body(const BwdArgs& a, const int block, unsig
       }
     }
     const unsigned long long m = __ballot(rows > 0);
-    if (rows > 0) lst[n_tiles + lanes_below(m)] = where | (uint32_t)(rows - 1) << 24;
+    if (rows > 0) lst[n_tiles + lanes_below(m)] = where | (uint32_t)(rows - 1) << kTileBits;
     n_tiles += __popcll(m);
   }
   n_tiles = __builtin_amdgcn_readfirstlane(n_tiles);
@@ -856,10 +859,10 @@ __device__ __forceinline__ void dq_body(const BwdArgs& a, const int block, unsig
   const unsigned char* s2 = vl;
   int s_last = 0;                          // its last row
   auto stage_tile = [&](int word) {
-    const size_t off = (size_t)(word & 0xFFFFFF) * TILE;
+    const size_t off = (size_t)(word & ((1 << kTileBits) - 1)) * TILE;
     s1 = (word < 0 ? kl : kp) + off;
     s2 = (word < 0 ? vl : vp) + off;
-    s_last = (word >> 24) & 63;
+    s_last = (word >> kTileBits) & (kTile - 1);
   };
   // load i of half MG of that tile, into ring entry MG: window by window, K and V in turn.  A tile that is not full has
   // its offsets set before each window and set back behind the last.
@@ -983,7 +986,7 @@ __device__ __forceinline__ void dq_body(const BwdArgs& a, const int block, unsig
       stage_tile(w_next);                  // past the end of the list the last tile again: nobody reads it
       v_word = (int)lst[min(t + 2, n_tiles - 1)];
     }
-    const int keys = ((w_own >> 24) & 63) + 1 - 32 * mg;
+    const int keys = ((w_own >> kTileBits) & (kTile - 1)) + 1 - 32 * mg;
     __builtin_amdgcn_sched_barrier(0);
     run_phase(0, std::true_type{}, keys, nothing);
     second_products(std::integral_constant<int, 1>{}, nothing);
