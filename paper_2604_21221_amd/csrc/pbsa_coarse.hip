@@ -400,7 +400,10 @@ __device__ __forceinline__ void select_body(const SelectArgs& a, const int bx, c
         acc = fma_4_rows<(x + 2) % 16>(a_q[x / 16], k4[c].z, acc);
         acc = fma_4_rows<(x + 3) % 16>(a_q[x / 16], k4[c].w, acc);
       }, std::make_integer_sequence<int, CPC>{});
-      if constexpr (r0 + NBUF < NR) PBSA_STAGE(r0 + NBUF)
+      if constexpr (r0 + NBUF < NR) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // this round has been read: its place is free
+        PBSA_STAGE(r0 + NBUF)
+      }
     }, std::make_integer_sequence<int, NR>{});
   }
 #undef PBSA_STAGE

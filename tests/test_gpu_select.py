@@ -21,6 +21,7 @@ CASES = [
     (128, 64, 2, 33, 2, 3), (128, 128, 3, 1, 0, 2), (128, 128, 4, 104, 1, 5), (128, 128, 6, 128, 0, 6),
     (64, 64, 43, 64, 2, 17), (128, 64, 43, 7, 2, 40), (128, 64, 81, 64, 3, 12), (64, 64, 81, 31, 3, 324),
     (64, 64, 161, 50, 1, 9), (128, 64, 161, 64, 3, 33),
+    (64, 64, 168, 50, 3, 9), (128, 64, 168, 1, 3, 40),
 ]
 
 
