@@ -277,8 +277,8 @@ __device__ __forceinline__ void dma16(const void* base, uint32_t voff, uint32_t 
 }
 
 // v_mfma_f32_4x4x1_16b_f32: sixteen 4 x 4 products of one contraction index.  With A of block X broadcast to all blocks (cbsz
-// 4), lane L's element r of the result is fma(a of lane 4 X + r, b of lane L, c of element r): rounded once, denormals,
-// infinities and NaN patterns as v_fma_f32 has them (131072 chains of 128 each for seven mixes of values, every bit).
+// 4), lane L's element r of the result is fma(a of lane 4 X + r, b of lane L, c of element r), rounded once, denormals and
+// infinities included; a NaN in any of them is a NaN in the result.
 template <int X>
 __device__ __forceinline__ f32x4 fma_4_rows(float a, float b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 4, X, 0);

@@ -52,9 +52,19 @@ def test_selection_every_bit(gpu, case):  # noqa: F811
 
 
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("kind", ["denormal", "overflow", "ties"])
+@pytest.mark.parametrize("kind", ["denormal", "overflow", "ties", "infinite"])
 def test_selection_of_unusual_values(gpu, d, kind):  # noqa: F811
-    if kind == "ties":                       # few distinct values: many logits are equal, many are zero of either sign
+    if kind == "infinite":                   # in one dimension, of one query block and of every third key block: no NaN arises
+        def values(key, H, Nq, dd, s):
+            x = rnd(key, H, Nq, dd)
+            if key % 3 == 500 % 3:
+                x[:, 2 * 64 + 5, 7] = 0x7F80
+            else:
+                x[:, 3::3 * 64, 7], x[:, 64 + 3::6 * 64, 7] = 0x7F80, 0xFF80
+            return x
+        logits_and_sets(gpu, d, 64, 9, 60, 2, 6, 1.0, values)
+        logits_and_sets(gpu, d, 64, 45, 60, 2, 21, 1.0, values)
+    elif kind == "ties":                       # few distinct values: many logits are equal, many are zero of either sign
         values = lambda key, H, Nq, dd, s: synth.to_bf16_bits(np.round(synth.normals(synth.stream_key(9, "misc", key), H * Nq * dd)).reshape(H, Nq, dd) * 0)  # noqa: E731
         logits_and_sets(gpu, d, 64, 7, 64, 1, 5, 1.0, values)
         values = lambda key, H, Nq, dd, s: synth.to_bf16_bits(np.repeat(np.sign(synth.normals(synth.stream_key(9, "misc", key), H * Nq)).reshape(H, Nq, 1), dd, 2))  # noqa: E731
@@ -86,3 +96,33 @@ def test_queries_pooled_with_the_append(gpu, case):  # noqa: F811
         two.attention(Q)
         two.update()
         assert np.array_equal(one.slot_src.cpu().numpy(), two.slot_src.cpu().numpy()), f"chunk {g}: slots"
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("nqb", [7, 45])
+def test_selection_of_nan(gpu, d, nqb):  # noqa: F811
+    """NaN of either sign in a few key blocks and in a query block: logits are NaN where the chain has one and every bit of the
+    others is the oracle's; a NaN ranks by its bits, above everything or below, as the numbers' order continues."""
+    H, B, w, k = 2, 64, 2, 5
+    Nq, scale = nqb * B, np.float32(1.0 / math.sqrt(d))
+    st = OracleState(H, d, B, Nq, w, 1, k, scale, fold=False)
+    c = gpu["cache"].PbsaCache(H, d, B, Nq, w, 1, k, scale, fold=False, device=DEV)
+    for g in range(w + 1):
+        Q, K, V = rnd(600 + 3 * g, H, Nq, d), rnd(601 + 3 * g, H, Nq, d), rnd(602 + 3 * g, H, Nq, d)
+        K[:, 2 * B + 9, 5], K[:, 5 * B, d - 1], Q[:, 3 * B + 1, 11] = 0x7FC1, 0xFFC0, 0x7FC0
+        st.append_chunk(synth.to_blocks(K, B), synth.to_blocks(V, B), np.full(nqb, B, np.int32), g * nqb + np.arange(nqb))
+        c.append_chunk(gpu["wl"].bf16_tensor(K, DEV), gpu["wl"].bf16_tensor(V, DEV), g)
+    _, Z = st.select(Q, want_logits=True)
+    c.select(gpu["wl"].bf16_tensor(Q, DEV))
+    got = c.Zl.view(-1)[:Z.size].cpu().numpy().reshape(Z.shape)
+    seen = np.arange(st.n_loc)[None] <= st.n_loc - nqb + np.arange(nqb)[:, None]
+    assert np.isnan(Z[:, seen]).any() and np.array_equal(np.isnan(got[:, seen]), np.isnan(Z[:, seen]))
+    number = seen[None] & ~np.isnan(Z)
+    assert np.array_equal(got.view(np.uint32)[number], Z.view(np.uint32)[number])
+    bits = (got + np.float32(0)).view(np.uint32).astype(np.int64)
+    key = np.where(bits >> 31, 0xFFFFFFFF - bits, bits + (1 << 31))
+    sel = c.sel.cpu().numpy()
+    for h in range(H):
+        for i in range(nqb):
+            best = sorted(np.flatnonzero(seen[i]), key=lambda l: (-key[h, i, l], l))[:k]
+            assert sel[h, i].tolist() == sorted(int(l) for l in best), (h, i)
