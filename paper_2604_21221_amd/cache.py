@@ -193,8 +193,8 @@ class PbsaCache:
         return pooled
 
     def _in_place(self, *tensors):
-        """Whether pbsa_append_chunk takes K and V (or None, and the queries) as they are and nothing but their bytes counts: bf16 on this GPU,
-        whole, rows contiguous and aligned; nothing that torch would record, transform or refuse in a copy (gradients,
+        """Whether pbsa_append_chunk takes K and V (or None) as they are and nothing but their bytes counts: bf16 on this
+        GPU, whole, rows contiguous and aligned; nothing that torch would record, transform or refuse in a copy (gradients,
         forward mode, function transforms, dispatch modes, tracing, inference tensors outside their mode); and not rows of
         the ring itself: K is copied before V is, and a launch knows no such order."""
         Kl, Vl = self.Kl, self.Vl
@@ -220,9 +220,11 @@ class PbsaCache:
             torch.autograd.graph.increment_version([dst for dst, src in ((self.Kl, K), (self.Vl, V)) if src is not None])
             pool = pool and K is not None
             args = self._full, K, V, pos * self.nqb, zero_tail, self.Kl, self.Vl, self.Kc_l if pool else None
-            # Up to 400 blocks the launch has room for the queries' (step without -> with them: 76.1 -> 72.8 us at 8 heads x 20
-            # blocks of 128, 128.4 -> 125.6 at 8 x 32, 72.3 -> 69.8 at 16 x 24 of 64; 88.1 -> 88.5 at 6 x 38 of 64); beyond, their
-            # bytes take it as long as they take the selection (187.3 -> 187.5 at 12 x 37 of 128, 181.6 -> 181.3 at 16 x 42).
+            # Up to 400 blocks the launch pools the queries for less than the selection takes to (step without -> with them,
+            # heads x blocks x block size at d = 64 | 128: 8 x 25 x 128 64.1 -> 61.4 us | 86.2 -> 83.1, 6 x 38 x 64
+            # 74.9 -> 74.0 | 89.6 -> 89.0, 10 x 30 x 64 57.9 -> 57.0 | 70.0 -> 68.8, 12 x 25 x 128 83.2 -> 81.8 | 101.8 -> 101.0,
+            # 12 x 33 x 128 87.7 -> 83.2 | 116.2 -> 114.6, 16 x 25 x 64 55.1 -> 54.0 | 69.8 -> 67.3); beyond, their bytes take it
+            # as long as they take the selection (187.3 -> 187.5 at 12 x 37 x 128 | d = 128, 181.6 -> 181.3 at 16 x 42).
             if (pool and Q is not None and self._pending is None and self.H * self.nqb <= 400
                     and pbsa.plain_rows(self.Kl, self.Vl, self.H, self.Nq, self.d, torch.is_grad_enabled(), Q)):
                 pbsa.pbsa_append_chunk(*args, None, Q, self.Qc)

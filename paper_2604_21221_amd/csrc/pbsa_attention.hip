@@ -790,8 +790,9 @@ attention_kernel(AttnArgs a, PlanArgs<PLAN> pl) {
   // tiles of both waves, ragged tiles, full tiles of wave 0 only, of wave 1 only.  Every part of the list is in ascending
   // candidate order.  With each wave sweeping all candidates, three LDS words each, and a division per selected block in a
   // loop unrolled for the largest shape the list took 3.4 us of a launch of 12 heads x 4680 rows, now 2.1 (four denoising
-  // passes at 8 + 16 blocks of 128 497.9 -> 485.7 us, a chained step 111.3 -> 109.7, select, forward and backward of
-  // 3 x 1500 x 64 44.8 -> 43.4; a chained step at 32 + 48 blocks of 64 175.0 -> 175.5).
+  // passes at 8 + 16 blocks of 128 497.9 -> 485.7 us, select, forward and backward of 3 x 1500 x 64 44.8 -> 43.4; nothing
+  // beyond noise in a chained step, whose launch holds the decisions too: 111.3 -> 109.7 and, at 32 + 48 blocks of 64,
+  // 175.0 -> 175.5).
   int* plen_s = reinterpret_cast<int*>(lblk + kLocMax);
   int* cnt_s = plen_s + PBSA_MAX_C_ATTEND + 1;
   // The first of each are fetched together (up to 384 local blocks, 128 slots, 256 selected blocks); the rest, at shapes beyond

@@ -3,15 +3,15 @@
 //     dV = P^T dO        dP = dO V^T        dZ = P o (dP - D),  D[q] = dO[q] . O[q]
 //     dQ = scale dZ K    dK = scale dZ^T Q
 // P is recomputed from the forward's log-sum-exp: exp2(z c2 - lse log2 e); nothing of the forward's
-// probabilities is stored.  A launch of prep, then one of dq and dkv together (bwd_walk_kernel), no atomics, every output
-// element written by exactly one lane:
+// probabilities is stored.  A launch of prep, then one of dq and dkv together (bwd_walk_kernel; one of each at d = 64 where
+// dq alone fills the chip), no atomics, every output element written by exactly one lane:
 //   prep   per row -lse log2 e and -D (fp32, D from the bf16 tensors); per local block the query blocks that attend it
 //   dq     one wave per 64 query rows: their Q and dO fragments stay in registers, the 64-key tiles they attend
 //          (persistent slots, then the blocks of their row of sel) stream through LDS; where there are few such waves, two
 //          or four share a walk
-//   dkv    two waves per 64-key tile, or twice two where there are few, each pair with half of the walk: its K and V fragments stay in registers, the 64-row tiles of the
-//          query blocks that attend it (all of them for a persistent slot; those whose row of sel names the block
-//          otherwise, which prep has written down) stream through LDS
+//   dkv    two waves per 64-key tile, or twice two where there are few, each pair with half of the walk: its K and V
+//          fragments stay in registers, the 64-row tiles of the query blocks that attend it (all of them for a persistent
+//          slot; those whose row of sel names the block otherwise, which prep has written down) stream through LDS
 // Both have a fixed side in registers (MFMA B operands) and a streamed side in LDS (A operands):
 //   A1 = T1 F1^T, A2 = T2 F2^T   32 streamed rows x 32 fixed rows per MFMA chain (v_mfma_f32_32x32x16_bf16)
 //          dq:  T1 = K, T2 = V, F1 = Q, F2 = dO   ->  A1 = Z^T / scale, A2 = dP^T     (keys x queries)
@@ -236,7 +236,7 @@ __global__ void __launch_bounds__(256) bwd_prep_kernel(BwdArgs a) {
 
 // 32 rows of an output, NT tiles of 32 dimensions each, whose transpose a wave holds in its accumulators (element v of tile
 // dt is dim 32 dt + 8 (v / 4) + 4 (lane / 32) + v % 4 of row lane % 32), times `scale`, to memory, rows [0, n_rows) of them,
-// through 32 NT KiB / 8 of LDS that nobody else uses: a lane's 16 bytes of a row go to LDS at chunk c ^ row and leave in
+// through 4 NT KiB of LDS that nobody else uses: a lane's 16 bytes of a row go to LDS at chunk c ^ row and leave in
 // instructions of 1 KiB.  Straight from the accumulators an instruction would write 32 bytes of each of 32 rows: 691.8 ->
 // 685.5 us for select, forward and backward at 12 x 4680 x 128 with 32 + 48 blocks of 64, 430.4 -> 426.0 with 8 + 16 blocks of
 // 128, 165.1 -> 162.7 at 16 x 2048 x 128.
@@ -504,10 +504,9 @@ __device__ __forceinline__ void dkv_body(const BwdArgs& a, const int block, unsi
   // at 3 x 1500 x 64, 133.7 -> 125.6 at 4 x 3000 x 128, 432.5 -> 425.5 at 12 x 4680 x 128 with 8 + 16 blocks of 128.  The large
   // ones are held by power: with zeros for data the same walks take 20 % less, at a higher clock.)
   // The compiler orders instructions without side effects as it likes: left alone it issued all the elementwise work
-  // behind the last MFMA, and a
-  // turn took 2700 cycles for 1024 cycles of matrix work, on a compute unit of its own too (12 heads x 4680 x 128 with
-  // 32 + 48 blocks of 64: select, forward and backward 969 -> 835 us; 8 + 16 blocks of 128: 640 -> 552 us).  An empty asm with the value as
-  // its operand (pin) keeps each MFMA and each slice where it stands.
+  // behind the last MFMA, and a turn took 2700 cycles for 1024 cycles of matrix work, on a compute unit of its own too
+  // (12 heads x 4680 x 128 with 32 + 48 blocks of 64: select, forward and backward 969 -> 835 us; 8 + 16 blocks of 128: 640 ->
+  // 552 us).  An empty asm with the value as its operand (pin) keeps each MFMA and each slice where it stands.
   // Per element: fma, exp2, multiply, half of two conversions.  The row's -D is what the accumulator starts from, and
   // rows that do not exist have -inf in the place of their -lse log2 e: their P is an exact zero without a mask.
   constexpr int NS = 2 * KS, EPS = 16 / NS;                // slices, accumulator elements per slice
@@ -702,8 +701,8 @@ __device__ __forceinline__ void dkv_body(const BwdArgs& a, const int block, unsi
 // for the first products, transposed for the second -- feeds two MFMAs.  The wave stages its own half tiles (32 keys of K
 // and of V per ring entry, two entries) and is the only one to read them: no barrier in the walk.  The two waves of a
 // workgroup have a row tile each or, dq_split, half of one row tile's walk each, four a quarter of it: the sums meet in LDS
-// at the end and are added in the order of the waves.  Q and dO fragments and the dQ^T accumulators fill the accumulator half of the register file
-// (128 + 128 registers at d = 128).  Bound at 12 x 4680 x 128: matrix and vector work in one wave per SIMD at the clock the
+// at the end and are added in the order of the waves.  Q and dO fragments and the dQ^T accumulators fill the accumulator
+// half of the register file (128 + 128 registers at d = 128).  Bound at 12 x 4680 x 128: matrix and vector work in one wave per SIMD at the clock the
 // chip holds under it (222 GFLOP in 215 us, 1.03 PFLOP/s; a library product of 8192^3 reaches 1.19).  The elementwise stages
 // are spread over 40 of a turn's 48 MFMAs; over 28 of them: 712.8 against 708.3 us for select, forward and backward, 89.8
 // against 88.2 at 3 x 1500 x 64.  Two waves to a workgroup that share the tiles both attend (half the traffic with
@@ -1143,7 +1142,9 @@ hipError_t launch_attention_bwd(const pbsa_params& p, const bf16_t* Q, const bf1
   // the shared launch saves where dq's walks are long and its waves fill the last round of 1024 places, the time dkv could
   // have had anyway: 12 x 4680 rows with 32 + 48 blocks of 64 (888 waves) 414 us as two launches and 422 as one, 13 x 4800 441
   // and 459; but 11 x 4680 (814 waves) 400 and 393, 16 x 4000 with 4 + 8 blocks 145 and 132, 12 x 4680 with 16 + 24 blocks 272
-  // and 248, 8 x 2000 with 6 + 8 blocks 95 and 71.
+  // and 248, 8 x 2000 with 6 + 8 blocks 95 and 71.  Beyond one round, the backward by itself with the same 32 + 48 blocks:
+  // 1036 waves 409 us as two launches and 350 as one, 1184 437 and 396, 1344 467 and 440, 1512 503 and 497, 1596 518 and 524,
+  // 1680 (where it is two again) 540 and 542.
   const int rounds = (n_tiles + 1023) / 1024;
   if (p.d == 64 && n_cand >= 64 && 5 * n_tiles >= 4 * 1024 * rounds) {
     e = launch_walk<64, kDq, 1>(a, head_items(n_row_tiles, p.H), 0, 2 * tile + (size_t)4 * n_cand + 16, stream);
@@ -1153,8 +1154,10 @@ hipError_t launch_attention_bwd(const pbsa_params& p, const bf16_t* Q, const bf1
   // Four waves share a walk where there are few walks: a workgroup of four has a compute unit to itself, and at up to 448
   // workgroups the longest walks, which come first, end half as late (2 waves -> 4: 52 -> 45 us at 3 x 1500 x 64, 309
   // workgroups; 99 -> 90 at 3 x 2000 x 128, 438; 140 -> 112 at 1 x 4680 x 128, 403; but 73 -> 74 at 6 x 1200 x 128, 510,
-  // 86 -> 92 at 4 x 3000 x 64, 836).  Walks of fewer than eight row tiles gain less than the meeting of the sums costs
-  // (50.0 -> 50.4 at 12 x 300 x 128, five row tiles).
+  // 86 -> 92 at 4 x 3000 x 64, 836; the backward by itself 35.3 -> 33.7 at 5 x 1100 x 128, 395, and 34.9 -> 37.4 at
+  // 6 x 1100 x 128, 474).  Walks of fewer than eight row tiles are left to two waves for 12 x 300 x 128 (five row tiles), where
+  // four gained nothing (50.0 -> 50.4); with fewer heads they would (21 -> 19 at 8 x 300 x 128, 22 -> 17 at 4 x 300 x 64,
+  // 43 -> 31 at 2 x 384 x 128 with 17 + 16 blocks).
   const size_t lds4 = 8 * tile + (size_t)4 * std::max(4 * n_cand, sub * p.nqb) + 16;
   if (n_tiles + p.H * (p.C + 1 + p.n_loc) * sub <= 448 && n_row_tiles >= 8 && lds4 <= 156 * 1024) {
     const unsigned n_dq = head_items(n_row_tiles, p.H);

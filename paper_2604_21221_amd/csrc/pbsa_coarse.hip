@@ -146,9 +146,9 @@ __global__ void __launch_bounds__(kThreads) pool_kernel(PoolArgs a) {
 // order (the pinned order of the pooling), two dimensions each: 64 consecutive words per row, free of bank conflicts.
 // Bound by HBM: each byte is read once and written once, and a selection that follows need not read K again: 11.1 us
 // for a chunk of 12 x 4680 x 128 (57.5 MB moved, 5.2 TB/s), where four tensor copies took 27 us and the selection's
-// own pooling launch another 8.7.  The chunk's queries can be pooled along (and are not copied): a third of the workgroups
-// more, which is nothing to a launch that leaves most of the chip idle, against the 1.3 to
-// 2.8 us the selection's own pooling takes (a step of 5 x 1000 x 64 40.7 -> 38.2 us, of 8 x 2500 x 128 76.1 -> 72.8).
+// own pooling launch another 8.7.  The chunk's queries can be pooled along (and are not copied): half as many workgroups
+// again, which read a third of the bytes and write next to none, against the 1.3 to 2.8 us that the selection takes to pool
+// them itself (a step of 5 x 1000 x 64 40.7 -> 38.2 us, of 8 x 2500 x 128 76.1 -> 72.8; up to which size: PbsaCache).
 // ------------------------------------------------------------------------------------------------
 struct AppendArgs {
   int B, Nq, nqb, n_loc_cap, slot0, zero_tail;
@@ -307,8 +307,7 @@ struct SelectGeo {
 // r ranks row r.  DX = 32 up to 8 waves; 16 beyond, where two rounds of 32 would not fit in LDS.  A query block is
 // looked at by exactly one workgroup, so that one pools it (Eq. 6, D / 2 threads per block, tokens added in ascending
 // order) while its pooled keys arrive; at least four waves, so that the four blocks are pooled and ranked side by side
-// whatever NM is.  Latency bound, a chain of phases; inside a
-// workgroup, by time stamps, against 64-bit products for the queries' addresses, chains of v_fma_f32 over two rounds in LDS
+// whatever NM is.  Latency bound, a chain of phases; inside a workgroup, by time stamps, against 64-bit products for the queries' addresses, chains of v_fma_f32 over two rounds in LDS
 // and all 32 bits of the threshold: pooling 2.5 -> 1.3 us, logits 1.2 -> 0.5, threshold 1.2 -> 0.8 at 2 heads x 4 blocks of 64
 // (16 columns of 64 dimensions); 3.7 -> 2.6, 2.7 -> 1.4, 2.6 -> 1.4 at 12 x 37 blocks of 128 (148 columns of 128).
 template <int D, int NM>
@@ -913,8 +912,9 @@ hipError_t launch_select_apply(const pbsa_params& p, const bf16_t* Q, const bf16
                                const int32_t* S_cnt, const bf16_t* Vl, const UpdateWs& ws, hipStream_t stream) {
   const PoolArgs pa = select_pool_args(p, Q, Kl, l_len, l_map, Kc_l, Qc, true);
   const FoldArgs fa = fold_args(pu, Kp, Vp, p_len, S_sum, S_cnt, Kl, Vl, ws);
-  // the fold / promote workgroups ride in the pooling launch: its workgroups have the same size and no LDS of their
-  // own (in the logits launch, 80 KB of LDS per workgroup, they would wait for places: measured slower)
+  // the fold / promote workgroups ride in the pooling launch, whose workgroups have the same size and no LDS (in the logits
+  // launch, whose workgroups take 36 to 145 KiB each, they would wait for places: 33.0 us for the call against 30.1, measured
+  // when those took 80)
   const int jpw = kFoldThreads / (p.d / 2), rows_per_wg = kFoldThreads / (pu.d / 4);
   const int n_fold_x = (2 * pu.B + rows_per_wg - 1) / rows_per_wg;
   const dim3 grid(n_fold_x * pu.H + (pa.n_jobs + jpw - 1) / jpw);

@@ -1,7 +1,8 @@
 """Backward where its kernels' tiles, lists and workgroup order can go wrong, every element against the fp64 oracle: a last
 row tile of 1, 31, 32, 33 and 63 rows (half tiles with no row, one row, all but one), one, three and nine heads (fewer and
 more than the eight dies the grid is dealt over), more query blocks than one word of the turned-around selection holds,
-blocks that every row, few rows and no row selected, and either side of the lines at which the launch is set up differently.  Bounds: those of test_gpu_parity_grad.py, derived there."""
+blocks that every row, few rows and no row selected, and either side of the lines at which the launch is set up differently.
+Bounds: those of test_gpu_parity_grad.py, derived there."""
 import pytest
 
 torch = pytest.importorskip("torch")
