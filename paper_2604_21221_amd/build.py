@@ -20,6 +20,7 @@ SOURCES = {
     "pbsa_coarse.hip": ["-ffp-contract=off", "-fhip-fp32-correctly-rounded-divide-sqrt"],
     # the attention launch can carry the update's decisions (pbsa_plan_device.h): correctly rounded division for those
     "pbsa_attention.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-fhip-fp32-correctly-rounded-divide-sqrt"],
+    "pbsa_attention_team.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-fhip-fp32-correctly-rounded-divide-sqrt"],
     "pbsa_layout.hip": [],
     "pbsa_mass.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "pbsa_backward.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],

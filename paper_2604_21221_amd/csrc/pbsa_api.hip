@@ -315,7 +315,7 @@ static int attention_fwd_mass(const pbsa_params* p, const void* Q, const void* K
       static_cast<const pbsa::bf16_t*>(Vl), l_len, l_map, sel, static_cast<pbsa::bf16_t*>(O), lse, &rows,
       scratch, stream);
   if (e != hipSuccess) return hip_fail(e);
-  e = pbsa::launch_mass_reduce(*p, rows, lse, Mt, stream);
+  e = pbsa::launch_mass_reduce(*p, rows, lse, Mt, pbsa::attn_team(*p, scratch != nullptr).waves > 0, stream);
   return e == hipSuccess ? PBSA_OK : hip_fail(e);
 }
 

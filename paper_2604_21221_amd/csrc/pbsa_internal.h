@@ -43,7 +43,9 @@ hipError_t launch_select_apply(const pbsa_params& p, const bf16_t* Q, const bf16
 // Scratch of the attention call that also produces the attention mass: what the attention kernel leaves for
 // the pass that follows it.  Per workgroup (128 query rows of a head) a tile list of list_cap ints: the ends of
 // the list's four parts, then a descriptor per tile; per wave r_slots records of 64 floats, one per tile in
-// the order the wave walks them (log2 of each row's share of its normaliser, absolute).
+// the order the wave walks them (log2 of each row's share of its normaliser, absolute).  By teams: the lengths of
+// two lists, for each 64 of the rows, and from int 4 on the lists, list_cap - 4 16-bit descriptors each (key block
+// times 2 plus the tile of it); r_slots records for each 64 rows, in list order.
 struct MassRows {
   float* R;
   int32_t* list;
@@ -60,6 +62,12 @@ struct AttnSplit {
   size_t o_bytes, bytes;
 };
 AttnSplit attn_split(const pbsa_params& p);
+// The attention by teams of `waves` waves to 64 rows (pbsa_attention_team.hip), each unit's keys in `parts` such workgroups;
+// waves = 0: by query tiles of 128 rows, as attn_split says.  scratch: whether the call was given attn_split(p).bytes.
+struct AttnTeam {
+  int waves, parts, units;
+};
+AttnTeam attn_team(const pbsa_params& p, bool scratch);
 
 // rows == nullptr: the plain attention kernel; split_ws: attn_split(p).bytes of scratch, or nullptr: nothing is split
 hipError_t launch_attention(const pbsa_params& p, const bf16_t* Q, const bf16_t* Kp, const bf16_t* Vp,
@@ -74,7 +82,8 @@ hipError_t launch_attention_plan(const pbsa_params& p, const bf16_t* Q, const bf
                                  const float* Kc_l, const float* Zl, float* Kc_p, int64_t* p_id, int32_t* S_cnt, int fold,
                                  const int64_t* l_id, float* scores, int32_t* slot_src, const UpdateWs& ws,
                                  void* split_ws, hipStream_t stream);
-hipError_t launch_mass_reduce(const pbsa_params& p, const MassRows& rows, const float* lse, float* Mt,
+// by_teams: the records are those of a launch by teams (attn_team)
+hipError_t launch_mass_reduce(const pbsa_params& p, const MassRows& rows, const float* lse, float* Mt, bool by_teams,
                               hipStream_t stream);
 // The update in two parts.  plan: scoring and retention -- reads the cache's metadata and pooled keys, writes the
 // decisions (scores, slot_src, p_id, Kc_p, S_cnt, and into the workspace the fold list, the promotions and the new

@@ -383,28 +383,37 @@ struct ReduceArgs {
 // workgroup are in flight together
 constexpr int kReduceThreads = 1024;
 
-template <int B>
+// TEAM: the attention went by teams, 64 rows each with a list of its own, whose tiles and records have the same numbers: the
+// lengths of the two lists, then (from entry 4 on) the two as 16-bit descriptors.
+template <int B, bool TEAM>
 __global__ void __launch_bounds__(kReduceThreads) mass_reduce_kernel(ReduceArgs a) {
   constexpr int G = kRowsPerWg / B, SUB = B / kTile;
+  constexpr int NL = TEAM ? 2 : 1;                         // lists
   extern __shared__ __align__(16) unsigned char smem[];
-  float* part = reinterpret_cast<float*>(smem);            // [tile][wave of the attention kernel]
-  int* meta_s = reinterpret_cast<int*>(part + 2 * a.list_cap);
-  int* pos_s = meta_s + a.list_cap;                        // [key block][tile of the block] -> list position or -1
+  float* part = reinterpret_cast<float*>(smem);            // [tile][64 rows: wave of the attention kernel, or team]
+  int* pos_s = reinterpret_cast<int*>(part + 2 * a.list_cap);   // [list][key block][tile of the block] -> list position or -1
   __shared__ int ends[4];
   const int n_qt = (a.Nq + kRowsPerWg - 1) / kRowsPerWg;
   const int logical = blockIdx.x, h = logical / n_qt, T0 = (logical % n_qt) * kRowsPerWg, i0 = T0 / B;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int32_t* list = a.list + (size_t)logical * a.list_cap;
-  if (tid < 4) ends[tid] = list[tid];
-  for (int i = tid; i < a.n_u * SUB; i += kReduceThreads) pos_s[i] = -1;
+  if constexpr (TEAM) {
+    if (tid < 2) ends[tid] = T0 + 64 * tid < a.Nq ? list[tid] : 0;
+  } else {
+    if (tid < 4) ends[tid] = list[tid];
+  }
+  for (int i = tid; i < NL * a.n_u * SUB; i += kReduceThreads) pos_s[i] = -1;
   __syncthreads();
-  const int n_shared = min(ends[1], a.list_cap - 4), n_list = min(ends[3], a.list_cap - 4);
-  const int solo1 = min(ends[2], n_list);                  // wave 0 alone: [n_shared, solo1), wave 1: [solo1, n_list)
-  for (int i = tid; i < n_list; i += kReduceThreads) {
-    const int m = list[4 + i];
-    meta_s[i] = m;
-    const int u = (m >> 10) & 1023, sub = (m >> 20) & 1;
-    if (u < a.n_u && sub < SUB) pos_s[u * SUB + sub] = i;
+  const int cap = a.list_cap - 4;
+  // whole: shared tiles [0, n_shared), then wave 0's own up to solo1, then wave 1's
+  const int n_shared = TEAM ? 0 : min(ends[1], cap), n_list = TEAM ? min(max(ends[0], ends[1]), cap) : min(ends[3], cap);
+  const int solo1 = TEAM ? 0 : min(ends[2], n_list);
+  for (int i = tid; i < NL * n_list; i += kReduceThreads) {
+    const int aw = TEAM && i >= n_list ? 1 : 0, at = i - aw * n_list;
+    if (TEAM && at >= ends[aw]) continue;
+    const int m = TEAM ? reinterpret_cast<const uint16_t*>(list + 4)[aw * cap + at] : list[4 + at];
+    const int u = TEAM ? m >> 1 : (m >> 10) & 1023, sub = TEAM ? m & 1 : (m >> 20) & 1;
+    if (u < a.n_u && sub < SUB) pos_s[(aw * a.n_u + u) * SUB + sub] = at;
   }
   // minus log2 of the normaliser of the rows this lane stands for, one per wave of the attention kernel; a row
   // that does not exist or attended nothing takes no part
@@ -427,7 +436,9 @@ __global__ void __launch_bounds__(kReduceThreads) mass_reduce_kernel(ReduceArgs 
       const int q = q0 + j, p = q >> 1, aw = q & 1;
       // the wave's record of the tile: shared tiles come first, then its own
       int slot = -1;
-      if (q < 2 * n_list) {
+      if (TEAM) {
+        if (p < n_list && p < ends[aw]) slot = p;
+      } else if (q < 2 * n_list) {
         if (p < n_shared) slot = p;
         else if (aw == 0 && p < solo1) slot = p;
         else if (aw == 1 && p >= solo1) slot = n_shared + (p - solo1);
@@ -452,13 +463,14 @@ __global__ void __launch_bounds__(kReduceThreads) mass_reduce_kernel(ReduceArgs 
     float v = 0.0f;
 #pragma unroll
     for (int sub = 0; sub < SUB; ++sub) {
-      const int p = pos_s[u * SUB + sub];
-      if (p >= 0) {
-        if constexpr (G == 2) {
-          v = v + part[2 * p + g];           // wave g of the attention kernel is query block g
-        } else {
-          v = v + part[2 * p];
-          v = v + part[2 * p + 1];
+      if constexpr (G == 2) {                // wave g of the attention kernel, or team g, is query block g
+        const int p = pos_s[((TEAM ? g : 0) * a.n_u + u) * SUB + sub];
+        if (p >= 0) v = v + part[2 * p + g];
+      } else {
+#pragma unroll
+        for (int aw = 0; aw < 2; ++aw) {
+          const int p = pos_s[((TEAM ? aw : 0) * a.n_u + u) * SUB + sub];
+          if (p >= 0) v = v + part[2 * p + aw];
         }
       }
     }
@@ -497,14 +509,15 @@ MassRows carve_mass_ws(const pbsa_params& p, void* base) {
   return m;
 }
 
-hipError_t launch_mass_reduce(const pbsa_params& p, const MassRows& rows, const float* lse, float* Mt,
+hipError_t launch_mass_reduce(const pbsa_params& p, const MassRows& rows, const float* lse, float* Mt, bool by_teams,
                               hipStream_t stream) {
   const int n_u = p.C + 1 + p.n_loc, sub = p.B / kTile;
   ReduceArgs a{p.H, p.Nq, p.nqb, (p.nqb + 3) & ~3, n_u, rows.r_slots, rows.list_cap, rows.R, rows.list, lse, Mt};
   const int n_wg = p.H * ((p.Nq + kRowsPerWg - 1) / kRowsPerWg);
-  const size_t lds = (size_t)rows.list_cap * 12 + (size_t)n_u * sub * 4;
-  if (p.B == 128) hipLaunchKernelGGL(mass_reduce_kernel<128>, dim3(n_wg), dim3(kReduceThreads), lds, stream, a);
-  else hipLaunchKernelGGL(mass_reduce_kernel<64>, dim3(n_wg), dim3(kReduceThreads), lds, stream, a);
+  const size_t lds = (size_t)rows.list_cap * 8 + (size_t)n_u * sub * (by_teams ? 8 : 4);
+  const auto kernel = p.B == 128 ? (by_teams ? mass_reduce_kernel<128, true> : mass_reduce_kernel<128, false>)
+                                 : (by_teams ? mass_reduce_kernel<64, true> : mass_reduce_kernel<64, false>);
+  hipLaunchKernelGGL(kernel, dim3(n_wg), dim3(kReduceThreads), lds, stream, a);
   return hipGetLastError();
 }
 
