@@ -256,7 +256,7 @@ __device__ __forceinline__ void coarse_dots(const float* const* cols, int n_cols
 struct SelectArgs {
   int H, nqb, n_loc, n_loc_cap, k, causal;
   float scale;
-  const float* Kc_l;
+  float* Kc_l;
   float* Qc;
   const int32_t* l_map;
   int32_t* sel;
@@ -264,6 +264,9 @@ struct SelectArgs {
   const bf16_t* Q;          // given: the query blocks are pooled here (into Qc), else Qc holds them
   int B, Nq;
   long q_stride_h, q_stride_t;
+  const bf16_t* Kl;         // KEYS: blocks from pool_from on are pooled from here
+  const int32_t* l_len;
+  int pool_from;
 };
 
 // One wave-wide global -> LDS load of 16 bytes per lane: LDS bytes [lds_off, lds_off + 1024) receive
@@ -283,6 +286,10 @@ template <int X>
 __device__ __forceinline__ f32x4 fma_4_rows(float a, float b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 4, X, 0);
 }
+
+constexpr int kOwnKeys = 12;      // the most key blocks that the selection pools itself
+template <int NM, bool KEYS>
+constexpr int select_waves() { return KEYS ? 8 : NM < 4 ? 4 : NM; }
 
 template <int D, int NM>
 struct SelectGeo {
@@ -310,7 +317,10 @@ struct SelectGeo {
 // whatever NM is.  Latency bound, a chain of phases; inside a workgroup, by time stamps, against 64-bit products for the queries' addresses, chains of v_fma_f32 over two rounds in LDS
 // and all 32 bits of the threshold: pooling 2.5 -> 1.3 us, logits 1.2 -> 0.5, threshold 1.2 -> 0.8 at 2 heads x 4 blocks of 64
 // (16 columns of 64 dimensions); 3.7 -> 2.6, 2.7 -> 1.4, 2.6 -> 1.4 at 12 x 37 blocks of 128 (148 columns of 128).
-template <int D, int NM>
+//
+// KEYS: the newest of the key blocks are pooled here too, by every workgroup of the head for itself (the first one also
+// leaves them in Kc_l), beside its four query blocks: eight waves pool 16 blocks of 64 dimensions at a time, 8 of 128.
+template <int D, int NM, bool KEYS = false>
 __device__ __forceinline__ void select_body(const SelectArgs& a, const int bx, const int h, unsigned char* smem) {
   using G = SelectGeo<D, NM>;
   constexpr int NCP = NM * 64;                        // padded columns
@@ -318,7 +328,7 @@ __device__ __forceinline__ void select_body(const SelectArgs& a, const int bx, c
   constexpr int CPC = DX / 4;                         // 16-byte chunks per column and round
   constexpr int NI = 64 * CPC / 64;                   // load instructions per wave and round (64 columns)
   constexpr int CPI = 64 / CPC;                       // columns per instruction
-  constexpr int NW = NM < 4 ? 4 : NM, NT = 64 * NW;   // waves, threads
+  constexpr int NW = select_waves<NM, KEYS>(), NT = 64 * NW;   // waves, threads
   float* qs = reinterpret_cast<float*>(smem + NBUF * BUF);                      // [4][D]
   float* zs = qs + 4 * D;                                                       // [4][NCP]
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -348,7 +358,54 @@ __device__ __forceinline__ void select_body(const SelectArgs& a, const int bx, c
     for (int r = 0; r < NBUF; ++r) PBSA_STAGE(r)
   }
 
-  if (a.Q) {
+  if constexpr (KEYS) {
+    static_assert(NBUF == NR, "a column's place holds all of it");
+    constexpr int JPS = NT / (D / 2), SW = (4 + kOwnKeys) / JPS;      // blocks at a time, times
+    const int c = threadIdx.x % (D / 2), n_stale = a.n_loc - a.pool_from;
+    float2 mean[SW];
+    int col[SW], slot[SW];                            // of a key block: its column (-1: it is nowhere) and place
+#pragma unroll
+    for (int w = 0; w < SW; ++w) {
+      const int job = w * JPS + (int)threadIdx.x / (D / 2), i = i0 + job, l = a.pool_from + job - 4;
+      const bf16_t* p = nullptr;
+      long pitch = 0;
+      int len = 0;
+      col[w] = -1;
+      slot[w] = 0;
+      if (job < 4) {
+        if (i < a.nqb) {
+          len = min(a.B, a.Nq - i * a.B);
+          pitch = a.q_stride_t;
+          p = a.Q + (size_t)h * a.q_stride_h + (size_t)i * a.B * pitch + 2 * c;
+        }
+      } else if (job < 4 + n_stale) {
+        slot[w] = a.l_map[l];
+        if (slot[w] >= 0 && slot[w] < a.n_loc_cap) {
+          len = max(0, min(a.l_len[l], a.B));
+          pitch = D;
+          p = a.Kl + ((size_t)h * a.n_loc_cap + slot[w]) * a.B * D + 2 * c;
+          col[w] = l;
+        }
+      }
+      float acc0 = 0.0f, acc1 = 0.0f;
+      pool_block(p, pitch, len, acc0, acc1);
+      const float fl = (float)len;
+      mean[w] = len > 0 ? make_float2(acc0 / fl, acc1 / fl) : make_float2(0.0f, 0.0f);
+      if (job < 4) {
+        if (i < a.nqb) *reinterpret_cast<float2*>(a.Qc + ((size_t)h * a.nqb + i) * D + 2 * c) = mean[w];
+        *reinterpret_cast<float2*>(qs + job * D + 2 * c) = mean[w];
+      }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // what was staged for those columns has arrived: it is written over
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < SW; ++w)
+      if (col[w] >= 0) {
+        const int r = 2 * c / DX, chunk = 2 * c % DX / 4;
+        *reinterpret_cast<float2*>(smem + r * BUF + col[w] * (DX * 4) + ((chunk ^ ((col[w] >> 1) % CPC)) << 4) + (c % 2) * 8) = mean[w];
+        if (bx == 0) *reinterpret_cast<float2*>(a.Kc_l + ((size_t)h * a.n_loc_cap + slot[w]) * D + 2 * c) = mean[w];
+      }
+  } else if (a.Q) {
     const int r = threadIdx.x / (D / 2), c = threadIdx.x % (D / 2), i = i0 + r;
     if (r < 4) {
       float acc0 = 0.0f, acc1 = 0.0f;
@@ -468,6 +525,133 @@ template <int D, int NM>
 __global__ void __launch_bounds__(64 * (NM < 4 ? 4 : NM)) select_kernel(SelectArgs a) {
   extern __shared__ __align__(1024) unsigned char smem[];
   select_body<D, NM>(a, blockIdx.x, blockIdx.y, smem);
+}
+
+// ------------------------------------------------------------------------------------------------
+// Fold + promote.  One thread owns 4 dimensions of one position t of K or V of one head: it adds
+// the dropped blocks' rows to the running sum in candidate order, rewrites the summary row, then
+// copies row t of every kept newcomer into its slot.  A slot that is both dropped and refilled is
+// read and written by the same thread, in that order.
+// ------------------------------------------------------------------------------------------------
+struct FoldArgs {
+  int H, B, d, C, n_loc_cap, n_evict, fold;
+  bf16_t* Kp;
+  bf16_t* Vp;
+  const bf16_t* Kl;
+  const bf16_t* Vl;
+  float* S_sum;
+  const int32_t* S_cnt;
+  const int32_t* fold_n;
+  const int32_t* fold_src;
+  const int32_t* fold_len;
+  const int32_t* promo_slot;
+  const int32_t* plen_new;  // the slots' lengths after the update ...
+  int32_t* p_len;           // ... which this kernel commits
+};
+
+constexpr int kFoldBatch = 40;
+constexpr int kPromoBatch = 8;
+
+template <int NT>
+__device__ __forceinline__ void fold_promote_body(const FoldArgs& a, const int bx, const int h) {
+  // per dropped candidate: its valid length and the address of its K and of its V block
+  __shared__ const bf16_t* fptr_s[2][kMaxCand];
+  __shared__ int flen_s[kMaxCand];
+  __shared__ int promo_dst[PBSA_MAX_C], promo_src[PBSA_MAX_C], n_promo_s;   // refilled slots, compacted
+  const int C = a.C, C1 = a.C + 1, ncand_max = a.C + a.n_evict;
+  if (bx == 0)                             // nothing in this launch reads p_len: the lists carry the lengths they need
+    for (int c = threadIdx.x; c < C1; c += NT) a.p_len[(size_t)h * C1 + c] = a.plen_new[(size_t)h * C1 + c];
+  const int nf = a.fold && a.S_sum ? a.fold_n[h] : 0;
+  const size_t blk = (size_t)a.B * a.d;
+  for (int f = threadIdx.x; f < nf; f += NT) {
+    const int src = a.fold_src[(size_t)h * ncand_max + f];
+    flen_s[f] = a.fold_len[(size_t)h * ncand_max + f];
+    fptr_s[0][f] = src < C ? a.Kp + ((size_t)h * C1 + src) * blk : a.Kl + ((size_t)h * a.n_loc_cap + (src - C)) * blk;
+    fptr_s[1][f] = src < C ? a.Vp + ((size_t)h * C1 + src) * blk : a.Vl + ((size_t)h * a.n_loc_cap + (src - C)) * blk;
+  }
+  if (threadIdx.x < 64) {                  // wave 0 compacts the slots that are refilled (usually few or none)
+    int n = 0;
+    for (int c0 = 0; c0 < C; c0 += 64) {
+      const int c = c0 + (int)threadIdx.x;
+      const int ps = c < C ? a.promo_slot[(size_t)h * C + c] : -1;
+      const uint64_t m = __ballot(ps >= 0);
+      if (ps >= 0) {
+        const int pos = n + lanes_below(m);
+        promo_dst[pos] = c;
+        promo_src[pos] = ps;
+      }
+      n += __popcll(m);
+    }
+    if (threadIdx.x == 0) n_promo_s = n;
+  }
+  __syncthreads();
+  const int n_promo = n_promo_s;
+  const int tpr = a.d / 4;                                     // threads per row: 4 dimensions each
+  const int rows_per_wg = NT / tpr;
+  const int row = bx * rows_per_wg + threadIdx.x / tpr;         // over [2][B]
+  const int xc = (threadIdx.x % tpr) * 4;
+  if (row >= 2 * a.B) return;
+  const int kv = row / a.B, t = row % a.B;
+  bf16_t* P = kv ? a.Vp : a.Kp;
+  const bf16_t* L = kv ? a.Vl : a.Kl;
+  const size_t rowoff = (size_t)t * a.d + xc;
+  const bf16_t* Lh = L + (size_t)h * a.n_loc_cap * blk + rowoff;
+  // promoted rows are independent of the fold: the first few are fetched before it starts
+  uint2 pv[kPromoBatch];
+#pragma unroll
+  for (int u = 0; u < kPromoBatch; ++u)
+    pv[u] = u < n_promo ? *reinterpret_cast<const uint2*>(Lh + (size_t)promo_src[u] * blk) : make_uint2(0u, 0u);
+  if (nf > 0) {
+    float* ssum = a.S_sum + ((size_t)h * 2 + kv) * blk + rowoff;
+    float4 acc = *reinterpret_cast<float4*>(ssum);
+    const int cnt = a.S_cnt[(size_t)h * a.B + t];     // already the new count (retain_kernel)
+    // rows are loaded kFoldBatch at a time (row t exists in every block, valid or not) and added in
+    // candidate order, the add predicated on t < len
+    for (int f0 = 0; f0 < nf; f0 += kFoldBatch) {
+      uint2 v[kFoldBatch];
+#pragma unroll
+      for (int u = 0; u < kFoldBatch; ++u)
+        v[u] = *reinterpret_cast<const uint2*>(fptr_s[kv][min(f0 + u, nf - 1)] + rowoff);
+#pragma unroll
+      for (int u = 0; u < kFoldBatch; ++u) {
+        if (f0 + u < nf && t < flen_s[f0 + u]) {
+          acc.x = acc.x + bf_lo(v[u].x);
+          acc.y = acc.y + bf_hi(v[u].x);
+          acc.z = acc.z + bf_lo(v[u].y);
+          acc.w = acc.w + bf_hi(v[u].y);
+        }
+      }
+    }
+    *reinterpret_cast<float4*>(ssum) = acc;
+    if (cnt > 0) {
+      const float fc = (float)cnt;
+      uint2 w;
+      w.x = f2bf_rne(acc.x / fc) | (f2bf_rne(acc.y / fc) << 16);
+      w.y = f2bf_rne(acc.z / fc) | (f2bf_rne(acc.w / fc) << 16);
+      *reinterpret_cast<uint2*>(P + ((size_t)h * C1 + C) * blk + rowoff) = w;
+    }
+  }
+  // promoted rows: stores after the fold's loads (a refilled slot was read above by this thread)
+#pragma unroll
+  for (int u = 0; u < kPromoBatch; ++u)
+    if (u < n_promo) *reinterpret_cast<uint2*>(P + ((size_t)h * C1 + promo_dst[u]) * blk + rowoff) = pv[u];
+  for (int u0 = kPromoBatch; u0 < n_promo; u0 += kPromoBatch) {     // more than a few: the rest, batch by batch
+#pragma unroll
+    for (int u = 0; u < kPromoBatch; ++u)
+      pv[u] = u0 + u < n_promo ? *reinterpret_cast<const uint2*>(Lh + (size_t)promo_src[u0 + u] * blk) : make_uint2(0u, 0u);
+#pragma unroll
+    for (int u = 0; u < kPromoBatch; ++u)
+      if (u0 + u < n_promo) *reinterpret_cast<uint2*>(P + ((size_t)h * C1 + promo_dst[u0 + u]) * blk + rowoff) = pv[u];
+  }
+}
+
+// The selection of a small chunk with everything that would be a pooling launch before it, and the fold / promote of the
+// update before it in workgroups of their own (n_fold_x of them per head, or none).
+template <int D>
+__global__ void __launch_bounds__(512) select_small_kernel(SelectArgs a, FoldArgs fa, int n_fold_x) {
+  extern __shared__ __align__(1024) unsigned char smem[];
+  if ((int)blockIdx.x < n_fold_x) fold_promote_body<512>(fa, blockIdx.x, blockIdx.y);
+  else select_body<D, 2, true>(a, blockIdx.x - n_fold_x, blockIdx.y, smem);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -625,124 +809,6 @@ __global__ void __launch_bounds__(kThreads) retain_kernel(RetainArgs a) {
   retain_body<kThreads>(a, blockIdx.x, L);
 }
 
-// ------------------------------------------------------------------------------------------------
-// Fold + promote.  One thread owns 4 dimensions of one position t of K or V of one head: it adds
-// the dropped blocks' rows to the running sum in candidate order, rewrites the summary row, then
-// copies row t of every kept newcomer into its slot.  A slot that is both dropped and refilled is
-// read and written by the same thread, in that order.
-// ------------------------------------------------------------------------------------------------
-struct FoldArgs {
-  int H, B, d, C, n_loc_cap, n_evict, fold;
-  bf16_t* Kp;
-  bf16_t* Vp;
-  const bf16_t* Kl;
-  const bf16_t* Vl;
-  float* S_sum;
-  const int32_t* S_cnt;
-  const int32_t* fold_n;
-  const int32_t* fold_src;
-  const int32_t* fold_len;
-  const int32_t* promo_slot;
-  const int32_t* plen_new;  // the slots' lengths after the update ...
-  int32_t* p_len;           // ... which this kernel commits
-};
-
-constexpr int kFoldBatch = 40;
-constexpr int kPromoBatch = 8;
-
-template <int NT>
-__device__ __forceinline__ void fold_promote_body(const FoldArgs& a, const int bx, const int h) {
-  // per dropped candidate: its valid length and the address of its K and of its V block
-  __shared__ const bf16_t* fptr_s[2][kMaxCand];
-  __shared__ int flen_s[kMaxCand];
-  __shared__ int promo_dst[PBSA_MAX_C], promo_src[PBSA_MAX_C], n_promo_s;   // refilled slots, compacted
-  const int C = a.C, C1 = a.C + 1, ncand_max = a.C + a.n_evict;
-  if (bx == 0)                             // nothing in this launch reads p_len: the lists carry the lengths they need
-    for (int c = threadIdx.x; c < C1; c += NT) a.p_len[(size_t)h * C1 + c] = a.plen_new[(size_t)h * C1 + c];
-  const int nf = a.fold && a.S_sum ? a.fold_n[h] : 0;
-  const size_t blk = (size_t)a.B * a.d;
-  for (int f = threadIdx.x; f < nf; f += NT) {
-    const int src = a.fold_src[(size_t)h * ncand_max + f];
-    flen_s[f] = a.fold_len[(size_t)h * ncand_max + f];
-    fptr_s[0][f] = src < C ? a.Kp + ((size_t)h * C1 + src) * blk : a.Kl + ((size_t)h * a.n_loc_cap + (src - C)) * blk;
-    fptr_s[1][f] = src < C ? a.Vp + ((size_t)h * C1 + src) * blk : a.Vl + ((size_t)h * a.n_loc_cap + (src - C)) * blk;
-  }
-  if (threadIdx.x < 64) {                  // wave 0 compacts the slots that are refilled (usually few or none)
-    int n = 0;
-    for (int c0 = 0; c0 < C; c0 += 64) {
-      const int c = c0 + (int)threadIdx.x;
-      const int ps = c < C ? a.promo_slot[(size_t)h * C + c] : -1;
-      const uint64_t m = __ballot(ps >= 0);
-      if (ps >= 0) {
-        const int pos = n + lanes_below(m);
-        promo_dst[pos] = c;
-        promo_src[pos] = ps;
-      }
-      n += __popcll(m);
-    }
-    if (threadIdx.x == 0) n_promo_s = n;
-  }
-  __syncthreads();
-  const int n_promo = n_promo_s;
-  const int tpr = a.d / 4;                                     // threads per row: 4 dimensions each
-  const int rows_per_wg = NT / tpr;
-  const int row = bx * rows_per_wg + threadIdx.x / tpr;         // over [2][B]
-  const int xc = (threadIdx.x % tpr) * 4;
-  if (row >= 2 * a.B) return;
-  const int kv = row / a.B, t = row % a.B;
-  bf16_t* P = kv ? a.Vp : a.Kp;
-  const bf16_t* L = kv ? a.Vl : a.Kl;
-  const size_t rowoff = (size_t)t * a.d + xc;
-  const bf16_t* Lh = L + (size_t)h * a.n_loc_cap * blk + rowoff;
-  // promoted rows are independent of the fold: the first few are fetched before it starts
-  uint2 pv[kPromoBatch];
-#pragma unroll
-  for (int u = 0; u < kPromoBatch; ++u)
-    pv[u] = u < n_promo ? *reinterpret_cast<const uint2*>(Lh + (size_t)promo_src[u] * blk) : make_uint2(0u, 0u);
-  if (nf > 0) {
-    float* ssum = a.S_sum + ((size_t)h * 2 + kv) * blk + rowoff;
-    float4 acc = *reinterpret_cast<float4*>(ssum);
-    const int cnt = a.S_cnt[(size_t)h * a.B + t];     // already the new count (retain_kernel)
-    // rows are loaded kFoldBatch at a time (row t exists in every block, valid or not) and added in
-    // candidate order, the add predicated on t < len
-    for (int f0 = 0; f0 < nf; f0 += kFoldBatch) {
-      uint2 v[kFoldBatch];
-#pragma unroll
-      for (int u = 0; u < kFoldBatch; ++u)
-        v[u] = *reinterpret_cast<const uint2*>(fptr_s[kv][min(f0 + u, nf - 1)] + rowoff);
-#pragma unroll
-      for (int u = 0; u < kFoldBatch; ++u) {
-        if (f0 + u < nf && t < flen_s[f0 + u]) {
-          acc.x = acc.x + bf_lo(v[u].x);
-          acc.y = acc.y + bf_hi(v[u].x);
-          acc.z = acc.z + bf_lo(v[u].y);
-          acc.w = acc.w + bf_hi(v[u].y);
-        }
-      }
-    }
-    *reinterpret_cast<float4*>(ssum) = acc;
-    if (cnt > 0) {
-      const float fc = (float)cnt;
-      uint2 w;
-      w.x = f2bf_rne(acc.x / fc) | (f2bf_rne(acc.y / fc) << 16);
-      w.y = f2bf_rne(acc.z / fc) | (f2bf_rne(acc.w / fc) << 16);
-      *reinterpret_cast<uint2*>(P + ((size_t)h * C1 + C) * blk + rowoff) = w;
-    }
-  }
-  // promoted rows: stores after the fold's loads (a refilled slot was read above by this thread)
-#pragma unroll
-  for (int u = 0; u < kPromoBatch; ++u)
-    if (u < n_promo) *reinterpret_cast<uint2*>(P + ((size_t)h * C1 + promo_dst[u]) * blk + rowoff) = pv[u];
-  for (int u0 = kPromoBatch; u0 < n_promo; u0 += kPromoBatch) {     // more than a few: the rest, batch by batch
-#pragma unroll
-    for (int u = 0; u < kPromoBatch; ++u)
-      pv[u] = u0 + u < n_promo ? *reinterpret_cast<const uint2*>(Lh + (size_t)promo_src[u0 + u] * blk) : make_uint2(0u, 0u);
-#pragma unroll
-    for (int u = 0; u < kPromoBatch; ++u)
-      if (u0 + u < n_promo) *reinterpret_cast<uint2*>(P + ((size_t)h * C1 + promo_dst[u0 + u]) * blk + rowoff) = pv[u];
-  }
-}
-
 // The bf16 view of a summary given by its running sums and counts (slot C of every head): row t of K and of V is
 // S_sum[t] / S_cnt[t], divided in fp32 and rounded to nearest even, where S_cnt[t] > 0; other rows stay as they are;
 // the slot's length is the number of such rows.  One thread per 4 dimensions of a row, as in the fold.
@@ -886,6 +952,36 @@ static FoldArgs fold_args(const pbsa_params& p, bf16_t* Kp, bf16_t* Vp, int32_t*
                   ws.fold_src, ws.fold_len, ws.promo_slot, ws.plen_new, p_len};
 }
 
+static SelectArgs select_args(const pbsa_params& p, const bf16_t* Q, const int32_t* l_map, float* Kc_l, float* Qc, int32_t* sel,
+                              float* Zl) {
+  return SelectArgs{p.H, p.nqb, p.n_loc, p.n_loc_cap, p.k, p.causal, p.scale, Kc_l, Qc, l_map, sel, Zl,
+                    Q, p.B, p.Nq, p.q_stride_h, p.q_stride_t, nullptr, nullptr, 0};
+}
+
+// Whether the selection pools the stale key blocks itself, and not a launch before it.  Every workgroup of a head then reads
+// them all, beside its own four query blocks: at most 12, and no more than 256 KiB together, which a compute unit takes 2 us
+// for (two launches -> one, us, heads x blocks: 4 x 4 of 64 x 64 7.8 -> 5.2, 16 x 12 of 64 x 64 8.2 -> 6.1, 16 x 8 of 128 x 64
+// 10.0 -> 8.4, 16 x 4 of 128 x 128 9.8 -> 9.0; beyond: 16 x 8 of 128 x 128 10.3 -> 11.2).
+static bool select_is_small(const pbsa_params& p, const float* Zl) {
+  const int n_stale = p.n_loc - p.pool_from;
+  return (p.k > 0 || Zl) && n_stale > 0 && n_stale <= kOwnKeys && p.nqb <= kOwnKeys && p.n_loc <= 128 &&
+         (4 + n_stale) * p.B * p.d * 2 <= 256 * 1024;
+}
+
+template <int D>
+static hipError_t launch_select_small(const pbsa_params& p, SelectArgs a, const bf16_t* Kl, const int32_t* l_len, const FoldArgs* fa,
+                                      hipStream_t stream) {
+  a.Kl = Kl;
+  a.l_len = l_len;
+  a.pool_from = p.pool_from;
+  constexpr size_t lds = SelectGeo<D, 2>::LDS;
+  const hipError_t e = allow_lds(select_small_kernel<D>, lds);
+  if (e != hipSuccess) return e;
+  const int n_fold_x = fa ? (2 * fa->B + 512 / (D / 4) - 1) / (512 / (D / 4)) : 0;
+  hipLaunchKernelGGL(select_small_kernel<D>, dim3(n_fold_x + (a.nqb + 3) / 4, a.H), dim3(512), lds, stream, a, fa ? *fa : FoldArgs{}, n_fold_x);
+  return hipGetLastError();
+}
+
 static hipError_t launch_select_logits(const pbsa_params& p, const bf16_t* Q, const int32_t* l_map, float* Kc_l, float* Qc,
                                        int32_t* sel, float* Zl, hipStream_t stream);
 
@@ -893,6 +989,10 @@ hipError_t launch_select(const pbsa_params& p, const bf16_t* Q, const bf16_t* Kl
                          const int32_t* l_map, float* Kc_l, float* Qc, int32_t* sel, float* Zl, bool pooled,
                          hipStream_t stream) {
   if (pooled) return launch_select_logits(p, nullptr, l_map, Kc_l, Qc, sel, Zl, stream);
+  if (select_is_small(p, Zl)) {
+    const SelectArgs a = select_args(p, Q, l_map, Kc_l, Qc, sel, Zl);
+    return p.d == 128 ? launch_select_small<128>(p, a, Kl, l_len, nullptr, stream) : launch_select_small<64>(p, a, Kl, l_len, nullptr, stream);
+  }
   const bool in_select = select_pools_queries(p, Zl);
   const PoolArgs pa = select_pool_args(p, Q, Kl, l_len, l_map, Kc_l, Qc, !in_select);
   if (pa.n_jobs > 0) {
@@ -912,6 +1012,10 @@ hipError_t launch_select_apply(const pbsa_params& p, const bf16_t* Q, const bf16
                                const int32_t* S_cnt, const bf16_t* Vl, const UpdateWs& ws, hipStream_t stream) {
   const PoolArgs pa = select_pool_args(p, Q, Kl, l_len, l_map, Kc_l, Qc, true);
   const FoldArgs fa = fold_args(pu, Kp, Vp, p_len, S_sum, S_cnt, Kl, Vl, ws);
+  if (select_is_small(p, Zl)) {
+    const SelectArgs a = select_args(p, Q, l_map, Kc_l, Qc, sel, Zl);
+    return p.d == 128 ? launch_select_small<128>(p, a, Kl, l_len, &fa, stream) : launch_select_small<64>(p, a, Kl, l_len, &fa, stream);
+  }
   // the fold / promote workgroups ride in the pooling launch, whose workgroups have the same size and no LDS (in the logits
   // launch, whose workgroups take 36 to 145 KiB each, they would wait for places: 33.0 us for the call against 30.1, measured
   // when those took 80)
@@ -929,8 +1033,7 @@ static hipError_t launch_select_logits(const pbsa_params& p, const bf16_t* Q, co
                                        int32_t* sel, float* Zl, hipStream_t stream) {
   if (p.k == 0 && !Zl) return hipSuccess;
 
-  SelectArgs a{p.H, p.nqb, p.n_loc, p.n_loc_cap, p.k, p.causal, p.scale, Kc_l, Qc, l_map, sel, Zl,
-               Q, p.B, p.Nq, p.q_stride_h, p.q_stride_t};
+  const SelectArgs a = select_args(p, Q, l_map, Kc_l, Qc, sel, Zl);
   const int nm = (p.n_loc + 63) / 64;
   if (p.d == 128) {
     if (nm <= 2) return launch_select_t<128, 2>(a, stream);
