@@ -44,11 +44,8 @@ attention_team_kernel(AttnArgs a, PlanArgs<PLAN> pl) {
     if ((int)blockIdx.x < n_plan) {
       const int hp = (int)blockIdx.x;
       if (hp >= a.H) return;
-      static_assert(plan_dev::score_head_lds_bytes<D, NT>(PBSA_MAX_N_LOC_AUX) <= (int)sizeof(L.ring), "scoring scratch must fit");
-      static_assert(sizeof(plan_dev::RetainLds) <= sizeof(L.ring), "retention scratch must fit");
-      plan_dev::score_head_body<D, NT>(pl.sa, hp, L.ring);
-      __syncthreads();                     // the head's rows are written, and the scoring scratch is dead
-      plan_dev::retain_body<NT>(pl.ra, hp, *reinterpret_cast<plan_dev::RetainLds*>(L.ring));
+      static_assert(plan_dev::score_lds_min<D>() <= (int)sizeof(L.ring) && sizeof(plan_dev::RetainLds) <= sizeof(L.ring), "scratch must fit");
+      plan_dev::decide_body<D, NT>(pl.sa, pl.ra, hp, L.ring, sizeof(L.ring));
       return;
     }
   }

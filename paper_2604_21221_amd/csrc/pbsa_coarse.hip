@@ -28,12 +28,6 @@ constexpr int kXC = 32;   // pooled-key dimensions staged through LDS per step
 
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
-// f(0), f(1), .. with the number as a constant
-template <typename F, int... I>
-__device__ __forceinline__ void unroll(F f, std::integer_sequence<int, I...>) {
-  (f(std::integral_constant<int, I>{}), ...);
-}
-
 __device__ __forceinline__ float bf_lo(uint32_t u) { return __uint_as_float(u << 16); }
 __device__ __forceinline__ float bf_hi(uint32_t u) { return __uint_as_float(u & 0xFFFF0000u); }
 
@@ -277,14 +271,6 @@ __device__ __forceinline__ void dma16(const void* base, uint32_t voff, uint32_t 
                :
                : "s"(lds_off), "v"(voff), "s"(base)
                : "memory", "m0");
-}
-
-// v_mfma_f32_4x4x1_16b_f32: sixteen 4 x 4 products of one contraction index.  With A of block X broadcast to all blocks (cbsz
-// 4), lane L's element r of the result is fma(a of lane 4 X + r, b of lane L, c of element r), rounded once, denormals and
-// infinities included; a NaN in any of them is a NaN in the result.
-template <int X>
-__device__ __forceinline__ f32x4 fma_4_rows(float a, float b, f32x4 c) {
-  return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 4, X, 0);
 }
 
 constexpr int kOwnKeys = 12;      // the most key blocks that the selection pools itself
@@ -806,7 +792,8 @@ __global__ void __launch_bounds__(kThreads) score_rows_z_kernel(ScoreArgs a) {
 // ------------------------------------------------------------------------------------------------
 __global__ void __launch_bounds__(kThreads) retain_kernel(RetainArgs a) {
   __shared__ RetainLds L;
-  retain_body<kThreads>(a, blockIdx.x, L);
+  const int h = blockIdx.x;
+  retain_body<kThreads>(a, h, retain_prefetch<kThreads>(a, h), a.A + (size_t)h * a.nU_max * a.nqb_pad, false, L);
 }
 
 // The bf16 view of a summary given by its running sums and counts (slot C of every head): row t of K and of V is

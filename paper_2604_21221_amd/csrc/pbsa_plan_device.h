@@ -7,6 +7,9 @@
 // file that includes this one is compiled with correctly rounded fp32 division.
 #pragma once
 
+#include <type_traits>
+#include <utility>
+
 #include "pbsa_internal.h"
 
 namespace pbsa {
@@ -74,6 +77,30 @@ __device__ __forceinline__ int nth_set_bit(uint64_t mask, int n) {
   return __ffsll((unsigned long long)mask) - 1;
 }
 
+// What retain_body needs of a head's metadata, in registers: asked for before anything else, so that it arrives while the
+// scores are computed.
+template <int NT>
+struct RetainPre {
+  static constexpr int EV = (PBSA_MAX_N_LOC_AUX + NT - 1) / NT;
+  int e_len[EV], e_map[EV], slot_len, cnt;
+  long long e_id[EV];
+};
+template <int NT>
+__device__ __forceinline__ RetainPre<NT> retain_prefetch(const RetainArgs& a, const int h) {
+  static_assert(NT >= 128 && NT > PBSA_MAX_C, "one thread per position of a block, and per slot");
+  RetainPre<NT> pre;
+  pre.slot_len = (int)threadIdx.x <= a.C ? a.p_len[(size_t)h * (a.C + 1) + threadIdx.x] : 0;
+#pragma unroll
+  for (int u = 0; u < RetainPre<NT>::EV; ++u) {
+    const int e = threadIdx.x + u * NT;
+    pre.e_len[u] = e < a.n_evict ? a.l_len[e] : 0;
+    pre.e_map[u] = e < a.n_evict ? a.l_map[e] : 0;
+    pre.e_id[u] = e < a.n_evict ? a.l_id[e] : 0;
+  }
+  pre.cnt = a.fold && (int)threadIdx.x < a.B ? a.S_cnt[(size_t)h * a.B + threadIdx.x] : 0;
+  return pre;
+}
+
 // LDS of retain_body
 struct RetainLds {
   alignas(16) float cs[kMaxCand + 4];   // candidate scores
@@ -91,9 +118,10 @@ struct RetainLds {
   int nf_s, npos_s;
 };
 
-// Retention (Eq. 8-9) of head h by one workgroup of NT threads (a multiple of 64, at least 128).
+// Retention (Eq. 8-9) of head h by one workgroup of NT threads (a multiple of 64, at least 128).  A: the head's matrix, columns
+// nqb_pad floats apart, in global memory or (in_lds) in LDS outside L.
 template <int NT>
-__device__ inline void retain_body(const RetainArgs& a, const int h, RetainLds& L) {
+__device__ inline void retain_body(const RetainArgs& a, const int h, const RetainPre<NT>& pre, const float* A, const bool in_lds, RetainLds& L) {
 #pragma clang fp contract(off)
   auto& cs = L.cs;
   auto& s = L.s;
@@ -111,16 +139,17 @@ __device__ inline void retain_body(const RetainArgs& a, const int h, RetainLds& 
   int& npos_s = L.npos_s;
   const int C = a.C, C1 = a.C + 1;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int32_t* plen = a.p_len + (size_t)h * C1;
-  for (int c = threadIdx.x; c < C1; c += NT) old_len[c] = plen[c];
-  for (int e = threadIdx.x; e < a.n_evict; e += NT) {
-    e_len[e] = max(0, min(a.l_len[e], a.B));
-    e_map[e] = min(max(a.l_map[e], 0), a.n_loc_cap - 1);
-    e_id[e] = a.l_id[e];
+  if ((int)threadIdx.x < C1) old_len[threadIdx.x] = pre.slot_len;
+#pragma unroll
+  for (int u = 0; u < RetainPre<NT>::EV; ++u) {
+    const int e = threadIdx.x + u * NT;
+    if (e < a.n_evict) {
+      e_len[e] = max(0, min(pre.e_len[u], a.B));
+      e_map[e] = min(max(pre.e_map[u], 0), a.n_loc_cap - 1);
+      e_id[e] = pre.e_id[u];
+    }
   }
-  // the summary's counts are needed at the very end: ask for them now, not after everything else
-  static_assert(NT >= 128, "one thread per position of a block");
-  const int cnt_mine = a.fold && threadIdx.x < a.B ? a.S_cnt[(size_t)h * a.B + threadIdx.x] : 0;
+  const int cnt_mine = pre.cnt;            // the summary's count of position threadIdx.x, needed at the very end
   if (threadIdx.x == 0) npos_s = 0;
   __syncthreads();
   // occupied slots: U position of slot c = number of occupied slots below it (C <= 64: one ballot)
@@ -136,18 +165,25 @@ __device__ inline void retain_body(const RetainArgs& a, const int h, RetainLds& 
     // where column j of U sits: the coarse matrix is in U order (occupied slots, then local blocks); the mass
     // matrix has a row for every slot, the summary included
     const int at = !a.fine ? j : j < nP ? nth_set_bit(occ_mask, j) : C + 1 + (j - nP);
-    const float4* col = reinterpret_cast<const float4*>(a.A + ((size_t)h * a.nU_max + at) * a.nqb_pad);
-    for (int i0 = 0; i0 < a.nqb; i0 += 64) {
-      float4 v[16];
+    const float4* col = reinterpret_cast<const float4*>(A + (size_t)at * a.nqb_pad);
+    auto add4 = [&](const float4& v, int i) {
+      acc = acc + v.x;
+      if (i + 1 < a.nqb) acc = acc + v.y;
+      if (i + 2 < a.nqb) acc = acc + v.z;
+      if (i + 3 < a.nqb) acc = acc + v.w;
+    };
+    if (in_lds) {
+#pragma unroll 1
+      for (int i = 0; i < a.nqb; i += 4) add4(col[i / 4], i);
+    } else {                               // 64 rows in flight together
+#pragma unroll 1
+      for (int i0 = 0; i0 < a.nqb; i0 += 64) {
+        float4 v[16];
 #pragma unroll
-      for (int u = 0; u < 16; ++u) v[u] = i0 + 4 * u < a.nqb ? col[i0 / 4 + u] : make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int u = 0; u < 16; ++u) v[u] = i0 + 4 * u < a.nqb ? col[i0 / 4 + u] : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const int i = i0 + 4 * u;
-        if (i + 0 < a.nqb) acc = acc + v[u].x;
-        if (i + 1 < a.nqb) acc = acc + v[u].y;
-        if (i + 2 < a.nqb) acc = acc + v[u].z;
-        if (i + 3 < a.nqb) acc = acc + v[u].w;
+        for (int u = 0; u < 16; ++u)
+          if (i0 + 4 * u < a.nqb) add4(v[u], i0 + 4 * u);
       }
     }
     s[j] = acc / (float)(a.fine ? a.Nq : a.nqb);
@@ -185,7 +221,7 @@ __device__ inline void retain_body(const RetainArgs& a, const int h, RetainLds& 
       const float mine = cs[x];
       int rank = 0;
       const int q_end = min(n4, (part + 1) * per);
-#pragma unroll 4
+#pragma unroll 1
       for (int q = part * per; q < q_end; ++q) {
         const float4 v = c4[q];
         const int y = 4 * q;
@@ -281,111 +317,184 @@ __device__ inline void retain_body(const RetainArgs& a, const int h, RetainLds& 
   }
 }
 
-// Rows of the block-level softmax (Eq. 7) of a whole head by one workgroup of NT threads, given the scaled local
-// logits Zl the selection call left: the same operations in the same order as score_rows_z_kernel (pooled keys of
-// the occupied slots staged once; per row the chain of each persistent column, the row maximum, the exponentials,
-// their sum in column order, the quotients stored column-major), with each wave working on R rows at a time: lane c
-// runs the chains of persistent column c for the R rows, lane r adds up row r.  No workgroup barrier in the row
-// loop: a wave reads only what it wrote itself.  lds: score_head_lds_bytes<D, NT>(n_loc) bytes.
-template <int D>
-constexpr int score_head_rows() { return D >= 128 ? 4 : 2; }
-template <int D, int NT>
-constexpr int score_head_lds_bytes(int n_loc) {
-  return 4 * (64 * (D + 4) + (NT / 64) * score_head_rows<D>() * (D + 64 + 64 * ((n_loc + 63) / 64)));
+// v_mfma_f32_4x4x1_16b_f32: sixteen 4 x 4 products of one contraction index.  With A of block X broadcast to all blocks (cbsz
+// 4), lane L's element r of the result is fma(a of lane 4 X + r, b of lane L, c of element r), rounded once, denormals and
+// infinities included; a NaN in any of them is a NaN in the result.
+typedef __attribute__((ext_vector_type(4))) float vec4;
+template <int X>
+__device__ __forceinline__ vec4 fma_4_rows(float a, float b, vec4 c) {
+  return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 4, X, 0);
+}
+template <typename F, int... I>
+__device__ __forceinline__ void unroll(F f, std::integer_sequence<int, I...>) {     // f(0), f(1), .. with the number as a constant
+  (f(std::integral_constant<int, I>{}), ...);
 }
 
+// The largest of the wave's numbers (a NaN counts as none).
+__device__ __forceinline__ float wave_max(float x) {
+#define PBSA_MAX_DPP(CTRL, ROWS)                                                                                        \
+  x = fmaxf(x, __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(x), __float_as_int(x), CTRL, ROWS, 0xF, false)));
+  PBSA_MAX_DPP(0x111, 0xF)                 // the lane 1, 2, 4, 8 places down in the row of 16
+  PBSA_MAX_DPP(0x112, 0xF)
+  PBSA_MAX_DPP(0x114, 0xF)
+  PBSA_MAX_DPP(0x118, 0xF)
+  PBSA_MAX_DPP(0x142, 0xA)                 // the last lane of the row before
+  PBSA_MAX_DPP(0x143, 0xC)                 // lane 31
+#undef PBSA_MAX_DPP
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
+}
+
+// One wave-wide global -> LDS load of 4 or 16 bytes per lane: LDS bytes [lds_off, lds_off + 64 * that) receive the lanes' bytes,
+// fetched from base + voff, side by side.  Completion is tracked by the issuing wave's vmcnt.
+__device__ __forceinline__ void stage4(const void* base, uint32_t voff, uint32_t lds_off) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" : : "s"(lds_off), "v"(voff), "s"(base) : "memory", "m0");
+}
+__device__ __forceinline__ void stage16(const void* base, uint32_t voff, uint32_t lds_off) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_off), "v"(voff), "s"(base) : "memory", "m0");
+}
+
+// Rows of the block-level softmax (Eq. 7) of a whole head by one workgroup of NT threads, given the scaled local
+// logits Zl the selection call left: the same operations in the same order as score_rows_kernel (per row the chain of each
+// persistent column, the row maximum, the exponentials, their sum in column order, the quotients stored column-major into
+// A, nqb_pad floats a column).  Pooled keys, queries and logits reach LDS by direct loads that are all in flight together, as
+// many rows at a time as fit; then each wave works on four rows at a time: lane c runs the chains of slot c as rows of one
+// matrix instruction per dimension (slots' keys lie there as the selection's do), and adds up row c of the wave's rows.
+// Bound by latency, and much of that is fetching instructions that run once: everything is in loops that are not unrolled.
+// Both halves of the decisions, workgroups of 256 threads, by time stamps: 9.4 -> 7.8 us at 2 heads x 4 blocks of 64, longer than
+// the attention beside them before and as long now; with rows and columns unrolled and more asked for at once 11.6.  A
+// chained step of 15 x 1386 x 64 whose 128 threads decided for 22 blocks, 46.3 -> 34.8.
+// lds: at least score_lds_min<D>() bytes.
+template <int D>
+struct ScoreGeo {
+  static constexpr int KEYS = 64 * D * 4;                                       // bytes of the slots' pooled keys
+  static constexpr int row_floats(int n_loc) { return 64 * ((n_loc + 63) / 64) + 65; }   // logits, then the slots', an odd pitch
+};
+template <int D>
+constexpr int score_lds_min() { return ScoreGeo<D>::KEYS + 4 * (D + ScoreGeo<D>::row_floats(PBSA_MAX_N_LOC_AUX)) * 4 + 1024; }
+
 template <int D, int NT>
-__device__ inline void score_head_body(const ScoreArgs& a, const int h, unsigned char* lds) {
+__device__ inline void score_head_body(const ScoreArgs& a, const int h, unsigned char* lds, const int lds_bytes, float* A) {
 #pragma clang fp contract(off)
-  constexpr int R = score_head_rows<D>(), NW = NT / 64, KP = D + 4, D4 = D / 4;
-  constexpr int NML_MAX = (PBSA_MAX_N_LOC_AUX + 63) / 64;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int nml = (a.n_loc + 63) / 64, EP = 64 + 64 * nml;
-  float* kct = reinterpret_cast<float*>(lds);            // [64][KP]
-  float* q_w = kct + 64 * KP + wave * R * D;             // [NW][R][D]
-  float* er_w = kct + 64 * KP + NW * R * D + wave * R * EP;   // [NW][R][EP]
-  const bool occ = lane < a.C && a.p_len[(size_t)h * (a.C + 1) + lane] > 0;
-  const uint64_t occ_mask = __ballot(occ);
-  const int nP = __popcll(occ_mask), nU = nP + a.n_loc;
-  for (int idx = threadIdx.x; idx < nP * D4; idx += NT) {
-    const int u = idx / D4, x4 = idx % D4;
-    const int slot = nth_set_bit(occ_mask, u);
-    *reinterpret_cast<float4*>(kct + u * KP + 4 * x4) =
-        reinterpret_cast<const float4*>(a.Kc_p + ((size_t)h * a.C + slot) * D)[x4];
+  constexpr int NW = NT / 64;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int nml = (a.n_loc + 63) / 64, EP = ScoreGeo<D>::row_floats(a.n_loc);
+  // rows at a time; the queries' last load may run up to 1 KiB over
+  const int cap = min((a.nqb + 3) & ~3, (lds_bytes - ScoreGeo<D>::KEYS - 1024) / ((D + EP) * 4) & ~3);
+  unsigned char* const qs_b = lds + ScoreGeo<D>::KEYS;
+  float* const qs = reinterpret_cast<float*>(qs_b);                             // [cap][D]
+  float* const er = qs + cap * D + 256;                                         // [cap][EP]
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds);
+  const uint32_t qs0 = lds0 + ScoreGeo<D>::KEYS, er0 = qs0 + cap * D * 4 + 1024;
+  const int slot_len = lane < a.C ? a.p_len[(size_t)h * (a.C + 1) + lane] : 0;
+  if (a.C > 0) {
+    // 1 KiB a load: eight slots' 32 dimensions 32 r .. (128 bytes a slot, 16-byte chunk c of slot j at c ^ ((j / 2) % 8))
+    const float* const kp = a.Kc_p + (size_t)h * a.C * D;
+#pragma unroll 1
+    for (int n = wave; n < 8 * (D / 32); n += NW) {
+      const int j = 8 * (n & 7) + (lane >> 3), chunk = (lane & 7) ^ ((j >> 1) & 7);
+      stage16(kp + 32 * (n >> 3), (uint32_t)(min(j, a.C - 1) * D * 4 + chunk * 16), lds0 + n * 1024);
+    }
   }
-  __syncthreads();
-  for (int i0 = R * wave; i0 < a.nqb; i0 += R * NW) {
-    for (int idx = lane; idx < R * D4; idx += 64) {
-      const int i = min(i0 + idx / D4, a.nqb - 1);
-      reinterpret_cast<float4*>(q_w)[idx] = reinterpret_cast<const float4*>(a.Qc + ((size_t)h * a.nqb + i) * D)[idx % D4];
+  uint64_t occ_mask = 0;
+  int nP = 0, at = 0;                                                           // occupied slots; this lane's place among them
+#pragma unroll 1
+  for (int r0 = 0; r0 < a.nqb; r0 += cap) {
+    const int rows = min(cap, a.nqb - r0);
+    if (r0 > 0) __syncthreads();                                                // the rows before are done with
+    const float* const q = a.Qc + ((size_t)h * a.nqb + r0) * D;
+#pragma unroll 1
+    for (int n = wave; n * 256 < rows * D; n += NW) stage16(q, (uint32_t)(min(n * 256 + lane * 4, rows * D - 4) * 4), qs0 + n * 1024);
+    const float* const z = a.Zl + ((size_t)h * a.nqb + r0) * a.n_loc;
+#pragma unroll 1
+    for (int r = wave; r < rows; r += NW)
+#pragma unroll 1
+      for (int m = 0; m < nml; ++m) stage4(z + (size_t)r * a.n_loc, (uint32_t)(min(64 * m + lane, a.n_loc - 1) * 4), er0 + (r * EP + 64 * m) * 4);
+    if (r0 == 0) {
+      occ_mask = __ballot(slot_len > 0);
+      nP = __popcll(occ_mask);
+      at = lanes_below(occ_mask);
     }
-    float zl[R][NML_MAX];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const float* zrow = a.Zl + ((size_t)h * a.nqb + min(i0 + r, a.nqb - 1)) * a.n_loc;
-#pragma unroll
-      for (int m = 0; m < NML_MAX; ++m) zl[r][m] = m < nml && lane + 64 * m < a.n_loc ? zrow[lane + 64 * m] : 0.0f;
-    }
-    __builtin_amdgcn_wave_barrier();
-    float accp[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) accp[r] = 0.0f;
-    if (lane < nP) {
-      const float4* k4p = reinterpret_cast<const float4*>(kct + lane * KP);
-      const float4* q4p = reinterpret_cast<const float4*>(q_w);
-#pragma unroll 4
-      for (int x4 = 0; x4 < D4; ++x4) {
-        const float4 k = k4p[x4];
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const float4 q = q4p[r * D4 + x4];
-          accp[r] = __builtin_fmaf(q.x, k.x, accp[r]);
-          accp[r] = __builtin_fmaf(q.y, k.y, accp[r]);
-          accp[r] = __builtin_fmaf(q.z, k.z, accp[r]);
-          accp[r] = __builtin_fmaf(q.w, k.w, accp[r]);
-        }
-      }
-    }
-    float ep[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const float zp = accp[r] * a.scale;
-      float mx = lane < nP ? zp : -INFINITY;
-#pragma unroll
-      for (int m = 0; m < NML_MAX; ++m)
-        if (m < nml && lane + 64 * m < a.n_loc) mx = fmaxf(mx, zl[r][m]);
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-      float* er = er_w + r * EP;
-      ep[r] = lane < nP ? pexp(zp - mx) : 0.0f;
-      if (lane < nP) er[lane] = ep[r];
-#pragma unroll
-      for (int m = 0; m < NML_MAX; ++m)
-        if (m < nml) {
-          zl[r][m] = lane + 64 * m < a.n_loc ? pexp(zl[r][m] - mx) : 0.0f;
-          if (lane + 64 * m < a.n_loc) er[nP + lane + 64 * m] = zl[r][m];
-        }
-    }
-    __builtin_amdgcn_wave_barrier();
+    const bool occ = slot_len > 0;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    const int sw = (lane >> 1) & 7;
     float s = 0.0f;
-    if (lane < R) {
-      const float* er = er_w + lane * EP;
-#pragma unroll 16
-      for (int j = 0; j < nU; ++j) s = s + er[j];
-    }
+#pragma unroll 1
+    for (int g = wave; 4 * g < rows; g += NW) {
+      vec4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 1
+      for (int m = 0; m < D / 16; ++m) {
+        const float qv = qs[(4 * g + (lane & 3)) * D + 16 * m + (lane >> 2)];
+        const unsigned char* kb = lds + (m >> 1) * 8192 + lane * 128;
+        float4 k[4];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const float sr = __shfl(s, r, 64);
-      if (i0 + r < a.nqb) {
-        float* acol = a.A + (size_t)h * a.nU_max * a.nqb_pad + i0 + r;
-        if (lane < nP) acol[(size_t)lane * a.nqb_pad] = ep[r] / sr;
+        for (int c = 0; c < 4; ++c) k[c] = *reinterpret_cast<const float4*>(kb + (((4 * (m & 1) + c) ^ sw) << 4));
+        unroll([&](auto C) {
+          constexpr int c = decltype(C)::value;
+          acc = fma_4_rows<4 * c + 0>(qv, k[c].x, acc);
+          acc = fma_4_rows<4 * c + 1>(qv, k[c].y, acc);
+          acc = fma_4_rows<4 * c + 2>(qv, k[c].z, acc);
+          acc = fma_4_rows<4 * c + 3>(qv, k[c].w, acc);
+        }, std::make_integer_sequence<int, 4>{});
+      }
+      float* const e4 = er + 4 * g * EP;
 #pragma unroll
-        for (int m = 0; m < NML_MAX; ++m)
-          if (m < nml && lane + 64 * m < a.n_evict) acol[(size_t)(nP + lane + 64 * m) * a.nqb_pad] = zl[r][m] / sr;
+      for (int r = 0; r < 4; ++r) e4[r * EP + 64 * nml + lane] = acc[r] * a.scale;
+#pragma unroll 1
+      for (int r = 0; r < 4; ++r) {
+        float* const row = e4 + r * EP;
+        const float zp = row[64 * nml + lane];
+        float mx = occ ? zp : -INFINITY;
+#pragma unroll 1
+        for (int j = lane; j < a.n_loc; j += 64) mx = fmaxf(mx, row[j]);
+        mx = wave_max(mx);
+        if (occ) row[64 * nml + at] = pexp(zp - mx);
+#pragma unroll 1
+        for (int j = lane; j < a.n_loc; j += 64) row[j] = pexp(row[j] - mx);
       }
     }
-    __builtin_amdgcn_wave_barrier();
+    // the sums: lane l adds up row l % 4 of the wave's group l / 4 (rows beyond the last have a place in LDS as well)
+    {
+      const int r = 4 * (wave + NW * (lane >> 2)) + (lane & 3);
+      if (r < rows) {
+        const float* const row = er + r * EP;
+#pragma unroll 8
+        for (int j = 0; j < nP; ++j) s = s + row[64 * nml + j];
+#pragma unroll 8
+        for (int j = 0; j < a.n_loc; ++j) s = s + row[j];
+      }
+    }
+    // the quotients of four rows side by side (padding rows as well, which nobody reads)
+    auto sum_of = [&](int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(s), l)); };
+#pragma unroll 1
+    for (int g = wave, l = 0; 4 * g < rows; g += NW, l += 4) {
+      const float* const e4 = er + 4 * g * EP;
+#pragma unroll 1
+      for (int u = lane; u < nP + a.n_evict; u += 64) {
+        const float* const e = e4 + (u < nP ? 64 * nml + u : u - nP);
+        float4 v;
+        v.x = e[0] / sum_of(l);
+        v.y = e[EP] / sum_of(l + 1);
+        v.z = e[2 * EP] / sum_of(l + 2);
+        v.w = e[3 * EP] / sum_of(l + 3);
+        *reinterpret_cast<float4*>(A + (size_t)u * a.nqb_pad + r0 + 4 * g) = v;
+      }
+    }
   }
+}
+
+// Both for head h, in the lds_bytes at lds.  The matrix between them stays in LDS where it leaves the scores room, and goes
+// through the workspace where not.
+template <int D, int NT>
+__device__ __forceinline__ void decide_body(const ScoreArgs& sa, const RetainArgs& ra, const int h, unsigned char* lds, const int lds_bytes) {
+  const RetainPre<NT> pre = retain_prefetch<NT>(ra, h);
+  constexpr int kKeep = score_lds_min<D>() > (int)sizeof(RetainLds) ? score_lds_min<D>() : (int)sizeof(RetainLds);
+  const int a_bytes = (sa.C + sa.n_evict) * sa.nqb_pad * 4, used = (lds_bytes - a_bytes) & ~15;
+  const bool fits = used >= kKeep;
+  float* const A = fits ? reinterpret_cast<float*>(lds + used) : sa.A + (size_t)h * sa.nU_max * sa.nqb_pad;
+  score_head_body<D, NT>(sa, h, lds, fits ? used : lds_bytes, A);
+  __syncthreads();                         // the head's rows are written, and the scoring scratch is dead
+  retain_body<NT>(ra, h, pre, A, fits, *reinterpret_cast<RetainLds*>(lds));
 }
 
 // The two argument blocks of the update's decisions, from the caller's pointers and the workspace
