@@ -70,7 +70,8 @@ attention_kernel(AttnArgs a, PlanArgs<PLAN> pl) {
   constexpr int SUB1 = Geo<D>::SUB_BYTES;
   constexpr int CH = D / 8, RPI = 64 / CH;          // 16-byte chunks per row, rows per wave instruction
   constexpr int NIW = (kTile / RPI) / 2;            // global_load_lds instructions per wave per tile
-  constexpr int SMEM = 4 * TILE;                    // K ring (2 tiles), V ring (2 tiles)
+  // K ring (2 tiles), V ring (2 tiles); the decisions' workgroups have use for more than d = 64 needs
+  constexpr int SMEM = PLAN ? 64 * 1024 : 4 * TILE;
   static_assert(PBSA_MAX_N_LOC * 8 + (PBSA_MAX_C_ATTEND + 1 + 8) * 4 <= SMEM, "setup scratch must fit");
   // the plain call takes the larger limits and keeps the list within two workgroups' share of a CU's LDS by
   // storing 16-bit descriptors (the mass variant's carry the key block as well)
@@ -98,7 +99,7 @@ attention_kernel(AttnArgs a, PlanArgs<PLAN> pl) {
     if ((int)blockIdx.x < n_plan) {
       const int hp = (int)blockIdx.x;
       if (hp >= a.H) return;
-      static_assert(plan_dev::score_lds_min<D>() <= SMEM && sizeof(plan_dev::RetainLds) <= SMEM, "scratch must fit");
+      static_assert(plan_dev::score_fits<D>(SMEM) && sizeof(plan_dev::RetainLds) <= SMEM, "scratch must fit");
       plan_dev::decide_body<D, kThreads>(pl.sa, pl.ra, hp, smem, SMEM);
       return;
     }

@@ -44,7 +44,7 @@ attention_team_kernel(AttnArgs a, PlanArgs<PLAN> pl) {
     if ((int)blockIdx.x < n_plan) {
       const int hp = (int)blockIdx.x;
       if (hp >= a.H) return;
-      static_assert(plan_dev::score_lds_min<D>() <= (int)sizeof(L.ring) && sizeof(plan_dev::RetainLds) <= sizeof(L.ring), "scratch must fit");
+      static_assert(plan_dev::score_fits<D>(sizeof(L.ring)) && sizeof(plan_dev::RetainLds) <= sizeof(L.ring), "scratch must fit");
       plan_dev::decide_body<D, NT>(pl.sa, pl.ra, hp, L.ring, sizeof(L.ring));
       return;
     }

@@ -19,9 +19,10 @@ __device__ __forceinline__ int lanes_below(uint64_t mask) {   // set bits of `ma
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-// exp(x) for x <= 0 from fp32 mul / fma / rint only (steps fixed in pbsa.h).
-__device__ __forceinline__ float pexp(float x) {
-  if (x < -64.0f) return 0.0f;
+// exp(x) for x <= 0 from fp32 mul / fma / rint only (steps fixed in pbsa.h).  Without a branch: several run side by side.
+__device__ __forceinline__ float pexp(float x0) {
+  const bool none = x0 < -64.0f;
+  const float x = none ? -64.0f : x0;
   float n = __builtin_rintf(x * 0x1.715476p+0f);
   float r = __builtin_fmaf(n, -0x1.630000p-1f, x);
   r = __builtin_fmaf(n, 0x1.bd0106p-13f, r);
@@ -32,7 +33,8 @@ __device__ __forceinline__ float pexp(float x) {
   p = __builtin_fmaf(p, r, 0.5f);
   p = __builtin_fmaf(p, r, 1.0f);
   p = __builtin_fmaf(p, r, 1.0f);
-  return p * __uint_as_float((uint32_t)((int)n + 127) << 23);
+  const float e = p * __uint_as_float((uint32_t)((int)n + 127) << 23);
+  return none ? 0.0f : e;
 }
 
 struct ScoreArgs {
@@ -330,18 +332,24 @@ __device__ __forceinline__ void unroll(F f, std::integer_sequence<int, I...>) { 
   (f(std::integral_constant<int, I>{}), ...);
 }
 
-// The largest of the wave's numbers (a NaN counts as none).
-__device__ __forceinline__ float wave_max(float x) {
-#define PBSA_MAX_DPP(CTRL, ROWS)                                                                                        \
-  x = fmaxf(x, __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(x), __float_as_int(x), CTRL, ROWS, 0xF, false)));
-  PBSA_MAX_DPP(0x111, 0xF)                 // the lane 1, 2, 4, 8 places down in the row of 16
-  PBSA_MAX_DPP(0x112, 0xF)
-  PBSA_MAX_DPP(0x114, 0xF)
-  PBSA_MAX_DPP(0x118, 0xF)
-  PBSA_MAX_DPP(0x142, 0xA)                 // the last lane of the row before
-  PBSA_MAX_DPP(0x143, 0xC)                 // lane 31
-#undef PBSA_MAX_DPP
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
+// The largest of the wave's numbers (a NaN counts as none), of four such at a time: the steps of one are as far apart as a
+// number must be from the data-parallel step that reads it.
+__device__ __forceinline__ void wave_max4(float (&x)[4]) {
+#define PBSA_STEP(HOW)                                                                                                  \
+  "v_max_f32_dpp %0, %0, %0 " HOW "\n\tv_max_f32_dpp %1, %1, %1 " HOW "\n\tv_max_f32_dpp %2, %2, %2 " HOW                \
+  "\n\tv_max_f32_dpp %3, %3, %3 " HOW "\n\t"
+  asm volatile("s_nop 1\n\t"
+               PBSA_STEP("row_shr:1 row_mask:0xf bank_mask:0xf")    // the lane 1, 2, 4, 8 places down in the row of 16
+               PBSA_STEP("row_shr:2 row_mask:0xf bank_mask:0xf")
+               PBSA_STEP("row_shr:4 row_mask:0xf bank_mask:0xf")
+               PBSA_STEP("row_shr:8 row_mask:0xf bank_mask:0xf")
+               PBSA_STEP("row_bcast:15 row_mask:0xa bank_mask:0xf") // the last lane of the row before
+               PBSA_STEP("row_bcast:31 row_mask:0xc bank_mask:0xf") // lane 31
+               "s_nop 1"
+               : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]));
+#undef PBSA_STEP
+#pragma unroll
+  for (int r = 0; r < 4; ++r) x[r] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x[r]), 63));
 }
 
 // One wave-wide global -> LDS load of 4 or 16 bytes per lane: LDS bytes [lds_off, lds_off + 64 * that) receive the lanes' bytes,
@@ -359,18 +367,21 @@ __device__ __forceinline__ void stage16(const void* base, uint32_t voff, uint32_
 // A, nqb_pad floats a column).  Pooled keys, queries and logits reach LDS by direct loads that are all in flight together, as
 // many rows at a time as fit; then each wave works on four rows at a time: lane c runs the chains of slot c as rows of one
 // matrix instruction per dimension (slots' keys lie there as the selection's do), and adds up row c of the wave's rows.
-// Bound by latency, and much of that is fetching instructions that run once: everything is in loops that are not unrolled.
-// Both halves of the decisions, workgroups of 256 threads, by time stamps: 9.4 -> 7.8 us at 2 heads x 4 blocks of 64, longer than
-// the attention beside them before and as long now; with rows and columns unrolled and more asked for at once 11.6.  A
-// chained step of 15 x 1386 x 64 whose 128 threads decided for 22 blocks, 46.3 -> 34.8.
-// lds: at least score_lds_min<D>() bytes.
+// Bound by latency, and much of that is fetching instructions that run once: nothing is unrolled but the four rows that a wave
+// works on side by side.  Both halves of the decisions, workgroups of 256 threads, by time stamps: 9.4 -> 7.4 us at 2 heads x 4
+// blocks of 64, longer than the attention beside them before; with rows and columns unrolled and more asked for at
+// once 11.6.  A chained step of 15 x 1386 x 64 whose 128 threads decide for 22 blocks, 46.3 -> 34.8; a step of 9 x 4458 x 128 with
+// 70 blocks and 280 columns and a short attention 134 -> 93.
 template <int D>
 struct ScoreGeo {
-  static constexpr int KEYS = 64 * D * 4;                                       // bytes of the slots' pooled keys
+  static constexpr int key_round(int C) { return ((C + 7) & ~7) * 128; }        // bytes of 32 dimensions of the slots' pooled keys
+  static constexpr int keys(int C) { return D / 32 * key_round(C); }
   static constexpr int row_floats(int n_loc) { return 64 * ((n_loc + 63) / 64) + 65; }   // logits, then the slots', an odd pitch
+  // rows at a time in so many bytes; the queries' last load may run up to 1 KiB over
+  static constexpr int rows(int bytes, int C, int n_loc) { return (bytes - keys(C) - 1024) / ((D + row_floats(n_loc)) * 4) & ~3; }
 };
 template <int D>
-constexpr int score_lds_min() { return ScoreGeo<D>::KEYS + 4 * (D + ScoreGeo<D>::row_floats(PBSA_MAX_N_LOC_AUX)) * 4 + 1024; }
+constexpr bool score_fits(int bytes) { return ScoreGeo<D>::rows(bytes, PBSA_MAX_C, PBSA_MAX_N_LOC_AUX) >= 4; }
 
 template <int D, int NT>
 __device__ inline void score_head_body(const ScoreArgs& a, const int h, unsigned char* lds, const int lds_bytes, float* A) {
@@ -378,21 +389,22 @@ __device__ inline void score_head_body(const ScoreArgs& a, const int h, unsigned
   constexpr int NW = NT / 64;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int nml = (a.n_loc + 63) / 64, EP = ScoreGeo<D>::row_floats(a.n_loc);
-  // rows at a time; the queries' last load may run up to 1 KiB over
-  const int cap = min((a.nqb + 3) & ~3, (lds_bytes - ScoreGeo<D>::KEYS - 1024) / ((D + EP) * 4) & ~3);
-  unsigned char* const qs_b = lds + ScoreGeo<D>::KEYS;
-  float* const qs = reinterpret_cast<float*>(qs_b);                             // [cap][D]
+  const int cap = min((a.nqb + 3) & ~3, ScoreGeo<D>::rows(lds_bytes, a.C, a.n_loc)), key_round = ScoreGeo<D>::key_round(a.C);
+  float* const qs = reinterpret_cast<float*>(lds + ScoreGeo<D>::keys(a.C));     // [cap][D]
   float* const er = qs + cap * D + 256;                                         // [cap][EP]
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds);
-  const uint32_t qs0 = lds0 + ScoreGeo<D>::KEYS, er0 = qs0 + cap * D * 4 + 1024;
+  const uint32_t qs0 = lds0 + ScoreGeo<D>::keys(a.C), er0 = qs0 + cap * D * 4 + 1024;
   const int slot_len = lane < a.C ? a.p_len[(size_t)h * (a.C + 1) + lane] : 0;
-  if (a.C > 0) {
+  {
     // 1 KiB a load: eight slots' 32 dimensions 32 r .. (128 bytes a slot, 16-byte chunk c of slot j at c ^ ((j / 2) % 8))
     const float* const kp = a.Kc_p + (size_t)h * a.C * D;
+    const int n8 = (a.C + 7) / 8;
 #pragma unroll 1
-    for (int n = wave; n < 8 * (D / 32); n += NW) {
-      const int j = 8 * (n & 7) + (lane >> 3), chunk = (lane & 7) ^ ((j >> 1) & 7);
-      stage16(kp + 32 * (n >> 3), (uint32_t)(min(j, a.C - 1) * D * 4 + chunk * 16), lds0 + n * 1024);
+    for (int n = wave; n < n8; n += NW) {
+      const int j = 8 * n + (lane >> 3), chunk = (lane & 7) ^ ((j >> 1) & 7);
+#pragma unroll 1
+      for (int r = 0; r < D / 32; ++r)
+        stage16(kp + 32 * r, (uint32_t)(min(j, a.C - 1) * D * 4 + chunk * 16), lds0 + r * key_round + n * 1024);
     }
   }
   uint64_t occ_mask = 0;
@@ -406,9 +418,13 @@ __device__ inline void score_head_body(const ScoreArgs& a, const int h, unsigned
     for (int n = wave; n * 256 < rows * D; n += NW) stage16(q, (uint32_t)(min(n * 256 + lane * 4, rows * D - 4) * 4), qs0 + n * 1024);
     const float* const z = a.Zl + ((size_t)h * a.nqb + r0) * a.n_loc;
 #pragma unroll 1
-    for (int r = wave; r < rows; r += NW)
+    for (int m = 0; m < nml; ++m) {
+      const uint32_t voff = (uint32_t)(min(64 * m + lane, a.n_loc - 1) * 4);
+      const float* zr = z + (size_t)wave * a.n_loc;
+      uint32_t to = er0 + (wave * EP + 64 * m) * 4;
 #pragma unroll 1
-      for (int m = 0; m < nml; ++m) stage4(z + (size_t)r * a.n_loc, (uint32_t)(min(64 * m + lane, a.n_loc - 1) * 4), er0 + (r * EP + 64 * m) * 4);
+      for (int r = wave; r < rows; r += NW, zr += (size_t)NW * a.n_loc, to += NW * EP * 4) stage4(zr, voff, to);
+    }
     if (r0 == 0) {
       occ_mask = __ballot(slot_len > 0);
       nP = __popcll(occ_mask);
@@ -425,10 +441,11 @@ __device__ inline void score_head_body(const ScoreArgs& a, const int h, unsigned
 #pragma unroll 1
       for (int m = 0; m < D / 16; ++m) {
         const float qv = qs[(4 * g + (lane & 3)) * D + 16 * m + (lane >> 2)];
-        const unsigned char* kb = lds + (m >> 1) * 8192 + lane * 128;
+        const unsigned char* kb = lds + (m >> 1) * key_round + min(lane, max((a.C + 7) & ~7, 8) - 1) * 128;
         float4 k[4];
 #pragma unroll
         for (int c = 0; c < 4; ++c) k[c] = *reinterpret_cast<const float4*>(kb + (((4 * (m & 1) + c) ^ sw) << 4));
+        asm volatile("" : "+v"(k[0].x), "+v"(k[1].x), "+v"(k[2].x), "+v"(k[3].x));     // all on their way before the first is used
         unroll([&](auto C) {
           constexpr int c = decltype(C)::value;
           acc = fma_4_rows<4 * c + 0>(qv, k[c].x, acc);
@@ -438,19 +455,38 @@ __device__ inline void score_head_body(const ScoreArgs& a, const int h, unsigned
         }, std::make_integer_sequence<int, 4>{});
       }
       float* const e4 = er + 4 * g * EP;
+      float zp[4], mx[4];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) e4[r * EP + 64 * nml + lane] = acc[r] * a.scale;
-#pragma unroll 1
       for (int r = 0; r < 4; ++r) {
-        float* const row = e4 + r * EP;
-        const float zp = row[64 * nml + lane];
-        float mx = occ ? zp : -INFINITY;
+        zp[r] = acc[r] * a.scale;
+        mx[r] = occ ? zp[r] : -INFINITY;
+      }
+      float x[4];
+      auto four = [&](int j) {             // of column j, on their way before the first is used
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x[r] = e4[r * EP + j];
+        asm volatile("" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]));
+      };
 #pragma unroll 1
-        for (int j = lane; j < a.n_loc; j += 64) mx = fmaxf(mx, row[j]);
-        mx = wave_max(mx);
-        if (occ) row[64 * nml + at] = pexp(zp - mx);
-#pragma unroll 1
-        for (int j = lane; j < a.n_loc; j += 64) row[j] = pexp(row[j] - mx);
+      for (int j = lane; j < a.n_loc; j += 64) {
+        four(j);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) mx[r] = fmaxf(mx[r], x[r]);
+      }
+      wave_max4(mx);
+      // the exponentials of a column's four rows, side by side; the slots' first
+#pragma unroll
+      for (int r = 0; r < 4; ++r) x[r] = zp[r];
+      for (int j = occ ? at + 64 * nml : -1, next = lane;; j = next, next += 64) {
+        if (j >= 0) {
+          if (j < 64 * nml) four(j);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) x[r] = pexp(x[r] - mx[r]);
+          asm volatile("" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]));
+#pragma unroll
+          for (int r = 0; r < 4; ++r) e4[r * EP + j] = x[r];
+        }
+        if (next >= a.n_loc) break;
       }
     }
     // the sums: lane l adds up row l % 4 of the wave's group l / 4 (rows beyond the last have a place in LDS as well)
@@ -460,7 +496,7 @@ __device__ inline void score_head_body(const ScoreArgs& a, const int h, unsigned
         const float* const row = er + r * EP;
 #pragma unroll 8
         for (int j = 0; j < nP; ++j) s = s + row[64 * nml + j];
-#pragma unroll 8
+#pragma unroll 16
         for (int j = 0; j < a.n_loc; ++j) s = s + row[j];
       }
     }
@@ -488,9 +524,8 @@ __device__ inline void score_head_body(const ScoreArgs& a, const int h, unsigned
 template <int D, int NT>
 __device__ __forceinline__ void decide_body(const ScoreArgs& sa, const RetainArgs& ra, const int h, unsigned char* lds, const int lds_bytes) {
   const RetainPre<NT> pre = retain_prefetch<NT>(ra, h);
-  constexpr int kKeep = score_lds_min<D>() > (int)sizeof(RetainLds) ? score_lds_min<D>() : (int)sizeof(RetainLds);
   const int a_bytes = (sa.C + sa.n_evict) * sa.nqb_pad * 4, used = (lds_bytes - a_bytes) & ~15;
-  const bool fits = used >= kKeep;
+  const bool fits = used >= (int)sizeof(RetainLds) && ScoreGeo<D>::rows(used, sa.C, sa.n_loc) >= min(sa.nqb_pad, 16);
   float* const A = fits ? reinterpret_cast<float*>(lds + used) : sa.A + (size_t)h * sa.nU_max * sa.nqb_pad;
   score_head_body<D, NT>(sa, h, lds, fits ? used : lds_bytes, A);
   __syncthreads();                         // the head's rows are written, and the scoring scratch is dead
