@@ -162,6 +162,13 @@ int pbsa_select_blocks(const pbsa_params* p, const void* Q, const void* Kl, cons
 int pbsa_select_pooled(const pbsa_params* p, const int32_t* l_map, const float* Kc_l, const float* Qc, int32_t* sel, float* Zl,
                        void* hip_stream);
 
+/* pbsa_append_chunk_pool of a chunk (K, V and Q given) and pbsa_select_pooled of the same chunk as one call, which is one
+ * launch where the chunk is small: the last nqb entries of l_map are slot0 .. slot0 + nqb - 1, the pooled keys of the other
+ * blocks are in Kc_l, Q has p's strides, and pool_from is not looked at.  The same block sets and logits, bit for bit. */
+int pbsa_append_select(const pbsa_params* p, const void* K, const void* V, int64_t k_stride_h, int64_t k_stride_t,
+                       int64_t v_stride_h, int64_t v_stride_t, int32_t slot0, int32_t zero_tail, const void* Q, void* Kl, void* Vl,
+                       const int32_t* l_map, float* Kc_l, float* Qc, int32_t* sel, float* Zl, void* hip_stream);
+
 /* PBSA fine stage (Eq. 3-5): for each query token one softmax, scaled by p->scale, over every
  * valid token of every non-empty persistent slot 0..C (summary included) and every valid token of
  * the local blocks listed in its query block's row of `sel`; O = P V.  bf16 MFMA with fp32

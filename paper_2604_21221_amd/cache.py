@@ -18,6 +18,10 @@ from . import pbsa
 _KEYS, _KEYS_AND_QUERIES = 1, 2              # what an append pooled
 
 
+class _Carried(tuple):
+    """Of an append that the selection is to take along, pooling keys and queries: what pbsa_append_chunk gave for that."""
+
+
 class PbsaCache:
     def __init__(self, H, d, B, Nq, window_chunks, C, k, scale, n_sink=0, causal=1, fold=True, device="cuda:0",
                  pass_logits=True, ring_chunks=None):
@@ -180,7 +184,7 @@ class PbsaCache:
         """append_chunk; pool: the pooled keys are taken as the rows pass, for a selection that follows at once (whoever
         appends by themselves may still change the rows in the ring, and the selection pools what it finds there), and with
         Q, where that is of use, the queries are pooled along.
-        Returns whether they were: nothing, _KEYS, or _KEYS_AND_QUERIES."""
+        Returns whether they were: nothing, _KEYS, _KEYS_AND_QUERIES, or (_Carried) an append that _select() is to complete."""
         if K is None or V is None:
             raise TypeError("append_chunk takes K and V (adopt_chunk declares a chunk that is in the ring already)")
         assert len(self.chunk_pos) <= self.w, "update() slides the window before the next append"
@@ -227,10 +231,17 @@ class PbsaCache:
             # as long as they take the selection (187.3 -> 187.5 at 12 x 37 x 128 | d = 128, 181.6 -> 181.3 at 16 x 42).
             if (pool and Q is not None and self._pending is None and self.H * self.nqb <= 400
                     and pbsa.plain_rows(self.Kl, self.Vl, self.H, self.Nq, self.d, torch.is_grad_enabled(), Q)):
+                if V is not None and self.stale_from >= self.n_loc:      # (nothing older is stale) the selection can take all of it
+                    carried = pbsa.pbsa_append_chunk(*args, None, Q, self.Qc, carried=True)
+                    return _Carried(carried) if carried is not None else _KEYS_AND_QUERIES
                 pbsa.pbsa_append_chunk(*args, None, Q, self.Qc)
                 return _KEYS_AND_QUERIES
             pbsa.pbsa_append_chunk(*args)
             return _KEYS if pool else 0
+        self._copy_chunk(pos, K, V, zero_tail)
+        return 0
+
+    def _copy_chunk(self, pos, K, V, zero_tail):
         for dst, src in ((self.Kl, K), (self.Vl, V)):
             if src is None:
                 continue
@@ -238,7 +249,6 @@ class PbsaCache:
             view[:, :self.Nq] = src
             if zero_tail and self.nqb * self.B > self.Nq:
                 view[:, self.Nq:] = 0
-        return 0
 
     def rewrite_chunk(self, K=None, V=None):
         """Between the denoising passes of one chunk (Sec. 3.1: each chunk is denoised in T passes over the
@@ -264,6 +274,16 @@ class PbsaCache:
 
     def _select(self, Q, pooled):
         """select; pooled: what of the newest chunk has just been pooled (_append); anything older that is stale has not."""
+        if isinstance(pooled, _Carried):
+            try:
+                l_map, l_len, _ = self._device_maps()
+                pbsa.pbsa_select_blocks(self.params(pool_from=self.n_loc, Q=Q), Q, self.Kl, l_len, l_map, self.Kc_l, self.Qc, self.sel,
+                                        self.Zl, pooled=True, append=pooled)
+            except BaseException:            # the chunk has been declared: its rows go to the ring all the same
+                self._copy_chunk(self.chunk_pos[-1], pooled[0], pooled[1], True)
+                raise
+            self.stale_from = self.n_loc
+            return self.sel
         l_map, l_len, _ = self._device_maps()
         fresh = pooled and self.stale_from == self.n_loc - self.nqb
         p = self.params(pool_from=self.n_loc if fresh else self.stale_from, Q=Q)

@@ -181,6 +181,26 @@ int pbsa_select_pooled(const pbsa_params* p, const int32_t* l_map, const float* 
   return e == hipSuccess ? PBSA_OK : hip_fail(e);
 }
 
+int pbsa_append_select(const pbsa_params* p, const void* K, const void* V, int64_t k_stride_h, int64_t k_stride_t,
+                       int64_t v_stride_h, int64_t v_stride_t, int32_t slot0, int32_t zero_tail, const void* Q, void* Kl, void* Vl,
+                       const int32_t* l_map, float* Kc_l, float* Qc, int32_t* sel, float* Zl, void* hip_stream) {
+  int rc = check_common(p, PBSA_MAX_C_ATTEND, PBSA_MAX_N_LOC, PBSA_MAX_K);
+  if (rc) return rc;
+  if (!K || !V || !Q || !Kl || !Vl || !l_map || !Kc_l || !Qc) return PBSA_EINVAL;
+  if (p->k > 0 && !sel) return PBSA_EINVAL;
+  if (slot0 < 0 || slot0 > p->n_loc_cap - p->nqb) return PBSA_EINVAL;
+  if ((rc = check_strides(k_stride_h, k_stride_t, p))) return rc;
+  if ((rc = check_strides(v_stride_h, v_stride_t, p))) return rc;
+  if ((rc = check_strides(p->q_stride_h, p->q_stride_t, p))) return rc;
+  if (!aligned16(K) || !aligned16(V) || !aligned16(Q) || !aligned16(Kl) || !aligned16(Vl) || !aligned16(Kc_l) || !aligned16(Qc))
+    return PBSA_EALIGN;
+  hipError_t e = pbsa::launch_append_select(*p, static_cast<const pbsa::bf16_t*>(K), static_cast<const pbsa::bf16_t*>(V), k_stride_h,
+                                            k_stride_t, v_stride_h, v_stride_t, slot0, zero_tail, static_cast<const pbsa::bf16_t*>(Q),
+                                            static_cast<pbsa::bf16_t*>(Kl), static_cast<pbsa::bf16_t*>(Vl), l_map, Kc_l, Qc, sel, Zl,
+                                            static_cast<hipStream_t>(hip_stream));
+  return e == hipSuccess ? PBSA_OK : hip_fail(e);
+}
+
 int pbsa_select_blocks(const pbsa_params* p, const void* Q, const void* Kl, const int32_t* l_len,
                        const int32_t* l_map, float* Kc_l, float* Qc, int32_t* sel, float* Zl, void* ws,
                        size_t ws_bytes, void* hip_stream) {

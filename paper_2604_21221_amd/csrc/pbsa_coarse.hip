@@ -261,6 +261,8 @@ struct SelectArgs {
   const bf16_t* Kl;         // KEYS: blocks from pool_from on are pooled from here
   const int32_t* l_len;
   int pool_from;
+  int chunk_slot;           // KEYS: -1, or they are those of a chunk that the same launch appends from this slot on, and Kl its
+  long k_stride_h, k_stride_t;   // token-major rows
 };
 
 // One wave-wide global -> LDS load of 16 bytes per lane: LDS bytes [lds_off, lds_off + 1024) receive
@@ -365,12 +367,20 @@ __device__ __forceinline__ void select_body(const SelectArgs& a, const int bx, c
           p = a.Q + (size_t)h * a.q_stride_h + (size_t)i * a.B * pitch + 2 * c;
         }
       } else if (job < 4 + n_stale) {
-        slot[w] = a.l_map[l];
-        if (slot[w] >= 0 && slot[w] < a.n_loc_cap) {
-          len = max(0, min(a.l_len[l], a.B));
-          pitch = D;
-          p = a.Kl + ((size_t)h * a.n_loc_cap + slot[w]) * a.B * D + 2 * c;
+        if (a.chunk_slot >= 0) {
+          slot[w] = a.chunk_slot + job - 4;
+          len = min(a.B, a.Nq - (job - 4) * a.B);
+          pitch = a.k_stride_t;
+          p = a.Kl + (size_t)h * a.k_stride_h + (size_t)(job - 4) * a.B * pitch + 2 * c;
           col[w] = l;
+        } else {
+          slot[w] = a.l_map[l];
+          if (slot[w] >= 0 && slot[w] < a.n_loc_cap) {
+            len = max(0, min(a.l_len[l], a.B));
+            pitch = D;
+            p = a.Kl + ((size_t)h * a.n_loc_cap + slot[w]) * a.B * D + 2 * c;
+            col[w] = l;
+          }
         }
       }
       float acc0 = 0.0f, acc1 = 0.0f;
@@ -631,13 +641,35 @@ __device__ __forceinline__ void fold_promote_body(const FoldArgs& a, const int b
   }
 }
 
-// The selection of a small chunk with everything that would be a pooling launch before it, and the fold / promote of the
-// update before it in workgroups of their own (n_fold_x of them per head, or none).
+// The selection of a small chunk with everything that would be a launch before it: the pooling; the fold / promote of the
+// update before it, in n_fold_x workgroups per head of their own; the copy of the chunk into the ring, one workgroup per
+// block of K and of V.
 template <int D>
-__global__ void __launch_bounds__(512) select_small_kernel(SelectArgs a, FoldArgs fa, int n_fold_x) {
+__global__ void __launch_bounds__(512) select_small_kernel(SelectArgs a, FoldArgs fa, int n_fold_x, AppendArgs ap) {
   extern __shared__ __align__(1024) unsigned char smem[];
-  if ((int)blockIdx.x < n_fold_x) fold_promote_body<512>(fa, blockIdx.x, blockIdx.y);
-  else select_body<D, 2, true>(a, blockIdx.x - n_fold_x, blockIdx.y, smem);
+  const int h = blockIdx.y, n_sel_x = (a.nqb + 3) / 4;
+  int bx = (int)blockIdx.x;
+  if (bx < n_fold_x) {
+    fold_promote_body<512>(fa, bx, h);
+    return;
+  }
+  bx -= n_fold_x;
+  if (bx < n_sel_x) {
+    select_body<D, 2, true>(a, bx, h, smem);
+    return;
+  }
+  bx -= n_sel_x;
+  constexpr int CPR = D / 8, RPS = 512 / CPR;              // 16-byte chunks per row, rows at a time
+  const int kv = bx & 1, i = bx >> 1, c = threadIdx.x % CPR;
+  const int len = min(ap.B, ap.Nq - i * ap.B), rows = ap.zero_tail ? ap.B : len;
+  const bf16_t* const src = ap.src[kv] + (size_t)h * ap.sh[kv] + (size_t)i * ap.B * ap.st[kv] + 8 * c;
+  bf16_t* const dst = ap.dst[kv] + ((size_t)h * ap.n_loc_cap + ap.slot0 + i) * ap.B * D + 8 * c;
+#pragma unroll 4
+  for (int r = threadIdx.x / CPR; r < rows; r += RPS) {
+    uint4 v = *reinterpret_cast<const uint4*>(src + (size_t)min(r, len - 1) * ap.st[kv]);
+    if (r >= len) v = make_uint4(0u, 0u, 0u, 0u);
+    *reinterpret_cast<uint4*>(dst + (size_t)r * D) = v;
+  }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -942,31 +974,34 @@ static FoldArgs fold_args(const pbsa_params& p, bf16_t* Kp, bf16_t* Vp, int32_t*
 static SelectArgs select_args(const pbsa_params& p, const bf16_t* Q, const int32_t* l_map, float* Kc_l, float* Qc, int32_t* sel,
                               float* Zl) {
   return SelectArgs{p.H, p.nqb, p.n_loc, p.n_loc_cap, p.k, p.causal, p.scale, Kc_l, Qc, l_map, sel, Zl,
-                    Q, p.B, p.Nq, p.q_stride_h, p.q_stride_t, nullptr, nullptr, 0};
+                    Q, p.B, p.Nq, p.q_stride_h, p.q_stride_t, nullptr, nullptr, 0, -1, 0, 0};
 }
 
 // Whether the selection pools the stale key blocks itself, and not a launch before it.  Every workgroup of a head then reads
 // them all, beside its own four query blocks: at most 12, and no more than 256 KiB together, which a compute unit takes 2 us
 // for (two launches -> one, us, heads x blocks: 4 x 4 of 64 x 64 7.8 -> 5.2, 16 x 12 of 64 x 64 8.2 -> 6.1, 16 x 8 of 128 x 64
 // 10.0 -> 8.4, 16 x 4 of 128 x 128 9.8 -> 9.0; beyond: 16 x 8 of 128 x 128 10.3 -> 11.2).
-static bool select_is_small(const pbsa_params& p, const float* Zl) {
-  const int n_stale = p.n_loc - p.pool_from;
+static bool select_is_small(const pbsa_params& p, int n_stale, const float* Zl) {
   return (p.k > 0 || Zl) && n_stale > 0 && n_stale <= kOwnKeys && p.nqb <= kOwnKeys && p.n_loc <= 128 &&
          (4 + n_stale) * p.B * p.d * 2 <= 256 * 1024;
 }
 
 template <int D>
+static hipError_t launch_select_small(const SelectArgs& a, const FoldArgs* fa, const AppendArgs* ap, hipStream_t stream) {
+  constexpr size_t lds = SelectGeo<D, 2>::LDS;
+  const hipError_t e = allow_lds(select_small_kernel<D>, lds);
+  if (e != hipSuccess) return e;
+  const int n_fold_x = fa ? (2 * fa->B + 512 / (D / 4) - 1) / (512 / (D / 4)) : 0;
+  hipLaunchKernelGGL(select_small_kernel<D>, dim3(n_fold_x + (a.nqb + 3) / 4 + (ap ? 2 * a.nqb : 0), a.H), dim3(512), lds, stream, a,
+                     fa ? *fa : FoldArgs{}, n_fold_x, ap ? *ap : AppendArgs{});
+  return hipGetLastError();
+}
 static hipError_t launch_select_small(const pbsa_params& p, SelectArgs a, const bf16_t* Kl, const int32_t* l_len, const FoldArgs* fa,
                                       hipStream_t stream) {
   a.Kl = Kl;
   a.l_len = l_len;
   a.pool_from = p.pool_from;
-  constexpr size_t lds = SelectGeo<D, 2>::LDS;
-  const hipError_t e = allow_lds(select_small_kernel<D>, lds);
-  if (e != hipSuccess) return e;
-  const int n_fold_x = fa ? (2 * fa->B + 512 / (D / 4) - 1) / (512 / (D / 4)) : 0;
-  hipLaunchKernelGGL(select_small_kernel<D>, dim3(n_fold_x + (a.nqb + 3) / 4, a.H), dim3(512), lds, stream, a, fa ? *fa : FoldArgs{}, n_fold_x);
-  return hipGetLastError();
+  return p.d == 128 ? launch_select_small<128>(a, fa, nullptr, stream) : launch_select_small<64>(a, fa, nullptr, stream);
 }
 
 static hipError_t launch_select_logits(const pbsa_params& p, const bf16_t* Q, const int32_t* l_map, float* Kc_l, float* Qc,
@@ -976,10 +1011,8 @@ hipError_t launch_select(const pbsa_params& p, const bf16_t* Q, const bf16_t* Kl
                          const int32_t* l_map, float* Kc_l, float* Qc, int32_t* sel, float* Zl, bool pooled,
                          hipStream_t stream) {
   if (pooled) return launch_select_logits(p, nullptr, l_map, Kc_l, Qc, sel, Zl, stream);
-  if (select_is_small(p, Zl)) {
-    const SelectArgs a = select_args(p, Q, l_map, Kc_l, Qc, sel, Zl);
-    return p.d == 128 ? launch_select_small<128>(p, a, Kl, l_len, nullptr, stream) : launch_select_small<64>(p, a, Kl, l_len, nullptr, stream);
-  }
+  if (select_is_small(p, p.n_loc - p.pool_from, Zl))
+    return launch_select_small(p, select_args(p, Q, l_map, Kc_l, Qc, sel, Zl), Kl, l_len, nullptr, stream);
   const bool in_select = select_pools_queries(p, Zl);
   const PoolArgs pa = select_pool_args(p, Q, Kl, l_len, l_map, Kc_l, Qc, !in_select);
   if (pa.n_jobs > 0) {
@@ -993,16 +1026,33 @@ hipError_t launch_select(const pbsa_params& p, const bf16_t* Q, const bf16_t* Kl
   return launch_select_logits(p, in_select ? Q : nullptr, l_map, Kc_l, Qc, sel, Zl, stream);
 }
 
+hipError_t launch_append_select(const pbsa_params& p, const bf16_t* K, const bf16_t* V, int64_t k_stride_h, int64_t k_stride_t,
+                                int64_t v_stride_h, int64_t v_stride_t, int32_t slot0, int32_t zero_tail, const bf16_t* Q, bf16_t* Kl,
+                                bf16_t* Vl, const int32_t* l_map, float* Kc_l, float* Qc, int32_t* sel, float* Zl, hipStream_t stream) {
+  if (!select_is_small(p, p.nqb, Zl)) {
+    const hipError_t e = launch_append(p, K, V, k_stride_h, k_stride_t, v_stride_h, v_stride_t, slot0, zero_tail, Kl, Vl, Kc_l, Q,
+                                       p.q_stride_h, p.q_stride_t, Qc, stream);
+    return e != hipSuccess ? e : launch_select_logits(p, nullptr, l_map, Kc_l, Qc, sel, Zl, stream);
+  }
+  SelectArgs a = select_args(p, Q, l_map, Kc_l, Qc, sel, Zl);
+  a.Kl = K;
+  a.pool_from = p.n_loc - p.nqb;
+  a.chunk_slot = slot0;
+  a.k_stride_h = (long)k_stride_h;
+  a.k_stride_t = (long)k_stride_t;
+  const AppendArgs ap{p.B, p.Nq, p.nqb, p.n_loc_cap, slot0, zero_tail, {(long)k_stride_h, (long)v_stride_h, 0},
+                      {(long)k_stride_t, (long)v_stride_t, 0}, {K, V, nullptr}, {Kl, Vl}, nullptr, nullptr};
+  return p.d == 128 ? launch_select_small<128>(a, nullptr, &ap, stream) : launch_select_small<64>(a, nullptr, &ap, stream);
+}
+
 hipError_t launch_select_apply(const pbsa_params& p, const bf16_t* Q, const bf16_t* Kl, const int32_t* l_len,
                                const int32_t* l_map, float* Kc_l, float* Qc, int32_t* sel, float* Zl,
                                const pbsa_params& pu, bf16_t* Kp, bf16_t* Vp, int32_t* p_len, float* S_sum,
                                const int32_t* S_cnt, const bf16_t* Vl, const UpdateWs& ws, hipStream_t stream) {
   const PoolArgs pa = select_pool_args(p, Q, Kl, l_len, l_map, Kc_l, Qc, true);
   const FoldArgs fa = fold_args(pu, Kp, Vp, p_len, S_sum, S_cnt, Kl, Vl, ws);
-  if (select_is_small(p, Zl)) {
-    const SelectArgs a = select_args(p, Q, l_map, Kc_l, Qc, sel, Zl);
-    return p.d == 128 ? launch_select_small<128>(p, a, Kl, l_len, &fa, stream) : launch_select_small<64>(p, a, Kl, l_len, &fa, stream);
-  }
+  if (select_is_small(p, p.n_loc - p.pool_from, Zl))
+    return launch_select_small(p, select_args(p, Q, l_map, Kc_l, Qc, sel, Zl), Kl, l_len, &fa, stream);
   // the fold / promote workgroups ride in the pooling launch, whose workgroups have the same size and no LDS (in the logits
   // launch, whose workgroups take 36 to 145 KiB each, they would wait for places: 33.0 us for the call against 30.1, measured
   // when those took 80)

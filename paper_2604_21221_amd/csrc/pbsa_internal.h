@@ -34,6 +34,10 @@ hipError_t launch_summary_view(const pbsa_params& p, const float* S_sum, const i
 hipError_t launch_select(const pbsa_params& p, const bf16_t* Q, const bf16_t* Kl, const int32_t* l_len,
                          const int32_t* l_map, float* Kc_l, float* Qc, int32_t* sel, float* Zl, bool pooled,
                          hipStream_t stream);
+// launch_append and launch_select of the same chunk; one launch where it is small
+hipError_t launch_append_select(const pbsa_params& p, const bf16_t* K, const bf16_t* V, int64_t k_stride_h, int64_t k_stride_t,
+                                int64_t v_stride_h, int64_t v_stride_t, int32_t slot0, int32_t zero_tail, const bf16_t* Q, bf16_t* Kl,
+                                bf16_t* Vl, const int32_t* l_map, float* Kc_l, float* Qc, int32_t* sel, float* Zl, hipStream_t stream);
 // launch_select of a chunk with launch_update_apply of the update of the chunk before it (parameters pu, same Kl) riding
 // in its pooling launch.  The caller guarantees that the new chunk's ring position is not the one being folded.
 hipError_t launch_select_apply(const pbsa_params& p, const bf16_t* Q, const bf16_t* Kl, const int32_t* l_len,
