@@ -545,7 +545,7 @@ struct FoldArgs {
   int32_t* p_len;           // ... which this kernel commits
 };
 
-constexpr int kFoldBatch = 40;
+constexpr int kFoldBatch = 40, kFoldFew = 8;
 constexpr int kPromoBatch = 8;
 
 template <int NT>
@@ -603,13 +603,13 @@ __device__ __forceinline__ void fold_promote_body(const FoldArgs& a, const int b
     const int cnt = a.S_cnt[(size_t)h * a.B + t];     // already the new count (retain_kernel)
     // rows are loaded kFoldBatch at a time (row t exists in every block, valid or not) and added in
     // candidate order, the add predicated on t < len
-    for (int f0 = 0; f0 < nf; f0 += kFoldBatch) {
-      uint2 v[kFoldBatch];
+    auto batch = [&](auto N, int f0) {
+      uint2 v[decltype(N)::value];
 #pragma unroll
-      for (int u = 0; u < kFoldBatch; ++u)
+      for (int u = 0; u < decltype(N)::value; ++u)
         v[u] = *reinterpret_cast<const uint2*>(fptr_s[kv][min(f0 + u, nf - 1)] + rowoff);
 #pragma unroll
-      for (int u = 0; u < kFoldBatch; ++u) {
+      for (int u = 0; u < decltype(N)::value; ++u) {
         if (f0 + u < nf && t < flen_s[f0 + u]) {
           acc.x = acc.x + bf_lo(v[u].x);
           acc.y = acc.y + bf_hi(v[u].x);
@@ -617,6 +617,12 @@ __device__ __forceinline__ void fold_promote_body(const FoldArgs& a, const int b
           acc.w = acc.w + bf_hi(v[u].y);
         }
       }
+    };
+    // (the code of a large batch takes longer to fetch than the few blocks of a small chunk to add)
+    if (nf <= kFoldFew) {
+      batch(std::integral_constant<int, kFoldFew>{}, 0);
+    } else {
+      for (int f0 = 0; f0 < nf; f0 += kFoldBatch) batch(std::integral_constant<int, kFoldBatch>{}, f0);
     }
     *reinterpret_cast<float4*>(ssum) = acc;
     if (cnt > 0) {
