@@ -1115,6 +1115,18 @@ static BwdWorkspace bwd_workspace(const pbsa_params& p) {
 }
 size_t bwd_workspace_bytes(const pbsa_params& p) { return bwd_workspace(p).bytes; }
 
+// When a launch whose workgroups have `waves` waves ends, in turns of 64 x 64 (about 1.4 us at d = 128, 1.0 at 64): with its longest
+// walk, or when the places have taken all of them; a workgroup costs 6 us beside its turns.
+static float walks_cost(const pbsa_params& p, int waves) {
+  const int sub = p.B / kTile, rows = (p.Nq + kTile - 1) / kTile, k = std::min(p.k, p.n_loc), tiles = p.H * rows;
+  const bool shared = waves == 4 || tiles <= 256;            // dq: the waves of a workgroup share a walk
+  const float own = p.d == 128 ? 4.3f : 6.0f, pairs = 0.5f * (float)waves;
+  const float dq = (float)((p.C + 1 + k) * sub) / (shared ? (float)waves : 1.0f), slot = (float)rows / pairs;
+  const float block = (float)rows * (float)k / (float)p.n_loc / pairs;
+  const float all = (float)(shared ? tiles : (tiles + 1) / 2) * (own + dq) + (float)(p.H * sub) * ((float)(p.C + 1) * (own + slot) + (float)p.n_loc * (own + block));
+  return std::max(own + std::max(dq, slot), 1.1f * all * (float)waves / 1024.0f + 3.5f);
+}
+
 hipError_t launch_attention_bwd(const pbsa_params& p, const bf16_t* Q, const bf16_t* Kp, const bf16_t* Vp,
                                 const int32_t* p_len, const bf16_t* Kl, const bf16_t* Vl, const int32_t* l_len,
                                 const int32_t* l_map, const int32_t* sel, const bf16_t* O, const bf16_t* dO,
@@ -1151,15 +1163,17 @@ hipError_t launch_attention_bwd(const pbsa_params& p, const bf16_t* Q, const bf1
     if (e != hipSuccess) return e;
     return launch_walk<64, kDkv, 2>(a, 0, n_dkv, lds_dkv, stream);
   }
-  // Four waves share a walk where there are few walks: a workgroup of four has a compute unit to itself, and at up to 448
-  // workgroups the longest walks, which come first, end half as late (2 waves -> 4: 52 -> 45 us at 3 x 1500 x 64, 309
-  // workgroups; 99 -> 90 at 3 x 2000 x 128, 438; 140 -> 112 at 1 x 4680 x 128, 403; but 73 -> 74 at 6 x 1200 x 128, 510,
-  // 86 -> 92 at 4 x 3000 x 64, 836; the backward by itself 35.3 -> 33.7 at 5 x 1100 x 128, 395, and 34.9 -> 37.4 at
-  // 6 x 1100 x 128, 474).  Walks of fewer than eight row tiles are left to two waves for 12 x 300 x 128 (five row tiles), where
-  // four gained nothing (50.0 -> 50.4); with fewer heads they would (21 -> 19 at 8 x 300 x 128, 22 -> 17 at 4 x 300 x 64,
-  // 43 -> 31 at 2 x 384 x 128 with 17 + 16 blocks).
+  // Four waves share a walk where the longest walks set the launch's end, which come first and then end half as late: a
+  // workgroup of four has a compute unit to itself, so a launch that the places set takes as long or, with more workgroups
+  // than units, longer.  walks_cost says which it is.  The backward by itself, two waves -> four, us, where it says four:
+  // 2 x 3689 x 128 with 58 row tiles and few slots 76 -> 51, 6 x 1000 x 128 with 17 + 20 blocks of 128 85 -> 65, 2 x 4234 x 64
+  // with 26 + 112 of 128 185 -> 161, 9 x 305 x 64 27 -> 20, 2 x 384 x 128 40 -> 29, 1 x 1681 x 64 56 -> 36; where it says two: 13 x 569
+  // x 64 34 | 40, 16 x 300 x 128 31 | 36, 3 x 4180 x 128 with 27 + 10 of 128 110 | 124, 12 x 1863 x 128 65 | 88.  (36 drawn shapes: never
+  // the slower by more than 1 us but for 12 x 212 x 128, 25 | 29, and 4 x 3701 x 128, 262 | 266.)  Up to 448
+  // workgroups, from eight row tiles on, four as before there was a model (8 x 600 x 64: 22.4 -> 20.9, which it puts at 16.0 | 18.1).
   const size_t lds4 = 8 * tile + (size_t)4 * std::max(4 * n_cand, sub * p.nqb) + 16;
-  if (n_tiles + p.H * (p.C + 1 + p.n_loc) * sub <= 448 && n_row_tiles >= 8 && lds4 <= 156 * 1024) {
+  const bool four = (n_tiles + p.H * (p.C + 1 + p.n_loc) * sub <= 448 && n_row_tiles >= 8) || walks_cost(p, 4) < 0.95f * walks_cost(p, 2);
+  if (four && lds4 <= 156 * 1024) {
     const unsigned n_dq = head_items(n_row_tiles, p.H);
     return p.d == 128 ? launch_walk<128, kDq | kDkv, 4>(a, n_dq, n_dkv, lds4, stream)
                       : launch_walk<64, kDq | kDkv, 4>(a, n_dq, n_dkv, lds4, stream);
