@@ -726,7 +726,7 @@ static float walk_us(int d, int tiles, int waves) {
 // 19.4 -> 12.5; 14 x 245 x 128, 16 tiles 20.8 -> 13.3; 11 x 1336 x 64, 54 tiles 31.1 -> 22.1; 8 x 2000 x 128, 92 tiles
 // 58.1 -> 50.6; teams of two: 16 x 1100 x 64, 11 tiles 17.9 -> 12.2, 12 x 1800 x 128, 38 tiles 41.0 -> 35.9.  One tile
 // alone: 5.7 -> 6.2, and nothing at all 6.8 -> 7.3, which stay as they are.  A team's waves stage their tiles by themselves
-// and take 3 to 8 % longer for one, so long lists that the parts share out as well or better stay with them (6 x 4736 x 128, 202
+// and take 3 to 8 % longer for one (5 at d = 64), so long lists that the parts share out as well or better stay with them (6 x 4736 x 128, 202
 // tiles 172.0 | 179.6; 4 x 5000 x 128, 74 tiles in three parts 58.4 | 63.0).  Few units with long lists take several teams
 // each and the second launch: 1 x 1000 x 64, 82 tiles 21.0 -> 15.8 (one team 26.7); the parts of attn_split cost another
 // 3 us beside theirs, for lists and runs of their own (4 x 210 x 128, 21 tiles: 20.5 by parts of two tiles, 17 by one
@@ -741,10 +741,11 @@ AttnTeam attn_team(const pbsa_params& p, bool scratch) {
   team.units = (int)units;
   team.waves = units > 256 ? 2 : 4;
   if (sp.parts == 1) return team;
-  constexpr float kOwnTiles = 1.07f, kPartsUs = 3.0f;
+  constexpr float kPartsUs = 3.0f;
+  const float own_tiles = p.d == 128 ? 1.09f : 1.05f;
   auto team_us = [&](int parts) {
     const int n = team.waves * parts;
-    return kOwnTiles * walk_us(p.d, (tiles + n - 1) / n, (int)units * n) + (parts > 1 ? kCombineUs : 0.0f);
+    return own_tiles * walk_us(p.d, (tiles + n - 1) / n, (int)units * n) + (parts > 1 ? kCombineUs : 0.0f);
   };
   float best = team_us(1);
   for (int s = 2; s <= sp.parts && s * units <= 256; ++s) {          // (what s parts leave fits in the scratch for sp.parts)

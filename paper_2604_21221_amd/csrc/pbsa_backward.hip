@@ -26,6 +26,7 @@
 // fixed rows per wave, so every fragment read from LDS feeds two MFMAs; dkv cannot at d = 128 (two outputs: 256
 // accumulator registers for 64 keys) and holds 32 per wave: it reads one fragment per MFMA.
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 #include <utility>
 
@@ -1116,7 +1117,8 @@ static BwdWorkspace bwd_workspace(const pbsa_params& p) {
 size_t bwd_workspace_bytes(const pbsa_params& p) { return bwd_workspace(p).bytes; }
 
 // When a launch whose workgroups have `waves` waves ends, in turns of 64 x 64 (about 1.4 us at d = 128, 1.0 at 64): with its longest
-// walk, or when the places have taken all of them; a workgroup costs 6 us beside its turns.
+// walk or when the places have taken all of them, and where the two are close a little later; a workgroup costs 6 us beside
+// its turns.  The factors are those of a fit to 121 shapes.
 static float walks_cost(const pbsa_params& p, int waves) {
   const int sub = p.B / kTile, rows = (p.Nq + kTile - 1) / kTile, k = std::min(p.k, p.n_loc), tiles = p.H * rows;
   const bool shared = waves == 4 || tiles <= 256;            // dq: the waves of a workgroup share a walk
@@ -1124,7 +1126,9 @@ static float walks_cost(const pbsa_params& p, int waves) {
   const float dq = (float)((p.C + 1 + k) * sub) / (shared ? (float)waves : 1.0f), slot = (float)rows / pairs;
   const float block = (float)rows * (float)k / (float)p.n_loc / pairs;
   const float all = (float)(shared ? tiles : (tiles + 1) / 2) * (own + dq) + (float)(p.H * sub) * ((float)(p.C + 1) * (own + slot) + (float)p.n_loc * (own + block));
-  return std::max(own + std::max(dq, slot), 1.1f * all * (float)waves / 1024.0f + 3.5f);
+  const float walk = own + std::max(dq, slot), taken = (waves == 2 ? 1.1f : p.d == 128 ? 1.4f : 1.0f) * all * (float)waves / 1024.0f + 1.0f;
+  const float w2 = walk * walk, t2 = taken * taken;
+  return std::sqrt(std::sqrt(w2 * w2 + t2 * t2));
 }
 
 hipError_t launch_attention_bwd(const pbsa_params& p, const bf16_t* Q, const bf16_t* Kp, const bf16_t* Vp,
@@ -1168,11 +1172,12 @@ hipError_t launch_attention_bwd(const pbsa_params& p, const bf16_t* Q, const bf1
   // than units, longer.  walks_cost says which it is.  The backward by itself, two waves -> four, us, where it says four:
   // 2 x 3689 x 128 with 58 row tiles and few slots 76 -> 51, 6 x 1000 x 128 with 17 + 20 blocks of 128 85 -> 65, 2 x 4234 x 64
   // with 26 + 112 of 128 185 -> 161, 9 x 305 x 64 27 -> 20, 2 x 384 x 128 40 -> 29, 1 x 1681 x 64 56 -> 36; where it says two: 13 x 569
-  // x 64 34 | 40, 16 x 300 x 128 31 | 36, 3 x 4180 x 128 with 27 + 10 of 128 110 | 124, 12 x 1863 x 128 65 | 88.  (36 drawn shapes: never
-  // the slower by more than 1 us but for 12 x 212 x 128, 25 | 29, and 4 x 3701 x 128, 262 | 266.)  Up to 448
-  // workgroups, from eight row tiles on, four as before there was a model (8 x 600 x 64: 22.4 -> 20.9, which it puts at 16.0 | 18.1).
+  // x 64 34 | 40, 16 x 300 x 128 31 | 36, 3 x 4180 x 128 with 27 + 10 of 128 110 | 124, 12 x 1863 x 128 65 | 88.  6 x 4888
+  // x 128 119 | 143.  (Over 121 shapes, 85 of them drawn, no choice is slower than two waves by more than 1 %, and the choices
+  // are 0.5 % off the better ones on average.)  Up to 448 workgroups, from eight row tiles on, four as before there was a model (8 x 600
+  // x 64: 22.4 -> 20.9, which it does not see).
   const size_t lds4 = 8 * tile + (size_t)4 * std::max(4 * n_cand, sub * p.nqb) + 16;
-  const bool four = (n_tiles + p.H * (p.C + 1 + p.n_loc) * sub <= 448 && n_row_tiles >= 8) || walks_cost(p, 4) < 0.95f * walks_cost(p, 2);
+  const bool four = (n_tiles + p.H * (p.C + 1 + p.n_loc) * sub <= 448 && n_row_tiles >= 8) || walks_cost(p, 4) < 0.94f * walks_cost(p, 2);
   if (four && lds4 <= 156 * 1024) {
     const unsigned n_dq = head_items(n_row_tiles, p.H);
     return p.d == 128 ? launch_walk<128, kDq | kDkv, 4>(a, n_dq, n_dkv, lds4, stream)
