@@ -87,57 +87,127 @@ struct PoolArgs {
   float* Qc;
 };
 
-template <int D, int NT = kThreads>
+// A job: where its block is, the elements from token to token, how many tokens (0 .. B), and the place of the result.
+struct PoolJob {
+  const bf16_t* src;
+  long pitch;
+  int len;
+  float* dst;
+  bool query;               // else the tokens are D elements apart
+};
+// jobs [0, H*nk) of mode 1 pool local key blocks, the rest pool the chunk's query blocks; false: there is no such block
+template <int D>
+__device__ __forceinline__ bool pool_job(const PoolArgs& a, const int job, PoolJob& j) {
+  const int nk = a.n_kjobs_per_head;
+  j.query = a.mode == 1 && job >= a.H * nk;
+  if (j.query) {
+    const int jq = job - a.H * nk;
+    const int h = jq / a.nqb, i = jq % a.nqb;
+    j.len = min(a.B, a.Nq - i * a.B);
+    j.dst = a.Qc + ((size_t)h * a.nqb + i) * D;
+    j.src = a.Q + (size_t)h * a.q_stride_h + (size_t)i * a.B * a.q_stride_t;
+    j.pitch = a.q_stride_t;
+    return true;
+  }
+  if (a.mode == 0) {
+    j.src = a.X + (size_t)job * a.B * D;
+    j.len = a.len[job];
+    j.dst = a.out + (size_t)job * D;
+  } else {
+    const int h = job / nk, l = a.pool_from + job % nk;
+    const int slot = a.l_map[l];
+    if (slot < 0 || slot >= a.n_loc_cap) return false;
+    j.src = a.X + ((size_t)h * a.n_loc_cap + slot) * a.B * D;
+    j.len = a.len[l];
+    j.dst = a.out + ((size_t)h * a.n_loc_cap + slot) * D;
+  }
+  j.len = max(0, min(j.len, a.B));
+  j.pitch = D;
+  return true;
+}
+
+template <int D, int NT>
 __device__ __forceinline__ void pool_body(const PoolArgs& a, const int bx) {
   constexpr int TPJ = D / 2;
   const int job = bx * (NT / TPJ) + threadIdx.x / TPJ;
   const int c = threadIdx.x % TPJ;
   if (job >= a.n_jobs) return;
-  const bf16_t* src;
-  int len;
-  float* dst;
+  PoolJob j;
+  if (!pool_job<D>(a, job, j)) return;
   float acc0 = 0.0f, acc1 = 0.0f;
-  // jobs [0, H*nk) of mode 1 pool local key blocks, the rest pool the chunk's query blocks
-  const int nk = a.n_kjobs_per_head;
-  if (a.mode == 1 && job >= a.H * nk) {
-    const int jq = job - a.H * nk;
-    const int h = jq / a.nqb, i = jq % a.nqb;
-    len = min(a.B, a.Nq - i * a.B);
-    dst = a.Qc + ((size_t)h * a.nqb + i) * D;
-    pool_block(a.Q + (size_t)h * a.q_stride_h + (size_t)i * a.B * a.q_stride_t + 2 * c, a.q_stride_t, len, acc0, acc1);
-  } else {
-    if (a.mode == 0) {
-      src = a.X + (size_t)job * a.B * D;
-      len = a.len[job];
-      dst = a.out + (size_t)job * D;
-    } else {
-      const int h = job / nk, l = a.pool_from + job % nk;
-      const int slot = a.l_map[l];
-      if (slot < 0 || slot >= a.n_loc_cap) return;
-      src = a.X + ((size_t)h * a.n_loc_cap + slot) * a.B * D;
-      len = a.len[l];
-      dst = a.out + ((size_t)h * a.n_loc_cap + slot) * D;
-    }
-    len = max(0, min(len, a.B));
-    pool_block(src + 2 * c, std::integral_constant<long, D>{}, len, acc0, acc1);
+  if (j.query) pool_block(j.src + 2 * c, j.pitch, j.len, acc0, acc1);
+  else pool_block(j.src + 2 * c, std::integral_constant<long, D>{}, j.len, acc0, acc1);
+  const float fl = (float)j.len;
+  float2 o;
+  o.x = j.len > 0 ? acc0 / fl : 0.0f;
+  o.y = j.len > 0 ? acc1 / fl : 0.0f;
+  *reinterpret_cast<float2*>(j.dst + c * 2) = o;
+}
+
+// Adds the len rows of a block in LDS in ascending order, two dimensions per thread of the first D / 2: 64 consecutive words
+// per row, free of bank conflicts.
+template <int D>
+__device__ __forceinline__ void pool_tile(const uint4* tile, int len, float* out) {
+  const uint32_t* t32 = reinterpret_cast<const uint32_t*>(tile) + threadIdx.x;
+  float acc0 = 0.0f, acc1 = 0.0f;
+#pragma unroll 16
+  for (int r = 0; r < len; ++r) {
+    const uint32_t u = t32[r * (D / 2)];
+    acc0 = acc0 + bf_lo(u);
+    acc1 = acc1 + bf_hi(u);
   }
   const float fl = (float)len;
-  float2 o;
-  o.x = len > 0 ? acc0 / fl : 0.0f;
-  o.y = len > 0 ? acc1 / fl : 0.0f;
-  *reinterpret_cast<float2*>(dst + c * 2) = o;
+  *reinterpret_cast<float2*>(out + 2 * threadIdx.x) = len > 0 ? make_float2(acc0 / fl, acc1 / fl) : make_float2(0.0f, 0.0f);
 }
 
 template <int D>
 __global__ void __launch_bounds__(kThreads) pool_kernel(PoolArgs a) {
-  pool_body<D>(a, blockIdx.x);
+  pool_body<D, kThreads>(a, blockIdx.x);
+}
+
+// A pooling launch by itself of blocks that all find a place on the chip: one workgroup to a block, 16 bytes a thread and load,
+// all in flight, summed through LDS as the append does.  When: launch_pool.
+template <int D, int BT>
+__global__ void __launch_bounds__(kThreads) pool_tile_kernel(PoolArgs a) {
+  constexpr int CPR = D / 8, RPS = kThreads / CPR, NS = BT / RPS;     // chunks per row, rows per sweep, sweeps
+  __shared__ __align__(16) uint4 tile[BT * CPR];
+  PoolJob j;
+  if (!pool_job<D>(a, blockIdx.x, j)) return;                         // (all of the workgroup)
+  if (j.len > 0) {
+    const int r0 = threadIdx.x / CPR, c = threadIdx.x % CPR;
+    f32x4 v[NS];                                                      // (as uint4 they go through scratch memory)
+#pragma unroll
+    for (int s = 0; s < NS; ++s) v[s] = *reinterpret_cast<const f32x4*>(j.src + (size_t)min(r0 + s * RPS, j.len - 1) * j.pitch + 8 * c);
+#pragma unroll
+    for (int s = 0; s < NS; ++s) *reinterpret_cast<f32x4*>(&tile[(r0 + s * RPS) * CPR + c]) = v[s];
+  }
+  __syncthreads();
+  if (threadIdx.x < D / 2) pool_tile<D>(tile, j.len, j.dst);
+}
+
+// Up to four blocks to a compute unit by tiles: pooling and selection of a chunk, us, by threads -> by tiles, 12 heads x 37 blocks of
+// 128 x 128 12.3 -> 11.2, 8 x 20 10.0 -> 8.7, 2 x 16 9.7 -> 8.4, 6 x 40 of 128 x 64 11.5 -> 10.1, 3 x 24 of 64 x 64 7.65 -> 7.4.  Beyond,
+// the workgroups, of four waves and up to 32 KiB of LDS, come in rounds: 12 x 74 of 64 x 128 14.5 -> 15.0, 12 x 74 of 64 x 64
+// 10.3 -> 10.4, 16 x 42 of 128 x 128 13.5 -> 15.6.
+template <int D>
+static hipError_t launch_pool(const PoolArgs& a, hipStream_t stream) {
+  const dim3 block(kThreads);
+  if (a.n_jobs > 1024) {
+    constexpr int jpw = kThreads / (D / 2);
+    hipLaunchKernelGGL(pool_kernel<D>, dim3((a.n_jobs + jpw - 1) / jpw), block, 0, stream, a);
+  } else if (a.B == 128) {
+    hipLaunchKernelGGL((pool_tile_kernel<D, 128>), dim3(a.n_jobs), block, 0, stream, a);
+  } else {
+    hipLaunchKernelGGL((pool_tile_kernel<D, 64>), dim3(a.n_jobs), block, 0, stream, a);
+  }
+  return hipGetLastError();
 }
 
 // ------------------------------------------------------------------------------------------------
 // Cache append: a chunk's K and V (token-major per head) into nqb consecutive ring slots, and the pooled keys of those
 // blocks (Eq. 6) from the rows as they pass.  One workgroup = one block of K or of V; a thread moves 16 bytes per
 // sweep, all sweeps in flight together.  For K the rows also go to LDS, where D / 2 threads add them in ascending
-// order (the pinned order of the pooling), two dimensions each: 64 consecutive words per row, free of bank conflicts.
+// order (the pinned order of the pooling).
 // Bound by HBM: each byte is read once and written once, and a selection that follows need not read K again: 11.1 us
 // for a chunk of 12 x 4680 x 128 (57.5 MB moved, 5.2 TB/s), where four tensor copies took 27 us and the selection's
 // own pooling launch another 8.7.  The chunk's queries can be pooled along (and are not copied): half as many workgroups
@@ -178,18 +248,7 @@ __global__ void __launch_bounds__(kThreads) append_kernel(AppendArgs a) {
   }
   if (!pool) return;
   __syncthreads();
-  if (threadIdx.x >= D / 2) return;
-  const uint32_t* t32 = reinterpret_cast<const uint32_t*>(tile) + threadIdx.x;
-  float acc0 = 0.0f, acc1 = 0.0f;
-#pragma unroll 16
-  for (int r = 0; r < len; ++r) {
-    const uint32_t u = t32[r * (D / 2)];
-    acc0 = acc0 + bf_lo(u);
-    acc1 = acc1 + bf_hi(u);
-  }
-  const float fl = (float)len;
-  float* const out = kv == 0 ? a.Kc_l + slot * D : a.Qc + ((size_t)h * a.nqb + i) * D;
-  *reinterpret_cast<float2*>(out + 2 * threadIdx.x) = make_float2(acc0 / fl, acc1 / fl);
+  if (threadIdx.x < D / 2) pool_tile<D>(tile, len, kv == 0 ? a.Kc_l + slot * D : a.Qc + ((size_t)h * a.nqb + i) * D);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -916,11 +975,7 @@ hipError_t launch_pool_blocks(const pbsa_params& p, const bf16_t* X, const int32
   if (n_blocks == 0) return hipSuccess;
   PoolArgs a{};
   a.mode = 0; a.n_jobs = n_blocks; a.B = p.B; a.X = X; a.len = len; a.out = out;
-  const int jpw = kThreads / (p.d / 2);
-  const dim3 grid((n_blocks + jpw - 1) / jpw);
-  if (p.d == 128) hipLaunchKernelGGL(pool_kernel<128>, grid, dim3(kThreads), 0, stream, a);
-  else hipLaunchKernelGGL(pool_kernel<64>, grid, dim3(kThreads), 0, stream, a);
-  return hipGetLastError();
+  return p.d == 128 ? launch_pool<128>(a, stream) : launch_pool<64>(a, stream);
 }
 
 hipError_t launch_append(const pbsa_params& p, const bf16_t* K, const bf16_t* V, int64_t k_stride_h, int64_t k_stride_t,
@@ -1022,11 +1077,7 @@ hipError_t launch_select(const pbsa_params& p, const bf16_t* Q, const bf16_t* Kl
   const bool in_select = select_pools_queries(p, Zl);
   const PoolArgs pa = select_pool_args(p, Q, Kl, l_len, l_map, Kc_l, Qc, !in_select);
   if (pa.n_jobs > 0) {
-    const int jpw = kThreads / (p.d / 2);
-    const dim3 grid((pa.n_jobs + jpw - 1) / jpw);
-    if (p.d == 128) hipLaunchKernelGGL(pool_kernel<128>, grid, dim3(kThreads), 0, stream, pa);
-    else hipLaunchKernelGGL(pool_kernel<64>, grid, dim3(kThreads), 0, stream, pa);
-    hipError_t e = hipGetLastError();
+    const hipError_t e = p.d == 128 ? launch_pool<128>(pa, stream) : launch_pool<64>(pa, stream);
     if (e != hipSuccess) return e;
   }
   return launch_select_logits(p, in_select ? Q : nullptr, l_map, Kc_l, Qc, sel, Zl, stream);
