@@ -607,7 +607,8 @@ struct FoldArgs {
 constexpr int kFoldBatch = 40, kFoldFew = 8;
 constexpr int kPromoBatch = 8;
 
-template <int NT>
+// FEW: up to so many dropped blocks take a batch of FEW instead of kFoldBatch
+template <int NT, int FEW>
 __device__ __forceinline__ void fold_promote_body(const FoldArgs& a, const int bx, const int h) {
   // per dropped candidate: its valid length and the address of its K and of its V block
   __shared__ const bf16_t* fptr_s[2][kMaxCand];
@@ -678,8 +679,8 @@ __device__ __forceinline__ void fold_promote_body(const FoldArgs& a, const int b
       }
     };
     // (the code of a large batch takes longer to fetch than the few blocks of a small chunk to add)
-    if (nf <= kFoldFew) {
-      batch(std::integral_constant<int, kFoldFew>{}, 0);
+    if (FEW > 0 && nf <= FEW) {
+      batch(std::integral_constant<int, FEW ? FEW : 1>{}, 0);
     } else {
       for (int f0 = 0; f0 < nf; f0 += kFoldBatch) batch(std::integral_constant<int, kFoldBatch>{}, f0);
     }
@@ -715,7 +716,7 @@ __global__ void __launch_bounds__(512) select_small_kernel(SelectArgs a, FoldArg
   const int h = blockIdx.y, n_sel_x = (a.nqb + 3) / 4;
   int bx = (int)blockIdx.x;
   if (bx < n_fold_x) {
-    fold_promote_body<512>(fa, bx, h);
+    fold_promote_body<512, kFoldFew>(fa, bx, h);
     return;
   }
   bx -= n_fold_x;
@@ -923,8 +924,9 @@ __global__ void __launch_bounds__(kThreads) summary_view_kernel(int H, int B, in
   *reinterpret_cast<uint2*>((kv ? Vp : Kp) + ((size_t)h * C1 + C) * blk + rowoff) = w;
 }
 
+template <int FEW>
 __global__ void __launch_bounds__(kFoldThreads) fold_promote_kernel(FoldArgs a) {
-  fold_promote_body<kFoldThreads>(a, blockIdx.x, blockIdx.y);
+  fold_promote_body<kFoldThreads, FEW>(a, blockIdx.x, blockIdx.y);
 }
 
 // The pooling of one chunk's selection call and the fold / promote of the update of the chunk before it, as one
@@ -934,7 +936,7 @@ template <int D>
 __global__ void __launch_bounds__(kFoldThreads) pool_fold_kernel(PoolArgs pa, FoldArgs fa, int n_fold_x) {
   const int n_fold = n_fold_x * fa.H, b = (int)blockIdx.x;      // the fold's workgroups run longest: they start first
   if (b >= n_fold) pool_body<D, kFoldThreads>(pa, b - n_fold);
-  else fold_promote_body<kFoldThreads>(fa, b % n_fold_x, b / n_fold_x);
+  else fold_promote_body<kFoldThreads, kFoldFew>(fa, b % n_fold_x, b / n_fold_x);
 }
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -1207,8 +1209,10 @@ hipError_t launch_update_apply(const pbsa_params& p, bf16_t* Kp, bf16_t* Vp, int
                                hipStream_t stream) {
   const FoldArgs fa = fold_args(p, Kp, Vp, p_len, S_sum, S_cnt, Kl, Vl, ws);
   const int rows_per_wg = kFoldThreads / (p.d / 4);
-  hipLaunchKernelGGL(fold_promote_kernel, dim3((2 * p.B + rows_per_wg - 1) / rows_per_wg, p.H), dim3(kFoldThreads), 0,
-                     stream, fa);
+  const dim3 grid((2 * p.B + rows_per_wg - 1) / rows_per_wg, p.H);
+  // (the choice costs the large batch 0.8 us of 13 by itself, at 12 heads x 74 blocks: only where the update may drop so few)
+  if (p.n_evict <= kFoldFew) hipLaunchKernelGGL(fold_promote_kernel<kFoldFew>, grid, dim3(kFoldThreads), 0, stream, fa);
+  else hipLaunchKernelGGL(fold_promote_kernel<0>, grid, dim3(kFoldThreads), 0, stream, fa);
   return hipGetLastError();
 }
 
