@@ -186,7 +186,7 @@ __global__ void __launch_bounds__(kThreads) pool_tile_kernel(PoolArgs a) {
 }
 
 // Up to four blocks to a compute unit by tiles: pooling and selection of a chunk, us, by threads -> by tiles, 12 heads x 37 blocks of
-// 128 x 128 12.3 -> 11.2, 8 x 20 10.0 -> 8.7, 2 x 16 9.7 -> 8.4, 6 x 40 of 128 x 64 11.5 -> 10.1, 3 x 24 of 64 x 64 7.65 -> 7.4.  Beyond,
+// 128 x 128 12.3 -> 11.1, 8 x 20 10.0 -> 8.7, 2 x 16 9.7 -> 8.1, 6 x 40 of 128 x 64 11.5 -> 9.7, 3 x 24 of 64 x 64 7.65 -> 7.15.  Beyond,
 // the workgroups, of four waves and up to 32 KiB of LDS, come in rounds: 12 x 74 of 64 x 128 14.5 -> 15.0, 12 x 74 of 64 x 64
 // 10.3 -> 10.4, 16 x 42 of 128 x 128 13.5 -> 15.6.
 template <int D>
