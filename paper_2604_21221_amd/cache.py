@@ -18,10 +18,6 @@ from . import pbsa
 _KEYS, _KEYS_AND_QUERIES = 1, 2              # what an append pooled
 
 
-class _Carried(tuple):
-    """Of an append that the selection is to take along, pooling keys and queries: what pbsa_append_chunk gave for that."""
-
-
 class PbsaCache:
     def __init__(self, H, d, B, Nq, window_chunks, C, k, scale, n_sink=0, causal=1, fold=True, device="cuda:0",
                  pass_logits=True, ring_chunks=None):
@@ -184,17 +180,52 @@ class PbsaCache:
         """append_chunk; pool: the pooled keys are taken as the rows pass, for a selection that follows at once (whoever
         appends by themselves may still change the rows in the ring, and the selection pools what it finds there), and with
         Q, where that is of use, the queries are pooled along.
-        Returns whether they were: nothing, _KEYS, _KEYS_AND_QUERIES, or (_Carried) an append that _select() is to complete."""
+        Returns whether they were: nothing, _KEYS, or _KEYS_AND_QUERIES."""
         if K is None or V is None:
             raise TypeError("append_chunk takes K and V (adopt_chunk declares a chunk that is in the ring already)")
         assert len(self.chunk_pos) <= self.w, "update() slides the window before the next append"
         pos = self.n_appended % self.ring
         pooled = self._write_chunk(pos, K, V, True, pool, Q)    # may refuse them: the chunk counts once it is there
+        self._declare(pos, chunk_id)
+        return pooled
+
+    def _declare(self, pos, chunk_id):
         self.chunk_pos.append(pos)
         self.chunk_ids.append(chunk_id)
         self.n_appended += 1
         self.stale_from = min(self.stale_from, self.n_loc - self.nqb)
-        return pooled
+
+    def _append_select(self, Q, K, V, chunk_id):
+        """How a step begins: append_chunk, then select(Q).  As one call where the append pools the queries along and nothing
+        older is stale.  What that call refuses the two decide, each for itself: a chunk counts once its append went
+        through."""
+        if (K is not None and V is not None and len(self.chunk_pos) <= self.w and self.stale_from >= self.n_loc
+                and self._append_pools_queries() and self._by_launch and self._in_place(K, V, Q)):
+            torch.autograd.graph.increment_version([self.Kl, self.Vl])       # as in _write_chunk
+            pos, stale_from = self.n_appended % self.ring, self.stale_from
+            self._declare(pos, chunk_id)                         # the maps of the call have the chunk in them
+            try:
+                l_map, _, _ = self._device_maps()
+                pbsa.pbsa_append_select(self.params(pool_from=self.n_loc, Q=Q), K, V, pos * self.nqb, True, Q, self.Kl, self.Vl,
+                                        l_map, self.Kc_l, self.Qc, self.sel, self.Zl)
+                self.stale_from = self.n_loc
+                return self.sel
+            except BaseException as e:
+                self.chunk_pos.pop()
+                self.chunk_ids.pop()
+                self.n_appended -= 1
+                self.stale_from = stale_from
+                if not isinstance(e, Exception):
+                    raise
+        return self._select(Q, self._append(K, V, chunk_id, True, Q))
+
+    def _append_pools_queries(self):
+        # Up to 400 blocks the launch pools the queries for less than the selection takes to (step without -> with them,
+        # heads x blocks x block size at d = 64 | 128: 8 x 25 x 128 64.1 -> 61.4 us | 86.2 -> 83.1, 6 x 38 x 64
+        # 74.9 -> 74.0 | 89.6 -> 89.0, 10 x 30 x 64 57.9 -> 57.0 | 70.0 -> 68.8, 12 x 25 x 128 83.2 -> 81.8 | 101.8 -> 101.0,
+        # 12 x 33 x 128 87.7 -> 83.2 | 116.2 -> 114.6, 16 x 25 x 64 55.1 -> 54.0 | 69.8 -> 67.3); beyond, their bytes take it
+        # as long as they take the selection (187.3 -> 187.5 at 12 x 37 x 128 | d = 128, 181.6 -> 181.3 at 16 x 42).
+        return self._pending is None and self.H * self.nqb <= 400
 
     def _in_place(self, *tensors):
         """Whether pbsa_append_chunk takes K and V (or None) as they are and nothing but their bytes counts: bf16 on this
@@ -224,24 +255,12 @@ class PbsaCache:
             torch.autograd.graph.increment_version([dst for dst, src in ((self.Kl, K), (self.Vl, V)) if src is not None])
             pool = pool and K is not None
             args = self._full, K, V, pos * self.nqb, zero_tail, self.Kl, self.Vl, self.Kc_l if pool else None
-            # Up to 400 blocks the launch pools the queries for less than the selection takes to (step without -> with them,
-            # heads x blocks x block size at d = 64 | 128: 8 x 25 x 128 64.1 -> 61.4 us | 86.2 -> 83.1, 6 x 38 x 64
-            # 74.9 -> 74.0 | 89.6 -> 89.0, 10 x 30 x 64 57.9 -> 57.0 | 70.0 -> 68.8, 12 x 25 x 128 83.2 -> 81.8 | 101.8 -> 101.0,
-            # 12 x 33 x 128 87.7 -> 83.2 | 116.2 -> 114.6, 16 x 25 x 64 55.1 -> 54.0 | 69.8 -> 67.3); beyond, their bytes take it
-            # as long as they take the selection (187.3 -> 187.5 at 12 x 37 x 128 | d = 128, 181.6 -> 181.3 at 16 x 42).
-            if (pool and Q is not None and self._pending is None and self.H * self.nqb <= 400
+            if (pool and Q is not None and self._append_pools_queries()
                     and pbsa.plain_rows(self.Kl, self.Vl, self.H, self.Nq, self.d, torch.is_grad_enabled(), Q)):
-                if V is not None and self.stale_from >= self.n_loc:      # (nothing older is stale) the selection can take all of it
-                    carried = pbsa.pbsa_append_chunk(*args, None, Q, self.Qc, carried=True)
-                    return _Carried(carried) if carried is not None else _KEYS_AND_QUERIES
                 pbsa.pbsa_append_chunk(*args, None, Q, self.Qc)
                 return _KEYS_AND_QUERIES
             pbsa.pbsa_append_chunk(*args)
             return _KEYS if pool else 0
-        self._copy_chunk(pos, K, V, zero_tail)
-        return 0
-
-    def _copy_chunk(self, pos, K, V, zero_tail):
         for dst, src in ((self.Kl, K), (self.Vl, V)):
             if src is None:
                 continue
@@ -249,6 +268,7 @@ class PbsaCache:
             view[:, :self.Nq] = src
             if zero_tail and self.nqb * self.B > self.Nq:
                 view[:, self.Nq:] = 0
+        return 0
 
     def rewrite_chunk(self, K=None, V=None):
         """Between the denoising passes of one chunk (Sec. 3.1: each chunk is denoised in T passes over the
@@ -263,10 +283,7 @@ class PbsaCache:
         """Declare the next ring position to hold chunk `chunk_id` whose K/V the producer has already
         written there in block-major layout (zero-copy append)."""
         assert len(self.chunk_pos) <= self.w, "update() slides the window before the next append"
-        self.chunk_pos.append(self.n_appended % self.ring)
-        self.chunk_ids.append(chunk_id)
-        self.n_appended += 1
-        self.stale_from = min(self.stale_from, self.n_loc - self.nqb)
+        self._declare(self.n_appended % self.ring, chunk_id)
 
     # -- the three calls ---------------------------------------------------------------------------
     def select(self, Q):
@@ -274,16 +291,6 @@ class PbsaCache:
 
     def _select(self, Q, pooled):
         """select; pooled: what of the newest chunk has just been pooled (_append); anything older that is stale has not."""
-        if isinstance(pooled, _Carried):
-            try:
-                l_map, l_len, _ = self._device_maps()
-                pbsa.pbsa_select_blocks(self.params(pool_from=self.n_loc, Q=Q), Q, self.Kl, l_len, l_map, self.Kc_l, self.Qc, self.sel,
-                                        self.Zl, pooled=True, append=pooled)
-            except BaseException:            # the chunk has been declared: its rows go to the ring all the same
-                self._copy_chunk(self.chunk_pos[-1], pooled[0], pooled[1], True)
-                raise
-            self.stale_from = self.n_loc
-            return self.sel
         l_map, l_len, _ = self._device_maps()
         fresh = pooled and self.stale_from == self.n_loc - self.nqb
         p = self.params(pool_from=self.n_loc if fresh else self.stale_from, Q=Q)
@@ -393,7 +400,7 @@ class PbsaCache:
 
     def step_fine(self, Q, K, V, chunk_id, O=None, lse=None):
         """The step with the fine-mass score: append, select, attend (recording the mass), update."""
-        self._select(Q, self._append(K, V, chunk_id, True, Q))
+        self._append_select(Q, K, V, chunk_id)
         O, Mt = self.attention_with_mass(Q, O, lse)
         self.update_fine(Mt)
         return O
@@ -456,7 +463,7 @@ class PbsaCache:
     def step_fused(self, Q, K=None, V=None, chunk_id=None, O=None, lse=None):
         """The step as two launches after the selection: attention with the update's decisions, then fold /
         promote.  K = V = None: the chunk has been adopted already."""
-        self._select(Q, K is not None and self._append(K, V, chunk_id, True, Q))
+        self._select(Q, 0) if K is None else self._append_select(Q, K, V, chunk_id)
         O = self.attention_with_plan(Q, O, lse)
         self.update_apply()
         return O
@@ -484,7 +491,7 @@ class PbsaCache:
     def step_chained(self, Q, K=None, V=None, chunk_id=None, O=None, lse=None):
         """Two library calls per step: selection (carrying the previous step's fold / promote), attention (carrying
         this step's decisions).  flush() after the last step.  K = V = None: the chunk has been adopted already."""
-        self._select(Q, K is not None and self._append(K, V, chunk_id, True, Q))
+        self._select(Q, 0) if K is None else self._append_select(Q, K, V, chunk_id)
         O = self.attention_with_plan(Q, O, lse)
         self.defer_apply()
         return O
@@ -494,7 +501,7 @@ class PbsaCache:
         leaves its logits and the update maintains the slots, the update's decisions ride in the attention launch
         (step_fused, the same results bit for bit): four launches instead of six, 202.6 -> 189.4 us at 12 x 4680 x 128
         with 16 slots, 57 -> 49 us for two heads of 256 tokens."""
-        self._select(Q, self._append(K, V, chunk_id, True, Q))
+        self._append_select(Q, K, V, chunk_id)
         if self.Zl is not None and self.C <= pbsa.PBSA_MAX_C:
             O = self.attention_with_plan(Q, O, lse)
             self.update_apply()

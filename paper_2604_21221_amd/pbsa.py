@@ -221,12 +221,9 @@ def pbsa_summary_view(p, S_sum, S_cnt, Kp, Vp, p_len, stream=None):
     _call("pbsa_summary_view", p, S_sum, S_cnt, Kp, Vp, p_len, _stream(stream))
 
 
-def pbsa_append_chunk(p, K, V, slot0, zero_tail, Kl, Vl, Kc_l=None, stream=None, Q=None, Qc=None, carried=False):
+def pbsa_append_chunk(p, K, V, slot0, zero_tail, Kl, Vl, Kc_l=None, stream=None, Q=None, Qc=None):
     """K, V: [H][Nq][d] bf16 with a contiguous last dimension, or None.  Q, Qc: the queries are pooled along
-    (pbsa_append_chunk_pool), for a pbsa_select_blocks with pooled=True.  carried: that call is to take the append along, as its
-    `append`; what it needs for that is returned, and nothing launched."""
-    if carried:
-        return K, V, slot0, zero_tail, Vl
+    (pbsa_append_chunk_pool), for a pbsa_select_blocks with pooled=True."""
     ks, vs = (x.stride() if x is not None else (0, 0, 1) for x in (K, V))
     if Q is not None:
         qs = Q.stride()
@@ -236,15 +233,15 @@ def pbsa_append_chunk(p, K, V, slot0, zero_tail, Kl, Vl, Kc_l=None, stream=None,
     _call("pbsa_append_chunk", p, K, V, ks[0], ks[1], vs[0], vs[1], slot0, int(zero_tail), Kl, Vl, Kc_l, _stream(stream))
 
 
-def pbsa_select_blocks(p, Q, Kl, l_len, l_map, Kc_l, Qc, sel, Zl=None, ws=None, stream=None, pooled=False, append=None):
-    """pooled: Qc and all of Kc_l have been written already (pbsa_select_pooled), or are by the pbsa_append_chunk that returned
-    `append` and is carried out by this call (pbsa_append_select)."""
-    if append is not None:
-        K, V, slot0, zero_tail, Vl = append
-        ks, vs = K.stride(), V.stride()
-        _call("pbsa_append_select", p, K, V, ks[0], ks[1], vs[0], vs[1], slot0, int(zero_tail), Q, Kl, Vl, l_map, Kc_l, Qc, sel, Zl,
-              _stream(stream))
-        return
+def pbsa_append_select(p, K, V, slot0, zero_tail, Q, Kl, Vl, l_map, Kc_l, Qc, sel, Zl=None, stream=None):
+    """K, V: [H][Nq][d] bf16 with a contiguous last dimension; Q has p's strides."""
+    ks, vs = K.stride(), V.stride()
+    _call("pbsa_append_select", p, K, V, ks[0], ks[1], vs[0], vs[1], slot0, int(zero_tail), Q, Kl, Vl, l_map, Kc_l, Qc, sel, Zl,
+          _stream(stream))
+
+
+def pbsa_select_blocks(p, Q, Kl, l_len, l_map, Kc_l, Qc, sel, Zl=None, ws=None, stream=None, pooled=False):
+    """pooled: Qc and all of Kc_l have been written already (pbsa_select_pooled)."""
     if pooled:
         _call("pbsa_select_pooled", p, l_map, Kc_l, Qc, sel, Zl, _stream(stream))
         return

@@ -8,7 +8,7 @@ torch = pytest.importorskip("torch")
 
 from paper_2604_21221_amd import pbsa  # noqa: E402
 from paper_2604_21221_amd.cache import PbsaCache  # noqa: E402
-from tests.test_cache_host import B, D, H, NQ, chunk, rows  # noqa: E402
+from tests.test_cache_host import B, D, H, NQ, chunk  # noqa: E402
 
 
 @pytest.fixture
@@ -16,30 +16,49 @@ def cache():
     return PbsaCache(H, D, B, NQ, 1, 3, 12, D ** -0.5, device="cpu")
 
 
-def test_an_append_whose_selection_fails_is_in_the_ring(cache, monkeypatch):
-    def refuse(*a, append=None, **k):
-        assert append is not None
-        raise pbsa.PbsaError(pbsa.PBSA_EHIP)
+def refuse(*a, **k):
+    raise pbsa.PbsaError(pbsa.PBSA_EHIP)
 
-    monkeypatch.setattr(pbsa, "pbsa_select_blocks", refuse)
-    with torch.no_grad():
-        cache.Kl.fill_(7.0)
-        cache.Vl.fill_(7.0)
-    k, v = chunk(1), chunk(2)
-    with pytest.raises(pbsa.PbsaError):
-        cache.step(chunk(0), k, v, 0)
-    assert torch.equal(rows(cache, cache.Kl), k) and torch.equal(rows(cache, cache.Vl), v)
-    tail = cache.Kl[:, :cache.nqb].reshape(H, -1, D)[:, NQ:]
-    assert tail.numel() and not tail.any()
-    assert cache.chunk_ids == [0] and cache.stale_from == 0
+
+def test_a_refused_call_is_made_as_two(cache, monkeypatch):
+    """What the one call refuses the two calls decide: a chunk counts once its append went through, whatever the selection
+    behind it says, and not before."""
+    launched, ok = [], []
+    monkeypatch.setattr(pbsa, "pbsa_append_select", refuse)
+    monkeypatch.setattr(pbsa, "pbsa_append_chunk", lambda *a, **k: launched.append(a))
+    with monkeypatch.context() as m:
+        m.setattr(pbsa, "pbsa_select_blocks", refuse)
+        with pytest.raises(pbsa.PbsaError):
+            cache.step(chunk(0), chunk(1), chunk(2), 0)
+    assert len(launched) == 1 and cache.chunk_ids == [0] and cache.n_appended == 1 and cache.stale_from == 0
+    with monkeypatch.context() as m:
+        m.setattr(pbsa, "pbsa_append_chunk", refuse)
+        with pytest.raises(pbsa.PbsaError):
+            cache.step(chunk(0), chunk(1), chunk(2), 1)
+    assert cache.chunk_ids == [0] and cache.n_appended == 1 and cache.stale_from == 0
+    for name in ("pbsa_select_blocks", "pbsa_attention_fwd_plan_split", "pbsa_attention_fwd_plan", "pbsa_memory_update_apply"):
+        monkeypatch.setattr(pbsa, name, lambda *a, name=name, **k: ok.append(name))
+    cache.step(chunk(0), chunk(1), chunk(2), 1)
+    assert cache.chunk_ids == [1] and cache.chunk_pos == [1] and cache.n_appended == 2 and ok[0] == "pbsa_select_blocks"
+
+
+def test_an_interrupted_call_declares_nothing(cache, monkeypatch):
+    def interrupt(*a, **k):
+        raise KeyboardInterrupt
+
+    monkeypatch.setattr(pbsa, "pbsa_append_select", interrupt)
+    with pytest.raises(KeyboardInterrupt):
+        cache.step(chunk(0), chunk(1), chunk(2), 0)
+    assert (cache.chunk_pos, cache.chunk_ids, cache.n_appended, cache.stale_from) == ([], [], 0, 0)
 
 
 @pytest.mark.parametrize("why", ["older block stale", "deferred update", "queries followed by autograd", "values through torch"])
 def test_when_an_append_is_not_carried(cache, monkeypatch, why):
-    launched, carried = [], []
-    monkeypatch.setattr(pbsa, "pbsa_append_chunk", lambda *a, carried=False, **k: launched.append(carried) or (a if carried else None))
+    selected = []
+    monkeypatch.setattr(pbsa, "pbsa_append_select", lambda *a, **k: pytest.fail("the append is no part of this selection"))
+    monkeypatch.setattr(pbsa, "pbsa_append_chunk", lambda *a, **k: None)
     for name in ("pbsa_select_blocks", "pbsa_select_blocks_apply"):
-        monkeypatch.setattr(pbsa, name, lambda *a, append=None, **k: carried.append(append is not None))
+        monkeypatch.setattr(pbsa, name, lambda *a, name=name, **k: selected.append(name))
     cache.adopt_chunk(0)
     cache.stale_from = cache.n_loc
     q, v = chunk(0), chunk(2)
@@ -51,8 +70,8 @@ def test_when_an_append_is_not_carried(cache, monkeypatch, why):
         q.requires_grad_()
     else:
         v = v.float()
-    cache._select(q, cache._append(chunk(1), v, 1, True, q))
-    assert not any(launched) and carried == [False]
+    cache._append_select(q, chunk(1), v, 1)
+    assert selected == ["pbsa_select_blocks_apply" if why == "deferred update" else "pbsa_select_blocks"]
 
 
 @pytest.mark.gpu
@@ -71,9 +90,9 @@ def test_a_carried_append_leaves_what_the_two_calls_do(d, b, nqb, tail, w):
         c.Vl.fill_(3.0)
     for g in range(w + 3):
         q, k, v = (torch.randn(nq, heads, d, generator=gen, device=dev).to(torch.bfloat16).transpose(0, 1) for _ in range(3))
-        pooled = one._append(k, v, g, True, q)
-        assert isinstance(pooled, tuple)
-        one._select(q, pooled)
+        with pytest.MonkeyPatch.context() as m:
+            m.setattr(pbsa, "pbsa_append_chunk", refuse)         # it is the one call
+            one._append_select(q, k, v, g)
         two.append_chunk(k, v, g)
         two.select(q)
         n = heads * nqb * two.n_loc
