@@ -383,6 +383,11 @@ __device__ __forceinline__ void select_body(const SelectArgs& a, const int bx, c
 
   const bool has_cols = NM >= 4 || wave < NM;         // the waves that own columns
 
+  int place[NM];                                      // KEYS: l_map of columns lane + 64 m
+  if constexpr (KEYS)
+#pragma unroll
+    for (int m = 0; m < NM; ++m) place[m] = a.l_map[min(lane + 64 * m, a.n_loc - 1)];
+
   // this lane's share of the staging: instruction n fills columns 64 wave + CPI n + lane / CPC, physical chunk
   // lane % CPC
   uint32_t goff[NI];
@@ -410,15 +415,18 @@ __device__ __forceinline__ void select_body(const SelectArgs& a, const int bx, c
     constexpr int JPS = NT / (D / 2), SW = (4 + kOwnKeys) / JPS;      // blocks at a time, times
     const int c = threadIdx.x % (D / 2), n_stale = a.n_loc - a.pool_from;
     float2 mean[SW];
-    int col[SW], slot[SW];                            // of a key block: its column (-1: it is nowhere) and place
+    int slot[SW];                                     // of a key block (-1: it is nowhere)
+    // an older block in the place of one of these has the new pooled keys too, and is staged with those from before
+    bool twice = false;
+#pragma unroll
+    for (int m = 0; m < NM; ++m) place[m] = lane + 64 * m < a.pool_from ? min(max(place[m], 0), a.n_loc_cap - 1) : -2;
 #pragma unroll
     for (int w = 0; w < SW; ++w) {
       const int job = w * JPS + (int)threadIdx.x / (D / 2), i = i0 + job, l = a.pool_from + job - 4;
       const bf16_t* p = nullptr;
       long pitch = 0;
       int len = 0;
-      col[w] = -1;
-      slot[w] = 0;
+      slot[w] = -1;
       if (job < 4) {
         if (i < a.nqb) {
           len = min(a.B, a.Nq - i * a.B);
@@ -431,17 +439,20 @@ __device__ __forceinline__ void select_body(const SelectArgs& a, const int bx, c
           len = min(a.B, a.Nq - (job - 4) * a.B);
           pitch = a.k_stride_t;
           p = a.Kl + (size_t)h * a.k_stride_h + (size_t)(job - 4) * a.B * pitch + 2 * c;
-          col[w] = l;
         } else {
-          slot[w] = a.l_map[l];
-          if (slot[w] >= 0 && slot[w] < a.n_loc_cap) {
+          const int at = a.l_map[l];
+          if (at >= 0 && at < a.n_loc_cap) {
             len = max(0, min(a.l_len[l], a.B));
             pitch = D;
-            p = a.Kl + ((size_t)h * a.n_loc_cap + slot[w]) * a.B * D + 2 * c;
-            col[w] = l;
+            p = a.Kl + ((size_t)h * a.n_loc_cap + at) * a.B * D + 2 * c;
+            slot[w] = at;
           }
         }
       }
+#pragma unroll
+      for (int x = 0; x < 64; x += D / 2)
+#pragma unroll
+        for (int m = 0; m < NM; ++m) twice |= __any(place[m] == __builtin_amdgcn_readlane(slot[w], x));
       float acc0 = 0.0f, acc1 = 0.0f;
       pool_block(p, pitch, len, acc0, acc1);
       const float fl = (float)len;
@@ -453,13 +464,25 @@ __device__ __forceinline__ void select_body(const SelectArgs& a, const int bx, c
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // what was staged for those columns has arrived: it is written over
     __syncthreads();
+    auto put = [&](int w, int j) {
+      const int r = 2 * c / DX, chunk = 2 * c % DX / 4;
+      *reinterpret_cast<float2*>(smem + r * BUF + j * (DX * 4) + ((chunk ^ ((j >> 1) % CPC)) << 4) + (c % 2) * 8) = mean[w];
+    };
 #pragma unroll
     for (int w = 0; w < SW; ++w)
-      if (col[w] >= 0) {
-        const int r = 2 * c / DX, chunk = 2 * c % DX / 4;
-        *reinterpret_cast<float2*>(smem + r * BUF + col[w] * (DX * 4) + ((chunk ^ ((col[w] >> 1) % CPC)) << 4) + (c % 2) * 8) = mean[w];
+      if (slot[w] >= 0) {
+        put(w, a.pool_from + w * JPS + (int)threadIdx.x / (D / 2) - 4);
         if (bx == 0) *reinterpret_cast<float2*>(a.Kc_l + ((size_t)h * a.n_loc_cap + slot[w]) * D + 2 * c) = mean[w];
       }
+    if (__builtin_expect(twice, false)) {
+#pragma unroll 1
+      for (int j = 0; j < a.pool_from; ++j) {
+        const int at = min(max(a.l_map[j], 0), a.n_loc_cap - 1);
+#pragma unroll
+        for (int w = 0; w < SW; ++w)
+          if (slot[w] == at) put(w, j);
+      }
+    }
   } else if (a.Q) {
     const int r = threadIdx.x / (D / 2), c = threadIdx.x % (D / 2), i = i0 + r;
     if (r < 4) {

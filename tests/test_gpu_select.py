@@ -131,6 +131,27 @@ def test_keys_pooled_by_the_selection(gpu, case):  # noqa: F811
         assert torch.equal(a, b), name
 
 
+@pytest.mark.parametrize("case", [(64, 64, 4), (64, 64, 12), (128, 64, 6), (128, 128, 4)], ids=lambda c: "d%d_B%d_%d_blocks" % c)
+def test_a_place_named_twice(gpu, case):  # noqa: F811
+    """Older blocks in the places of blocks that the selection pools itself: their columns have the new pooled keys too, as if
+    those had been pooled before."""
+    d, B, nqb = case
+    H, cap, pbsa = 2, 3 * nqb, gpu["pbsa"]
+    K, Q = gpu["wl"].bf16_tensor(rnd(971, H, cap * B, d), DEV).view(H, cap, B, d), gpu["wl"].bf16_tensor(rnd(972, H, nqb * B, d), DEV)
+    l_map = torch.arange(cap, dtype=torch.int32, device=DEV)
+    l_map[0], l_map[nqb], l_map[2 * nqb - 1] = 3 * nqb - 1, 2 * nqb, 3 * nqb - 1
+    l_len = torch.full((cap,), B, dtype=torch.int32, device=DEV)
+    new = lambda *s, t=torch.float32, x=5.0: torch.full(s, x, dtype=t, device=DEV)  # noqa: E731
+    Kc, Qc, k = new(H, cap, d), new(H, nqb, d), 5
+    sel, want = (new(H, nqb, k, t=torch.int32, x=-1) for _ in range(2))
+    Zl, Zw = new(H, nqb, cap), new(H, nqb, cap)
+    p = pbsa.make_params(H, d, B, nqb * B, cap, cap, 1, k, np.float32(d ** -0.5), pool_from=2 * nqb)
+    pbsa.pbsa_select_blocks(p, Q, K, l_len, l_map, Kc, Qc, sel, Zl)
+    pbsa.pbsa_select_blocks(p, Q, K, l_len, l_map, Kc, Qc, want, Zw, pooled=True)
+    assert torch.equal(Kc[:, :2 * nqb], new(H, 2 * nqb, d)) and not bool((Kc[:, 2 * nqb:] == 5.0).any())
+    assert torch.equal(Zl.view(torch.int32), Zw.view(torch.int32)) and torch.equal(sel, want)
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("nqb", [7, 45])
 def test_selection_of_nan(gpu, d, nqb):  # noqa: F811
