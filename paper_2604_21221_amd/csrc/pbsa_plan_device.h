@@ -489,6 +489,10 @@ __device__ inline void score_head_body(const ScoreArgs& a, const int h, unsigned
         if (next >= a.n_loc) break;
       }
     }
+    // the rest reads what other lanes of this wave wrote, in LDS that no other wave touches: in order for the hardware, and so
+    // for the compiler
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
     // the sums: lane l adds up row l % 4 of the wave's group l / 4 (rows beyond the last have a place in LDS as well)
     {
       const int r = 4 * (wave + NW * (lane >> 2)) + (lane & 3);
