@@ -1063,13 +1063,32 @@ static SelectArgs select_args(const pbsa_params& p, const bf16_t* Q, const int32
                     Q, p.B, p.Nq, p.q_stride_h, p.q_stride_t, nullptr, nullptr, 0, -1, 0, 0};
 }
 
+// Workgroups per head that fold beside a small selection (each of 512 threads, four dimensions of a row to one).
+static int small_fold_x(int B, int d) { return (2 * B + 512 / (d / 4) - 1) / (512 / (d / 4)); }
+
 // Whether the selection pools the stale key blocks itself, and not a launch before it.  Every workgroup of a head then reads
-// them all, beside its own four query blocks: at most 12, and no more than 256 KiB together, which a compute unit takes 2 us
-// for (two launches -> one, us, heads x blocks: 4 x 4 of 64 x 64 7.8 -> 5.2, 16 x 12 of 64 x 64 8.2 -> 6.1, 16 x 8 of 128 x 64
-// 10.0 -> 8.4, 16 x 4 of 128 x 128 9.8 -> 9.0; beyond: 16 x 8 of 128 x 128 10.3 -> 11.2).
-static bool select_is_small(const pbsa_params& p, int n_stale, const float* Zl) {
-  return (p.k > 0 || Zl) && n_stale > 0 && n_stale <= kOwnKeys && p.nqb <= kOwnKeys && p.n_loc <= 128 &&
-         (4 + n_stale) * p.B * p.d * 2 <= 256 * 1024;
+// them all, beside its own four query blocks: at most 12 blocks, and a workgroup has a compute unit to itself, so no more
+// than 256 of them.  Beyond 128 KiB a workgroup only chunks of whole blocks, whose loops over the rows are the shorter
+// ones, and where the heads are few.  Two launches -> one, us, heads x blocks:
+//   the selection by itself (a denoising pass): 12 x 4 of 64 x 64 7.9 -> 6.6, 256 x 4 8.9 -> 7.0, 64 x 12 8.9 -> 7.6, 12 x 4 of
+//   64 x 128 8.8 -> 8.4, 12 x 4 of 128 x 64 8.6 -> 7.6, 256 x 1 7.3 -> 6.4; 96 x 12 of 64 x 64 9.8 | 13.8, 384 x 1 7.0 | 8.6, 192 x 8
+//   9.9 | 13.7; beyond 128 KiB with whole blocks 16 x 12 of 64 x 128 8.5 -> 8.0, 16 x 8 of 128 x 64 8.5 -> 8.4, 16 x 4 of 128 x 128
+//   8.9 -> 8.4, but 16 x 12 of 128 x 64 8.6 | 8.8, 64 x 12 of 64 x 128 9.0 | 13.1, 64 x 8 of 128 x 64 8.7 | 8.9; with a last block that is
+//   not whole 12 x 6 of 64 x 128 8.8 | 9.7, 12 x 12 of 128 x 64 9.0 | 9.3, 12 x 4 of 128 x 128 9.4 | 10.6;
+//   with the append, whose copies come behind (a step): 12 x 4 of 64 x 64 22.0 -> 20.7, 96 x 4 32.9 -> 32.1, 32 x 12 33.6 -> 32.4, 64 x 4 of
+//   128 x 64 42.5 -> 40.5; 256 x 1 of 64 x 64 40.5 | 42.0, 64 x 12 45.4 | 45.6; beyond 128 KiB with whole blocks 16 x 12 of 64 x 128
+//   36.8 -> 35.7, 16 x 12 of 128 x 64 33.4 -> 31.3, 32 x 4 of 128 x 128 45.6 -> 43.9, but 32 x 12 of 64 x 128 46.9 | 48.0, 64 x 4 of 128 x 128
+//   59.5 | 60.3; with a last block that is not 12 x 6 of 64 x 128 26.9 | 27.4, 64 x 4 of 128 x 128 60.7 | 62.3;
+//   with the fold of the update before, whose workgroups count as well (a chained step): 12 x 4 of 64 x 64
+//   18.4 -> 15.9, 12 x 12 of 64 x 128 27.5 -> 26.5, 12 x 12 of 128 x 64 25.4 -> 23.2, 12 x 2 of 128 x 128 26.3 -> 25.1; 64 x 8 of
+//   64 x 64 30.9 | 31.2, 32 x 12 of 128 x 64 32.1 | 33.5, 64 x 1 of 128 x 128 34.9 | 37.1, 256 x 1 75 | 89.
+static bool select_is_small(const pbsa_params& p, int n_stale, const float* Zl, int fold_x, bool append) {
+  if (!(p.k > 0 || Zl) || n_stale < 1 || n_stale > kOwnKeys || p.nqb > kOwnKeys || p.n_loc > 128) return false;
+  const int bytes = (4 + n_stale) * p.B * p.d * 2;
+  const long wgs = (long)p.H * ((p.nqb + 3) / 4 + fold_x);
+  if (fold_x > 0) return bytes <= 256 * 1024 && wgs <= 256;
+  if (bytes <= 128 * 1024) return wgs <= (append ? 128 : 256);
+  return p.Nq % p.B == 0 && bytes <= 256 * 1024 && wgs <= 64 && (append || p.d * n_stale <= 1024);
 }
 
 template <int D>
@@ -1077,7 +1096,7 @@ static hipError_t launch_select_small(const SelectArgs& a, const FoldArgs* fa, c
   constexpr size_t lds = SelectGeo<D, 2>::LDS;
   const hipError_t e = allow_lds(select_small_kernel<D>, lds);
   if (e != hipSuccess) return e;
-  const int n_fold_x = fa ? (2 * fa->B + 512 / (D / 4) - 1) / (512 / (D / 4)) : 0;
+  const int n_fold_x = fa ? small_fold_x(fa->B, D) : 0;
   hipLaunchKernelGGL(select_small_kernel<D>, dim3(n_fold_x + (a.nqb + 3) / 4 + (ap ? 2 * a.nqb : 0), a.H), dim3(512), lds, stream, a,
                      fa ? *fa : FoldArgs{}, n_fold_x, ap ? *ap : AppendArgs{});
   return hipGetLastError();
@@ -1097,7 +1116,7 @@ hipError_t launch_select(const pbsa_params& p, const bf16_t* Q, const bf16_t* Kl
                          const int32_t* l_map, float* Kc_l, float* Qc, int32_t* sel, float* Zl, bool pooled,
                          hipStream_t stream) {
   if (pooled) return launch_select_logits(p, nullptr, l_map, Kc_l, Qc, sel, Zl, stream);
-  if (select_is_small(p, p.n_loc - p.pool_from, Zl))
+  if (select_is_small(p, p.n_loc - p.pool_from, Zl, 0, false))
     return launch_select_small(p, select_args(p, Q, l_map, Kc_l, Qc, sel, Zl), Kl, l_len, nullptr, stream);
   const bool in_select = select_pools_queries(p, Zl);
   const PoolArgs pa = select_pool_args(p, Q, Kl, l_len, l_map, Kc_l, Qc, !in_select);
@@ -1111,7 +1130,7 @@ hipError_t launch_select(const pbsa_params& p, const bf16_t* Q, const bf16_t* Kl
 hipError_t launch_append_select(const pbsa_params& p, const bf16_t* K, const bf16_t* V, int64_t k_stride_h, int64_t k_stride_t,
                                 int64_t v_stride_h, int64_t v_stride_t, int32_t slot0, int32_t zero_tail, const bf16_t* Q, bf16_t* Kl,
                                 bf16_t* Vl, const int32_t* l_map, float* Kc_l, float* Qc, int32_t* sel, float* Zl, hipStream_t stream) {
-  if (!select_is_small(p, p.nqb, Zl)) {
+  if (!select_is_small(p, p.nqb, Zl, 0, true)) {
     const hipError_t e = launch_append(p, K, V, k_stride_h, k_stride_t, v_stride_h, v_stride_t, slot0, zero_tail, Kl, Vl, Kc_l, Q,
                                        p.q_stride_h, p.q_stride_t, Qc, stream);
     return e != hipSuccess ? e : launch_select_logits(p, nullptr, l_map, Kc_l, Qc, sel, Zl, stream);
@@ -1133,7 +1152,7 @@ hipError_t launch_select_apply(const pbsa_params& p, const bf16_t* Q, const bf16
                                const int32_t* S_cnt, const bf16_t* Vl, const UpdateWs& ws, hipStream_t stream) {
   const PoolArgs pa = select_pool_args(p, Q, Kl, l_len, l_map, Kc_l, Qc, true);
   const FoldArgs fa = fold_args(pu, Kp, Vp, p_len, S_sum, S_cnt, Kl, Vl, ws);
-  if (select_is_small(p, p.n_loc - p.pool_from, Zl))
+  if (select_is_small(p, p.n_loc - p.pool_from, Zl, small_fold_x(pu.B, pu.d), false))
     return launch_select_small(p, select_args(p, Q, l_map, Kc_l, Qc, sel, Zl), Kl, l_len, &fa, stream);
   // the fold / promote workgroups ride in the pooling launch, whose workgroups have the same size and no LDS (in the logits
   // launch, whose workgroups take 36 to 145 KiB each, they would wait for places: 33.0 us for the call against 30.1, measured

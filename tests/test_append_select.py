@@ -75,14 +75,17 @@ def test_when_an_append_is_not_carried(cache, monkeypatch, why):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("d,b,nqb,tail,w", [(64, 64, 1, 1, 0), (64, 64, 4, 33, 4), (64, 64, 12, 64, 2), (64, 64, 13, 5, 1), (64, 128, 5, 127, 1),
+@pytest.mark.parametrize("case", [(64, 64, 1, 1, 0), (64, 64, 4, 33, 4), (64, 64, 12, 64, 2), (64, 64, 13, 5, 1), (64, 128, 5, 127, 1),
                                             (128, 64, 12, 9, 3), (128, 64, 3, 64, 41), (128, 64, 3, 2, 42), (128, 128, 4, 65, 2),
-                                            (128, 128, 5, 128, 2)])
-def test_a_carried_append_leaves_what_the_two_calls_do(d, b, nqb, tail, w):
-    """On either side of what one launch takes (12 blocks, 256 KiB, 128 local blocks): every bit of the ring, the pooled keys and
-    queries, the block sets and the logits; inputs token-major as a model has them."""
-    dev, heads, nq = "cuda:0", 3, (nqb - 1) * b + tail
-    print(f"[case] carried append d={d} B={b} {nqb} blocks, last {tail}, window {w}", flush=True)
+                                            (128, 128, 5, 128, 2), (64, 64, 1, 1, 0, 128), (64, 64, 1, 1, 0, 129), (64, 128, 12, 128, 1, 21),
+                                            (64, 128, 12, 128, 1, 22)])
+def test_a_carried_append_leaves_what_the_two_calls_do(case):
+    """On either side of what one launch takes (12 blocks, 128 local blocks, 128 KiB and 128 workgroups, with whole blocks 256 KiB and
+    64): every bit of the ring, the pooled keys and queries, the block sets and the logits; inputs token-major as a model
+    has them."""
+    (d, b, nqb, tail, w), heads = case[:5], case[5] if len(case) > 5 else 3
+    dev, nq = "cuda:0", (nqb - 1) * b + tail
+    print(f"[case] carried append H={heads} d={d} B={b} {nqb} blocks, last {tail}, window {w}", flush=True)
     one, two = (PbsaCache(heads, d, b, nq, w, 1, 4, np.float32(1 / math.sqrt(d)), device=dev) for _ in range(2))
     gen = torch.Generator(device=dev).manual_seed(d + nq)
     for c in (one, two):
