@@ -93,22 +93,19 @@ struct PoolJob {
   long pitch;
   int len;
   float* dst;
-  bool query;               // else the tokens are D elements apart
 };
-// jobs [0, H*nk) of mode 1 pool local key blocks, the rest pool the chunk's query blocks; false: there is no such block
+// jobs [0, H*nk) of mode 1 pool local key blocks, the rest pool the chunk's query blocks
+__device__ __forceinline__ bool pool_is_query(const PoolArgs& a, const int job) { return a.mode == 1 && job >= a.H * a.n_kjobs_per_head; }
 template <int D>
-__device__ __forceinline__ bool pool_job(const PoolArgs& a, const int job, PoolJob& j) {
+__device__ __forceinline__ PoolJob pool_query_job(const PoolArgs& a, const int job) {
+  const int jq = job - a.H * a.n_kjobs_per_head, h = jq / a.nqb, i = jq % a.nqb;
+  return {a.Q + (size_t)h * a.q_stride_h + (size_t)i * a.B * a.q_stride_t, (long)a.q_stride_t, min(a.B, a.Nq - i * a.B),
+          a.Qc + ((size_t)h * a.nqb + i) * D};
+}
+// false: there is no such block
+template <int D>
+__device__ __forceinline__ bool pool_key_job(const PoolArgs& a, const int job, PoolJob& j) {
   const int nk = a.n_kjobs_per_head;
-  j.query = a.mode == 1 && job >= a.H * nk;
-  if (j.query) {
-    const int jq = job - a.H * nk;
-    const int h = jq / a.nqb, i = jq % a.nqb;
-    j.len = min(a.B, a.Nq - i * a.B);
-    j.dst = a.Qc + ((size_t)h * a.nqb + i) * D;
-    j.src = a.Q + (size_t)h * a.q_stride_h + (size_t)i * a.B * a.q_stride_t;
-    j.pitch = a.q_stride_t;
-    return true;
-  }
   if (a.mode == 0) {
     j.src = a.X + (size_t)job * a.B * D;
     j.len = a.len[job];
@@ -133,10 +130,14 @@ __device__ __forceinline__ void pool_body(const PoolArgs& a, const int bx) {
   const int c = threadIdx.x % TPJ;
   if (job >= a.n_jobs) return;
   PoolJob j;
-  if (!pool_job<D>(a, job, j)) return;
   float acc0 = 0.0f, acc1 = 0.0f;
-  if (j.query) pool_block(j.src + 2 * c, j.pitch, j.len, acc0, acc1);
-  else pool_block(j.src + 2 * c, std::integral_constant<long, D>{}, j.len, acc0, acc1);
+  if (pool_is_query(a, job)) {             // (a branch with all of its work in it: 2 to 4 % of the launch against one for the place, one for the sum)
+    j = pool_query_job<D>(a, job);
+    pool_block(j.src + 2 * c, j.pitch, j.len, acc0, acc1);
+  } else {
+    if (!pool_key_job<D>(a, job, j)) return;
+    pool_block(j.src + 2 * c, std::integral_constant<long, D>{}, j.len, acc0, acc1);
+  }
   const float fl = (float)j.len;
   float2 o;
   o.x = j.len > 0 ? acc0 / fl : 0.0f;
@@ -172,7 +173,8 @@ __global__ void __launch_bounds__(kThreads) pool_tile_kernel(PoolArgs a) {
   constexpr int CPR = D / 8, RPS = kThreads / CPR, NS = BT / RPS;     // chunks per row, rows per sweep, sweeps
   __shared__ __align__(16) uint4 tile[BT * CPR];
   PoolJob j;
-  if (!pool_job<D>(a, blockIdx.x, j)) return;                         // (all of the workgroup)
+  if (pool_is_query(a, blockIdx.x)) j = pool_query_job<D>(a, blockIdx.x);
+  else if (!pool_key_job<D>(a, blockIdx.x, j)) return;                // (all of the workgroup)
   if (j.len > 0) {
     const int r0 = threadIdx.x / CPR, c = threadIdx.x % CPR;
     f32x4 v[NS];                                                      // (as uint4 they go through scratch memory)
@@ -185,14 +187,22 @@ __global__ void __launch_bounds__(kThreads) pool_tile_kernel(PoolArgs a) {
   if (threadIdx.x < D / 2) pool_tile<D>(tile, j.len, j.dst);
 }
 
-// Up to four blocks to a compute unit by tiles: pooling and selection of a chunk, us, by threads -> by tiles, 12 heads x 37 blocks of
-// 128 x 128 12.3 -> 11.1, 8 x 20 10.0 -> 8.7, 2 x 16 9.7 -> 8.1, 6 x 40 of 128 x 64 11.5 -> 9.7, 3 x 24 of 64 x 64 7.65 -> 7.15.  Beyond,
-// the workgroups, of four waves and up to 32 KiB of LDS, come in rounds: 12 x 74 of 64 x 128 14.5 -> 15.0, 12 x 74 of 64 x 64
-// 10.3 -> 10.4, 16 x 42 of 128 x 128 13.5 -> 15.6.
+// By tiles as long as the blocks find places side by side, four to a compute unit at most, and by threads beyond; sooner where
+// all blocks are whole, whose loops over the rows have no test in them by threads, and at d = 128, where a wave of those is
+// a block of its own.  Pooling and selection of a chunk, us, by threads -> by tiles, heads x blocks (as many older and newer):
+//   not whole: 8 x 32 of 64 x 64 8.7 -> 8.4, 16 x 32 8.7 -> 8.4, 8 x 32 of 64 x 128 10.5 -> 8.9, 16 x 32 10.5 -> 9.2, 8 x 32 of 128 x 128
+//   10.9 -> 9.9, 12 x 32 11.2 -> 10.5, 8 x 16 of 128 x 64 8.9 -> 8.9; 16 x 16 of 128 x 64 9.1 | 9.1, 28 x 16 9.1 | 9.5, 32 x 16 9.2 | 9.7;
+//   whole: 8 x 32 of 64 x 64 8.1 -> 7.9, 12 x 32 8.2 -> 8.1, 16 x 32 8.3 | 8.3, 12 x 32 of 64 x 128 8.9 | 8.9, 16 x 32 9.0 | 9.2, 4 x 16 of
+//   128 x 64 8.4 -> 8.3, 12 x 16 8.5 | 9.0, 24 x 16 8.8 | 9.4, 4 x 16 of 128 x 128 9.2 -> 9.0, 8 x 16 9.2 | 9.4, 20 x 16 9.6 | 10.3.
+static int pool_tile_jobs(const PoolArgs& a, int d) {
+  const bool whole = a.mode == 0 || a.Nq % a.B == 0;       // (mode 0 has its lengths on the device: whole as a rule)
+  if (d == 64) return whole ? 768 : 1024;
+  return whole ? 128 : a.B == 64 ? 512 : 1024;
+}
 template <int D>
 static hipError_t launch_pool(const PoolArgs& a, hipStream_t stream) {
   const dim3 block(kThreads);
-  if (a.n_jobs > 1024) {
+  if (a.n_jobs > pool_tile_jobs(a, D)) {
     constexpr int jpw = kThreads / (D / 2);
     hipLaunchKernelGGL(pool_kernel<D>, dim3((a.n_jobs + jpw - 1) / jpw), block, 0, stream, a);
   } else if (a.B == 128) {

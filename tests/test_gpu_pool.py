@@ -1,5 +1,5 @@
-"""Pooling by tiles (up to 1024 blocks in a launch) and by threads (more), bit for bit against additions in the pinned order: the
-largest launch of the one and the smallest of the other, lengths of none, one, around a sweep's rows, whole and beyond."""
+"""Pooling by tiles (up to 768 blocks in a launch at d = 64, 128 at d = 128) and by threads (more), bit for bit against additions in
+the pinned order: the largest launch of the one and the smallest of the other, lengths of none, one, around a sweep's rows, whole and beyond."""
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -8,7 +8,7 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-@pytest.mark.parametrize("n", [1, 1024, 1025])
+@pytest.mark.parametrize("n", [1, 128, 129, 768, 769, 1024, 1025])
 @pytest.mark.parametrize("d,B", [(64, 64), (64, 128), (128, 64), (128, 128)])
 def test_pooling_every_bit(d, B, n):
     from paper_2604_21221_amd import pbsa
@@ -27,3 +27,31 @@ def test_pooling_every_bit(d, B, n):
     got = out.cpu()
     assert torch.equal(torch.isnan(got), torch.isnan(want))
     assert torch.equal(got.nan_to_num(0.5).view(torch.int32), want.nan_to_num(0.5).view(torch.int32))
+
+
+@pytest.mark.parametrize("d,B,blocks,heads,tail", [
+    (64, 64, 16, (24, 25), 64),              # whole blocks: 768 in the launch, 800
+    (64, 128, 16, (32, 33), 77),             # a last one that is not: 1024, 1056
+    (128, 64, 16, (4, 5), 64),               # 128, 160
+    (128, 64, 16, (16, 17), 3),              # 512, 544
+    (128, 128, 16, (32, 33), 1),             # 1024, 1056
+])
+def test_pooling_for_a_selection(d, B, blocks, heads, tail):
+    """A chunk's keys and queries on either side of each line of the selection's pooling launch: as the append pools them."""
+    import numpy as np
+    from paper_2604_21221_amd.cache import PbsaCache
+    for H in heads:
+        print(f"[case] pooling launch d={d} B={B} {H} heads x {blocks}, last {tail}", flush=True)
+        nq = (blocks - 1) * B + tail
+        one, two = (PbsaCache(H, d, B, nq, 0, 1, 2, np.float32(d ** -0.5), device=DEV) for _ in range(2))
+        gen = torch.Generator(device=DEV).manual_seed(d + nq)
+        q, k, v = (torch.randn(nq, H, d, generator=gen, device=DEV).to(torch.bfloat16).transpose(0, 1) for _ in range(3))
+        one.append_chunk(k, v, 0)
+        one.select(q)
+        two._write_chunk(0, k, v, True, True, q)
+        two.append_chunk(k, v, 0)
+        if H * blocks > 400:                 # its append leaves the queries to the selection
+            two.stale_from = two.n_loc
+            two.select(q)
+        for name in ("Kc_l", "Qc"):
+            assert torch.equal(getattr(one, name).view(torch.int32), getattr(two, name).view(torch.int32)), name
