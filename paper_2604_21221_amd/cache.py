@@ -18,6 +18,10 @@ from . import pbsa
 _KEYS, _KEYS_AND_QUERIES = 1, 2              # what an append pooled
 
 
+class _Carried(tuple):
+    """K, V and id of a chunk whose append the selection takes along: nothing of it is launched or declared yet."""
+
+
 class PbsaCache:
     def __init__(self, H, d, B, Nq, window_chunks, C, k, scale, n_sink=0, causal=1, fold=True, device="cuda:0",
                  pass_logits=True, ring_chunks=None):
@@ -180,10 +184,17 @@ class PbsaCache:
         """append_chunk; pool: the pooled keys are taken as the rows pass, for a selection that follows at once (whoever
         appends by themselves may still change the rows in the ring, and the selection pools what it finds there), and with
         Q, where that is of use, the queries are pooled along.
-        Returns whether they were: nothing, _KEYS, or _KEYS_AND_QUERIES."""
+        Returns whether they were: nothing, _KEYS, or _KEYS_AND_QUERIES -- or the append itself (_Carried), which _select()
+        then makes, where it would pool the queries along and nothing older is stale."""
         if K is None or V is None:
             raise TypeError("append_chunk takes K and V (adopt_chunk declares a chunk that is in the ring already)")
         assert len(self.chunk_pos) <= self.w, "update() slides the window before the next append"
+        if (pool and Q is not None and self.stale_from >= self.n_loc and self._append_pools_queries() and self._by_launch
+                and self._in_place(K, V, Q)):
+            return _Carried((K, V, chunk_id))
+        return self._append_now(K, V, chunk_id, pool, Q)
+
+    def _append_now(self, K, V, chunk_id, pool, Q):
         pos = self.n_appended % self.ring
         pooled = self._write_chunk(pos, K, V, True, pool, Q)    # may refuse them: the chunk counts once it is there
         self._declare(pos, chunk_id)
@@ -196,28 +207,24 @@ class PbsaCache:
         self.stale_from = min(self.stale_from, self.n_loc - self.nqb)
 
     def _append_select(self, Q, K, V, chunk_id):
-        """How a step begins: append_chunk, then select(Q).  As one call where the append pools the queries along and nothing
-        older is stale.  What that call refuses the two decide, each for itself: a chunk counts once its append went
-        through."""
-        if (K is not None and V is not None and len(self.chunk_pos) <= self.w and self.stale_from >= self.n_loc
-                and self._append_pools_queries() and self._by_launch and self._in_place(K, V, Q)):
-            torch.autograd.graph.increment_version([self.Kl, self.Vl])       # as in _write_chunk
-            pos, stale_from = self.n_appended % self.ring, self.stale_from
-            self._declare(pos, chunk_id)                         # the maps of the call have the chunk in them
-            try:
-                l_map, _, _ = self._device_maps()
-                pbsa.pbsa_append_select(self.params(pool_from=self.n_loc, Q=Q), K, V, pos * self.nqb, True, Q, self.Kl, self.Vl,
-                                        l_map, self.Kc_l, self.Qc, self.sel, self.Zl)
-                self.stale_from = self.n_loc
-                return self.sel
-            except BaseException as e:
-                self.chunk_pos.pop()
-                self.chunk_ids.pop()
-                self.n_appended -= 1
-                self.stale_from = stale_from
-                if not isinstance(e, Exception):
-                    raise
-        return self._select(Q, self._append(K, V, chunk_id, True, Q))
+        """_append and _select as one call.  False: it was refused, and the cache stands where it stood."""
+        torch.autograd.graph.increment_version([self.Kl, self.Vl])       # as in _write_chunk
+        pos, stale_from = self.n_appended % self.ring, self.stale_from
+        self._declare(pos, chunk_id)                             # the maps of the call have the chunk in them
+        try:
+            l_map, _, _ = self._device_maps()
+            pbsa.pbsa_append_select(self.params(pool_from=self.n_loc, Q=Q), K, V, pos * self.nqb, True, Q, self.Kl, self.Vl,
+                                    l_map, self.Kc_l, self.Qc, self.sel, self.Zl)
+        except BaseException as e:
+            self.chunk_pos.pop()
+            self.chunk_ids.pop()
+            self.n_appended -= 1
+            self.stale_from = stale_from
+            if not isinstance(e, Exception):
+                raise
+            return False
+        self.stale_from = self.n_loc
+        return True
 
     def _append_pools_queries(self):
         # Up to 400 blocks the launch pools the queries for less than the selection takes to (step without -> with them,
@@ -290,7 +297,13 @@ class PbsaCache:
         return self._select(Q, False)
 
     def _select(self, Q, pooled):
-        """select; pooled: what of the newest chunk has just been pooled (_append); anything older that is stale has not."""
+        """select; pooled: what of the newest chunk has just been pooled (_append); anything older that is stale has not.  A
+        carried append that is refused is made as two calls, which decide each for itself: a chunk counts once its append
+        went through, whatever becomes of the selection."""
+        if isinstance(pooled, _Carried):
+            if self._append_select(Q, *pooled):
+                return self.sel
+            pooled = self._append_now(*pooled, True, Q)
         l_map, l_len, _ = self._device_maps()
         fresh = pooled and self.stale_from == self.n_loc - self.nqb
         p = self.params(pool_from=self.n_loc if fresh else self.stale_from, Q=Q)
@@ -400,7 +413,7 @@ class PbsaCache:
 
     def step_fine(self, Q, K, V, chunk_id, O=None, lse=None):
         """The step with the fine-mass score: append, select, attend (recording the mass), update."""
-        self._append_select(Q, K, V, chunk_id)
+        self._select(Q, self._append(K, V, chunk_id, True, Q))
         O, Mt = self.attention_with_mass(Q, O, lse)
         self.update_fine(Mt)
         return O
@@ -463,7 +476,7 @@ class PbsaCache:
     def step_fused(self, Q, K=None, V=None, chunk_id=None, O=None, lse=None):
         """The step as two launches after the selection: attention with the update's decisions, then fold /
         promote.  K = V = None: the chunk has been adopted already."""
-        self._select(Q, 0) if K is None else self._append_select(Q, K, V, chunk_id)
+        self._select(Q, K is not None and self._append(K, V, chunk_id, True, Q))
         O = self.attention_with_plan(Q, O, lse)
         self.update_apply()
         return O
@@ -491,7 +504,7 @@ class PbsaCache:
     def step_chained(self, Q, K=None, V=None, chunk_id=None, O=None, lse=None):
         """Two library calls per step: selection (carrying the previous step's fold / promote), attention (carrying
         this step's decisions).  flush() after the last step.  K = V = None: the chunk has been adopted already."""
-        self._select(Q, 0) if K is None else self._append_select(Q, K, V, chunk_id)
+        self._select(Q, K is not None and self._append(K, V, chunk_id, True, Q))
         O = self.attention_with_plan(Q, O, lse)
         self.defer_apply()
         return O
@@ -501,7 +514,7 @@ class PbsaCache:
         leaves its logits and the update maintains the slots, the update's decisions ride in the attention launch
         (step_fused, the same results bit for bit): four launches instead of six, 202.6 -> 189.4 us at 12 x 4680 x 128
         with 16 slots, 57 -> 49 us for two heads of 256 tokens."""
-        self._append_select(Q, K, V, chunk_id)
+        self._select(Q, self._append(K, V, chunk_id, True, Q))
         if self.Zl is not None and self.C <= pbsa.PBSA_MAX_C:
             O = self.attention_with_plan(Q, O, lse)
             self.update_apply()

@@ -42,7 +42,7 @@ def test_attention_shares_no_scratch(cache, monkeypatch):
             assert not any(overlap(w, t) for w in ws), name
 
 
-CALLS = ("pbsa_append_chunk", "pbsa_append_select", "pbsa_select_blocks", "pbsa_pool_blocks", "pbsa_attention_fwd", "pbsa_attention_fwd_split",
+CALLS = ("pbsa_append_chunk", "pbsa_select_blocks", "pbsa_pool_blocks", "pbsa_attention_fwd", "pbsa_attention_fwd_split",
          "pbsa_attention_fwd_plan_split", "pbsa_attention_fwd_mass_split", "pbsa_attention_fwd_plan",
          "pbsa_attention_fwd_mass", "pbsa_attention_bwd", "pbsa_memory_update", "pbsa_memory_update_apply",
          "pbsa_memory_update_fine")
@@ -78,9 +78,8 @@ def test_append_refuses_a_missing_tensor(cache, monkeypatch, call, missing):
 def test_step_is_append_select_attention_update(cache, monkeypatch):
     calls = record(monkeypatch)
     cache.step(chunk(0), chunk(1), chunk(2), 0)
-    assert [n for n, _ in calls] == ["pbsa_append_select", "pbsa_attention_fwd_plan", "pbsa_memory_update_apply"]
+    assert [n for n, _ in calls] == ["pbsa_append_chunk", "pbsa_select_blocks", "pbsa_attention_fwd_plan", "pbsa_memory_update_apply"]
     cache.Zl = None                          # without the logits the decisions are taken behind the attention
-    cache.stale_from = 0                     # and with an older block stale the selection is a call of its own
     del calls[:]
     cache.step(chunk(0), chunk(1), chunk(2), 1)
     assert [n for n, _ in calls] == ["pbsa_append_chunk", "pbsa_select_blocks", "pbsa_attention_fwd_split", "pbsa_memory_update"]
@@ -98,22 +97,14 @@ def test_a_failed_append_declares_nothing(cache, monkeypatch, call, why):
     bad = torch.zeros(H, NQ + 1, D, dtype=torch.bfloat16)
     args = [] if call == "append_chunk" else [chunk(5)]
 
-    refused = []
-
-    def refuse(name):
-        def f(*a, **k):
-            refused.append(name)
-            raise pbsa.PbsaError(pbsa.PBSA_EINVAL)
-        return f
+    def refuse(*a):
+        raise pbsa.PbsaError(pbsa.PBSA_EINVAL)
 
     with monkeypatch.context() as m:
         if why == "library":
-            for name in ("pbsa_append_chunk", "pbsa_append_select"):
-                m.setattr(pbsa, name, refuse(name))
-        with pytest.raises(pbsa.PbsaError if why == "library" else Exception):
+            m.setattr(pbsa, "pbsa_append_chunk", refuse)
+        with pytest.raises(Exception):
             getattr(cache, call)(*args, bad if why == "K" else chunk(2), bad if why == "V" else chunk(3), 1)
-    if why == "library":                     # a step asks for both in one call first
-        assert refused == ["pbsa_append_select"] * bool(args) + ["pbsa_append_chunk"]
     assert books(cache) == before
     del calls[:]
     cache.append_chunk(chunk(2), chunk(3), 1)
@@ -129,8 +120,8 @@ def test_who_pools_the_newest_chunk(cache, monkeypatch):
     nqb = cache.nqb
 
     def pooling():                           # by the append; from which block by the selection; of how many
-        kc = [n == "pbsa_append_select" or a[7] is not None for n, a in calls if n.startswith("pbsa_append")]
-        sel = [(a[0].pool_from, a[0].n_loc) for n, a in calls if n in ("pbsa_append_select", "pbsa_select_blocks")]
+        kc = [a[7] is not None for n, a in calls if n == "pbsa_append_chunk"]
+        sel = [(a[0].pool_from, a[0].n_loc) for n, a in calls if n == "pbsa_select_blocks"]
         del calls[:]
         return kc, sel
 
@@ -152,8 +143,7 @@ def test_who_pools_the_newest_chunk(cache, monkeypatch):
     assert pooling() == ([True], [(0, 2 * nqb)])
     # a step that ends between the two leaves nothing behind for the selection that follows
     with monkeypatch.context() as m:
-        for name in ("pbsa_append_select", "pbsa_select_blocks"):
-            m.setattr(pbsa, name, lambda *a, **k: 1 / 0)
+        m.setattr(pbsa, "pbsa_select_blocks", lambda *a, **k: 1 / 0)
         with pytest.raises(ZeroDivisionError):
             cache.step(chunk(0), chunk(1), chunk(2), 5)
     cache.select(chunk(2))
@@ -347,12 +337,9 @@ def test_who_pools_the_queries(cache, monkeypatch):
     def steps(Q):
         del asked[:]
         cache.step(Q, chunk(1), chunk(2), cache.n_appended)
-        return "as one call" if asked[0][0] == "pbsa_append_select" else (asked[0][1], asked[1][2])
+        return asked[0][1], asked[1][2]
 
-    assert steps(chunk(0)) == "as one call"
-    with monkeypatch.context() as m:         # where that is refused, by two
-        m.setattr(pbsa, "pbsa_append_select", lambda *a, **k: 1 / 0)
-        assert steps(chunk(0)) == (True, True)
+    assert steps(chunk(0)) == (True, True)
     assert steps(torch.zeros(H, NQ, D + 1, dtype=torch.bfloat16)[:, :, 1:]) == (False, False)       # rows that are not aligned
     assert steps(chunk(0).requires_grad_()) == (False, False)
     cache.stale_from = 0                     # an older block is stale: the selection pools, the queries too

@@ -99,19 +99,49 @@ def test_queries_pooled_with_the_append(gpu, case):  # noqa: F811
 
 
 @pytest.mark.parametrize("case", [(64, 64, 1, 1, 0), (64, 64, 12, 9, 4), (64, 64, 13, 64, 2), (64, 128, 5, 65, 3), (128, 64, 12, 64, 1),
-                                  (128, 64, 5, 3, 31), (128, 128, 4, 127, 4), (128, 128, 5, 128, 1), (64, 128, 4, 1, 2), (128, 64, 8, 64, 1),
-                                  (128, 64, 9, 64, 1), (128, 128, 4, 128, 2), (64, 64, 1, 64, 1, 51), (64, 64, 1, 64, 1, 52),
-                                  (64, 64, 1, 5, 1, 128), (64, 64, 1, 5, 1, 129), (64, 64, 1, 5, 1, 256), (64, 64, 1, 5, 1, 257),
-                                  (64, 128, 12, 128, 1, 21), (64, 128, 12, 128, 1, 22)],
-                         ids=lambda c: "d%d_B%d_%d_blocks_last%d_w%d" % c[:5] + ("_%d_heads" % c[5] if len(c) > 5 else ""))
+                                  (128, 64, 5, 3, 31), (128, 128, 4, 127, 4), (128, 128, 5, 128, 1)],
+                         ids=lambda c: "d%d_B%d_%d_blocks_last%d_w%d" % c)
 def test_keys_pooled_by_the_selection(gpu, case):  # noqa: F811
+    """A chunk whose stale keys the selection pools itself (up to 12 blocks and 256 KiB with the queries; 13 and more are pooled by
+    a launch ahead), in a chained step with the update before it in the same launch, and after rewriting: every bit of what
+    a step with everything pooled by its append leaves."""
+    d, B, nqb, tail, w = case
+    H, Nq, scale = 3, (nqb - 1) * B + tail, np.float32(1.0 / math.sqrt(d))
+    one = gpu["cache"].PbsaCache(H, d, B, Nq, w, 3, 4, scale, device=DEV)
+    two = gpu["cache"].PbsaCache(H, d, B, Nq, w, 3, 4, scale, device=DEV, ring_chunks=w + 2)
+    for g in range(w + 3):
+        Q, K, V = (gpu["wl"].bf16_tensor(rnd(950 + 3 * g + i, Nq, H, d), DEV).transpose(0, 1) for i in range(3))
+        one.step(Q, K, V, g)
+        two.append_chunk(V, K, g)            # as it was before a denoising pass
+        if two._pending is None:
+            two.select(K)
+        two.rewrite_chunk(K, V)
+        two.select(Q)
+        two.attention_with_plan(Q)
+        two.defer_apply()
+        n = H * nqb * (len(one.chunk_pos) + (one.n_appended > w)) * nqb
+        for name in ("Qc", "sel", "slot_src", "scores", "Kc_p", "S_cnt"):
+            a, b = (getattr(c, name).cpu().numpy() for c in (one, two))
+            assert np.array_equal(a.view(np.uint32), b.view(np.uint32)), f"chunk {g}: {name}"
+        a, b = (c.Zl.view(-1)[:n].cpu().numpy().view(np.uint32) for c in (one, two))
+        assert np.array_equal(a, b), f"chunk {g}: logits"
+    two.flush()
+    for name in ("Kp", "Vp", "p_len", "S_sum"):
+        a, b = (getattr(c, name).cpu() for c in (one, two))
+        assert torch.equal(a, b), name
+
+
+@pytest.mark.parametrize("case", [(64, 128, 4, 1, 2, 3), (128, 64, 8, 64, 1, 3), (128, 64, 9, 64, 1, 3), (128, 128, 4, 128, 2, 3),
+                                  (64, 64, 1, 64, 1, 51), (64, 64, 1, 64, 1, 52), (64, 64, 1, 5, 1, 128), (64, 64, 1, 5, 1, 129),
+                                  (64, 64, 1, 5, 1, 256), (64, 64, 1, 5, 1, 257), (64, 128, 12, 128, 1, 21), (64, 128, 12, 128, 1, 22)],
+                         ids=lambda c: "d%d_B%d_%d_blocks_last%d_w%d_%d_heads" % c)
+def test_keys_pooled_on_either_side_of_a_line(gpu, case):  # noqa: F811
     """A chunk whose stale keys the selection pools itself or a launch ahead of it -- up to 12 blocks, 128 KiB and 256 workgroups
     (128 with an append) or, of whole blocks, 256 KiB and 64; with the fold of the update before it in the same launch, a
     chained step, 256 KiB and 256 workgroups with those of the fold -- on either side of each line, and after rewriting:
     every bit of what a step with everything pooled by its append leaves."""
-    case, heads = case[:5], case[5] if len(case) > 5 else 3
-    d, B, nqb, tail, w = case
-    H, Nq, scale = heads, (nqb - 1) * B + tail, np.float32(1.0 / math.sqrt(d))
+    d, B, nqb, tail, w, H = case
+    Nq, scale = (nqb - 1) * B + tail, np.float32(1.0 / math.sqrt(d))
     one = gpu["cache"].PbsaCache(H, d, B, Nq, w, 3, 4, scale, device=DEV)
     two = gpu["cache"].PbsaCache(H, d, B, Nq, w, 3, 4, scale, device=DEV, ring_chunks=w + 2)
     for g in range(w + 3):
