@@ -164,7 +164,9 @@ int pbsa_select_pooled(const pbsa_params* p, const int32_t* l_map, const float* 
 
 /* pbsa_append_chunk_pool of a chunk (K, V and Q given) and pbsa_select_pooled of the same chunk as one call, which is one
  * launch where the chunk is small: the last nqb entries of l_map are slot0 .. slot0 + nqb - 1, the pooled keys of the other
- * blocks are in Kc_l, Q has p's strides, and pool_from is not looked at.  The same block sets and logits, bit for bit. */
+ * blocks are in Kc_l, Q has p's strides, and pool_from is not looked at.  K, V and Q do not overlap what the call writes (the
+ * chunk's slots of Kl and Vl above all: the launch reads K for the pooled keys while it copies).  The same block sets and
+ * logits, bit for bit.  After an error of the arguments nothing has been written. */
 int pbsa_append_select(const pbsa_params* p, const void* K, const void* V, int64_t k_stride_h, int64_t k_stride_t,
                        int64_t v_stride_h, int64_t v_stride_t, int32_t slot0, int32_t zero_tail, const void* Q, void* Kl, void* Vl,
                        const int32_t* l_map, float* Kc_l, float* Qc, int32_t* sel, float* Zl, void* hip_stream);

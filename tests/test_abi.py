@@ -314,6 +314,26 @@ def test_pooled_append_and_selection_argument_checks(L):
         assert select(**kw) == code, kw
 
 
+def test_append_select_argument_checks(L):
+    """pbsa_append_select checks what pbsa_append_chunk_pool and pbsa_select_pooled check, K, V and Q alike."""
+    dense = (200 * 128, 128)
+
+    def call(p=None, K=P, V=P, ks=dense, vs=dense, slot0=0, Q=P, Kl=P, Vl=P, l_map=P, Kc_l=P, Qc=P, sel=P, Zl=P):
+        rc = L.pbsa_append_select(ctypes.byref(p or good()), K, V, *ks, *vs, slot0, 1, Q, Kl, Vl, l_map, Kc_l, Qc, sel, Zl, None)
+        assert rc != pbsa.PBSA_OK
+        return rc
+
+    wrong = [(dict(slot0=n), pbsa.PBSA_EINVAL) for n in (-1, 13, 2 ** 31 - 1, -2 ** 31)]       # 4 blocks per chunk, 16 slots
+    wrong += [({n: None}, pbsa.PBSA_EINVAL) for n in ("K", "V", "Q", "Kl", "Vl", "l_map", "Kc_l", "Qc", "sel")]
+    wrong += [({n: P + 8}, pbsa.PBSA_EALIGN) for n in ("K", "V", "Q", "Kl", "Vl", "Kc_l", "Qc")]
+    for strides, code in (((200 * 128, 120), pbsa.PBSA_EINVAL), ((-128, 128), pbsa.PBSA_EINVAL), ((200 * 132, 132), pbsa.PBSA_EALIGN),
+                          ((200 * 128 + 4, 128), pbsa.PBSA_EALIGN)):
+        wrong += [(dict(ks=strides), code), (dict(vs=strides), code), (dict(p=good(q_strides=strides)), code)]
+    wrong += [(dict(p=good(d=96)), pbsa.PBSA_ESHAPE), (dict(p=good(B=32)), pbsa.PBSA_ESHAPE), (dict(p=good(n_loc=2)), pbsa.PBSA_EINVAL)]
+    for kw, code in wrong:
+        assert call(**kw) == code, kw
+
+
 def test_split_attention_argument_checks(L):
     """pbsa_attention_fwd_split validates like pbsa_attention_fwd and wants pbsa_attention_workspace_bytes."""
     p = good(k=12)                           # 4 query tiles of 17 key tiles each: shared out
