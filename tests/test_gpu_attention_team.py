@@ -122,3 +122,60 @@ def test_a_block_named_twice_counts_once():
     once = c.attention(Q)
     c.sel[:, :, 0] = c.sel[:, :, 3]
     assert torch.equal(c.attention(Q), once) and not torch.equal(once, want)
+
+
+LONGEST = [                                  # 672 local blocks, one to a chunk, and 336 slots
+    (300, 64, 64, 64, 671, 336, 672, [64, 63]),   # teams of two, 505 tiles of 1009 to a wave
+    (257, 64, 128, 64, 671, 336, 672, [128, 65]),     # 1009 of 2018, all that a wave's list holds
+    (260, 128, 128, 1, 671, 336, 672, None),
+    (200, 64, 128, 40, 671, 336, 672, [128, 1]),  # teams of four, 505 of 2018
+    (100, 128, 128, 64, 671, 336, 672, None),     # two teams to a unit, 253 each
+    (10, 64, 128, 128, 671, 336, 672, [97]),      # twelve, 43
+    (4, 64, 64, 300, 133, 336, 672, [64, 40]),    # twelve, five units a head, the last of 44 rows
+    (1, 64, 64, 64, 671, 336, 672, None),         # sixteen, 16
+    (270, 64, 128, 64, 511, 192, 512, [128, 70]),     # recording the mass: the longest that the later pass takes, 705 to a wave
+]
+
+
+@pytest.mark.parametrize("H,d,B,Nq,w,C,k,lens", LONGEST)
+def test_team_with_the_longest_lists(H, d, B, Nq, w, C, k, lens):
+    test_team_matches_fp64(H, d, B, Nq, w, C, k, lens)
+
+
+def kernels(call):
+    """Names of the library's kernels that the call launches."""
+    from torch.profiler import ProfilerActivity, profile
+    call()
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        call()
+        torch.cuda.synchronize()
+    names = [e.name for e in p.events() if "pbsa::" in e.name]
+    if not names:
+        pytest.skip("the profiler sees no kernels here")
+    return names
+
+
+@pytest.mark.parametrize("H,d,B,Nq,w,C,k,waves,parts", [
+    (2, 64, 64, 65, 0, 1, 2, 4, 1), (3, 64, 128, 321, 1, 2, 3, 4, 1), (4, 128, 64, 256, 1, 3, 5, 4, 1),
+    (16, 64, 64, 1090, 1, 4, 6, 2, 1), (10, 128, 128, 3201, 1, 1, 2, 2, 1),
+    (1, 64, 64, 1000, 1, 64, 16, 4, 11), (1, 128, 128, 1990, 2, 16, 16, 4, 6),
+    (1, 64, 64, 10752, 3, 336, 672, 0, 6),   # by query tiles of 128 rows, in parts
+    (1, 128, 128, 2688, 31, 336, 672, 4, 6),
+    (1, 64, 64, 64, 0, 1, 0, 0, 1),          # two tiles
+    (9, 64, 64, 3700, 0, 2, 3, 0, 1),        # 522 units
+    *[(*c[:7], waves, parts) for c, waves, parts in zip(LONGEST, (2, 2, 2, 4, 4, 4, 4, 4, 2), (1, 1, 1, 1, 2, 12, 12, 16, 1))],
+])
+def test_which_kernel_runs(H, d, B, Nq, w, C, k, waves, parts):
+    """What the cases of this file are for is what they reach: teams of so many waves, several to a unit or not, or none."""
+    from paper_2604_21221_amd.cache import PbsaCache
+    print(f"[case] route H={H} d={d} B={B} Nq={Nq} C={C} k={k}", flush=True)
+    c = PbsaCache(H, d, B, Nq, w, C, k, d ** -0.5, fold=False, device=DEV)
+    for g in range(w + 1):
+        c.adopt_chunk(g)
+    c._installed = C                         # as by set_persistent(): empty slots all the same
+    Q = torch.zeros(H, Nq, d, dtype=torch.bfloat16, device=DEV)
+    names = kernels(lambda: c.attention(Q))
+    want = f"attention_team_kernel<{d}, {waves}, false, false>" if waves else f"attention_kernel<{d}, {B}, false, false, {str(parts > 1).lower()}>"
+    assert want in names[0] and len(names) == 1 + (parts > 1), names
+    assert parts == 1 or "combine_kernel" in names[1]

@@ -36,3 +36,19 @@ def test_backward_two_waves_and_four(gpu, case):  # noqa: F811
         if g < w:                            # nothing is evicted yet: both sides only close the chunk
             st.update()
             c.update()
+
+
+@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
+def test_which_backward_runs(gpu, case):  # noqa: F811
+    from tests.test_gpu_attention_team import kernels
+    name, H, d, B, Nq, w, C, k = case[:8]
+    print(f"[case] bwd route {name}", flush=True)
+    c = gpu["cache"].PbsaCache(H, d, B, Nq, w, C, k, d ** -0.5, causal=case[9], device="cuda:0")
+    for g in range(w + 1):
+        c.adopt_chunk(g)
+    Q = torch.zeros(H, Nq, d, dtype=torch.bfloat16, device="cuda:0")
+    c.select(Q)
+    lse = torch.zeros(H, Nq, device="cuda:0")
+    O = c.attention(Q, lse=lse)
+    names = kernels(lambda: c.attention_bwd(Q, O, Q, lse))
+    assert f", {4 if name.startswith('four') else 2}>" in next(n for n in names if "bwd_walk_kernel" in n), names
