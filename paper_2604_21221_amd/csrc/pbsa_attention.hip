@@ -720,8 +720,8 @@ static float walk_us(int d, int tiles, int waves) {
   return (float)tiles * (d == 128 ? 1.3f + 0.65f * load * load : 1.0f + 0.2f * load * load);
 }
 
-// By teams wherever they fit on the chip in one round -- 256 units of 64 rows in teams of four waves, 512 in teams of two --
-// and the list has a tile for more than one of them.  Against query tiles of 128 rows, whole or in the parts of attn_split
+// By teams wherever they fit on the chip in one round -- 256 units of 64 rows in teams of four waves, 512 in teams of two, the
+// workgroups that take decisions not counted -- and the list has a tile for more than one of them.  Against query tiles of 128 rows, whole or in the parts of attn_split
 // and with their second launch (us): 2 x 256 rows of 64 with 7 tiles 13.4 in a step -> 11.4; 5 x 1000 x 64, 26 tiles
 // 19.4 -> 12.5; 14 x 245 x 128, 16 tiles 20.8 -> 13.3; 11 x 1336 x 64, 54 tiles 31.1 -> 22.1; 8 x 2000 x 128, 92 tiles
 // 58.1 -> 50.6; teams of two: 16 x 1100 x 64, 11 tiles 17.9 -> 12.2, 12 x 1800 x 128, 38 tiles 41.0 -> 35.9.  One tile
@@ -740,7 +740,6 @@ AttnTeam attn_team(const pbsa_params& p, bool scratch) {
   if (sp.parts > 1 && !scratch) return team;
   team.units = (int)units;
   team.waves = units > 256 ? 2 : 4;
-  if (sp.parts == 1) return team;
   constexpr float kPartsUs = 3.0f;
   const float own_tiles = p.d == 128 ? 1.09f : 1.05f;
   auto team_us = [&](int parts) {
@@ -748,6 +747,21 @@ AttnTeam attn_team(const pbsa_params& p, bool scratch) {
     return own_tiles * walk_us(p.d, (tiles + n - 1) / n, (int)units * n) + (parts > 1 ? kCombineUs : 0.0f);
   };
   float best = team_us(1);
+  // Not where the update's decisions, which ride as one more workgroup to a head and ahead of the units, leave as many of those
+  // without a place, short walks end before short decisions have, and query tiles would find places beside them: with
+  // decisions | attention alone, query tiles | teams: 28 x 539 x 64, 10 tiles 12.9 15.2 | 12.8 8.8; 130 x 170 x 64, 10 14.2 17.1 | 14.5
+  // 11.2; 36 x 846 x 128, 10 18.8 23.7 | 19.2 16.4; 152 x 39 x 64, 5 9.9 13.0 | 9.8 7.4; 214 x 35 x 128, 3 9.4 15.6 | 9.3 8.9.  Longer
+  // lists gain more than that costs (91 x 104 x 64, 22 tiles 19.6 -> 18.6 | 19.6 -> 12.1; 128 x 209 x 128, 28 42.2 -> 40.3 | 42.4 -> 35.1), and
+  // decisions over more blocks end late by either way (5 x 3227 x 128, 8 tiles, 51 x 51 blocks 27.6 | 19.8).  All calls of a
+  // shape go one way, whether they take decisions along or not: their outputs agree bit for bit.
+  const int k = p.k < p.n_loc ? p.k : p.n_loc, decisions = p.nqb * (p.n_loc + p.C) <= 256 ? p.nqb * (p.n_loc + p.C) : 0;
+  if (sp.parts == 1 && p.C <= PBSA_MAX_C && units + p.H > 1024 / team.waves && n_wg + p.H <= 512 && decisions > 0) {
+    const float longer = (p.d == 128 ? 9.0f : 7.3f) + (float)decisions / (float)(64 * team.waves);    // by, beside the tiles
+    // (a query tile over two blocks of 64 has some that only one of them selected)
+    const float whole = (float)tiles + (p.B == 64 && p.Nq > 64 ? 0.5f * (float)std::min(k, p.n_loc - k) : 0.0f);
+    if (best + longer > whole * walk_us(p.d, 1, (int)n_wg * 2)) return AttnTeam{0, 1, 0};
+  }
+  if (sp.parts == 1) return team;
   for (int s = 2; s <= sp.parts && s * units <= 256; ++s) {          // (what s parts leave fits in the scratch for sp.parts)
     const float us = team_us(s);
     if (us < best - (team.parts == 1 ? kSplitWorthUs : 0.0f)) {

@@ -164,6 +164,13 @@ def kernels(call):
     (1, 128, 128, 2688, 31, 336, 672, 4, 6),
     (1, 64, 64, 64, 0, 1, 0, 0, 1),          # two tiles
     (9, 64, 64, 3700, 0, 2, 3, 0, 1),        # 522 units
+    (28, 64, 128, 539, 0, 2, 2, 0, 1),       # 252 units and 28 workgroups that take decisions, short lists
+    (25, 64, 128, 539, 0, 2, 2, 4, 1),       # 225 and 25
+    (28, 64, 128, 539, 0, 30, 2, 4, 1),      # long lists
+    (19, 64, 128, 781, 1, 2, 1, 0, 1),       # 7 x 16 pairs of a query block and a column
+    (15, 64, 128, 1075, 3, 2, 2, 4, 1),      # 9 x 38
+    (36, 128, 128, 846, 1, 3, 1, 0, 1),      # 504 units
+    (458, 128, 128, 5, 0, 1, 1, 2, 1),       # where query tiles would find no places either
     *[(*c[:7], waves, parts) for c, waves, parts in zip(LONGEST, (2, 2, 2, 4, 4, 4, 4, 4, 2), (1, 1, 1, 1, 2, 12, 12, 16, 1))],
 ])
 def test_which_kernel_runs(H, d, B, Nq, w, C, k, waves, parts):
@@ -179,3 +186,8 @@ def test_which_kernel_runs(H, d, B, Nq, w, C, k, waves, parts):
     want = f"attention_team_kernel<{d}, {waves}, false, false>" if waves else f"attention_kernel<{d}, {B}, false, false, {str(parts > 1).lower()}>"
     assert want in names[0] and len(names) == 1 + (parts > 1), names
     assert parts == 1 or "combine_kernel" in names[1]
+
+
+@pytest.mark.parametrize("H,d,B,Nq,w,C,k,lens", [(28, 64, 128, 539, 0, 2, 2, [128, 65]), (36, 128, 128, 846, 1, 3, 1, [127, 64, 0])])
+def test_where_decisions_keep_teams_away(H, d, B, Nq, w, C, k, lens):
+    test_team_matches_fp64(H, d, B, Nq, w, C, k, lens)
