@@ -1116,19 +1116,33 @@ static BwdWorkspace bwd_workspace(const pbsa_params& p) {
 }
 size_t bwd_workspace_bytes(const pbsa_params& p) { return bwd_workspace(p).bytes; }
 
-// When a launch whose workgroups have `waves` waves ends, in turns of 64 x 64 (about 1.4 us at d = 128, 1.0 at 64): with its longest
-// walk or when the places have taken all of them, and where the two are close a little later; a workgroup costs 6 us beside
-// its turns.  The factors are those of a fit to 121 shapes.
-static float walks_cost(const pbsa_params& p, int waves) {
+// Whether four waves to a walk end a launch sooner than two.  It ends with its longest walk or when the places have taken all
+// of them, and where the two are close a little later: microseconds of a workgroup beside its turns, of a turn (64 x 64) of dQ
+// and of dK / dV, of the places for what their turns take, and of the launch beside that, fitted to 800 shapes (of two waves within
+// 3 % at d = 64 and 5 % at 128, of four within 8 and 9).  Where the places set the end four waves are not only no better: the
+// longest walks then depend on which blocks the rows select, where they are many (24 row tiles), and that is not known here, so
+// past 1.2 times the longest walk it is two (all rows selecting the same blocks, 8 x 970 x 64 with 8 blocks 22 -> 30 us by four, 5 x 4729 x 64 with 15 + 36 87 -> 114).
+static bool four_waves_end_sooner(const pbsa_params& p) {
+  struct Fit {
+    float own, dq, dkv, places, launch;
+  };
+  static constexpr Fit kFit[2][2] = {{{7.7f, 1.24f, 0.77f, 1.13f, 1.3f}, {4.4f, 1.26f, 0.85f, 1.29f, 5.8f}},      // d = 64: two, four
+                                     {{5.8f, 1.87f, 1.11f, 1.55f, 6.3f}, {4.9f, 1.87f, 1.20f, 1.56f, 9.4f}}};     // 128
   const int sub = p.B / kTile, rows = (p.Nq + kTile - 1) / kTile, k = std::min(p.k, p.n_loc), tiles = p.H * rows;
-  const bool shared = waves == 4 || tiles <= 256;            // dq: the waves of a workgroup share a walk
-  const float own = p.d == 128 ? 4.3f : 6.0f, pairs = 0.5f * (float)waves;
-  const float dq = (float)((p.C + 1 + k) * sub) / (shared ? (float)waves : 1.0f), slot = (float)rows / pairs;
-  const float block = (float)rows * (float)k / (float)p.n_loc / pairs;
-  const float all = (float)(shared ? tiles : (tiles + 1) / 2) * (own + dq) + (float)(p.H * sub) * ((float)(p.C + 1) * (own + slot) + (float)p.n_loc * (own + block));
-  const float walk = own + std::max(dq, slot), taken = (waves == 2 ? 1.1f : p.d == 128 ? 1.4f : 1.0f) * all * (float)waves / 1024.0f + 1.0f;
-  const float w2 = walk * walk, t2 = taken * taken;
-  return std::sqrt(std::sqrt(w2 * w2 + t2 * t2));
+  float us[2], walk = 0.0f, taken = 0.0f;
+  for (int four = 0; four < 2; ++four) {
+    const Fit& f = kFit[p.d == 128][four];
+    const float waves = four ? 4.0f : 2.0f;
+    const bool shared = four || tiles <= 256;              // dq: the waves of a workgroup share a walk
+    const float dq = f.dq * (float)((p.C + 1 + k) * sub) / (shared ? waves : 1.0f), slot = f.dkv * (float)rows / (0.5f * waves);
+    const float block = slot * (float)k / (float)p.n_loc;
+    walk = f.own + std::max(dq, slot);
+    taken = f.places * waves / 1024.0f * ((float)(shared ? tiles : (tiles + 1) / 2) * (f.own + dq) +
+                                          (float)(p.H * sub) * ((float)(p.C + 1) * (f.own + slot) + (float)p.n_loc * (f.own + block)));
+    const float w2 = walk * walk, t2 = taken * taken;
+    us[four] = f.launch + std::sqrt(std::sqrt(w2 * w2 + t2 * t2));
+  }
+  return us[1] < 0.95f * us[0] && (rows < 24 || taken <= 1.2f * walk);
 }
 
 hipError_t launch_attention_bwd(const pbsa_params& p, const bf16_t* Q, const bf16_t* Kp, const bf16_t* Vp,
@@ -1169,15 +1183,16 @@ hipError_t launch_attention_bwd(const pbsa_params& p, const bf16_t* Q, const bf1
   }
   // Four waves share a walk where the longest walks set the launch's end, which come first and then end half as late: a
   // workgroup of four has a compute unit to itself, so a launch that the places set takes as long or, with more workgroups
-  // than units, longer.  walks_cost says which it is.  The backward by itself, two waves -> four, us, where it says four:
-  // 2 x 3689 x 128 with 58 row tiles and few slots 76 -> 51, 6 x 1000 x 128 with 17 + 20 blocks of 128 85 -> 65, 2 x 4234 x 64
-  // with 26 + 112 of 128 185 -> 161, 9 x 305 x 64 27 -> 20, 2 x 384 x 128 40 -> 29, 1 x 1681 x 64 56 -> 36; where it says two: 13 x 569
-  // x 64 34 | 40, 16 x 300 x 128 31 | 36, 3 x 4180 x 128 with 27 + 10 of 128 110 | 124, 12 x 1863 x 128 65 | 88.  6 x 4888
-  // x 128 119 | 143.  (Over 121 shapes, 85 of them drawn, no choice is slower than two waves by more than 1 %, and the choices
-  // are 0.5 % off the better ones on average.)  Up to 448 workgroups, from eight row tiles on, four as before there was a model (8 x 600
-  // x 64: 22.4 -> 20.9, which it does not see).
+  // than units, longer.  The backward by itself, two waves -> four, us, where it is four:
+  // 2 x 4866 x 128 with 8 + 2 blocks of 64 95 -> 64, 3 x 2582 x 64 with 2 + 6 of 128 41 -> 29, 4 x 125 x 128 with 57 + 1 of 128 117 -> 69,
+  // 5 x 408 x 128 with 5 + 6 of 128 32 -> 26, 1 x 344 x 64 with 16 + 3 of 64 20 -> 16, 13 x 333 x 128 with 43 + 6 of 64 62 -> 57; where it is two:
+  // 19 x 1424 x 64 with 15 + 8 of 128 96 | 125, 2 x 4258 x 128 with 22 + 23 of 128 104 to 113 | 112 to 123, 7 x 1899 x 64 with 2 + 9 of 64
+  // 34 | 35, and for what selections it may meet 3 x 2105 x 64 with 44 + 2 of 128 66 | 52 to 61.
+  // (Over 800 shapes, each with rows that select alike and not, one was slower by four, by 2 %; 12 % of the backward's
+  // time, where the better way each time would give 16.)  Up to 448 workgroups, from eight row tiles on, four in any case (8 x 600 x 64: 22.4 -> 20.9,
+  // which the model does not see).
   const size_t lds4 = 8 * tile + (size_t)4 * std::max(4 * n_cand, sub * p.nqb) + 16;
-  const bool four = (n_tiles + p.H * (p.C + 1 + p.n_loc) * sub <= 448 && n_row_tiles >= 8) || walks_cost(p, 4) < 0.94f * walks_cost(p, 2);
+  const bool four = (n_tiles + p.H * (p.C + 1 + p.n_loc) * sub <= 448 && n_row_tiles >= 8) || four_waves_end_sooner(p);
   if (four && lds4 <= 156 * 1024) {
     const unsigned n_dq = head_items(n_row_tiles, p.H);
     return p.d == 128 ? launch_walk<128, kDq | kDkv, 4>(a, n_dq, n_dkv, lds4, stream)

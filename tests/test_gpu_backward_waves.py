@@ -52,3 +52,17 @@ def test_which_backward_runs(gpu, case):  # noqa: F811
     O = c.attention(Q, lse=lse)
     names = kernels(lambda: c.attention_bwd(Q, O, Q, lse))
     assert f", {4 if name.startswith('four') else 2}>" in next(n for n in names if "bwd_walk_kernel" in n), names
+
+
+LINES = [
+    ("four_past",    12, 64, 128, 205,  1, 40, 2, 0, 1, [128, 64] * 20),   # few row tiles, though the places set the end
+    ("four_24_rows", 9, 64,  64,  1500, 0, 4, 3, 0, 1, [64, 7, 0, 64]),
+    ("two_25_rows",  9, 128, 64,  1549, 0, 3, 3, 0, 1, [64, 9, 33]),      # many, and the places set it
+    ("two_512",      8, 64,  128, 970,  1, 7, 1, 0, 0, [70] * 7),
+]
+
+
+@pytest.mark.parametrize("case", LINES, ids=[c[0] for c in LINES])
+def test_backward_at_the_models_lines(gpu, case):  # noqa: F811
+    test_which_backward_runs(gpu, case)
+    test_backward_two_waves_and_four(gpu, case)
