@@ -730,7 +730,7 @@ static float walk_us(int d, int tiles, int waves) {
 // tiles 172.0 | 179.6; 4 x 5000 x 128, 74 tiles in three parts 58.4 | 63.0).  Few units with long lists take several teams
 // each and the second launch: 1 x 1000 x 64, 82 tiles 21.0 -> 15.8 (one team 26.7); the parts of attn_split cost another
 // 3 us beside theirs, for lists and runs of their own (4 x 210 x 128, 21 tiles: 20.5 by parts of two tiles, 17 by one
-// team).  A call without scratch whose shape has use for it walks whole, bit for bit as ever.
+// team).  A call without scratch whose shape has use for it walks whole (one team to a unit would need none).
 AttnTeam attn_team(const pbsa_params& p, bool scratch) {
   const long units = (long)p.H * ((p.Nq + 63) / 64), n_wg = (long)p.H * ((p.Nq + kRowsPerWg - 1) / kRowsPerWg);
   const int tiles = (p.C + 1 + (p.k < p.n_loc ? p.k : p.n_loc)) * (p.B / kTile);

@@ -1,7 +1,10 @@
-// Coarse stage and persistent-memory update kernels for gfx950 (HBM / latency bound, no MFMA).
+// Coarse stage and persistent-memory update kernels for gfx950 (HBM / latency bound; fp32 chains on matrix instructions).
 //
-//   pool_kernel         block representatives by average pooling            (Eq. 6)
+//   pool_kernel         block representatives by average pooling, by threads (Eq. 6)
+//   pool_tile_kernel    the same, a workgroup to a block
+//   append_kernel       a chunk into the ring, pooled as it passes
 //   select_kernel       coarse logits + row-wise top-k block selection      (Eq. 10-11)
+//   select_small_kernel a small chunk's selection with its pooling, its append or the fold before it
 //   score_rows_kernel   block-level softmax rows over persistent + local    (Eq. 7)
 //   retain_kernel       column mean, Top-C retention, slot assignment       (Eq. 8-9)
 //   fold_promote_kernel dropped blocks -> running-mean summary; kept newcomers -> slots
@@ -969,7 +972,7 @@ template <int D>
 __global__ void __launch_bounds__(kFoldThreads) pool_fold_kernel(PoolArgs pa, FoldArgs fa, int n_fold_x) {
   const int n_fold = n_fold_x * fa.H, b = (int)blockIdx.x;      // the fold's workgroups run longest: they start first
   if (b >= n_fold) pool_body<D, kFoldThreads>(pa, b - n_fold);
-  else fold_promote_body<kFoldThreads, kFoldFew>(fa, b % n_fold_x, b / n_fold_x);
+  else fold_promote_body<kFoldThreads, kFoldFew>(fa, b % n_fold_x, b / n_fold_x);    // (no faster with the batch chosen by the host: 15.0 | 15.2 us)
 }
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }

@@ -1,4 +1,4 @@
-"""The attention by teams of waves: lists with fewer tiles than a team has waves, with one more, of every length that the limits
+"""The attention by teams of waves: lists with fewer tiles than a team has waves, with one more, up to the longest that the limits
 allow; units of one row; tiles of 1, 32, 33 and 63 keys; teams of four and of two, several teams to a unit.  Against fp64 with the
 bound derived in test_gpu_attention_split.py."""
 import pytest
